@@ -20,6 +20,7 @@
 // positions per tile.
 #include "ca_cnn.h"
 #include "ca_launch.h"
+#include "ca_reduce.h"
 
 namespace ca {
 namespace {
@@ -883,15 +884,16 @@ constexpr int kFileW5 = 12256;
 constexpr int kFileB5 = 12272;
 
 // Sum the workgroup partials; scatter to the model-file order.
-__global__ __launch_bounds__(kBlock) void k_cnn_reduce(const float *partial, int grid,
-                                                       float *grad, float *loss)
+static_assert(kCnnGradStride % kReduceCols == 0, "whole column groups");
+__global__ __launch_bounds__(kReduceThreads) void k_cnn_reduce(const float *partial, int grid,
+                                                               float *grad, float *loss)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= kCnnGradStride)
+    __shared__ float s_sum[kReduceCols];
+    column_sums(partial, grid, kCnnGradStride, s_sum);
+    if (threadIdx.x >= kReduceCols)
         return;
-    float v = 0.0f;
-    for (int g = 0; g < grid; ++g)
-        v += partial[(int64_t)g * kCnnGradStride + i];
+    const int i = blockIdx.x * kReduceCols + threadIdx.x;
+    const float v = s_sum[threadIdx.x];
     if (i < kCnnWElems) {
         const int l = i < kCnnWOff[1] ? 0 : i < kCnnWOff[2] ? 1 : i < kCnnWOff[3] ? 2 : 3;
         const FileLayer L = file_layer(l);
@@ -1040,8 +1042,8 @@ hipError_t launch_cnn_grad(const CnnTrainArgs &a, int grid, hipStream_t s)
 hipError_t launch_cnn_reduce(const float *partial, int grid, float *grad_out, float *loss_out,
                              hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cnn_reduce, dim3((kCnnGradStride + kBlock - 1) / kBlock), dim3(kBlock), 0,
-                       s, partial, grid, grad_out, loss_out);
+    hipLaunchKernelGGL(k_cnn_reduce, dim3(kCnnGradStride / kReduceCols), dim3(kReduceThreads), 0, s,
+                       partial, grid, grad_out, loss_out);
     return hipGetLastError();
 }
 
