@@ -21,6 +21,7 @@
 // activations are bfloat16, sums are float32 MFMA accumulators.
 #include "ca_cnn.h"
 #include "ca_launch.h"
+#include "ca_reduce.h"
 
 namespace ca {
 namespace {
@@ -49,19 +50,6 @@ struct alignas(16) FwdLds {
     __bf16 h3[kPos * 32];
     float z[kC2Win];
     float fb[kC2Floats];   // the model's float block (biases, w4, b4, colour statistics)
-};
-
-// The backward pass adds the signals at the pre-activations (ReLU and masks
-// applied) of layers 3, 2 and 1, the logit gradients and a zero line.
-struct alignas(16) GradLds {
-    FwdLds f;
-    __bf16 dp3[kPos * 32];
-    __bf16 dp2[3 * kPos * 16];
-    __bf16 dp1[5 * kPos * 8];
-    __bf16 zero[kPos * 32];
-    __bf16 ones[4];
-    float dz[kC2Win];
-    float loss[kBlock / 64];
 };
 
 // Clear a buffer (both guards included); a workgroup-wide loop.
@@ -629,306 +617,635 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_windows(const uint8_t *model,
 // Per window: the forward pass; dz = scale w (sigmoid(z) - t) on the
 // central positions inside the strip; the signals at the pre-activations
 // dP3 = [h3 > 0] w4 dz, dP2 = [h2 > 0] (flipped-W3 convolution of dP3),
-// dP1 = [h1 > 0] (flipped-W2 convolution of dP2), each stored in bfloat16
-// (the input-gradient convolutions are forward-shaped GEMMs on MFMA); then
-// the weight and bias gradients as sums over the window's positions, in
-// float32 registers that every thread keeps across the windows of its
-// workgroup.  Work units of 4 output channels x 4 inputs (one 3x3 tap of a
-// layer, frame orientation, one output line): thread t holds units t, t+256,
-// t+512 in the order
-//   [0, 288)    layer 3: o4 (8), tap (9), c4 (4)
-//   [288, 504)  layer 2: o4 (4), tap (9), c4 (2), line (3)
-//   [504, 684)  layer 1: o4 (2), tap (9), c4 (2), line (5)
-//   [684, 714)  biases: layer 3 o4 (8); layer 2 o4 (4) x line (3); layer 1
-//               o4 (2) x line (5)
-//   [714, 723)  w4 o4 (8), b4.
-// Each workgroup writes its unit sums; k_cnn2d_reduce adds them up in a
-// fixed order (deterministic) and maps them to model-file order.
+// dP1 = [h1 > 0] (flipped-W2 convolution of dP2), each stored in bfloat16;
+// then the weight gradients as GEMMs whose K runs over the positions,
+//   dW[o][tap][c] = sum_n dP[n][o] X[n + tap][c].
+// All of it is MFMA work.  The four waves of a workgroup take 32 positions of
+// the window each: two 16-position tiles of every forward-shaped GEMM and one
+// K step of every weight-gradient tile, whose accumulators (28 tiles, 112
+// registers) a wave keeps across its windows and the workgroup adds up at the
+// end.  The weight gradients' operands are columns of position-major buffers:
+// ds_read_b64_tr_b16 delivers them transposed, so a tap is a row offset and
+// needs no second layout (4 rows x 16 channels a read; K index 8 g + e of a
+// fragment is position 4 g + e for e < 4, 16 + 4 g + e - 4 otherwise, in both
+// operands).  Taps are numbered as in the frame, so vertical strips swap a
+// tap's two offsets and every window adds to the same accumulators.
+//
+// Bound by LDS bandwidth: about 131 fragment reads of 1 KB a wave and window
+// (4,100 cycles a compute unit at 128 bytes a cycle) beside 2,400 cycles of
+// MFMA a SIMD; 80 KB of LDS and 256 registers let two workgroups share a
+// compute unit.  16-byte chunks of the 16- and 32-channel rows are permuted
+// by position (XOR), which spreads 16 rows over all banks.  Measured, 14,336
+// windows: 3137 us with the weight gradients as 4 x 4 outer products on the
+// vector units (723 work units a workgroup), 298 us so (kernel trace); of a SIMD's cycles
+// about half issue vector instructions and a fifth MFMAs.
 
-struct Unit {
-    int kind;         // 0 product, 1 bias, 2 w4 / b4 (from the logit gradients)
-    int p_off, p_step;   // dP (or h3): 4 channels at p_off + n p_step
-    int q_off, q_step;   // input: 4 channels at q_off + n q_step (ones for a bias)
-    bool is_b4;
+constexpr int kDW3 = 0;                        // [32][9 taps x 16]
+constexpr int kDW2 = kDW3 + 32 * 144;          // [16][9 x 8, bias, 7 spare]
+constexpr int kDW1 = kDW2 + 16 * 80;           // [8][9 x 8, bias, 7 spare]
+constexpr int kDB3 = kDW1 + 8 * 80;            // [32]
+constexpr int kDW4 = kDB3 + 32;                // [32]
+constexpr int kDB4 = kDW4 + 32;
+constexpr int kDLoss = kDB4 + 1;
+static_assert(kDLoss < kC2GradStride && kC2GradStride % kReduceCols == 0, "gradient layout");
+
+struct alignas(16) GradLds {
+    __bf16 w3[10 * 512];          // layer 3's A fragments, [mt 5 + ks][lane][8]
+    __bf16 f3[9 * 512];           // the flipped layer 3's, [3 da + dl][lane][8]
+    __bf16 x0[kC2Band * kPos * 8];
+    __bf16 h1[5 * kPos * 8];
+    __bf16 h2[3 * kPos * 16];
+    __bf16 d[5 * kPos * 8];       // dP3 [kPos][32], later dP1 [5][kPos][8]
+    __bf16 dp2[3 * kPos * 16];
+    __bf16 ones[8];
+    float fb[kC2Floats];
 };
+static_assert(kPos * 32 <= 5 * kPos * 8, "dP3 fits where dP1 is kept");
+static_assert(sizeof(GradLds) <= 81920, "two workgroups per compute unit");
+static_assert((2 * kDB3 + 4 * 66) * sizeof(float) <= sizeof(GradLds), "sums fit the LDS");
 
-__device__ Unit unit_of(int u, bool hz, const GradLds &G)
+// Element offset of channels c .. c + 3 (c a multiple of 4) of position row
+// `pos` in a 16- or 32-channel buffer line (the chunk permutation above).
+__device__ __forceinline__ int off16(int pos, int c)
 {
-    // offsets are in bfloat16 elements from the start of GradLds
-    const __bf16 *base = reinterpret_cast<const __bf16 *>(&G);
-    auto off = [&](const __bf16 *p) { return (int)(p - base); };
-    Unit U{0, 0, 0, 0, 0, false};
-    auto taps = [&](int tap, int &da, int &dl) {
-        const int dy = tap / 3, dx = tap - 3 * (tap / 3);
-        da = hz ? dy : dx;
-        dl = hz ? dx : dy;
-    };
-    int da = 0, dl = 0;
-    if (u < 288) {
-        const int o4 = u % 8, tap = (u / 8) % 9, c4 = u / 72;
-        taps(tap, da, dl);
-        U.p_off = off(G.dp3 + 32 + 4 * o4);
-        U.p_step = 32;
-        U.q_off = off(G.f.h2 + (da * kPos + dl) * 16 + 4 * c4);
-        U.q_step = 16;
-    } else if (u < 504) {
-        const int v = u - 288;
-        const int o4 = v % 4, tap = (v / 4) % 9, c4 = (v / 36) % 2, r = v / 72;
-        taps(tap, da, dl);
-        U.p_off = off(G.dp2 + (r * kPos + 1) * 16 + 4 * o4);
-        U.p_step = 16;
-        U.q_off = off(G.f.h1 + ((r + da) * kPos + dl) * 8 + 4 * c4);
-        U.q_step = 8;
-    } else if (u < 684) {
-        const int v = u - 504;
-        const int o4 = v % 2, tap = (v / 2) % 9, c4 = (v / 18) % 2, r = v / 36;
-        taps(tap, da, dl);
-        U.p_off = off(G.dp1 + (r * kPos + 1) * 8 + 4 * o4);
-        U.p_step = 8;
-        U.q_off = off(G.f.x0 + ((r + da) * kPos + dl) * 8 + 4 * c4);
-        U.q_step = 8;
-    } else if (u < 714) {
-        U.kind = 1;
-        U.q_off = off(G.ones);
-        U.q_step = 0;
-        if (u < 692) {
-            U.p_off = off(G.dp3 + 32 + 4 * (u - 684));
-            U.p_step = 32;
-        } else if (u < 704) {
-            const int v = u - 692;
-            U.p_off = off(G.dp2 + ((v / 4) * kPos + 1) * 16 + 4 * (v % 4));
-            U.p_step = 16;
-        } else {
-            const int v = u - 704;
-            U.p_off = off(G.dp1 + ((v / 2) * kPos + 1) * 8 + 4 * (v % 2));
-            U.p_step = 8;
-        }
-    } else {
-        U.kind = 2;
-        U.is_b4 = u == 722;
-        U.p_off = off(G.f.h3 + 32 + 4 * (u - 714));
-        U.p_step = 32;
-    }
-    return U;
+    return pos * 16 + ((((c >> 3) ^ (pos >> 3)) & 1) << 3) + (c & 7);
+}
+__device__ __forceinline__ int off32(int pos, int c)
+{
+    return pos * 32 + ((((c >> 3) ^ (pos >> 2)) & 3) << 3) + (c & 7);
 }
 
-__global__ __launch_bounds__(kBlock) void k_cnn2d_grad(Cnn2dTrainArgs a)
+// Eight K values of one column of a position-major buffer: this lane's rows
+// (of 16) at p and at q, transposed over the lanes of its group of 16.
+__device__ __forceinline__ bf16x8 transposed(const __bf16 *p, const __bf16 *q)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)q);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+__device__ __forceinline__ bf16x8 frag_at(const __bf16 *p)
+{
+    return *reinterpret_cast<const bf16x8 *>(p);
+}
+__device__ __forceinline__ f32x4 mma(const bf16x8 &a, const bf16x8 &b, const f32x4 &c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// The same value, which the compiler takes for a new one: offsets derived
+// from it are computed where they are used instead of being kept in registers
+// over the whole window loop (with the accumulators, they spilled).
+__device__ __forceinline__ int fresh(int v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+
+// A lane's place in its wave's 32 positions of a window.
+struct Place {
+    int col, g;    // column of a tile, lane group
+    int p0;        // its position in the wave's first tile
+    // transposed reads: rows 4 g + col / 4 (and 16 on), chunk q = col % 4
+    int q, r0;
+    __device__ __forceinline__ Place(int lane, int wv)
+        : col(lane & 15), g(lane >> 4), p0(32 * wv + col), q(col & 3),
+          r0(32 * wv + 4 * g + (col >> 2))
+    {
+    }
+};
+
+// f(k) of this lane's K group k = 4 ks + g (small numbers): a byte of a
+// constant, one bit-field extract.
+template <class F>
+__device__ __forceinline__ int by_group(int ks, int g, F f)
+{
+    uint32_t packed = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        packed |= (uint32_t)f(4 * ks + i) << (8 * i);
+    return (int)((packed >> (8 * g)) & 0xFFu);
+}
+
+// v where the activation h is positive, else zero, as bfloat16.  h is a
+// ReLU's output, so positive means not all bits zero.
+__device__ __forceinline__ bf16x4 relu_mask(const f32x4 &v, const bf16x4 &h)
+{
+    typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+    const u16x4 bits = __builtin_bit_cast(u16x4, h);
+    bf16x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        o[j] = to_bf16(bits[j] != 0 ? v[j] : 0.0f);
+    return o;
+}
+
+__global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 {
     extern __shared__ __align__(16) uint8_t c2_smem[];
     GradLds &G = *reinterpret_cast<GradLds *>(c2_smem);
-    FwdLds &L = G.f;
-    const __bf16 *lds = reinterpret_cast<const __bf16 *>(&G);
-    const float *fb = L.fb;
-    stage_floats(L, a.model);
-    clear(L.x0, kC2Band * kPos * 8);
-    clear(L.h1, 5 * kPos * 8);
-    clear(L.h2, 3 * kPos * 16);
-    clear(L.h3, kPos * 32);
-    clear(G.dp3, kPos * 32);
-    clear(G.dp2, 3 * kPos * 16);
-    clear(G.dp1, 5 * kPos * 8);
-    clear(G.zero, kPos * 32);
-    if (threadIdx.x < 4)
-        G.ones[threadIdx.x] = to_bf16(1.0f);
-    float acc[3][16];
+    constexpr int kL8 = kPos * 8, kL16 = kPos * 16;   // elements of a buffer line
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wv = tid >> 6;
+    {
+        uint4 *z = reinterpret_cast<uint4 *>(&G);
+        for (int i = tid; i < (int)(sizeof(GradLds) / 16); i += kBlock)
+            z[i] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        const float *src = reinterpret_cast<const float *>(a.model + kC2FloatsOff);
+        for (int i = tid; i < kC2Floats; i += kBlock)
+            G.fb[i] = src[i];
+        if (tid < 8)
+            G.ones[tid] = to_bf16(1.0f);
+        __syncthreads();
+    }
+    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 acc3[2][9], accb3[2], acc2[5], acc1[5];
+    accb3[0] = accb3[1] = zero4;
 #pragma unroll
-    for (int s = 0; s < 3; ++s)
+    for (int t = 0; t < 9; ++t)
+        acc3[0][t] = acc3[1][t] = zero4;
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-            acc[s][e] = 0.0f;
-    float loss = 0.0f;
-    const int t = threadIdx.x;
-    for (int wi = blockIdx.x; wi < a.n; wi += gridDim.x) {
-        const int32_t *g = a.geom + 8 * wi;
-        const bool hz = g[0] != 0;
+    for (int t = 0; t < 5; ++t)
+        acc2[t] = acc1[t] = zero4;
+    float pw4[2][4], pb4 = 0.0f, loss = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        pw4[0][j] = pw4[1][j] = 0.0f;
+
+    // a contiguous share of the windows: those of one strip have one
+    // orientation, so its weights are loaded about once a strip
+    const int w_begin = (int)((int64_t)blockIdx.x * a.n / gridDim.x);
+    const int w_end = (int)((int64_t)(blockIdx.x + 1) * a.n / gridDim.x);
+    int cur = -1;
+    // The next window's input: pixels p, p + 32, p + 64, p + 96 (p = tid % 32)
+    // of band line tid / 32, fetched a window ahead (the fourth byte of a word
+    // is the next pixel's or, the window having eight lines, the next line's)
+    // and encoded while dW1 runs.
+    uint32_t raw[4];
+    bf16x8 enc[4];
+    const bool loads = tid < kC2Band * 32;
+    auto fetch = [&](int wi) {
+        if (loads) {
+            const uint8_t *src = a.win + (int64_t)wi * (8 * kC2Win * 3) + (tid >> 5) * (kC2Win * 3)
+                                 + (tid & 31) * 3;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                __builtin_memcpy(&raw[k], src + 96 * k, 4);
+        }
+    };
+    int last_w = 0, last_h = 0;
+    float rw = 0.0f, rh = 0.0f;
+    auto encode_window = [&](int wi) {
+        const int32_t *geo = a.geom + 8 * wi;
+        const bool hz = uniform_int(geo[0]) != 0;
+        const int line = uniform_int(geo[1]), start = uniform_int(geo[2]);
+        const int W = uniform_int(geo[3]), H = uniform_int(geo[4]);
         const int lo = uniform_int(a.range[2 * wi]), hi = uniform_int(a.range[2 * wi + 1]);
-        const uint32_t line_ok = band_lines(g[1], hz ? g[4] : g[3]);
+        if (W != last_w || H != last_h) {
+            rw = coord_scale(W);
+            rh = coord_scale(H);
+            last_w = W;
+            last_h = H;
+        }
+        const int t = fresh(tid);
+        const int across = line - 3 + (t >> 5), n0 = t & 31;
+        const bool in_line = across >= 0 && across < (hz ? H : W);
+        int x2 = 2 * (hz ? start + n0 : across) - (W - 1);
+        int y2 = 2 * (hz ? across : start + n0) - (H - 1);
+        const int dx = hz ? 64 : 0, dy = 64 - dx;
+        const float *fb = G.fb;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int n = n0 + 32 * k;
+            bf16x8 v;
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                v[c] = to_bf16(((float)((raw[k] >> (8 * c)) & 0xFFu) - fb[kC2FMean + c])
+                               * fb[kC2FInv + c]);
+            v[3] = to_bf16((float)(x2 + k * dx) * rw);
+            v[4] = to_bf16((float)(y2 + k * dy) * rh);
+            v[5] = v[6] = v[7] = to_bf16(0.0f);
+            enc[k] = in_line && n >= lo && n < hi ? v : bf16x8{};
+        }
+    };
+    if (w_begin < w_end) {
+        fetch(w_begin);
+        encode_window(w_begin);
+    }
+    for (int wi = w_begin; wi < w_end; ++wi) {
+        const int32_t *geo = a.geom + 8 * wi;
+        const bool hz = uniform_int(geo[0]) != 0;
+        const int line = uniform_int(geo[1]);
+        const int lo = uniform_int(a.range[2 * wi]), hi = uniform_int(a.range[2 * wi + 1]);
+        const uint32_t line_ok = band_lines(line, uniform_int(hz ? geo[4] : geo[3]));
         const __bf16 *A = reinterpret_cast<const __bf16 *>(a.model) + (hz ? 0 : kC2Orient);
-        __syncthreads();
-        load_window(L, a.win + (int64_t)wi * (8 * kC2Win * 3), g, fb, line_ok, lo, hi);
-        FwdW W;
-        load_fwd_weights(W, a.model, hz, fb);
-        __syncthreads();
-        forward(L, W, line_ok, lo, hi);
-        // logit gradients and the loss (soft binary cross entropy)
-        if (t < kC2Win) {
-            float dz = 0.0f;
-            if (t >= kTrainHalo && t < kC2Win - kTrainHalo && t >= lo && t < hi) {
-                const int q = t - kTrainHalo;
-                const float tg = a.target[(int64_t)wi * kTrainOut + q];
-                const float wt = a.weight[(int64_t)wi * kTrainOut + q];
-                const float z = L.z[t];
-                const float s = sigmoid(z);
-                // -(t log s + (1 - t) log(1 - s)) = max(z, 0) - z t + log(1 + e^-|z|)
-                loss += a.scale * wt * (fmaxf(z, 0.0f) - z * tg + log1pf(__expf(-fabsf(z))));
-                dz = a.scale * wt * (s - tg);
+        if (cur != (int)hz) {
+            cur = (int)hz;
+            const int col = lane & 15, g = lane >> 4;
+            for (int f = wv; f < 19; f += kWaves) {
+                const __bf16 *src = f < 10 ? A + kC2A[2] + ((f / 5) * 16 + col) * 160 + 32 * (f % 5)
+                                           : A + kC2F3 + col * 288 + 32 * (f - 10);
+                *reinterpret_cast<bf16x8 *>(G.w3 + f * 512 + lane * 8) = frag_at(src + 8 * g);
             }
-            G.dz[t] = dz;
+        }
+        if (loads) {
+            const int t = fresh(tid);
+            __bf16 *dst = G.x0 + (t >> 5) * kL8 + ((t & 31) + 1) * 8;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                *reinterpret_cast<bf16x8 *>(dst + 32 * 8 * k) = enc[k];
         }
         __syncthreads();
-        // w4 and b4 (before h3 is overwritten)
+        if (wi + 1 < w_end)
+            fetch(wi + 1);
+        // targets and loss weights of this lane's two positions (zero where
+        // a position carries no loss)
+        float tgt[2], lw[2], tops[2];
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const int u = t + kBlock * s;
-            if (u < 714 || u >= kC2Units)
-                continue;
-            const Unit U = unit_of(u, hz, G);
-            for (int n = 0; n < kC2Win; ++n) {
-                const float dz = G.dz[n];
-                if (U.is_b4) {
-                    acc[s][0] += dz;
-                } else {
-                    const bf16x4 h = *reinterpret_cast<const bf16x4 *>(lds + U.p_off + n * U.p_step);
+        for (int t = 0; t < 2; ++t) {
+            const int n = 32 * wv + (lane & 15) + 16 * t;
+            const bool in = n >= lo && n < hi;
+            const bool has = in && n >= kTrainHalo && n < kC2Win - kTrainHalo;
+            tops[t] = in ? __builtin_inff() : 0.0f;
+            const int64_t k = (int64_t)wi * kTrainOut + (has ? n - kTrainHalo : 0);
+            tgt[t] = a.target[k];
+            lw[t] = has ? a.scale * a.weight[k] : 0.0f;
+        }
+        {
+            // layer 1 by output-line pairs: lane groups 0-1 hold the first line
+            const Place L(fresh(lane), wv);
+            const Frag<96, 1> w1 = load_frag<96, 1>(A + kC2P1);
+            const f32x4 b1 = *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[0] + 4 * (L.g & 1));
+            int o[3];   // K group k: line k / 3 of four, dl = k % 3
 #pragma unroll
-                    for (int o = 0; o < 4; ++o)
-                        acc[s][4 * o] += (float)h[o] * dz;
+            for (int ks = 0; ks < 3; ++ks) {
+                o[ks] = by_group(ks, L.g, [](int k) { return k / 3; }) * kL8
+                        + (L.p0 + by_group(ks, L.g, [](int k) { return k % 3; })) * 8;
+            }
+            // the last pair's fourth input line does not exist; its weights
+            // are zero for the pair's first line and the second is dropped:
+            // any finite line
+            const int o_last = o[2] - (8 + L.g >= 9 ? kL8 : 0);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                f32x4 acc[2];
+                acc[0] = acc[1] = b1;
+#pragma unroll
+                for (int ks = 0; ks < 3; ++ks) {
+                    const __bf16 *x = G.x0 + 2 * i * kL8 + (i == 2 && ks == 2 ? o_last : o[ks]);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t] = mma(w1.a[0][ks], frag_at(x + t * 128), acc[t]);
+                }
+                const int ln = 2 * i + (L.g >> 1);
+                if (ln < 5)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        *reinterpret_cast<bf16x4 *>(G.h1 + ln * kL8 + (L.p0 + 16 * t + 1) * 8
+                                                    + 4 * (L.g & 1)) =
+                            relu_bf16(acc[t], line_in(line_ok, ln + 1) ? tops[t] : 0.0f);
+            }
+        }
+        const Frag<96, 1> w2 = load_frag<96, 1>(A + kC2A[1]);
+        __syncthreads();
+        {
+            const Place L(fresh(lane), wv);
+            int o[3];   // K group k (of 9): da = k / 3, dl = k % 3
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) {
+                // (groups 9 .. 11 have zero weights: any finite values)
+                o[ks] = by_group(ks, L.g, [](int k) { return k < 9 ? k / 3 : 0; }) * kL8
+                        + (L.p0 + by_group(ks, L.g, [](int k) { return k % 3; })) * 8;
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                f32x4 acc[2];
+                acc[0] = acc[1] = *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[1] + 4 * L.g);
+#pragma unroll
+                for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t] = mma(w2.a[0][ks], frag_at(G.h1 + i * kL8 + o[ks] + t * 128),
+                                     acc[t]);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    *reinterpret_cast<bf16x4 *>(G.h2 + i * kL16
+                                                + off16(L.p0 + 16 * t + 1, 4 * L.g)) =
+                        relu_bf16(acc[t], line_in(line_ok, i + 2) ? tops[t] : 0.0f);
+            }
+        }
+        __syncthreads();
+        {
+            // layer 3, the 1x1 layer, the loss and dP3: a position's 32
+            // channels sit in the four lane groups of its column
+            const Place L(fresh(lane), wv);
+            const int frag = (L.g * 16 + L.col) * 8;
+            f32x4 acc[2][2];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                acc[mt][0] = acc[mt][1] =
+                    *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[2] + 16 * mt + 4 * L.g);
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                // K group k (of 18; two more have zero weights): tap k / 2,
+                // half k % 2
+                const __bf16 *x =
+                    G.h2 + by_group(ks, L.g, [](int k) { return k < 18 ? k / 6 : 0; }) * kL16
+                    + off16(L.p0 + by_group(ks, L.g, [](int k) { return k / 2 % 3; }),
+                            8 * (L.g & 1));
+                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 256);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const bf16x8 w = frag_at(G.w3 + (mt * 5 + ks) * 512 + frag);
+                    acc[mt][0] = mma(w, x0, acc[mt][0]);
+                    acc[mt][1] = mma(w, x1, acc[mt][1]);
+                }
+            }
+            f32x4 w4[2];
+            w4[0] = *reinterpret_cast<const f32x4 *>(G.fb + kC2FW4 + 4 * L.g);
+            w4[1] = *reinterpret_cast<const f32x4 *>(G.fb + kC2FW4 + 16 + 4 * L.g);
+            float zs[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float top = line_in(line_ok, 3) ? tops[t] : 0.0f;
+                bf16x4 h[2];
+                float z = 0.0f;
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    h[mt] = relu_bf16(acc[mt][t], top);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        z = fmaf(w4[mt][j], (float)h[mt][j], z);
+                }
+                z += __shfl_xor(z, 16, 64);
+                z += __shfl_xor(z, 32, 64);
+                z += G.fb[kC2FB4];
+                zs[t] = z;
+                const float dz = lw[t] * (sigmoid(z) - tgt[t]);
+                pb4 += dz;    // every lane group alike; the first one's is taken
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    f32x4 dp;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        pw4[mt][j] = fmaf((float)h[mt][j], dz, pw4[mt][j]);
+                        dp[j] = w4[mt][j] * dz;
+                    }
+                    *reinterpret_cast<bf16x4 *>(G.d + off32(L.p0 + 16 * t + 1, 16 * mt + 4 * L.g)) =
+                        relu_mask(dp, h[mt]);
+                }
+            }
+            if (L.g < 2) {   // lane group t takes tile t's loss
+                // -(t log s + (1 - t) log(1 - s)) = max(z, 0) - z t + log(1 + e^-|z|)
+                const float z = L.g ? zs[1] : zs[0], tg = L.g ? tgt[1] : tgt[0];
+                loss += (L.g ? lw[1] : lw[0])
+                        * (fmaxf(z, 0.0f) - z * tg + log1pf(__expf(-fabsf(z))));
+            }
+            if (tid < 8)   // guard positions of dP3
+                *reinterpret_cast<bf16x8 *>(G.d + (tid >> 2) * (kPos - 1) * 32 + (tid & 3) * 8) =
+                    bf16x8{};
+        }
+        __syncthreads();
+        {
+            // dP2: output line i takes tap line 2 - i of the one dP3 line
+            const Place L(fresh(lane), wv);
+            const int frag = (L.g * 16 + L.col) * 8;
+            bf16x8 x[2][3];
+#pragma unroll
+            for (int dl = 0; dl < 3; ++dl) {
+                const __bf16 *d = G.d + off32(L.p0 + dl, 8 * L.g);
+                x[0][dl] = frag_at(d);
+                x[1][dl] = frag_at(d + 512);
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                f32x4 acc[2];
+                acc[0] = acc[1] = zero4;
+#pragma unroll
+                for (int dl = 0; dl < 3; ++dl) {
+                    const bf16x8 w = frag_at(G.f3 + ((2 - i) * 3 + dl) * 512 + frag);
+                    acc[0] = mma(w, x[0][dl], acc[0]);
+                    acc[1] = mma(w, x[1][dl], acc[1]);
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int o = i * kL16 + off16(L.p0 + 16 * t + 1, 4 * L.g);
+                    *reinterpret_cast<bf16x4 *>(G.dp2 + o) =
+                        relu_mask(acc[t], *reinterpret_cast<const bf16x4 *>(G.h2 + o));
                 }
             }
         }
-        // dP3 = [h3 > 0] w4 dz
-        for (int i = t; i < kC2Win * 32; i += kBlock) {
-            const int n = i >> 5, o = i & 31;
-            const float h = (float)L.h3[(n + 1) * 32 + o];
-            G.dp3[(n + 1) * 32 + o] = to_bf16(h > 0.0f ? fb[kC2FW4 + o] * G.dz[n] : 0.0f);
-        }
-        __syncthreads();
-        // dP2 = [h2 > 0] (flipped W3 * dP3): output lines 0..2 of layer 2;
-        // the dP3 line sits at band line 3, i.e. input line 2 of the GEMM
-        gemm3x3<32, 288, 1, 3>(load_frag<288, 1>(A + kC2F3), G.dp3, 2, 3, G.zero,
-                               [&](int i, int m0, int n, const f32x4 &v) {
-                                   const __bf16 *h = L.h2 + (i * kPos + n + 1) * 16 + m0;
-                                   bf16x4 o;
+        {
+            // dW3
+            const Place L(fresh(lane), wv);
+            bf16x8 p[2];
 #pragma unroll
-                                   for (int j = 0; j < 4; ++j)
-                                       o[j] = to_bf16((float)h[j] > 0.0f ? v[j] : 0.0f);
-                                   *reinterpret_cast<bf16x4 *>(G.dp2 + (i * kPos + n + 1) * 16 + m0) = o;
-                               });
-        __syncthreads();
-        // dP1 = [h1 > 0] (flipped W2 * dP2): lines 0..4 of layer 1; dP2 lines
-        // are GEMM input lines 2..4
-        gemm3x3<16, 160, 1, 5>(load_frag<160, 1>(A + kC2F2), G.dp2, 2, 5, G.zero,
-                               [&](int i, int m0, int n, const f32x4 &v) {
-                                   if (m0 >= 8)
-                                       return;
-                                   const __bf16 *h = L.h1 + (i * kPos + n + 1) * 8 + m0;
-                                   bf16x4 o;
+            for (int mt = 0; mt < 2; ++mt) {
+                const __bf16 *d = G.d + off32(L.r0 + 1, 16 * mt + 4 * L.q);
+                p[mt] = transposed(d, d + 512);
+                const __bf16 one = to_bf16(1.0f);
+                accb3[mt] = mma(p[mt], bf16x8{one, one, one, one, one, one, one, one}, accb3[mt]);
+            }
+            int o[3];
 #pragma unroll
-                                   for (int j = 0; j < 4; ++j)
-                                       o[j] = to_bf16((float)h[j] > 0.0f ? v[j] : 0.0f);
-                                   *reinterpret_cast<bf16x4 *>(G.dp1 + (i * kPos + n + 1) * 8 + m0) = o;
-                               });
-        __syncthreads();
-        // weight and bias gradients
+            for (int dl = 0; dl < 3; ++dl)
+                o[dl] = off16(L.r0 + dl, 4 * L.q);
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const int u = t + kBlock * s;
-            if (u >= 714)
-                continue;
-            const Unit U = unit_of(u, hz, G);
-            for (int n = 0; n < kC2Win; ++n) {
-                const bf16x4 p = *reinterpret_cast<const bf16x4 *>(lds + U.p_off + n * U.p_step);
-                const bf16x4 q = *reinterpret_cast<const bf16x4 *>(lds + U.q_off + n * U.q_step);
+            for (int tap = 0; tap < 9; ++tap) {
+                const int dy = tap / 3, dx = tap % 3;
+                const __bf16 *x = G.h2 + (hz ? dy * kL16 + o[dx] : dx * kL16 + o[dy]);
+                const bf16x8 xt = transposed(x, x + 256);
 #pragma unroll
-                for (int o = 0; o < 4; ++o)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        acc[s][4 * o + c] += (float)p[o] * (float)q[c];
+                for (int mt = 0; mt < 2; ++mt)
+                    acc3[mt][tap] = mma(p[mt], xt, acc3[mt][tap]);
             }
         }
-    }
-    // loss: wave sums, then the workgroup's
+        const Frag<192, 1> f2 = load_frag<192, 1>(A + kC2F2);
+        __syncthreads();
+        {
+            // dP1 by output-line pairs (i0, i0 + 1) from dP2 lines i0 - 2 ..
+            // i0 + 1 (K steps of lines that do not exist are left out, or
+            // read as zeros where half a step exists)
+            const Place L(fresh(lane), wv);
+            int od[6];   // K group k: input line k / 6 of four, dl, half
 #pragma unroll
-    for (int dd = 32; dd >= 1; dd >>= 1)
-        loss += __shfl_xor(loss, dd, 64);
+            for (int ks = 0; ks < 6; ++ks) {
+                od[ks] = by_group(ks, L.g, [](int k) { return k / 6; }) * kL16
+                         + off16(L.p0 + by_group(ks, L.g, [](int k) { return k % 6 / 2; }),
+                                 8 * (L.g & 1));
+            }
+#pragma unroll
+            for (int i0 = 0; i0 < 6; i0 += 2) {
+                f32x4 acc[2];
+                acc[0] = acc[1] = zero4;
+#pragma unroll
+                for (int ks = (i0 == 0 ? 3 : 0); ks < (i0 == 0 ? 6 : i0 == 2 ? 5 : 2); ++ks) {
+                    const int last = (4 * ks + 3) / 6 + i0 - 2;   // the step's last input line
+                    const bool off = last > 2 && L.g >= 6 * (5 - i0) - 4 * ks;   // line > 2
+                    const int o = od[ks] + (i0 - 2) * kL16 - (off ? kL16 : 0);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        bf16x8 x = frag_at(G.dp2 + o + t * 256);
+                        if (last > 2 && off)
+                            x = bf16x8{};
+                        acc[t] = mma(f2.a[0][ks], x, acc[t]);
+                    }
+                }
+                const int ln = i0 + (L.g >> 1);
+                if (ln < 5)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const int o = ln * kL8 + (L.p0 + 16 * t + 1) * 8 + 4 * (L.g & 1);
+                        *reinterpret_cast<bf16x4 *>(G.d + o) =
+                            relu_mask(acc[t], *reinterpret_cast<const bf16x4 *>(G.h1 + o));
+                    }
+            }
+        }
+        // dW2 and dW1: a tile's 16 columns are two taps of 8 channels (chunks
+        // q < 2 and q >= 2 of the lane's reads); the tenth tap reads ones, its
+        // columns are the bias gradients
+        const int sy = hz ? kL8 : 8, sx = hz ? 8 : kL8;
+        auto tap_offset = [&](const Place &L, int t) {
+            const int e = 2 * t, o = 2 * t + 1;
+            return L.r0 * 8 + 4 * (L.q & 1)
+                   + (L.q >= 2 ? (o / 3) * sy + (o % 3) * sx : (e / 3) * sy + (e % 3) * sx);
+        };
+        {
+            const Place L(fresh(lane), wv);
+            const int o = off16(L.r0 + 1, 4 * L.q);
+            bf16x8 p[3];
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                p[r] = transposed(G.dp2 + r * kL16 + o, G.dp2 + r * kL16 + o + 256);
+#pragma unroll
+            for (int t = 0; t < 5; ++t) {
+                const bool ones = t == 4 && L.q >= 2;
+                const __bf16 *x = ones ? G.ones : G.h1 + tap_offset(L, t);
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    const __bf16 *xr = ones ? x : x + r * kL8;
+                    acc2[t] = mma(p[r], transposed(xr, ones ? x : xr + 128), acc2[t]);
+                }
+            }
+        }
+        __syncthreads();
+        {
+            // rows 8 .. 15 of dW1's tiles repeat rows 0 .. 7
+            const Place L(fresh(lane), wv);
+            const int o = (L.r0 + 1) * 8 + 4 * (L.q & 1);
+            bf16x8 p[5];
+#pragma unroll
+            for (int r = 0; r < 5; ++r)
+                p[r] = transposed(G.d + r * kL8 + o, G.d + r * kL8 + o + 128);
+#pragma unroll
+            for (int t = 0; t < 5; ++t) {
+                const bool ones = t == 4 && L.q >= 2;
+                const __bf16 *x = ones ? G.ones : G.x0 + tap_offset(L, t);
+#pragma unroll
+                for (int r = 0; r < 5; ++r) {
+                    const __bf16 *xr = ones ? x : x + r * kL8;
+                    acc1[t] = mma(p[r], transposed(xr, ones ? x : xr + 128), acc1[t]);
+                }
+            }
+        }
+        if (wi + 1 < w_end)
+            encode_window(wi + 1);
+        __syncthreads();
+    }
+
+    // the workgroup's sums, in a fixed order: (wave 0 + wave 2) + (wave 1 +
+    // wave 3)
+    float *sum = reinterpret_cast<float *>(&G);
+    float *tail = sum + 2 * kDB3;    // [4 waves][66]: b3, w4, b4, loss
+    const int col = lane & 15, g = lane >> 4;
+    auto each = [&](auto fn) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = 4 * g + j;
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+                    fn(kDW3 + (16 * mt + o) * 144 + tap * 16 + col, acc3[mt][tap][j]);
+#pragma unroll
+            for (int t = 0; t < 5; ++t) {
+                fn(kDW2 + o * 80 + t * 16 + col, acc2[t][j]);
+                if (g < 2)
+                    fn(kDW1 + o * 80 + t * 16 + col, acc1[t][j]);
+            }
+        }
+    };
+    auto over_columns = [](float v) {
+#pragma unroll
+        for (int d = 1; d < 16; d *= 2)
+            v += __shfl_xor(v, d, 64);
+        return v;
+    };
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const float vw = over_columns(pw4[mt][j]);
+            if (col == 0) {
+                tail[66 * wv + 16 * mt + 4 * g + j] = accb3[mt][j];
+                tail[66 * wv + 32 + 16 * mt + 4 * g + j] = vw;
+            }
+        }
+    pb4 = over_columns(pb4);
+    loss = over_columns(loss);
+    loss += __shfl_xor(loss, 16, 64);   // lane groups 0 and 1
+    if (lane == 0) {
+        tail[66 * wv + 64] = pb4;
+        tail[66 * wv + 65] = loss;
+    }
+    if (wv >= 2)
+        each([&](int i, float v) { sum[(wv - 2) * kDB3 + i] = v; });
     __syncthreads();
-    if ((t & 63) == 0)
-        G.loss[t >> 6] = loss;
+    if (wv < 2)
+        each([&](int i, float v) { sum[wv * kDB3 + i] += v; });
     __syncthreads();
     float *out = a.partial + (int64_t)blockIdx.x * kC2GradStride;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        const int u = t + kBlock * s;
-        if (u < kC2Units)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                out[16 * u + e] = acc[s][e];
-    }
-    if (t == 0) {
-        float l = 0.0f;
-        for (int w2 = 0; w2 < kBlock / 64; ++w2)
-            l += G.loss[w2];
-        out[16 * kC2Units] = l;
-    }
+    for (int i = tid; i < kDB3; i += kBlock)
+        out[i] = sum[i] + sum[kDB3 + i];
+    if (tid < 66)
+        out[kDB3 + tid] = (tail[tid] + tail[132 + tid]) + (tail[66 + tid] + tail[198 + tid]);
 }
 
-// Gradient in model-file order from the workgroups' unit sums (fixed order:
-// workgroups, then a layer's output lines); the normaliser gets zero.
-__global__ __launch_bounds__(kBlock) void k_cnn2d_reduce(const float *partial, int grid,
-                                                         float *grad, float *loss)
+// Gradient in model-file order from the workgroups' sums; the normaliser
+// gets zero.
+__global__ __launch_bounds__(kReduceThreads) void k_cnn2d_reduce(const float *partial, int grid,
+                                                                 float *grad, float *loss)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i > kC2Params)
+    __shared__ float s_sum[kReduceCols];
+    column_sums(partial, grid, kC2GradStride, s_sum);
+    if (threadIdx.x >= kReduceCols)
         return;
-    // the (unit, entry) pairs summed for parameter i
-    int u0 = -1, e0 = 0, step = 0, count = 0;
-    if (i == kC2Params) {
-        u0 = kC2Units;
-        count = 1;
-    } else if (i >= kC2FileW[0] && i < kC2FileB4) {
-        int l = 2;
-        while (l > 0 && i < kC2FileW[l])
-            --l;
-        constexpr int cin[3] = {5, 8, 16}, cout[3] = {8, 16, 32};
-        const int wn = cout[l] * cin[l] * 9;
-        if (i >= kC2FileW4) {
-            const int o = i - kC2FileW4;
-            u0 = 714 + o / 4;
-            e0 = 4 * (o % 4);
-            count = 1;
-        } else if (i < kC2FileW[l] + wn) {
-            const int r = i - kC2FileW[l];
-            const int o = r / (cin[l] * 9), c = (r / 9) % cin[l], tap = r % 9;
-            e0 = 4 * (o % 4) + c % 4;
-            if (l == 2) {
-                u0 = o / 4 + 8 * (tap + 9 * (c / 4));
-                count = 1;
-            } else if (l == 1) {
-                u0 = 288 + o / 4 + 4 * (tap + 9 * (c / 4));
-                step = 72;
-                count = 3;
-            } else {
-                u0 = 504 + o / 4 + 2 * (tap + 9 * (c / 4));
-                step = 36;
-                count = 5;
-            }
-        } else {
-            const int o = i - (kC2FileW[l] + wn);
-            e0 = 4 * (o % 4);
-            if (l == 2) {
-                u0 = 684 + o / 4;
-                count = 1;
-            } else if (l == 1) {
-                u0 = 692 + o / 4;
-                step = 4;
-                count = 3;
-            } else {
-                u0 = 704 + o / 4;
-                step = 2;
-                count = 5;
-            }
-        }
-    } else if (i == kC2FileB4) {
-        u0 = 722;
-        count = 1;
-    }
-    float v = 0.0f;
-    for (int g = 0; g < grid; ++g)
-        for (int k = 0; k < count; ++k)
-            v += partial[(int64_t)g * kC2GradStride + 16 * (u0 + k * step) + e0];
-    if (i == kC2Params)
+    const int i = blockIdx.x * kReduceCols + threadIdx.x;
+    const float v = s_sum[threadIdx.x];
+    if (i < kC2FileW[0])
+        grad[i] = 0.0f;
+    if (i < kDW2) {
+        const int o = i / 144, k = i % 144;
+        grad[kC2FileW[2] + (o * 16 + k % 16) * 9 + k / 16] = v;
+    } else if (i < kDB3) {
+        const int l = i < kDW1 ? 1 : 0;
+        const int cin = l ? 8 : 5;
+        const int r = i - (l ? kDW2 : kDW1);
+        const int o = r / 80, k = r % 80;
+        if (k < 72 && k % 8 < cin)
+            grad[kC2FileW[l] + (o * cin + k % 8) * 9 + k / 8] = v;
+        else if (k == 72)
+            grad[kC2FileB[l] + o] = v;
+    } else if (i < kDW4) {
+        grad[kC2FileB[2] + i - kDB3] = v;
+    } else if (i <= kDB4) {
+        grad[kC2FileW4 + i - kDW4] = v;   // w4, then b4
+    } else if (i == kDLoss) {
         *loss = v;
-    else
-        grad[i] = v;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_cnn2d_sgd(float *master, float *mom, const float *grad,
@@ -976,17 +1293,29 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_pack(const float *master, uint
             da = tap / 3;
             dl = tap % 3;
             real = m < cout[l] && tap < 9 && c < cin[l];
+        } else if (e < kC2F3) {
+            // flipped layer 2 for two output lines at once: row m = 8 s + c is
+            // input channel c at the pair's line s; K = (3 lo + dl') 16 + o
+            // over four dP2 lines lo (tap da' = lo - s)
+            const int r = e - kC2F2;
+            const int m = r / 192, k = r % 192;
+            l = 1;
+            c = m % 8;
+            o = k % 16;
+            const int tap = k / 16;
+            da = 2 - (tap / 3 - m / 8);
+            dl = 2 - tap % 3;
+            real = da >= 0 && da < 3;
         } else {
-            l = e < kC2F3 ? 1 : 2;
-            const int r = e - (l == 1 ? kC2F2 : kC2F3);
-            const int kp = l == 1 ? 160 : 288;
-            const int m = r / kp, k = r % kp;
-            const int tap = k / cout[l];
-            o = k % cout[l];
+            const int r = e - kC2F3;
+            const int m = r / 288, k = r % 288;
+            const int tap = k / 32;
+            l = 2;
             c = m;
+            o = k % 32;
             da = 2 - tap / 3;
             dl = 2 - tap % 3;
-            real = m < cin[l] && tap < 9;
+            real = true;
         }
         if (real) {
             const int dy = orient == 0 ? da : dl, dx = orient == 0 ? dl : da;
@@ -1060,8 +1389,8 @@ hipError_t launch_cnn2d_grad(const Cnn2dTrainArgs &a, int grid, hipStream_t s)
 hipError_t launch_cnn2d_reduce(const float *partial, int grid, float *grad_out, float *loss_out,
                                hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cnn2d_reduce, dim3((kC2Params + 1 + kBlock - 1) / kBlock), dim3(kBlock),
-                       0, s, partial, grid, grad_out, loss_out);
+    hipLaunchKernelGGL(k_cnn2d_reduce, dim3(kC2GradStride / kReduceCols), dim3(kReduceThreads), 0,
+                       s, partial, grid, grad_out, loss_out);
     return hipGetLastError();
 }
 
