@@ -20,117 +20,11 @@
 // positions per tile.
 #include "ca_cnn.h"
 #include "ca_launch.h"
+#include "ca_mfma.h"
 #include "ca_reduce.h"
 
 namespace ca {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// One 16x16 tile of D = A (16 x 32k) * B (32k x 16) with A rows and B columns
-// read as 8 consecutive bf16 per lane.  Lane l holds A[l % 16][8 (l / 16) ..]
-// and B[8 (l / 16) ..][l % 16]; the result D[4 (l / 16) + j][l % 16], j < 4.
-template <int KSTEPS>
-__device__ __forceinline__ f32x4 mfma_tile(const __bf16 *a_row, const __bf16 *b_col)
-{
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(a_row + 32 * ks);
-        const bf16x8 b = *reinterpret_cast<const bf16x8 *>(b_col + 32 * ks);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-__device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }
-
-// Forward convolution layer over a window: Y[n][m] = relu(b[m] + sum_k
-// W[m][k] X[(n + G - 2) CIN + k]) for the 128 window positions, zero for
-// positions outside [lo, hi).
-template <int CIN, int COUT, int KP>
-__device__ void conv_forward(const __bf16 *W, const float *bias, const __bf16 *X, __bf16 *Y, int lo,
-                             int hi)
-{
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    constexpr int MT = COUT / 16;
-    constexpr int NT = kCnnWin / 16;
-    const int kq = 8 * (lane >> 4);
-    for (int tile = wv; tile < MT * NT; tile += 4) {
-        const int mt = tile % MT;
-        const int nt = tile / MT;
-        const int m = mt * 16 + (lane & 15);
-        const int n = nt * 16 + (lane & 15);
-        const f32x4 acc = mfma_tile<KP / 32>(W + m * KP + kq, X + (n + kCnnGuard - 2) * CIN + kq);
-        const int mo = mt * 16 + 4 * (lane >> 4);
-        const bool inside = n >= lo && n < hi;
-        __bf16 o[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float v = acc[j] + bias[mo + j];
-            v = v > 0.0f ? v : 0.0f;
-            o[j] = inside ? to_bf16(v) : to_bf16(0.0f);
-        }
-        __bf16 *dst = Y + (n + kCnnGuard) * COUT + mo;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            dst[j] = o[j];
-    }
-}
-
-// Logits of all 128 window positions into z (valid for the central 112).
-// Weights w (GEMM layout) may live in LDS or in global memory.
-__device__ void window_forward(const __bf16 *w, const float *fb, const __bf16 *x0, __bf16 *h1,
-                               __bf16 *h2, __bf16 *h3, __bf16 *h4, float *zo, int lo, int hi)
-{
-    conv_forward<24, 16, 128>(w + kCnnWOff[0], fb + kCnnBOff[0], x0, h1, lo, hi);
-    __syncthreads();
-    conv_forward<16, 32, 96>(w + kCnnWOff[1], fb + kCnnBOff[1], h1, h2, lo, hi);
-    __syncthreads();
-    conv_forward<32, 32, 160>(w + kCnnWOff[2], fb + kCnnBOff[2], h2, h3, lo, hi);
-    __syncthreads();
-    conv_forward<32, 16, 160>(w + kCnnWOff[3], fb + kCnnBOff[3], h3, h4, lo, hi);
-    __syncthreads();
-    const int n = threadIdx.x;
-    if (n < kCnnWin) {
-        const __bf16 *h = h4 + (n + kCnnGuard) * 16;
-        float z = fb[kCnnW5Off + 16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-            z = fmaf(fb[kCnnW5Off + c], (float)h[c], z);
-        zo[n] = z;
-    }
-    __syncthreads();
-}
-
-// One uint8 window [8][128][3] into the position-major input buffer,
-// zero outside [lo, hi).
-__device__ void load_window(__bf16 *x0, const uint8_t *src, int lo, int hi)
-{
-    for (int i = threadIdx.x; i < kCnnLines * kCnnWin * 3; i += kBlock) {
-        const int line = i / (kCnnWin * 3);
-        const int rem = i - line * (kCnnWin * 3);
-        const int n = rem / 3, ch = rem - 3 * (rem / 3);
-        const float v = (n >= lo && n < hi) ? ((float)src[i] - 128.0f) * (1.0f / 64.0f) : 0.0f;
-        x0[(n + kCnnGuard) * 24 + 3 * line + ch] = to_bf16(v);
-    }
-}
-
-__device__ __forceinline__ float sigmoid(float z) { return 1.0f / (1.0f + __expf(-z)); }
-
-// Clear the guard rows 0..G-1 and W+G..W+2G-1 of a position-major buffer.
-__device__ void zero_guards(__bf16 *buf, int chans)
-{
-    for (int i = threadIdx.x; i < 2 * kCnnGuard * chans; i += kBlock) {
-        const int row = i / chans;
-        const int r = row < kCnnGuard ? row : kCnnWin + row;
-        buf[r * chans + i % chans] = to_bf16(0.0f);
-    }
-}
 
 // --------------------------------------------------- wave-level forward --
 //
@@ -228,7 +122,6 @@ template <int CIN, int COUT, int MT, int KS>
 __device__ __forceinline__ void wave_conv(const bf16x8 (&A)[MT][KS], const float (&bias)[MT][4],
                                           const __bf16 *X, __bf16 *Y, int lo, int hi, int lane)
 {
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     const int kq = 8 * (lane >> 4);
     // this lane's B-fragment offsets (K index 32 ks + kq = tap * CIN + c) and
     // output offsets, for position lane % 16; tiles 16 rows on add t 16 CIN
@@ -620,251 +513,511 @@ __global__ __launch_bounds__(kCnnWaveBlock) __attribute__((amdgpu_waves_per_eu(2
 //   input gradients   dX_{l-1} = flipped-weight convolution of dP_l (a
 //                     forward-shaped GEMM), masked by h_{l-1} > 0;
 //   weight gradients  dW_l[o][t C_in + c] = sum_n dP_l[n][o] X[n + t - 2][c],
-//                     an MFMA GEMM whose reduction runs over the 128
-//                     positions; the tiles stay in registers across all the
-//                     windows of a workgroup;
-//   bias gradients    per-thread sums of dP_l, reduced at the end.
+//                     an MFMA GEMM whose K runs over the 128 positions.
+//                     Both operands are columns of position-major buffers,
+//                     which ds_read_b64_tr_b16 delivers transposed, so a tap
+//                     is a row offset;
+//   bias gradients    the same GEMM against a column of ones.
+//
+// The four waves of a workgroup take 32 positions each (two tiles) in the
+// forward-shaped GEMMs.  In the weight gradients wave (a, b) takes half a of
+// the positions and half b of the tiles (output channels 16 b .. of the
+// 32-channel layers, half of the columns of the others): 24 tiles and three
+// bias columns, 108 registers kept across the workgroup's windows.  A split of
+// the tiles alone reads each operand twice as often, one of the positions
+// alone needs 200 registers.  The 1x1 layer, the loss and dP4 are formed in
+// the registers of the last convolution.
+//
+// Bound by LDS reads (about 150 fragments of 1 KB a wave and window) and the
+// vector instructions beside them; 77 KB of LDS and 256 registers let two
+// workgroups share a compute unit.  Measured, 14,336 windows: 791 us with
+// channel-major copies of the signals and element-wise gathered operands, 258
+// us so (kernel trace).
 
-struct __attribute__((aligned(16))) CnnGradLds {
-    float fb[128];
+struct alignas(16) CnnGradLds {
+    __bf16 w3[10 * 512];          // layer 3's A fragments, [5 mt + ks][lane][8]
+    __bf16 f3[10 * 512];          // the flipped layer 3's
+    __bf16 f4[6 * 512];           // the flipped layer 4's, [3 mt + ks]
     __bf16 x0[kCnnRows * 24];
     __bf16 h1[kCnnRows * 16];
     __bf16 h2[kCnnRows * 32];
-    __bf16 h3[kCnnRows * 32];   // later dP2, position-major
-    __bf16 h4[kCnnRows * 16];   // later dP4, position-major
-    __bf16 d32[kCnnRows * 32];  // dP3, position-major
-    __bf16 t[2][32 * kCnnWin];  // channel-major dP of two consecutive layers
-    float z[kCnnWin];           // logits, then dL/dz
+    __bf16 h3[kCnnRows * 32];
+    __bf16 d16[kCnnRows * 16];    // dP4, later dP1
+    __bf16 d3[kCnnRows * 32];     // dP3
+    __bf16 d2[kCnnRows * 32];     // dP2
+    __bf16 ones[8];
+    float fb[128];
 };
+static_assert(sizeof(CnnGradLds) <= 81920, "two workgroups per compute unit");
+constexpr int kGradTail = 18;     // w5 [16], b5, loss
+static_assert((kCnnWElems + 3 * 64 + 4 * kGradTail) * sizeof(float) <= sizeof(CnnGradLds),
+              "sums fit the LDS");
 
-// Input gradient of one layer: Dout/Tout[n][c] = [h(n, c) > 0] * sum_k'
-// Wf[c][k'] D[(n + G - 2) CI + k'], zero outside [lo, hi).  CI = channels of
-// dP (the layer's outputs), CO = the layer's inputs.
-template <int CI, int CO, int KP>
-__device__ void input_grad(const __bf16 *Wf, const __bf16 *D, const __bf16 *Hmask, __bf16 *Dout,
-                           __bf16 *Tout, int lo, int hi)
+__global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
 {
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    constexpr int MT = CO / 16;
-    constexpr int NT = kCnnWin / 16;
-    const int kq = 8 * (lane >> 4);
-    for (int tile = wv; tile < MT * NT; tile += 4) {
-        const int mt = tile % MT;
-        const int nt = tile / MT;
-        const int m = mt * 16 + (lane & 15);
-        const int n = nt * 16 + (lane & 15);
-        const f32x4 acc = mfma_tile<KP / 32>(Wf + m * KP + kq, D + (n + kCnnGuard - 2) * CI + kq);
-        const int mo = mt * 16 + 4 * (lane >> 4);
-        const bool inside = n >= lo && n < hi;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool open = inside && (float)Hmask[(n + kCnnGuard) * CO + mo + j] > 0.0f;
-            const __bf16 o = to_bf16(open ? acc[j] : 0.0f);
-            if (Dout)
-                Dout[(n + kCnnGuard) * CO + mo + j] = o;
-            Tout[(mo + j) * kCnnWin + n] = o;
-        }
-    }
-}
-
-// Weight-gradient tiles of one layer, accumulated in registers: tile i of
-// wave wv is tile wv + 4 i of the layer's (COUT / 16) x (KP / 16) tiles.
-template <int CIN, int COUT, int KP, int NPW>
-__device__ __forceinline__ void weight_grad(f32x4 (&acc)[NPW], const __bf16 *T, const __bf16 *X)
-{
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    constexpr int MT = COUT / 16;
-    constexpr int TILES = MT * (KP / 16);
-    const int kq = 8 * (lane >> 4);
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) {
-        const int tile = wv + 4 * i;
-        if (tile < TILES) {
-            const int mt = tile % MT;
-            const int nt = tile / MT;
-            const __bf16 *a_row = T + (mt * 16 + (lane & 15)) * kCnnWin + kq;
-            const __bf16 *b_col = X + (kq + kCnnGuard - 2) * CIN + nt * 16 + (lane & 15);
-            f32x4 c = acc[i];
-#pragma unroll
-            for (int ks = 0; ks < kCnnWin / 32; ++ks) {
-                const bf16x8 av = *reinterpret_cast<const bf16x8 *>(a_row + 32 * ks);
-                bf16x8 bv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    bv[e] = b_col[(32 * ks + e) * CIN];
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
-            }
-            acc[i] = c;
-        }
-    }
-}
-
-template <int COUT, int KP, int NPW>
-__device__ __forceinline__ void store_weight_grad(const f32x4 (&acc)[NPW], float *out)
-{
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    constexpr int MT = COUT / 16;
-    constexpr int TILES = MT * (KP / 16);
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) {
-        const int tile = wv + 4 * i;
-        if (tile < TILES) {
-            const int o = (tile % MT) * 16 + 4 * (lane >> 4);
-            const int k = (tile / MT) * 16 + (lane & 15);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                out[(o + j) * KP + k] = acc[i][j];
-        }
-    }
-}
-
-// Sum of a channel-major dP over this thread's share of positions: 16
-// channels -> 16 threads x 8 positions per channel, 32 -> 8 x 16.
-template <int C>
-__device__ __forceinline__ float bias_share(const __bf16 *T)
-{
-    constexpr int per = kCnnWin * C / kBlock;
-    const int c = threadIdx.x / (kBlock / C);
-    const int n0 = (threadIdx.x % (kBlock / C)) * per;
-    float v = 0.0f;
-#pragma unroll
-    for (int i = 0; i < per; ++i)
-        v += (float)T[c * kCnnWin + n0 + i];
-    return v;
-}
-
-__global__ __launch_bounds__(kBlock) void k_cnn_grad(CnnTrainArgs a)
-{
-    __shared__ CnnGradLds s;
+    extern __shared__ __align__(16) uint8_t cnn_smem[];
+    CnnGradLds &G = *reinterpret_cast<CnnGradLds *>(cnn_smem);
     const int tid = threadIdx.x;
+    const int lane = tid & 63, wv = uniform_int(tid >> 6);
+    const int half_n = wv >> 1, half_t = wv & 1;
     const __bf16 *W = reinterpret_cast<const __bf16 *>(a.model);
     const __bf16 *Wf = reinterpret_cast<const __bf16 *>(a.model + kCnnFlipOff);
-    const float *mf = reinterpret_cast<const float *>(a.model + kCnnFloatsOff);
-    for (int i = tid; i < 128; i += kBlock)
-        s.fb[i] = i < kCnnFloats ? mf[i] : 0.0f;
-    zero_guards(s.x0, 24);
-    zero_guards(s.h1, 16);
-    zero_guards(s.h2, 32);
-    zero_guards(s.h3, 32);
-    zero_guards(s.h4, 16);
-    zero_guards(s.d32, 32);
+    {
+        uint4 *z = reinterpret_cast<uint4 *>(&G);
+        for (int i = tid; i < (int)(sizeof(CnnGradLds) / 16); i += kBlock)
+            z[i] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        const float *mf = reinterpret_cast<const float *>(a.model + kCnnFloatsOff);
+        if (tid < kCnnFloats)
+            G.fb[tid] = mf[tid];
+        if (tid < 8)
+            G.ones[tid] = to_bf16(1.0f);
+        const Place L(lane);
+        for (int f = wv; f < 26; f += 4) {
+            const int k = f < 10 ? f : f < 20 ? f - 10 : f - 20;
+            const int ks = f < 20 ? k % 5 : k % 3, mt = f < 20 ? k / 5 : k / 3;
+            const __bf16 *src = f < 10   ? W + kCnnWOff[2] + (16 * mt + L.col) * 160
+                                : f < 20 ? Wf + kCnnFOff[1] + (16 * mt + L.col) * 160
+                                         : Wf + kCnnFOff[2] + (16 * mt + L.col) * 96;
+            *reinterpret_cast<bf16x8 *>(G.w3 + f * 512 + lane * 8) = frag_at(src + 32 * ks + 8 * L.g);
+        }
+        __syncthreads();
+    }
 
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 g1[2], g2[3], g3[5], g4[3];
+    f32x4 g1[4], g2[5], g3[10], g4[5], gb2 = zero4, gb3 = zero4, gb4 = zero4;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        g1[i] = zero4;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        g2[i] = g4[i] = zero4;
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
+    for (int i = 0; i < 10; ++i) {
         g3[i] = zero4;
-    float pb1 = 0.0f, pb2 = 0.0f, pb3 = 0.0f, pb4 = 0.0f, pw5 = 0.0f, pb5 = 0.0f, ploss = 0.0f;
+        if (i < 5)
+            g2[i] = g4[i] = zero4;
+        if (i < 4)
+            g1[i] = zero4;
+    }
+    float pw5[4] = {0.0f, 0.0f, 0.0f, 0.0f}, pb5 = 0.0f, ploss = 0.0f;
 
-    for (int wi = blockIdx.x; wi < a.n; wi += gridDim.x) {
+    // The next window's bytes: position tid % 128, lines 4 (tid / 128) .. + 3,
+    // fetched a window ahead.  A load is four bytes from the pixel on; line 7's
+    // starts a byte early, so none leaves the window.
+    uint32_t raw[4];
+    auto fetch = [&](int wi) {
+        const int n = tid & 127, j0 = 4 * (tid >> 7);
+        const uint8_t *src =
+            a.win + (int64_t)wi * (kCnnLines * kCnnWin * 3) + j0 * (kCnnWin * 3) + 3 * n;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int back = j == 3 && j0 ? 1 : 0;
+            __builtin_memcpy(&raw[j], src + j * (kCnnWin * 3) - back, 4);
+            raw[j] >>= 8 * back;
+        }
+    };
+    const int w_begin = (int)((int64_t)blockIdx.x * a.n / gridDim.x);
+    const int w_end = (int)((int64_t)(blockIdx.x + 1) * a.n / gridDim.x);
+    if (w_begin < w_end)
+        fetch(w_begin);
+    for (int wi = w_begin; wi < w_end; ++wi) {
         const int lo = uniform_int(a.range[2 * wi]);
         const int hi = uniform_int(a.range[2 * wi + 1]);
-        load_window(s.x0, a.win + (int64_t)wi * (kCnnLines * kCnnWin * 3), lo, hi);
-        __syncthreads();
-        window_forward(W, s.fb, s.x0, s.h1, s.h2, s.h3, s.h4, s.z, lo, hi);
-
-        // loss and dL/dz at the central positions inside the strip
-        if (tid < kCnnWin) {
-            const int n = tid;
-            float dz = 0.0f;
-            if (n >= kCnnHalo && n < kCnnWin - kCnnHalo && n >= lo && n < hi) {
-                const int64_t j = (int64_t)wi * kCnnOut + (n - kCnnHalo);
-                const float wt = a.weight[j] * a.scale;
-                const float t = a.target[j];
-                const float z = s.z[n];
-                dz = wt * (sigmoid(z) - t);
-                // soft binary cross entropy in its logit form
-                ploss += wt * (fmaxf(z, 0.0f) - z * t + log1pf(expf(-fabsf(z))));
-            }
-            pb5 += dz;
-            s.z[n] = dz;
-        }
-        __syncthreads();
-        // layer 5 (1x1): dW5, and dP4 = [h4 > 0] w5 dz, in place of h4
         {
-            const int c = tid & 15;
-            const float w5 = s.fb[kCnnW5Off + c];
+            const int t = fresh(tid);
+            const int n = t & 127;
+            const bool in = n >= lo && n < hi;
+            bf16x4 o[3];
 #pragma unroll
-            for (int i = 0; i < kCnnWin * 16 / kBlock; ++i) {
-                const int n = (tid >> 4) + 16 * i;
-                const float h = (float)s.h4[(n + kCnnGuard) * 16 + c];
-                const float dz = s.z[n];
-                pw5 = fmaf(dz, h, pw5);
-                const __bf16 v = to_bf16(h > 0.0f ? w5 * dz : 0.0f);
-                s.h4[(n + kCnnGuard) * 16 + c] = v;
-                s.t[0][c * kCnnWin + n] = v;
+            for (int k = 0; k < 12; ++k) {
+                const float b = (float)((raw[k / 3] >> (8 * (k % 3))) & 0xFFu);
+                o[k >> 2][k & 3] = to_bf16(in ? fmaf(b, 1.0f / 64.0f, -2.0f) : 0.0f);
+            }
+            bf16x4 *dst =
+                reinterpret_cast<bf16x4 *>(G.x0 + (n + kCnnGuard) * 24 + 12 * (t >> 7));
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                dst[k] = o[k];
+        }
+        __syncthreads();
+        if (wi + 1 < w_end)
+            fetch(wi + 1);
+        // targets and loss weights of this lane's two positions (weight zero
+        // where a position carries no loss)
+        float tgt[2], lw[2], tops[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int n = 32 * wv + (lane & 15) + 16 * t;
+            const bool in = n >= lo && n < hi;
+            const bool has = in && n >= kCnnHalo && n < kCnnWin - kCnnHalo;
+            tops[t] = in ? __builtin_inff() : 0.0f;
+            const int64_t j = (int64_t)wi * kCnnOut + (has ? n - kCnnHalo : 0);
+            tgt[t] = a.target[j];
+            lw[t] = has ? a.weight[j] * a.scale : 0.0f;
+        }
+        // A fragment (mt, ks) of a layer's weights in global memory
+        auto weights = [&](const __bf16 *w, const Place &L, int kp, int mt, int ks) {
+            return frag_at(w + (16 * mt + L.col) * kp + 32 * ks + 8 * L.g);
+        };
+        {
+            // layer 1: 24 -> 16
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            f32x4 acc[2];
+            acc[0] = acc[1] = *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[0] + 4 * L.g);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8 w = weights(W + kCnnWOff[0], L, 128, 0, ks);
+                const __bf16 *x = G.x0 + (p0 + kCnnGuard - 2) * 24 + 32 * ks + 8 * L.g;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = mma(w, frag_at(x + 384 * t), acc[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                *reinterpret_cast<bf16x4 *>(G.h1 + act_off<16>(p0 + 16 * t + kCnnGuard, 4 * L.g)) =
+                    relu_bf16(acc[t], tops[t]);
+        }
+        __syncthreads();
+        {
+            // layer 2: 16 -> 32
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            f32x4 acc[2][2];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                acc[mt][0] = acc[mt][1] =
+                    *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[1] + 16 * mt + 4 * L.g);
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) {
+                const __bf16 *x =
+                    G.h1 + act_off<16>(p0 + kCnnGuard - 2 + 2 * ks + (L.g >> 1), 8 * (L.g & 1));
+                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 256);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const bf16x8 w = weights(W + kCnnWOff[1], L, 96, mt, ks);
+                    acc[mt][0] = mma(w, x0, acc[mt][0]);
+                    acc[mt][1] = mma(w, x1, acc[mt][1]);
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    *reinterpret_cast<bf16x4 *>(
+                        G.h2 + act_off<32>(p0 + 16 * t + kCnnGuard, 16 * mt + 4 * L.g)) =
+                        relu_bf16(acc[mt][t], tops[t]);
+        }
+        __syncthreads();
+        {
+            // layer 3: 32 -> 32
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            const int frag = (16 * L.g + L.col) * 8;
+            f32x4 acc[2][2];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                acc[mt][0] = acc[mt][1] =
+                    *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[2] + 16 * mt + 4 * L.g);
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                const __bf16 *x = G.h2 + act_off<32>(p0 + kCnnGuard - 2 + ks, 8 * L.g);
+                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 512);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const bf16x8 w = frag_at(G.w3 + (5 * mt + ks) * 512 + frag);
+                    acc[mt][0] = mma(w, x0, acc[mt][0]);
+                    acc[mt][1] = mma(w, x1, acc[mt][1]);
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    *reinterpret_cast<bf16x4 *>(
+                        G.h3 + act_off<32>(p0 + 16 * t + kCnnGuard, 16 * mt + 4 * L.g)) =
+                        relu_bf16(acc[mt][t], tops[t]);
+        }
+        __syncthreads();
+        {
+            // layer 4 (32 -> 16), the 1x1 layer, the loss and dP4: a position's
+            // 16 channels sit in the four lane groups of its column
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            f32x4 acc[2];
+            acc[0] = acc[1] = *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[3] + 4 * L.g);
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                const bf16x8 w = weights(W + kCnnWOff[3], L, 160, 0, ks);
+                const __bf16 *x = G.h3 + act_off<32>(p0 + kCnnGuard - 2 + ks, 8 * L.g);
+                acc[0] = mma(w, frag_at(x), acc[0]);
+                acc[1] = mma(w, frag_at(x + 512), acc[1]);
+            }
+            const f32x4 w5 = *reinterpret_cast<const f32x4 *>(G.fb + kCnnW5Off + 4 * L.g);
+            const float b5 = G.fb[kCnnW5Off + 16];
+            float zs[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const bf16x4 h = relu_bf16(acc[t], tops[t]);
+                float z = 0.0f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    z = fmaf(w5[j], (float)h[j], z);
+                z += __shfl_xor(z, 16, 64);
+                z += __shfl_xor(z, 32, 64);
+                z += b5;
+                zs[t] = z;
+                const float dz = lw[t] * (sigmoid(z) - tgt[t]);
+                pb5 += dz;    // every lane group alike; the first one's is taken
+                f32x4 dp;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    pw5[j] = fmaf((float)h[j], dz, pw5[j]);
+                    dp[j] = w5[j] * dz;
+                }
+                *reinterpret_cast<bf16x4 *>(G.d16 + act_off<16>(p0 + 16 * t + kCnnGuard, 4 * L.g)) =
+                    relu_mask(dp, h);
+            }
+            if (L.g < 2) {   // lane group t takes tile t's loss
+                // soft binary cross entropy in its logit form
+                const float z = L.g ? zs[1] : zs[0], tg = L.g ? tgt[1] : tgt[0];
+                ploss += (L.g ? lw[1] : lw[0])
+                         * (fmaxf(z, 0.0f) - z * tg + log1pf(expf(-fabsf(z))));
             }
         }
         __syncthreads();
-        // layer 4: 32 -> 16
-        weight_grad<32, 16, 160, 3>(g4, s.t[0], s.h3);
-        input_grad<16, 32, 96>(Wf + kCnnFOff[2], s.h4, s.h3, s.d32, s.t[1], lo, hi);
-        pb4 += bias_share<16>(s.t[0]);
-        __syncthreads();
-        // layer 3: 32 -> 32
-        weight_grad<32, 32, 160, 5>(g3, s.t[1], s.h2);
-        input_grad<32, 32, 160>(Wf + kCnnFOff[1], s.d32, s.h2, s.h3, s.t[0], lo, hi);
-        pb3 += bias_share<32>(s.t[1]);
-        __syncthreads();
-        // layer 2: 16 -> 32
-        weight_grad<16, 32, 96, 3>(g2, s.t[0], s.h1);
-        input_grad<32, 16, 160>(Wf + kCnnFOff[0], s.h3, s.h1, nullptr, s.t[1], lo, hi);
-        pb2 += bias_share<32>(s.t[0]);
-        __syncthreads();
-        // layer 1: 24 -> 16
-        weight_grad<24, 16, 128, 2>(g1, s.t[1], s.x0);
-        pb1 += bias_share<16>(s.t[1]);
-        __syncthreads();
-    }
-
-    float *out = a.partial + (int64_t)blockIdx.x * kCnnGradStride;
-    store_weight_grad<16, 128, 2>(g1, out + kCnnWOff[0]);
-    store_weight_grad<32, 96, 3>(g2, out + kCnnWOff[1]);
-    store_weight_grad<32, 160, 5>(g3, out + kCnnWOff[2]);
-    store_weight_grad<16, 160, 3>(g4, out + kCnnWOff[3]);
-
-    float *red = reinterpret_cast<float *>(&s.t[0][0]);   // 7 x 256 floats
-    red[0 * kBlock + tid] = pb1;
-    red[1 * kBlock + tid] = pb2;
-    red[2 * kBlock + tid] = pb3;
-    red[3 * kBlock + tid] = pb4;
-    red[4 * kBlock + tid] = pw5;
-    red[5 * kBlock + tid] = pb5;
-    red[6 * kBlock + tid] = ploss;
-    __syncthreads();
-    if (tid < 128) {
-        const int r = tid;
-        float v = 0.0f;
-        if (r < 16) {                       // b1: threads 16 r .. 16 r + 15
-            for (int i = 0; i < 16; ++i)
-                v += red[0 * kBlock + 16 * r + i];
-        } else if (r < 48) {                // b2: threads 8 o .. 8 o + 7
-            for (int i = 0; i < 8; ++i)
-                v += red[1 * kBlock + 8 * (r - 16) + i];
-        } else if (r < 80) {                // b3
-            for (int i = 0; i < 8; ++i)
-                v += red[2 * kBlock + 8 * (r - 48) + i];
-        } else if (r < 96) {                // b4
-            for (int i = 0; i < 16; ++i)
-                v += red[3 * kBlock + 16 * (r - 80) + i];
-        } else if (r < 112) {               // w5[c]: threads c + 16 i
-            for (int i = 0; i < 16; ++i)
-                v += red[4 * kBlock + (r - 96) + 16 * i];
-        } else if (r == 112 || r == 113) {  // b5, loss
-            for (int i = 0; i < kBlock; ++i)
-                v += red[(r == 112 ? 5 : 6) * kBlock + i];
+        const __bf16 one = to_bf16(1.0f);
+        const bf16x8 ones8 = {one, one, one, one, one, one, one, one};
+        {
+            // dP3 = [h3 > 0] (flipped W4 * dP4)
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            const int frag = (16 * L.g + L.col) * 8;
+            f32x4 acc[2][2];
+            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = zero4;
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) {
+                const __bf16 *x =
+                    G.d16 + act_off<16>(p0 + kCnnGuard - 2 + 2 * ks + (L.g >> 1), 8 * (L.g & 1));
+                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 256);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const bf16x8 w = frag_at(G.f4 + (3 * mt + ks) * 512 + frag);
+                    acc[mt][0] = mma(w, x0, acc[mt][0]);
+                    acc[mt][1] = mma(w, x1, acc[mt][1]);
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int o = act_off<32>(p0 + 16 * t + kCnnGuard, 16 * mt + 4 * L.g);
+                    *reinterpret_cast<bf16x4 *>(G.d3 + o) =
+                        relu_mask(acc[mt][t], *reinterpret_cast<const bf16x4 *>(G.h3 + o));
+                }
         }
-        out[kCnnWElems + r] = v;
+        {
+            // dW4: columns 80 half_t .. + 79 (tap = tile / 2, channels 16 (tile % 2) ..)
+            const Place L(fresh(lane));
+            const int r = 64 * half_n + L.r + kCnnGuard;
+            const __bf16 *d = G.d16 + act_off<16>(r, 4 * L.q);
+            int o[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                const int tile = 5 * half_t + i;
+                o[i] = act_off<32>(r - 2 + (tile >> 1), 16 * (tile & 1) + 4 * L.q);
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bf16x8 p = transposed(d + 512 * s, d + 512 * s + 256);
+#pragma unroll
+                for (int i = 0; i < 5; ++i)
+                    g4[i] = mma(p, transposed(G.h3 + o[i] + 1024 * s, G.h3 + o[i] + 1024 * s + 512),
+                                g4[i]);
+                gb4 = mma(p, ones8, gb4);
+            }
+        }
+        __syncthreads();
+        {
+            // dP2 = [h2 > 0] (flipped W3 * dP3)
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            const int frag = (16 * L.g + L.col) * 8;
+            f32x4 acc[2][2];
+            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = zero4;
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                const __bf16 *x = G.d3 + act_off<32>(p0 + kCnnGuard - 2 + ks, 8 * L.g);
+                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 512);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const bf16x8 w = frag_at(G.f3 + (5 * mt + ks) * 512 + frag);
+                    acc[mt][0] = mma(w, x0, acc[mt][0]);
+                    acc[mt][1] = mma(w, x1, acc[mt][1]);
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int o = act_off<32>(p0 + 16 * t + kCnnGuard, 16 * mt + 4 * L.g);
+                    *reinterpret_cast<bf16x4 *>(G.d2 + o) =
+                        relu_mask(acc[mt][t], *reinterpret_cast<const bf16x4 *>(G.h2 + o));
+                }
+        }
+        {
+            // dW3: output channels 16 half_t ..
+            const Place L(fresh(lane));
+            const int r = 64 * half_n + L.r + kCnnGuard;
+            const __bf16 *d = G.d3 + act_off<32>(r, 16 * half_t + 4 * L.q);
+            int o[10];
+#pragma unroll
+            for (int i = 0; i < 10; ++i)
+                o[i] = act_off<32>(r - 2 + (i >> 1), 16 * (i & 1) + 4 * L.q);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bf16x8 p = transposed(d + 1024 * s, d + 1024 * s + 512);
+#pragma unroll
+                for (int i = 0; i < 10; ++i)
+                    g3[i] = mma(p, transposed(G.h2 + o[i] + 1024 * s, G.h2 + o[i] + 1024 * s + 512),
+                                g3[i]);
+                gb3 = mma(p, ones8, gb3);
+            }
+        }
+        __syncthreads();
+        {
+            // dP1 = [h1 > 0] (flipped W2 * dP2)
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
+            f32x4 acc[2];
+            acc[0] = acc[1] = zero4;
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                const bf16x8 w = weights(Wf + kCnnFOff[0], L, 160, 0, ks);
+                const __bf16 *x = G.d2 + act_off<32>(p0 + kCnnGuard - 2 + ks, 8 * L.g);
+                acc[0] = mma(w, frag_at(x), acc[0]);
+                acc[1] = mma(w, frag_at(x + 512), acc[1]);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int o = act_off<16>(p0 + 16 * t + kCnnGuard, 4 * L.g);
+                *reinterpret_cast<bf16x4 *>(G.d16 + o) =
+                    relu_mask(acc[t], *reinterpret_cast<const bf16x4 *>(G.h1 + o));
+            }
+        }
+        {
+            // dW2: output channels 16 half_t .., a tile a tap
+            const Place L(fresh(lane));
+            const int r = 64 * half_n + L.r + kCnnGuard;
+            const __bf16 *d = G.d2 + act_off<32>(r, 16 * half_t + 4 * L.q);
+            int o[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                o[i] = act_off<16>(r - 2 + i, 4 * L.q);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bf16x8 p = transposed(d + 1024 * s, d + 1024 * s + 512);
+#pragma unroll
+                for (int i = 0; i < 5; ++i)
+                    g2[i] = mma(p, transposed(G.h1 + o[i] + 512 * s, G.h1 + o[i] + 512 * s + 256),
+                                g2[i]);
+                gb2 = mma(p, ones8, gb2);
+            }
+        }
+        __syncthreads();
+        {
+            // dW1: columns 64 half_t .. + 63 of the 120 (contiguous in the
+            // rows); columns 120 .. 127 read ones, the bias gradient
+            const Place L(fresh(lane));
+            const int r = 64 * half_n + L.r + kCnnGuard;
+            const __bf16 *d = G.d16 + act_off<16>(r, 4 * L.q);
+            const __bf16 *x = G.x0 + (r - 2) * 24 + 64 * half_t + 4 * L.q;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bf16x8 p = transposed(d + 512 * s, d + 512 * s + 256);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool one_col = i == 3 && half_t == 1 && L.q >= 2;
+                    const __bf16 *b = one_col ? G.ones : x + 16 * i + 768 * s;
+                    g1[i] = mma(p, transposed(b, one_col ? b : b + 384), g1[i]);
+                }
+            }
+        }
+        __syncthreads();
     }
+
+    // The workgroup's sums in a fixed order: half 1 of the positions through
+    // the LDS, added to half 0's; the 1x1 layer's and the loss over all waves.
+    float *sum = reinterpret_cast<float *>(&G);
+    float *bias = sum + kCnnWElems;            // [3][2][32]: b4, b3, b2 by half_t (32 slots)
+    float *tail = bias + 3 * 64;               // [4 waves][kGradTail]
+    const Place L(lane);
+    auto each = [&](auto fn) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = 4 * L.g + j;
+#pragma unroll
+            for (int i = 0; i < 10; ++i)
+                fn(kCnnWOff[2] + (16 * half_t + o) * 160 + 16 * i + L.col, g3[i][j]);
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                fn(kCnnWOff[3] + o * 160 + 16 * (5 * half_t + i) + L.col, g4[i][j]);
+                fn(kCnnWOff[1] + (16 * half_t + o) * 96 + 16 * i + L.col, g2[i][j]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                fn(kCnnWOff[0] + o * 128 + 16 * (4 * half_t + i) + L.col, g1[i][j]);
+        }
+    };
+#pragma unroll
+    for (int d = 1; d < 16; d *= 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            pw5[j] += __shfl_xor(pw5[j], d, 64);
+        pb5 += __shfl_xor(pb5, d, 64);
+        ploss += __shfl_xor(ploss, d, 64);
+    }
+    ploss += __shfl_xor(ploss, 16, 64);        // lane groups 0 and 1
+    if (L.col == 0)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            tail[kGradTail * wv + 4 * L.g + j] = pw5[j];
+    if (lane == 0) {
+        tail[kGradTail * wv + 16] = pb5;
+        tail[kGradTail * wv + 17] = ploss;
+    }
+    if (half_n == 1) {
+        each([&](int i, float v) { sum[i] = v; });
+        if (L.col == 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                bias[32 * half_t + 4 * L.g + j] = gb4[j];
+                bias[64 + 32 * half_t + 4 * L.g + j] = gb3[j];
+                bias[128 + 32 * half_t + 4 * L.g + j] = gb2[j];
+            }
+    }
+    __syncthreads();
+    float *out = a.partial + (int64_t)blockIdx.x * kCnnGradStride;
+    if (half_n == 0) {
+        each([&](int i, float v) { out[i] = v + sum[i]; });
+        if (L.col == 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int o = 4 * L.g + j;
+                float *b = out + kCnnWElems;
+                if (half_t == 0)
+                    b[kCnnBOff[3] + o] = gb4[j] + bias[o];
+                b[kCnnBOff[2] + 16 * half_t + o] = gb3[j] + bias[64 + 32 * half_t + o];
+                b[kCnnBOff[1] + 16 * half_t + o] = gb2[j] + bias[128 + 32 * half_t + o];
+            }
+        if (half_t == 1 && L.col == 8)         // column 120 of dW1
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int o = 4 * L.g + j;
+                out[kCnnWElems + kCnnBOff[0] + o] = g1[3][j] + sum[kCnnWOff[0] + o * 128 + 120];
+            }
+    }
+    if (tid < kGradTail)
+        out[kCnnWElems + kCnnW5Off + tid] =
+            (tail[tid] + tail[kGradTail + tid])
+            + (tail[2 * kGradTail + tid] + tail[3 * kGradTail + tid]);
+    else if (tid >= kCnnW5Off + kGradTail && tid < kCnnGradStride - kCnnWElems)
+        out[kCnnWElems + tid] = 0.0f;
 }
 
 // Parameter layout of the model file (float32): per layer W[o][c][t], b[o].
@@ -1035,7 +1188,7 @@ hipError_t launch_cnn_grad(const CnnTrainArgs &a, int grid, hipStream_t s)
 {
     if (grid <= 0)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_cnn_grad, dim3(grid), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_cnn_grad, dim3(grid), dim3(kBlock), sizeof(CnnGradLds), s, a);
     return hipGetLastError();
 }
 

@@ -21,14 +21,11 @@
 // activations are bfloat16, sums are float32 MFMA accumulators.
 #include "ca_cnn.h"
 #include "ca_launch.h"
+#include "ca_mfma.h"
 #include "ca_reduce.h"
 
 namespace ca {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPos = kC2Win + 2;   // positions of a buffer line, guards included
 constexpr int kC2Halo = 3;         // the network's receptive-field radius
@@ -37,9 +34,6 @@ constexpr int kTrainHalo = 8;      // training windows carry logits 8 .. 119
 constexpr int kTrainOut = kC2Win - 2 * kTrainHalo;
 constexpr int kC2Floats = 96;      // floats of the model's float block
 constexpr int kWaves = kBlock / 64;
-
-__device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }
 
 // LDS of the forward pass: input (7 lines, 8 channels: RGBXY and 3 zeros),
 // layer 1 (5 lines x 8), layer 2 (3 x 16), layer 3 (1 x 32), logits.
@@ -271,8 +265,6 @@ __device__ __forceinline__ uint32_t band_lines(int line, int extent)
     return ok;
 }
 
-__device__ __forceinline__ float sigmoid(float z) { return 1.0f / (1.0f + __expf(-z)); }
-
 // ----------------------------------------------------------- inference --
 
 // Learned candidates, wave level.  A workgroup takes one (frame, strip) item
@@ -364,17 +356,6 @@ __device__ __forceinline__ void wave_gemm3x3(const Frag<KP, MT> &F, const float 
             for (int mt = 0; mt < MT; ++mt)
                 epi(i, nt, mt, acc[nt][mt]);
     }
-}
-
-// ReLU and the frame / strip mask in one median: clamp to [0, +inf) where
-// the activation exists, to [0, 0] elsewhere; stored as bfloat16.
-__device__ __forceinline__ bf16x4 relu_bf16(const f32x4 &acc, float top)
-{
-    bf16x4 o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        o[j] = to_bf16(__builtin_amdgcn_fmed3f(acc[j], 0.0f, top));
-    return o;
 }
 
 // The 1x1 layer's weights this lane needs (its 8 of layer 3's 32 channels).
@@ -637,7 +618,8 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_windows(const uint8_t *model,
 // compute unit.  16-byte chunks of the 16- and 32-channel rows are permuted
 // by position (XOR), which spreads 16 rows over all banks.  Measured, 14,336
 // windows: 3137 us with the weight gradients as 4 x 4 outer products on the
-// vector units (723 work units a workgroup), 298 us so (kernel trace); of a SIMD's cycles
+// vector units (723 work units a workgroup), 295 us so (kernel trace); of a
+// SIMD's cycles
 // about half issue vector instructions and a fifth MFMAs.
 
 constexpr int kDW3 = 0;                        // [32][9 taps x 16]
@@ -675,48 +657,6 @@ __device__ __forceinline__ int off32(int pos, int c)
     return pos * 32 + ((((c >> 3) ^ (pos >> 2)) & 3) << 3) + (c & 7);
 }
 
-// Eight K values of one column of a position-major buffer: this lane's rows
-// (of 16) at p and at q, transposed over the lanes of its group of 16.
-__device__ __forceinline__ bf16x8 transposed(const __bf16 *p, const __bf16 *q)
-{
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
-    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p);
-    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)q);
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-__device__ __forceinline__ bf16x8 frag_at(const __bf16 *p)
-{
-    return *reinterpret_cast<const bf16x8 *>(p);
-}
-__device__ __forceinline__ f32x4 mma(const bf16x8 &a, const bf16x8 &b, const f32x4 &c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// The same value, which the compiler takes for a new one: offsets derived
-// from it are computed where they are used instead of being kept in registers
-// over the whole window loop (with the accumulators, they spilled).
-__device__ __forceinline__ int fresh(int v)
-{
-    asm("" : "+v"(v));
-    return v;
-}
-
-// A lane's place in its wave's 32 positions of a window.
-struct Place {
-    int col, g;    // column of a tile, lane group
-    int p0;        // its position in the wave's first tile
-    // transposed reads: rows 4 g + col / 4 (and 16 on), chunk q = col % 4
-    int q, r0;
-    __device__ __forceinline__ Place(int lane, int wv)
-        : col(lane & 15), g(lane >> 4), p0(32 * wv + col), q(col & 3),
-          r0(32 * wv + 4 * g + (col >> 2))
-    {
-    }
-};
-
 // f(k) of this lane's K group k = 4 ks + g (small numbers): a byte of a
 // constant, one bit-field extract.
 template <class F>
@@ -727,19 +667,6 @@ __device__ __forceinline__ int by_group(int ks, int g, F f)
     for (int i = 0; i < 4; ++i)
         packed |= (uint32_t)f(4 * ks + i) << (8 * i);
     return (int)((packed >> (8 * g)) & 0xFFu);
-}
-
-// v where the activation h is positive, else zero, as bfloat16.  h is a
-// ReLU's output, so positive means not all bits zero.
-__device__ __forceinline__ bf16x4 relu_mask(const f32x4 &v, const bf16x4 &h)
-{
-    typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
-    const u16x4 bits = __builtin_bit_cast(u16x4, h);
-    bf16x4 o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        o[j] = to_bf16(bits[j] != 0 ? v[j] : 0.0f);
-    return o;
 }
 
 __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
@@ -876,14 +803,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         }
         {
             // layer 1 by output-line pairs: lane groups 0-1 hold the first line
-            const Place L(fresh(lane), wv);
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
             const Frag<96, 1> w1 = load_frag<96, 1>(A + kC2P1);
             const f32x4 b1 = *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[0] + 4 * (L.g & 1));
             int o[3];   // K group k: line k / 3 of four, dl = k % 3
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks) {
                 o[ks] = by_group(ks, L.g, [](int k) { return k / 3; }) * kL8
-                        + (L.p0 + by_group(ks, L.g, [](int k) { return k % 3; })) * 8;
+                        + (p0 + by_group(ks, L.g, [](int k) { return k % 3; })) * 8;
             }
             // the last pair's fourth input line does not exist; its weights
             // are zero for the pair's first line and the second is dropped:
@@ -904,7 +832,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                 if (ln < 5)
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
-                        *reinterpret_cast<bf16x4 *>(G.h1 + ln * kL8 + (L.p0 + 16 * t + 1) * 8
+                        *reinterpret_cast<bf16x4 *>(G.h1 + ln * kL8 + (p0 + 16 * t + 1) * 8
                                                     + 4 * (L.g & 1)) =
                             relu_bf16(acc[t], line_in(line_ok, ln + 1) ? tops[t] : 0.0f);
             }
@@ -912,13 +840,14 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         const Frag<96, 1> w2 = load_frag<96, 1>(A + kC2A[1]);
         __syncthreads();
         {
-            const Place L(fresh(lane), wv);
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
             int o[3];   // K group k (of 9): da = k / 3, dl = k % 3
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks) {
                 // (groups 9 .. 11 have zero weights: any finite values)
                 o[ks] = by_group(ks, L.g, [](int k) { return k < 9 ? k / 3 : 0; }) * kL8
-                        + (L.p0 + by_group(ks, L.g, [](int k) { return k % 3; })) * 8;
+                        + (p0 + by_group(ks, L.g, [](int k) { return k % 3; })) * 8;
             }
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
@@ -933,7 +862,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
                     *reinterpret_cast<bf16x4 *>(G.h2 + i * kL16
-                                                + off16(L.p0 + 16 * t + 1, 4 * L.g)) =
+                                                + off16(p0 + 16 * t + 1, 4 * L.g)) =
                         relu_bf16(acc[t], line_in(line_ok, i + 2) ? tops[t] : 0.0f);
             }
         }
@@ -941,7 +870,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         {
             // layer 3, the 1x1 layer, the loss and dP3: a position's 32
             // channels sit in the four lane groups of its column
-            const Place L(fresh(lane), wv);
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
             const int frag = (L.g * 16 + L.col) * 8;
             f32x4 acc[2][2];
 #pragma unroll
@@ -954,7 +884,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                 // half k % 2
                 const __bf16 *x =
                     G.h2 + by_group(ks, L.g, [](int k) { return k < 18 ? k / 6 : 0; }) * kL16
-                    + off16(L.p0 + by_group(ks, L.g, [](int k) { return k / 2 % 3; }),
+                    + off16(p0 + by_group(ks, L.g, [](int k) { return k / 2 % 3; }),
                             8 * (L.g & 1));
                 const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 256);
 #pragma unroll
@@ -994,7 +924,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                         pw4[mt][j] = fmaf((float)h[mt][j], dz, pw4[mt][j]);
                         dp[j] = w4[mt][j] * dz;
                     }
-                    *reinterpret_cast<bf16x4 *>(G.d + off32(L.p0 + 16 * t + 1, 16 * mt + 4 * L.g)) =
+                    *reinterpret_cast<bf16x4 *>(G.d + off32(p0 + 16 * t + 1, 16 * mt + 4 * L.g)) =
                         relu_mask(dp, h[mt]);
                 }
             }
@@ -1011,12 +941,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         __syncthreads();
         {
             // dP2: output line i takes tap line 2 - i of the one dP3 line
-            const Place L(fresh(lane), wv);
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
             const int frag = (L.g * 16 + L.col) * 8;
             bf16x8 x[2][3];
 #pragma unroll
             for (int dl = 0; dl < 3; ++dl) {
-                const __bf16 *d = G.d + off32(L.p0 + dl, 8 * L.g);
+                const __bf16 *d = G.d + off32(p0 + dl, 8 * L.g);
                 x[0][dl] = frag_at(d);
                 x[1][dl] = frag_at(d + 512);
             }
@@ -1032,7 +963,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                 }
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    const int o = i * kL16 + off16(L.p0 + 16 * t + 1, 4 * L.g);
+                    const int o = i * kL16 + off16(p0 + 16 * t + 1, 4 * L.g);
                     *reinterpret_cast<bf16x4 *>(G.dp2 + o) =
                         relu_mask(acc[t], *reinterpret_cast<const bf16x4 *>(G.h2 + o));
                 }
@@ -1040,11 +971,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         }
         {
             // dW3
-            const Place L(fresh(lane), wv);
+            const Place L(fresh(lane));
+            const int r0 = 32 * wv + L.r;
             bf16x8 p[2];
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
-                const __bf16 *d = G.d + off32(L.r0 + 1, 16 * mt + 4 * L.q);
+                const __bf16 *d = G.d + off32(r0 + 1, 16 * mt + 4 * L.q);
                 p[mt] = transposed(d, d + 512);
                 const __bf16 one = to_bf16(1.0f);
                 accb3[mt] = mma(p[mt], bf16x8{one, one, one, one, one, one, one, one}, accb3[mt]);
@@ -1052,7 +984,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             int o[3];
 #pragma unroll
             for (int dl = 0; dl < 3; ++dl)
-                o[dl] = off16(L.r0 + dl, 4 * L.q);
+                o[dl] = off16(r0 + dl, 4 * L.q);
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap) {
                 const int dy = tap / 3, dx = tap % 3;
@@ -1069,12 +1001,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             // dP1 by output-line pairs (i0, i0 + 1) from dP2 lines i0 - 2 ..
             // i0 + 1 (K steps of lines that do not exist are left out, or
             // read as zeros where half a step exists)
-            const Place L(fresh(lane), wv);
+            const Place L(fresh(lane));
+            const int p0 = 32 * wv + L.col;
             int od[6];   // K group k: input line k / 6 of four, dl, half
 #pragma unroll
             for (int ks = 0; ks < 6; ++ks) {
                 od[ks] = by_group(ks, L.g, [](int k) { return k / 6; }) * kL16
-                         + off16(L.p0 + by_group(ks, L.g, [](int k) { return k % 6 / 2; }),
+                         + off16(p0 + by_group(ks, L.g, [](int k) { return k % 6 / 2; }),
                                  8 * (L.g & 1));
             }
 #pragma unroll
@@ -1098,7 +1031,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                 if (ln < 5)
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
-                        const int o = ln * kL8 + (L.p0 + 16 * t + 1) * 8 + 4 * (L.g & 1);
+                        const int o = ln * kL8 + (p0 + 16 * t + 1) * 8 + 4 * (L.g & 1);
                         *reinterpret_cast<bf16x4 *>(G.d + o) =
                             relu_mask(acc[t], *reinterpret_cast<const bf16x4 *>(G.h1 + o));
                     }
@@ -1108,14 +1041,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         // q < 2 and q >= 2 of the lane's reads); the tenth tap reads ones, its
         // columns are the bias gradients
         const int sy = hz ? kL8 : 8, sx = hz ? 8 : kL8;
-        auto tap_offset = [&](const Place &L, int t) {
+        auto tap_offset = [&](const Place &L, int r0, int t) {
             const int e = 2 * t, o = 2 * t + 1;
-            return L.r0 * 8 + 4 * (L.q & 1)
+            return r0 * 8 + 4 * (L.q & 1)
                    + (L.q >= 2 ? (o / 3) * sy + (o % 3) * sx : (e / 3) * sy + (e % 3) * sx);
         };
         {
-            const Place L(fresh(lane), wv);
-            const int o = off16(L.r0 + 1, 4 * L.q);
+            const Place L(fresh(lane));
+            const int r0 = 32 * wv + L.r;
+            const int o = off16(r0 + 1, 4 * L.q);
             bf16x8 p[3];
 #pragma unroll
             for (int r = 0; r < 3; ++r)
@@ -1123,7 +1057,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 #pragma unroll
             for (int t = 0; t < 5; ++t) {
                 const bool ones = t == 4 && L.q >= 2;
-                const __bf16 *x = ones ? G.ones : G.h1 + tap_offset(L, t);
+                const __bf16 *x = ones ? G.ones : G.h1 + tap_offset(L, r0, t);
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
                     const __bf16 *xr = ones ? x : x + r * kL8;
@@ -1134,8 +1068,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         __syncthreads();
         {
             // rows 8 .. 15 of dW1's tiles repeat rows 0 .. 7
-            const Place L(fresh(lane), wv);
-            const int o = (L.r0 + 1) * 8 + 4 * (L.q & 1);
+            const Place L(fresh(lane));
+            const int r0 = 32 * wv + L.r;
+            const int o = (r0 + 1) * 8 + 4 * (L.q & 1);
             bf16x8 p[5];
 #pragma unroll
             for (int r = 0; r < 5; ++r)
@@ -1143,7 +1078,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 #pragma unroll
             for (int t = 0; t < 5; ++t) {
                 const bool ones = t == 4 && L.q >= 2;
-                const __bf16 *x = ones ? G.ones : G.x0 + tap_offset(L, t);
+                const __bf16 *x = ones ? G.ones : G.x0 + tap_offset(L, r0, t);
 #pragma unroll
                 for (int r = 0; r < 5; ++r) {
                     const __bf16 *xr = ones ? x : x + r * kL8;
