@@ -388,10 +388,10 @@ void ca_graph_destroy(ca_graph *graph);
                                       every frame shape; 0 (default) = the autotuned value
                                       of each shape (ca_autotune), else 1 */
 #define CA_OPT_RANSAC_LANES 8  /* split: lanes per RANSAC attempt, 2, 4, 8 or 16 (a
-                                  workgroup takes 256 / lanes attempts); 0 (default) = the
-                                  fewest lanes that give the batch at least one attempt
-                                  workgroup per compute unit, at most 8.  Results do
-                                  not depend on it. */
+                                  workgroup takes 256 / lanes attempts; 8 and 16 are taken
+                                  as 4); 0 (default) = the fewest of 1, 2 and 4 that give
+                                  the batch at least one attempt workgroup per compute
+                                  unit.  Results do not depend on it. */
 #define CA_SCHEDULE_SPLIT 0    /* per (sub-)batch two launches: strip scoring, then RANSAC
                                   whose last group per frame selects the circle */
 #define CA_SCHEDULE_FUSED 1    /* one persistent launch drawing both kinds of work from

@@ -155,7 +155,7 @@ int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const c
     pl->t_iota = p.t_iota;
     pl->P = 2 * S;
     pl->groups = ca::attempt_groups(p.ransac_attempts, ca::kLanesPerAttempt);
-    pl->rec_groups = ca::attempt_groups(p.ransac_attempts, ca::kMaxLanesPerAttempt);
+    pl->rec_groups = ca::attempt_groups(p.ransac_attempts, ca::kRecordLanes);
     pl->sg_len = sg_len;
     // distinct frame shapes in order of first appearance
     int32_t n_shapes = 0, longest = 0;
@@ -354,19 +354,17 @@ hipError_t launch_class_strips(const ca::StripArgs &base, const Plan *pl,
     return ca::launch_strips(a, pl->lds, st);
 }
 
-// Lanes per RANSAC attempt of an n-frame split call: the fewest that give
-// at least one attempt workgroup per compute unit (a small batch otherwise
-// leaves most of the device idle), at most 8 (measured on 8 x 640x480 with
-// 256 attempts: 16.5, 14.4, 13.5 and 15.4 us per launch at 2, 4, 8 and 16
-// lanes; beyond 8 the per-attempt solves repeated on every lane cost more
-// than the shorter point loops save).
+// Lanes per RANSAC attempt of an n-frame split call: the fewest that give at
+// least one attempt workgroup per compute unit (a small batch otherwise leaves
+// most of the device idle).  Measured per launch: 64 x 1080p with 1024 attempts
+// 15.5, 18.1 and 22.1 us at 1, 2 and 4 lanes; 8 x 640x480 with 256 attempts
+// 10.3 and 9.8 us at 2 and 4.
 int32_t ransac_lanes(const ca_ctx *ctx, int32_t n, int32_t attempts)
 {
     if (ctx->ransac_lanes > 0)
-        return (int32_t)ctx->ransac_lanes;
-    constexpr int32_t kAutoMaxLanes = 8;
-    int32_t lanes = ca::kLanesPerAttempt;
-    while (lanes < kAutoMaxLanes
+        return (int32_t)std::min<int64_t>(ctx->ransac_lanes, ca::kMaxLanesPerAttempt);
+    int32_t lanes = 1;
+    while (lanes < ca::kMaxLanesPerAttempt
            && (int64_t)n * ca::attempt_groups(attempts, lanes) < (int64_t)ctx->n_cu)
         lanes *= 2;
     return lanes;

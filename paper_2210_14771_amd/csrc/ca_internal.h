@@ -12,9 +12,12 @@ namespace ca {
 constexpr int kBlock = 256;      // threads per workgroup (k_strips_pair: two strips, 2 kBlock)
 constexpr size_t kPairLdsMax = 65536;  // LDS bytes the paired strip kernel may take
 constexpr int kHalfThreads = 128; // threads per half strip
-constexpr int kLanesPerAttempt = 2;   // lanes sharing one RANSAC attempt (fused schedule, and
-                                      // the split schedule when a batch fills the device)
-constexpr int kMaxLanesPerAttempt = 16;  // small batches spread attempts over more workgroups
+// Lanes that compute on one RANSAC attempt (its triple and its solves; the
+// inlier passes are tiles of 16 attempts): 1, 2 or 4, that is 4, 2 or 1 tiles a
+// wavefront and 256, 128 or 64 attempts a workgroup.
+constexpr int kLanesPerAttempt = 4;   // fused schedule (two tiles a wavefront spill beside the strips)
+constexpr int kMaxLanesPerAttempt = 4;   // small batches spread attempts over more workgroups
+constexpr int kRecordLanes = 16;      // the plan's record array is laid out for 16 lanes
 // Attempt groups (workgroups) per frame with `lanes` lanes per attempt.
 inline int attempt_groups(int attempts, int lanes) { return (attempts * lanes + kBlock - 1) / kBlock; }
 constexpr int kChunk = 8;        // most pixels one thread scores per pass (a 1920-pixel line in one pass)
@@ -75,7 +78,7 @@ struct RansacArgs {
     int32_t refine;
     int32_t sampler;
     int32_t groups;         // attempt groups (workgroups of kBlock / lanes attempts) per frame
-    int32_t lanes;          // lanes per attempt: 2, 4, 8 or 16
+    int32_t lanes;          // lanes per attempt: 1, 2 or 4
     int32_t frame0;         // first frame of this launch (blockIdx.y counts from it)
     uint32_t *groups_done;  // per frame: groups finished (the last one selects), or null
     const ca_result *keep = nullptr;   // as in StripArgs: frames to skip

@@ -8,8 +8,10 @@
 //               and the argmax -- the two operations the paper singles out as
 //               needing block-wide cooperation (Section 2.2.6) -- are wave64
 //               shuffle scans/reductions joined through LDS.
-//   RANSAC item (frame, group of 256 attempts): one thread per attempt; the
-//               kept points are compacted into LDS and read by broadcast.
+//   RANSAC item (frame, group of attempts): the kept points are compacted into
+//               LDS; tiles of 16 attempts are tested against 16 points at a
+//               time, and their inliers' moments summed, by matrix
+//               instructions; a lane solves for each attempt.
 //   selection   (frame): merge the best attempt of every group; done by the
 //               group that finishes last.
 //
@@ -30,7 +32,7 @@
 // integer luma and Sobel, exact integer quantisers for |g| and the angle,
 // float32 table lookups and products in a fixed order, float64 circle
 // arithmetic without contraction (build with -ffp-contract=off), integer
-// inlier moments (summed here in float64, exact below 2^53).
+// inlier moments (summed here exactly, as 8-bit digits).
 #include "ca_internal.h"
 #include "ca_launch.h"
 
@@ -450,15 +452,35 @@ __device__ void strip_work(const StripArgs &a, const StripLds &c, int f, int s, 
 
 // ------------------------------------------------------------ RANSAC ------
 
-// Kept points of one frame in LDS, compacted in canonical order and padded
-// to a multiple of the lanes per attempt with far-away points whose moments
-// are zero (never inside a band, so they add nothing).
+// Kept points of one frame in LDS, compacted in canonical order, and what the
+// matrix instructions need of them.  The inlier passes are contractions over
+// the points: squared distances (K = 4 features of a point, float32), then the
+// inlier moments W M, where W is the 0/1 inlier matrix (attempts x points) and
+// M the points' moments, integers split into signed 8-bit digits, so that
+// v_mfma_i32_16x16x64_i8 sums them exactly.
+//
+// A digit block holds 64 points: row (moment digit) r of lane group g is the
+// 16 bytes of points 64 c + 16 t + 4 g + j (t, j < 4), the order in which a
+// lane of the distance tiles holds its points.
+//   rows  0.. 3  u (2 digits), v (2)      rows 16..19  count (1 digit)
+//   rows  4.. 7  u^2                      rows 20..23  u v
+//   rows  8..11  v^2                      rows 24..27  digits 4, 5 of u z and of v z
+//   rows 12..15  digits 0..3 of u z       rows 28..31  digits 0..3 of v z
+// with z = u^2 + v^2; |u|, |v| <= 8192 (frames of at most 16384), so 4 digits
+// hold u^2, u v, v^2 and 6 hold u z, v z.  The final pass has rows of its own:
+// 0..3 the score units Q = floor(score 2^24), 4 the count.
+constexpr int kPointBlocks = kBlock / 64;
+constexpr int kDigitRows = 32;
+constexpr int kFinalRows = 8;
+
+// T tiles of 16 attempts per wavefront, X of them exchanged at a time.
+template <int X>
 struct Lds {
-    double2 uv[kBlock];     // shifted coordinates u, v
-    double2 m1[kBlock];     // u^2, u v
-    double2 m2[kBlock];     // v^2, floor(score * 2^24)
-    double2 m3[kBlock];     // u z, v z  (z = u^2 + v^2)
-    int iu[kBlock], iv[kBlock];
+    float feat[4][kBlock];                               // z, u, v, 1
+    int8_t digit[kPointBlocks * 4][kDigitRows][16];      // [block, lane group]
+    int8_t fin[kPointBlocks * 4][kFinalRows][16];
+    int4 xch[4][X * 64];       // per wavefront: digit sums [attempt][lane group], then the
+                               // attempts' distance features and bounds
     int wcount[4];
     uint64_t wbest[4];
 };
@@ -490,11 +512,10 @@ __device__ __forceinline__ int below(uint64_t u, int k)
     return (int)(((u >> 32) * (uint64_t)(uint32_t)k) >> 32);
 }
 
-__device__ bool pick_triple(const RansacArgs &a, uint64_t uid, int att, int n, int t[3])
+// The attempt's point indices; c: its Philox words (the random sampler).
+__device__ bool pick_triple(const RansacArgs &a, const uint64_t c[4], int att, int n, int t[3])
 {
     if (a.sampler == 0) {
-        uint64_t c[4] = {(uint64_t)(uint32_t)att, uid, 0, 0};
-        philox4x64_10(c, a.seed, 0);
         const int i0 = below(c[0], n);
         int i1 = below(c[1], n - 1);
         i1 += i1 >= i0;
@@ -551,72 +572,19 @@ __device__ __forceinline__ Band make_band(double cx, double cy, double r2, doubl
     return b;
 }
 
-// Sum over the lanes of one attempt (adjacent lanes of a quad).  The partial
-// sums are integers below 2^53, so every order gives the same exact total.
-template <int kCtrl>
-__device__ __forceinline__ double quad_xor(double v)
+// The inlier test of the method: (r - t)^2 <= d^2 <= (r + t)^2 in float64.
+__device__ __forceinline__ bool in_band(double u, double v, const Band &b)
 {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-template <int LANES>
-__device__ __forceinline__ double lane_sum(double v)
-{
-    static_assert(LANES == 2 || LANES == 4 || LANES == 8 || LANES == 16, "attempt lanes");
-    v += quad_xor<0xB1>(v);  // quad_perm [1, 0, 3, 2]
-    if (LANES >= 4)
-        v += quad_xor<0x4E>(v);  // quad_perm [2, 3, 0, 1]
-    if (LANES >= 8)
-        v += __shfl_xor(v, 4, 64);
-    if (LANES >= 16)
-        v += __shfl_xor(v, 8, 64);
-    return v;
-}
-
-__device__ __forceinline__ double in_band(const double2 p, const Band &b)
-{
-    const double du = p.x - b.cx;
-    const double dv = p.y - b.cy;
+    const double du = u - b.cx;
+    const double dv = v - b.cy;
     const double d2 = du * du + dv * dv;
-    return (b.lo2 <= d2 && d2 <= b.hi2) ? 1.0 : 0.0;
+    return b.lo2 <= d2 && d2 <= b.hi2;
 }
 
 // Inlier moments of one band: count, sum u, v, u^2, u v, v^2, u z, v z.
 struct Moments {
     double m, su, sv, suu, suv, svv, suz, svz;
 };
-
-// Lane `sub` of the attempt takes points sub, sub + LANES, ...;
-// nk = padded point count / LANES (wave-uniform).
-template <int LANES>
-__device__ Moments band_moments(const Lds &L, int nk, int sub, const Band &b)
-{
-    Moments s = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int k = 0; k < nk; ++k) {
-        const int i = k * LANES + sub;
-        const double2 p = L.uv[i];
-        const double w = in_band(p, b);
-        const double2 m1 = L.m1[i], m2 = L.m2[i], m3 = L.m3[i];
-        s.m += w;
-        s.su = fma(w, p.x, s.su);
-        s.sv = fma(w, p.y, s.sv);
-        s.suu = fma(w, m1.x, s.suu);
-        s.suv = fma(w, m1.y, s.suv);
-        s.svv = fma(w, m2.x, s.svv);
-        s.suz = fma(w, m3.x, s.suz);
-        s.svz = fma(w, m3.y, s.svz);
-    }
-    s.m = lane_sum<LANES>(s.m);
-    s.su = lane_sum<LANES>(s.su);
-    s.sv = lane_sum<LANES>(s.sv);
-    s.suu = lane_sum<LANES>(s.suu);
-    s.suv = lane_sum<LANES>(s.suv);
-    s.svv = lane_sum<LANES>(s.svv);
-    s.suz = lane_sum<LANES>(s.suz);
-    s.svz = lane_sum<LANES>(s.svz);
-    return s;
-}
 
 // Coope least-squares circle from the inlier moments (Section 2.2.5).  The
 // centred sums C = m S_ab - S_a S_b are integers; with kExact (every product
@@ -660,83 +628,389 @@ __device__ bool coope_solve(const Moments &s, double &cx, double &cy, double &r2
     return true;
 }
 
-// One attempt (Section 2.2.5): draw a triple, circle through it, `refine`
-// inlier passes with least-squares refits, then count the inliers and their
-// score sum and apply the circle limits.  `key` is set for kept circles (on
-// the attempt's first lane).
-template <bool kExact, int LANES>
-__device__ void run_attempt(const RansacArgs &a, const Lds &L, const FrameDev &d, int n, int nk,
-                            int sub, int att, bool active, ca_attempt &rec, uint64_t &key)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// LDS written by some lanes of a wave and read by others next: keep the
+// compiler from moving memory operations across (the hardware keeps a wave's
+// LDS operations in order).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The float32 form of an attempt's inlier test.  d^2 - mid = z - 2 cx u - 2 cy
+// v + (|c|^2 - mid), with mid and half the middle and half width of
+// [lo2, hi2]: its absolute value less half, e, is negative inside the band.
+// |e| > E decides; otherwise, and for larger circles and values that are not
+// numbers, the float64 test does, so every decision is the float64 one.
+// E bounds what float32 loses, with u = 2^-24 and S the sum of the terms'
+// largest absolute values Z = U^2 + V^2, A, B, K: the coefficients are rounded
+// once (u (A + B + K), and z beyond 2^24 u Z), and the matrix unit forms the
+// sum as a chain of fused multiply-adds from z on (u (Z + A) + u (Z + A + B) +
+// u half): below 3 u S + u half together.  A fourth u S covers float64's own
+// roundings of |c|^2, mid and d^2, together below 2^-48 (|c|^2 + Z): with m the
+// smaller of U and V, |c| <= S / (2 m), so S < 2^26 m^2 keeps them below it.
+struct Quick {
+    float x, y, k;     // features of u, v and 1
+    float half, E;
+};
+
+__device__ __forceinline__ Quick quick_test(const Band &b, bool on, float U, float V)
+{
+    Quick q = {0.0f, 0.0f, 0.0f, -1.0f, -1.0f};   // off: every point is outside
+    const double mid = 0.5 * (b.lo2 + b.hi2);
+    const float half = (float)(0.5 * (b.hi2 - b.lo2));
+    const float x = (float)(-2.0 * b.cx), y = (float)(-2.0 * b.cy);
+    const float k = (float)((b.cx * b.cx + b.cy * b.cy) - mid);
+    const float S = (U * U + V * V) + fabsf(x) * U + fabsf(y) * V + fabsf(k);
+    const float m = fminf(U, V);
+    if (on && S < 0x1p26f * m * m) {
+        q.x = x;
+        q.y = y;
+        q.k = k;
+        q.half = half;
+        q.E = 0x1p-22f * S + 0x1p-21f * half;
+    } else if (on) {
+        q.E = __builtin_inff();
+    }
+    return q;
+}
+
+// One wavefront's T tiles of 16 attempts.  Lane l computes on attempt
+// l % (16 T) (the random triple, the solves; lanes repeat each other for T <
+// 4); in the matrix tiles its column is attempt 16 t + l % 16 of tile t.
+// U, V: the largest |u|, |v| of the frame.
+template <int T, int X>
+struct AttemptWave {
+    static_assert(T == 1 || T == 2 || T == 4, "lane l computes on attempt l % (16 T)");
+    static_assert(T % X == 0 && 16 * T * 24 <= X * 1024, "features fit the exchange buffer");
+    Lds<X> &L;
+    const int lane, wv, n;       // n: points (uniform)
+
+    // Four points (d: this lane's column of a distance tile) against a band: a
+    // byte -1 for each inlier, 0 for the others; least: the smallest |e|.  Four tests are four subtractions, two minima, two byte permutes
+    // that spread the sign bits and an or: nothing passes through the scalar
+    // unit, whose round trips cost more than the tests (with two compares a
+    // test there 25 us a launch of 64 frames x 1024 attempts instead of 15.5).
+    static __device__ __forceinline__ uint32_t inside4(const f32x4 &d, float half, float &least)
+    {
+        uint32_t s[4];
+        least = __builtin_inff();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float e = fabsf(d[j]) - half;
+            least = fminf(least, fabsf(e));
+            s[j] = __float_as_uint(e);
+        }
+        // selector 9 (11): the sign of the second (first) operand, spread over
+        // a byte; 12: zero
+        return __builtin_amdgcn_perm(s[1], s[0], 0x0C0C0B09u)
+               | __builtin_amdgcn_perm(s[3], s[2], 0x0B090C0Cu);
+    }
+
+    // The float64 test, for those 16-point groups p of block c in which some
+    // point is too close (least[p] <= E) to the edge of some band of tile t;
+    // w: the float32 decisions, replaced there.  (When a frame's attempts agree
+    // on a circle with such a point, they all come here.)
+    __device__ __forceinline__ void settle(i32x4 &w, const float (&least)[4], float E, int c, int t,
+                                           const Band &own)
+    {
+        Band b = own;
+        if (T > 1) {
+            const int src = 16 * t + (lane & 15);
+            b.cx = __shfl(own.cx, src, 64);
+            b.cy = __shfl(own.cy, src, 64);
+            b.lo2 = __shfl(own.lo2, src, 64);
+            b.hi2 = __shfl(own.hi2, src, 64);
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (!__any(least[p] <= E))
+                continue;
+            const int i = 64 * c + 16 * p + 4 * (lane >> 4);
+            uint32_t v = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v |= in_band((double)L.feat[1][i + j], (double)L.feat[2][i + j], b) ? 0xFFu << (8 * j)
+                                                                                    : 0u;
+            w[p] = E >= 0.0f ? (int)v : 0;   // E < 0: no attempt in this column
+        }
+    }
+
+    // Publish this lane's attempt's test and run one inlier pass over all
+    // points: acc[t] receives minus tile t's digit sums (rows 4 (lane / 16) ..
+    // of attempt 16 t + lane % 16).  kFinal: the final pass's rows.
+    template <bool kFinal>
+    __device__ __forceinline__ void pass(const Band &own, bool on, float U, float V,
+                                         i32x4 (&acc)[T][kFinal ? 1 : 2])
+    {
+        const int col = lane & 15, g = lane >> 4;
+        const Quick q = quick_test(own, on, U, V);
+        float b[T], half[T], E[T];
+        if (T == 1) {   // this lane's column is its own attempt
+            b[0] = g == 0 ? 1.0f : g == 1 ? q.x : g == 2 ? q.y : q.k;
+            half[0] = q.half;
+            E[0] = q.E;
+        } else {
+            float *feat = reinterpret_cast<float *>(L.xch[wv]);   // [16 T][4]
+            float2 *bound = reinterpret_cast<float2 *>(feat + 64 * T);
+            wave_sync();
+            if (lane < 16 * T) {
+                reinterpret_cast<float4 *>(feat)[lane] = make_float4(1.0f, q.x, q.y, q.k);
+                bound[lane] = make_float2(q.half, q.E);
+            }
+            wave_sync();
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                b[t] = feat[(16 * t + col) * 4 + g];
+                half[t] = bound[16 * t + col].x;
+                E[t] = bound[16 * t + col].y;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            acc[t][0] = i32x4{0, 0, 0, 0};
+            if (!kFinal)
+                acc[t][kFinal ? 0 : 1] = i32x4{0, 0, 0, 0};
+        }
+#pragma unroll 1
+        for (int c = 0; 64 * c < n; ++c) {
+            float a[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                a[p] = L.feat[g][64 * c + 16 * p + col];
+            i32x4 m[kFinal ? 1 : 2];
+            if (kFinal) {
+                m[0] = *reinterpret_cast<const i32x4 *>(L.fin[4 * c + g][col & (kFinalRows - 1)]);
+            } else {
+                m[0] = *reinterpret_cast<const i32x4 *>(L.digit[4 * c + g][col]);
+                m[kFinal ? 0 : 1] =
+                    *reinterpret_cast<const i32x4 *>(L.digit[4 * c + g][16 + col]);
+            }
+            // a tile's distances are formed between the tests of the one before
+            auto distance = [&](int t, int p) {
+                return __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    a[p], b[t], f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            };
+            f32x4 d[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                d[p] = distance(0, p);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                i32x4 w;
+                float least[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    w[p] = (int)inside4(d[p], half[t], least[p]);
+                    if (t + 1 < T)
+                        d[p] = distance(t + 1, p);
+                }
+                if (__any(fminf(fminf(least[0], least[1]), fminf(least[2], least[3])) <= E[t]))
+                    settle(w, least, E[t], c, t, own);
+#pragma unroll
+                for (int k = 0; k < (kFinal ? 1 : 2); ++k)
+                    acc[t][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], w, acc[t][k], 0, 0, 0);
+            }
+        }
+    }
+
+    // Hand every tile's sums to the lanes that compute on its attempts: fn
+    // receives the four lane groups' words of this lane's attempt.
+    template <class Pack, class Fn>
+    __device__ __forceinline__ void exchange(Pack pack, Fn fn)
+    {
+        const int col = lane & 15, g = lane >> 4;
+        int4 *x = L.xch[wv];
+#pragma unroll
+        for (int t0 = 0; t0 < T; t0 += X) {
+            wave_sync();
+#pragma unroll
+            for (int t = t0; t < t0 + X; ++t)
+                x[(t - t0) * 64 + col * 4 + g] = pack(t);
+            wave_sync();
+            const int t = (lane >> 4) & (T - 1);
+            if (t >= t0 && t < t0 + X) {
+                const int4 *s = x + (t - t0) * 64 + col * 4;
+                fn(s[0], s[1], s[2], s[3]);
+            }
+        }
+    }
+};
+
+// Two adjacent digits' sums (each below 2^15 in size, negated) as one word.
+__device__ __forceinline__ int digit_pair(int lo, int hi) { return -(lo + hi * 256); }
+__device__ __forceinline__ double digits4(int lo, int hi)
+{
+    return fma(65536.0, (double)hi, (double)lo);
+}
+
+// Attempts (Section 2.2.5) of one wavefront: draw a triple, circle through it,
+// `refine` inlier passes with least-squares refits, then count the inliers and
+// their score sum and apply the circle limits.  `key` is set for kept circles
+// (on the attempt's first lane).  c: Philox words of this lane's attempt.
+template <int T, int X>
+__device__ void run_attempts(const RansacArgs &a, Lds<X> &L, const FrameDev &d, int n, int lane,
+                             int wv, bool exact, const uint64_t c[4], int att, bool active,
+                             ca_attempt &rec, uint64_t &key)
 {
     const int ox = d.W / 2, oy = d.H / 2;
-    if (n >= 3 && active) {
+    const float U = (float)(ox > d.W - 1 - ox ? ox : d.W - 1 - ox);
+    const float V = (float)(oy > d.H - 1 - oy ? oy : d.H - 1 - oy);
+    AttemptWave<T, X> wave{L, lane, wv, n};
+    bool ok = false;
+    double cx = 0, cy = 0, r2 = 0;
+    if (active) {
         int t[3];
-        if (!pick_triple(a, d.uid, att, n, t)) {
+        if (!pick_triple(a, c, att, n, t)) {
             rec.i0 = rec.i1 = rec.i2 = -1;
             rec.fail_stage = -1;
         } else {
             rec.i0 = t[0];
             rec.i1 = t[1];
             rec.i2 = t[2];
-            const int64_t x0 = L.iu[t[0]], x1 = L.iu[t[1]], x2 = L.iu[t[2]];
-            const int64_t y0 = L.iv[t[0]], y1 = L.iv[t[1]], y2 = L.iv[t[2]];
-            const int64_t D = 2 * (x0 * (y1 - y2) + x1 * (y2 - y0) + x2 * (y0 - y1));
-            bool ok = D != 0;
-            double cx = 0, cy = 0, r2 = 0;
+            // |x|, |y| <= 2^13: first-order terms fit 32 bits
+            const int x0 = (int)L.feat[1][t[0]], x1 = (int)L.feat[1][t[1]], x2 = (int)L.feat[1][t[2]];
+            const int y0 = (int)L.feat[2][t[0]], y1 = (int)L.feat[2][t[1]], y2 = (int)L.feat[2][t[2]];
+            const int D = 2 * (x0 * (y1 - y2) + x1 * (y2 - y0) + x2 * (y0 - y1));
+            ok = D != 0;
             if (ok) {
-                const int64_t z0 = x0 * x0 + y0 * y0, z1 = x1 * x1 + y1 * y1, z2 = x2 * x2 + y2 * y2;
-                const int64_t Nx = z0 * (y1 - y2) + z1 * (y2 - y0) + z2 * (y0 - y1);
-                const int64_t Ny = z0 * (x2 - x1) + z1 * (x0 - x2) + z2 * (x1 - x0);
+                const int z0 = x0 * x0 + y0 * y0, z1 = x1 * x1 + y1 * y1, z2 = x2 * x2 + y2 * y2;
+                const int64_t Nx = (int64_t)z0 * (y1 - y2) + (int64_t)z1 * (y2 - y0)
+                                   + (int64_t)z2 * (y0 - y1);
+                const int64_t Ny = (int64_t)z0 * (x2 - x1) + (int64_t)z1 * (x0 - x2)
+                                   + (int64_t)z2 * (x1 - x0);
                 cx = (double)Nx / (double)D;
                 cy = (double)Ny / (double)D;
                 const double ddx = (double)x0 - cx, ddy = (double)y0 - cy;
                 r2 = ddx * ddx + ddy * ddy;
-                for (int k = 1; k <= a.refine; ++k) {
-                    const Band bd = make_band(cx, cy, r2, a.t_ri);
-                    if (!coope_solve<kExact>(band_moments<LANES>(L, nk, sub, bd), cx, cy, r2)) {
-                        rec.fail_stage = k;
-                        ok = false;
-                        break;
-                    }
-                }
-            }
-            if (ok) {
-                const Band bd = make_band(cx, cy, r2, a.t_ri);
-                double cnt = 0, qs = 0;
-                for (int k = 0; k < nk; ++k) {
-                    const int i = k * LANES + sub;
-                    const double w = in_band(L.uv[i], bd);
-                    cnt += w;
-                    qs = fma(w, L.m2[i].y, qs);
-                }
-                cnt = lane_sum<LANES>(cnt);
-                qs = lane_sum<LANES>(qs);
-                const double acx = (double)ox + cx;
-                const double acy = (double)oy + cy;
-                const double r = sqrt(r2);
-                const double ex = acx - (double)(d.W - 1) / 2.0;
-                const double ey = acy - (double)(d.H - 1) / 2.0;
-                const double dlim = a.d_max * (double)d.W;
-                const bool kept = r >= a.r_min * (double)d.W && r <= a.r_max * (double)d.W
-                                  && ex * ex + ey * ey <= dlim * dlim;
-                rec.status = kept ? 2 : 1;
-                rec.inliers = (int32_t)cnt;
-                rec.qsum = (uint64_t)qs;
-                rec.cx = acx;
-                rec.cy = acy;
-                rec.r2 = r2;
-                if (kept && sub == 0)
-                    key = (rec.qsum << 16) | (uint64_t)(0xFFFFu - (uint32_t)att);
             }
         }
     }
+    for (int k = 1; k <= a.refine; ++k) {
+        if (!__any(ok))
+            break;
+        i32x4 acc[T][2];
+        wave.template pass<false>(make_band(cx, cy, r2, a.t_ri), ok, U, V, acc);
+        Moments s;
+        wave.exchange(
+            [&](int t) {
+                return make_int4(digit_pair(acc[t][0][0], acc[t][0][1]),
+                                 digit_pair(acc[t][0][2], acc[t][0][3]),
+                                 digit_pair(acc[t][1][0], acc[t][1][1]),
+                                 digit_pair(acc[t][1][2], acc[t][1][3]));
+            },
+            [&](const int4 &g0, const int4 &g1, const int4 &g2, const int4 &g3) {
+                s.su = (double)g0.x;
+                s.sv = (double)g0.y;
+                s.m = (double)g0.z;
+                s.suu = digits4(g1.x, g1.y);
+                s.suv = digits4(g1.z, g1.w);
+                s.svv = digits4(g2.x, g2.y);
+                s.suz = fma(0x1p32, (double)g2.z, digits4(g3.x, g3.y));
+                s.svz = fma(0x1p32, (double)g2.w, digits4(g3.z, g3.w));
+            });
+        // (exact is uniform over the workgroup)
+        if (ok
+            && !(exact ? coope_solve<true>(s, cx, cy, r2) : coope_solve<false>(s, cx, cy, r2))) {
+            rec.fail_stage = k;
+            ok = false;
+        }
+    }
+    if (!__any(ok))
+        return;
+    i32x4 acc[T][1];
+    wave.template pass<true>(make_band(cx, cy, r2, a.t_ri), ok, U, V, acc);
+    double qs = 0;
+    int cnt = 0;
+    wave.exchange(
+        [&](int t) {
+            return make_int4(digit_pair(acc[t][0][0], acc[t][0][1]),
+                             digit_pair(acc[t][0][2], acc[t][0][3]), -acc[t][0][0], 0);
+        },
+        [&](const int4 &g0, const int4 &g1, const int4 &, const int4 &) {
+            qs = digits4(g0.x, g0.y);
+            cnt = g1.z;
+        });
+    if (!ok)
+        return;
+    const double acx = (double)ox + cx;
+    const double acy = (double)oy + cy;
+    const double r = sqrt(r2);
+    const double ex = acx - (double)(d.W - 1) / 2.0;
+    const double ey = acy - (double)(d.H - 1) / 2.0;
+    const double dlim = a.d_max * (double)d.W;
+    const bool kept = r >= a.r_min * (double)d.W && r <= a.r_max * (double)d.W
+                      && ex * ex + ey * ey <= dlim * dlim;
+    rec.status = kept ? 2 : 1;
+    rec.inliers = cnt;
+    rec.qsum = (uint64_t)qs;
+    rec.cx = acx;
+    rec.cy = acy;
+    rec.r2 = r2;
+    if (kept && lane < 16 * T)
+        key = (rec.qsum << 16) | (uint64_t)(0xFFFFu - (uint32_t)att);
 }
 
-// One RANSAC item: attempts [g * A, g * A + A) of frame f (A = kBlock /
-// LANES), LANES lanes per attempt.  Writes the group's best attempt to its
-// record (device scope) and ends with a barrier.
-template <int LANES>
-__device__ void ransac_work(const RansacArgs &a, Lds &L, int f, int g)
+// Balanced base-256 digits of v (below 128 * 256^(n - 1) in size): the bytes
+// of (v + 0x80..80) ^ 0x80..80, each a signed digit.
+__device__ __forceinline__ uint64_t balanced(int64_t v)
+{
+    constexpr uint64_t bias = 0x0000808080808080ull;
+    return ((uint64_t)v + bias) ^ bias;
+}
+
+// The digits of one point (or zeros, for padding) into the blocks.
+template <int X>
+__device__ __forceinline__ void store_digits(Lds<X> &L, int i, bool real, int u, int v, uint32_t q)
+{
+    const int blk = 4 * (i >> 6) + ((i >> 2) & 3);
+    const int at = 4 * ((i >> 4) & 3) + (i & 3);
+    const int z = u * u + v * v;
+    const uint64_t du = balanced(u), dv = balanced(v);
+    const uint64_t uu = balanced((int64_t)u * u), uv = balanced((int64_t)u * v);
+    const uint64_t vv = balanced((int64_t)v * v);
+    const uint64_t uz = balanced((int64_t)u * z), vz = balanced((int64_t)v * z);
+    const uint64_t dq = balanced(q);
+    auto put = [&](int row, uint64_t x, int first, int count) {
+#pragma unroll
+        for (int k = 0; k < count; ++k)
+            L.digit[blk][row + k][at] = (int8_t)(real ? (x >> (8 * (first + k))) & 0xFF : 0);
+    };
+    put(0, du, 0, 2);
+    put(2, dv, 0, 2);
+    put(4, uu, 0, 4);
+    put(8, vv, 0, 4);
+    put(12, uz, 0, 4);
+    put(16, 1, 0, 4);    // the count, and three rows of zeros
+    put(20, uv, 0, 4);
+    put(24, uz, 4, 2);
+    put(26, vz, 4, 2);
+    put(28, vz, 0, 4);
+#pragma unroll
+    for (int k = 0; k < kFinalRows; ++k)
+        L.fin[blk][k][at] = (int8_t)(!real ? 0 : k < 4 ? (dq >> (8 * k)) & 0xFF : k == 4 ? 1 : 0);
+}
+
+// One RANSAC item: attempts [64 T g, 64 T (g + 1)) of frame f, 16 T a
+// wavefront.  Writes the group's best attempt to its record (device scope)
+// and ends with a barrier.
+//
+// Bound by vector issue and by the latency of the float64 solves.  The inlier
+// passes test every point against every attempt (33.5 M tests for 64 frames of
+// 128 candidates and 1024 attempts); in float64 on the vector units a test and
+// its eight moment sums are about 20 instructions, on the matrix units the
+// test's subtraction and its share of the packing remain (9 for four points).
+// Measured per launch (dispatch events): 64 x 1080p, 1024 attempts, 128
+// candidates: 28.7 us with the moments summed in float64 by two lanes an
+// attempt, 15.5 us so, of which 5.9 are the launch, the candidates and the
+// choice; 8 x 640x480, 256 attempts, 64 candidates: 10.5 -> 9.8 us.  One more
+// refit costs 2.3 us at the former size: 1.0 the solve and the two exchanges,
+// 0.65 each 64 points.
+template <int T, int X>
+__device__ void ransac_work(const RansacArgs &a, Lds<X> &L, int f, int g)
 {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -746,12 +1020,20 @@ __device__ void ransac_work(const RansacArgs &a, Lds &L, int f, int g)
     const FrameDev d = a.fd[f];
     const int ox = d.W / 2, oy = d.H / 2;
 
+    uint64_t pt = 0;
+    if (tid < a.P)
+        pt = load_dev(reinterpret_cast<const uint64_t *>(a.cand + (int64_t)f * a.P + tid));
+    // the attempt's random words, while the candidates load
+    const int att = g * (64 * T) + wv * (16 * T) + (lane & (16 * T - 1));
+    uint64_t c[4] = {(uint64_t)(uint32_t)att, d.uid, 0, 0};
+    if (a.sampler == 0)
+        philox4x64_10(c, a.seed, 0);
+
     // filter (Section 2.2.5) and stable compaction in canonical order
     bool keep = false;
     int x = 0, y = 0;
     float sc = 0.0f;
     if (tid < a.P) {
-        const uint64_t pt = load_dev(reinterpret_cast<const uint64_t *>(a.cand + (int64_t)f * a.P + tid));
         x = (int16_t)(uint16_t)(pt & 0xFFFFu);
         y = (int16_t)(uint16_t)((pt >> 16) & 0xFFFFu);
         sc = __uint_as_float((uint32_t)(pt >> 32));
@@ -769,25 +1051,20 @@ __device__ void ransac_work(const RansacArgs &a, Lds &L, int f, int g)
     for (int w = 0; w < wv; ++w)
         base += L.wcount[w];
     const int n = uniform(L.wcount[0] + L.wcount[1] + L.wcount[2] + L.wcount[3]);
-    const int nk = (n + LANES - 1) / LANES;
     if (keep) {
         const int j = base + before;
         const int u = x - ox, v = y - oy;
-        const double du = (double)u, dv = (double)v;
-        const double z = (double)((int64_t)u * u + (int64_t)v * v);
-        L.iu[j] = u;
-        L.iv[j] = v;
-        L.uv[j] = make_double2(du, dv);
-        L.m1[j] = make_double2((double)((int64_t)u * u), (double)((int64_t)u * v));
-        L.m2[j] = make_double2((double)((int64_t)v * v), (double)(uint32_t)(sc * 16777216.0f));
-        L.m3[j] = make_double2(du * z, dv * z);
+        L.feat[0][j] = (float)(u * u + v * v);
+        L.feat[1][j] = (float)u;
+        L.feat[2][j] = (float)v;
+        L.feat[3][j] = 1.0f;
+        store_digits(L, j, true, u, v, (uint32_t)(sc * 16777216.0f));
     }
-    if (tid >= n && tid < nk * LANES) {
-        // padding: squared distance ~1e300 exceeds every band's outer radius
-        L.uv[tid] = make_double2(1e150, 1e150);
-        L.m1[tid] = make_double2(0.0, 0.0);
-        L.m2[tid] = make_double2(0.0, 0.0);
-        L.m3[tid] = make_double2(0.0, 0.0);
+    if (tid >= n && tid < ((n + 63) & ~63)) {
+        // padding: far outside every band, and no moments
+        L.feat[0][tid] = 1e30f;
+        L.feat[1][tid] = L.feat[2][tid] = L.feat[3][tid] = 0.0f;
+        store_digits(L, tid, false, 0, 0, 0);
     }
     __syncthreads();
 
@@ -797,16 +1074,12 @@ __device__ void ransac_work(const RansacArgs &a, Lds &L, int f, int g)
     const bool exact =
         uniform((double)n * (double)n * (U > V ? U : V) * (U * U + V * V) < 0x1p52 ? 1 : 0) != 0;
 
-    const int sub = tid & (LANES - 1);
-    const int att = g * (kBlock / LANES) + tid / LANES;
     const bool active = att < a.attempts;
     uint64_t key = 0;
     ca_attempt rec = {};
-    if (exact)
-        run_attempt<true, LANES>(a, L, d, n, nk, sub, att, active, rec, key);
-    else
-        run_attempt<false, LANES>(a, L, d, n, nk, sub, att, active, rec, key);
-    if (a.dbg && active && sub == 0)
+    if (n >= 3)
+        run_attempts<T, X>(a, L, d, n, lane, wv, exact, c, att, active, rec, key);
+    if (a.dbg && active && lane < 16 * T)
         a.dbg[(int64_t)f * a.attempts + att] = rec;
 
     // best kept attempt of this group: keys are unique per attempt
@@ -981,15 +1254,15 @@ __global__ __launch_bounds__(2 * kBlock) void k_strips_pair(StripArgs a)
 
 // RANSAC groups of frames frame0 .. frame0 + gridDim.y - 1; the last group
 // of a frame to finish selects its circle and rearms the frame's counter.
-template <int LANES>
+template <int T>
 __global__ __launch_bounds__(kBlock) void k_ransac(RansacArgs a, SelectArgs sel)
 {
-    __shared__ Lds L;
+    __shared__ Lds<T> L;
     __shared__ int s_last;
     const int f = a.frame0 + (int)blockIdx.y;
     if (a.keep && learned_kept(a.keep[f], a.keep_frac))
         return;   // no group of this frame counts or selects
-    ransac_work<LANES>(a, L, f, blockIdx.x);
+    ransac_work<T, T>(a, L, f, blockIdx.x);
     if (threadIdx.x == 0)
         s_last = add_dev(a.groups_done + f, 1u) == (uint32_t)(a.groups - 1);
     __syncthreads();
@@ -1045,7 +1318,13 @@ __device__ Ticket decode_ticket(int k, int q, int nq, int B, int S, int G, int l
     return tk;
 }
 
-__global__ __launch_bounds__(kBlock) void k_fused(FusedArgs a)
+// The persistent kernel's RANSAC items share the strips' LDS: they exchange
+// one tile at a time.
+constexpr int kFusedTiles = 4 / kLanesPerAttempt;
+typedef Lds<1> FusedLds;
+static_assert(sizeof(FusedLds) <= 18944, "LDS of a fused workgroup beside its score tables");
+
+__global__ __launch_bounds__(kBlock, 4) void k_fused(FusedArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ uint32_t s_scan[4];
@@ -1062,7 +1341,7 @@ __global__ __launch_bounds__(kBlock) void k_fused(FusedArgs a)
 
     load_tables(a.s, smem);
     const StripLds c = carve_strip_lds(smem, a.s.sg_len, s_scan, s_best);
-    Lds &L = *reinterpret_cast<Lds *>(c.tile);
+    FusedLds &L = *reinterpret_cast<FusedLds *>(c.tile);
     // a workgroup can never legitimately take more items than its queue holds
     const int Bq = (B - q + a.nq - 1) / a.nq;
     const int max_items = Bq * (S + G);
@@ -1102,7 +1381,7 @@ __global__ __launch_bounds__(kBlock) void k_fused(FusedArgs a)
                 }
             }
             __syncthreads();
-            ransac_work<kLanesPerAttempt>(a.r, L, tk.f, tk.idx);
+            ransac_work<kFusedTiles, 1>(a.r, L, tk.f, tk.idx);
             if (tid == 0)
                 s_last = add_dev(groups_done + tk.f, 1u) == (uint32_t)(G - 1);
             __syncthreads();
@@ -1172,10 +1451,13 @@ size_t strip_lds_bytes(int sg_len, int line_pitch)
     return (size_t)(sg_len + kQtBins + kLumaLevels) * sizeof(float) + 16 + 3 * (size_t)line_pitch;
 }
 
+// what a fused workgroup takes for its RANSAC items (at least)
+constexpr size_t kFusedWorkBytes = 18944;
+
 size_t fused_lds_bytes(int sg_len, int line_pitch)
 {
     const size_t tile = 3 * (size_t)line_pitch;
-    const size_t work = tile > sizeof(Lds) ? tile : sizeof(Lds);
+    const size_t work = tile > kFusedWorkBytes ? tile : kFusedWorkBytes;
     return (size_t)(sg_len + kQtBins + kLumaLevels) * sizeof(float) + 16 + work;
 }
 
@@ -1206,17 +1488,14 @@ hipError_t launch_ransac(const RansacArgs &a, const SelectArgs &sel, int n_frame
         return hipSuccess;
     const dim3 grid(a.groups, n_frames);
     switch (a.lanes) {
+    case 1:
+        launch_maybe_timed(k_ransac<4>, grid, dim3(kBlock), 0, s, start, stop, a, sel);
+        break;
     case 2:
         launch_maybe_timed(k_ransac<2>, grid, dim3(kBlock), 0, s, start, stop, a, sel);
         break;
     case 4:
-        launch_maybe_timed(k_ransac<4>, grid, dim3(kBlock), 0, s, start, stop, a, sel);
-        break;
-    case 8:
-        launch_maybe_timed(k_ransac<8>, grid, dim3(kBlock), 0, s, start, stop, a, sel);
-        break;
-    case 16:
-        launch_maybe_timed(k_ransac<16>, grid, dim3(kBlock), 0, s, start, stop, a, sel);
+        launch_maybe_timed(k_ransac<1>, grid, dim3(kBlock), 0, s, start, stop, a, sel);
         break;
     default:
         return hipErrorInvalidValue;
