@@ -281,6 +281,21 @@ __device__ __forceinline__ void store_row24(__bf16 *row, const uint32_t (&u)[6])
     }
 }
 
+// Line j's six bytes of two adjacent positions (b03: the first four, b45: the
+// other two in its low half) into bytes 3j .. 3j + 2 of each position's 24.
+__device__ __forceinline__ void put_line(uint32_t (&u)[2][6], int j, uint32_t b03, uint32_t b45)
+{
+    const uint32_t p0 = b03 & 0xFFFFFFu;
+    const uint32_t p1 = (b03 >> 24) | ((b45 & 0xFFFFu) << 8);
+    const int k = 3 * j;
+    u[0][k >> 2] |= p0 << (8 * (k & 3));
+    if ((k & 3) > 1)
+        u[0][(k >> 2) + 1] |= p0 >> (32 - 8 * (k & 3));
+    u[1][k >> 2] |= p1 << (8 * (k & 3));
+    if ((k & 3) > 1)
+        u[1][(k >> 2) + 1] |= p1 >> (32 - 8 * (k & 3));
+}
+
 __device__ __forceinline__ void wave_gather(__bf16 *x0, const uint8_t *frame, int W, int H, int rs,
                                             bool horizontal, int pos, int L, int start, int lane)
 {
@@ -306,18 +321,8 @@ __device__ __forceinline__ void wave_gather(__bf16 *x0, const uint8_t *frame, in
                 const uint32_t sh = (uint32_t)(reinterpret_cast<uintptr_t>(q) & 3);
                 const uint32_t *w = reinterpret_cast<const uint32_t *>(q - sh);
                 const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
-                const uint32_t b03 = __builtin_amdgcn_alignbyte(w1, w0, sh);
-                const uint32_t b47 = __builtin_amdgcn_alignbyte(w2, w1, sh);
-                // bytes 3j .. 3j + 2 of each position's 24
-                const uint32_t p0 = b03 & 0xFFFFFFu;
-                const uint32_t p1 = (b03 >> 24) | ((b47 & 0xFFFFu) << 8);
-                const int k = 3 * j;
-                u[0][k >> 2] |= p0 << (8 * (k & 3));
-                if ((k & 3) > 1)
-                    u[0][(k >> 2) + 1] |= p0 >> (32 - 8 * (k & 3));
-                u[1][k >> 2] |= p1 << (8 * (k & 3));
-                if ((k & 3) > 1)
-                    u[1][(k >> 2) + 1] |= p1 >> (32 - 8 * (k & 3));
+                put_line(u, j, __builtin_amdgcn_alignbyte(w1, w0, sh),
+                         __builtin_amdgcn_alignbyte(w2, w1, sh));
             }
         } else {
 #pragma unroll
@@ -386,7 +391,9 @@ __global__ __launch_bounds__(kBlock) void k_mfma_probe(float *out)
 }
 
 // Logits of the central positions of uint8 windows [n][8][128][3]: one
-// wavefront per window.
+// wavefront per window.  A byte at a time (48 rounds of loads, divisions and
+// two-byte LDS writes a lane) the input took longer than the layers: 37.5 us
+// for 3,584 windows, 22.6 with two loads a line, fetched a window ahead.
 __global__ __launch_bounds__(kCnnWaveBlock) void k_cnn_windows(const uint8_t *model,
                                                                const uint8_t *win,
                                                                const int32_t *range, float *z_out,
@@ -401,18 +408,42 @@ __global__ __launch_bounds__(kCnnWaveBlock) void k_cnn_windows(const uint8_t *mo
     load_wave_frag(fr, model, lane);
     wave_clear(x0, lane);
     const int waves = gridDim.x * (kCnnWaveBlock / 64);
-    for (int wi = blockIdx.x * (kCnnWaveBlock / 64) + wv; wi < n_windows; wi += waves) {
+    // the next window's bytes: six of each line, positions 2 lane and 2 lane +
+    // 1, loaded while a window's layers run
+    uint32_t four[kCnnLines];
+    uint16_t two[kCnnLines];
+    auto fetch = [&](int wi) {
+        const uint8_t *src = win + (int64_t)wi * (kCnnLines * kCnnWin * 3) + 6 * lane;
+#pragma unroll
+        for (int j = 0; j < kCnnLines; ++j) {
+            __builtin_memcpy(&four[j], src + j * (kCnnWin * 3), 4);
+            __builtin_memcpy(&two[j], src + j * (kCnnWin * 3) + 4, 2);
+        }
+    };
+    const int first = blockIdx.x * (kCnnWaveBlock / 64) + wv;
+    if (first < n_windows)
+        fetch(first);
+    for (int wi = first; wi < n_windows; wi += waves) {
         const int lo = uniform_int(range[2 * wi]);
         const int hi = uniform_int(range[2 * wi + 1]);
-        const uint8_t *src = win + (int64_t)wi * (kCnnLines * kCnnWin * 3);
         wave_sync();
-        for (int i = lane; i < kCnnLines * kCnnWin * 3; i += 64) {
-            const int line = i / (kCnnWin * 3);
-            const int rem = i - line * (kCnnWin * 3);
-            const int n = rem / 3, ch = rem - 3 * (rem / 3);
-            const float v = (n >= lo && n < hi) ? ((float)src[i] - 128.0f) * (1.0f / 64.0f) : 0.0f;
-            x0[(n + kCnnGuard) * 24 + 3 * line + ch] = to_bf16(v);
+        {
+            uint32_t u[2][6] = {};
+#pragma unroll
+            for (int j = 0; j < kCnnLines; ++j)
+                put_line(u, j, four[j], two[j]);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int n = 2 * lane + k;
+                if (!(n >= lo && n < hi))
+#pragma unroll
+                    for (int i = 0; i < 6; ++i)
+                        u[k][i] = 0x80808080u;   // (128 - 128) / 64 = 0
+                store_row24(x0 + (n + kCnnGuard) * 24, u[k]);
+            }
         }
+        if (wi + waves < n_windows)
+            fetch(wi + waves);
         wave_forward(fr, x0, hb, lo, hi, lane, [&](int n, float z) {
             if (n >= kCnnHalo && n < kCnnWin - kCnnHalo)
                 z_out[(int64_t)wi * kCnnOut + n - kCnnHalo] = z;

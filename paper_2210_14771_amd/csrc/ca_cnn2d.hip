@@ -35,24 +35,6 @@ constexpr int kTrainOut = kC2Win - 2 * kTrainHalo;
 constexpr int kC2Floats = 96;      // floats of the model's float block
 constexpr int kWaves = kBlock / 64;
 
-// LDS of the forward pass: input (7 lines, 8 channels: RGBXY and 3 zeros),
-// layer 1 (5 lines x 8), layer 2 (3 x 16), layer 3 (1 x 32), logits.
-struct alignas(16) FwdLds {
-    __bf16 x0[kC2Band * kPos * 8];
-    __bf16 h1[5 * kPos * 8];
-    __bf16 h2[3 * kPos * 16];
-    __bf16 h3[kPos * 32];
-    float z[kC2Win];
-    float fb[kC2Floats];   // the model's float block (biases, w4, b4, colour statistics)
-};
-
-// Clear a buffer (both guards included); a workgroup-wide loop.
-__device__ void clear(__bf16 *p, int n)
-{
-    for (int i = threadIdx.x; i < n; i += kBlock)
-        p[i] = to_bf16(0.0f);
-}
-
 // The A operand of a layer's GEMMs (weights [M][KP], M = 16 MT output
 // channels) as this lane's MFMA fragments: loaded once, kept in registers
 // for every tile of every window the workgroup computes.
@@ -75,52 +57,6 @@ __device__ __forceinline__ Frag<KP, MT> load_frag(const __bf16 *A)
     return f;
 }
 
-// One 3x3 convolution layer over a window as GEMMs, one per output line i:
-// acc[m][n] = sum_k A[m][k] B_i[k][n] with B_i[(3 da + dl) CP + c][n] =
-// X[line i + da][n + dl - 1][c] (lines outside [x_lo, x_hi) read the zero
-// line).  A wave takes position tiles (16 positions of one output line) and
-// computes all MT channel tiles of each from one read of its B fragments;
-// epi(i, m0, n, acc) receives rows m0 .. m0 + 3 of column n.
-template <int CP, int KP, int MT, int OUT_LINES, class Epi>
-__device__ __forceinline__ void gemm3x3(const Frag<KP, MT> &F, const __bf16 *X, int x_lo,
-                                        int x_hi, const __bf16 *zero, Epi epi)
-{
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    constexpr int NT = kC2Win / 16;
-    constexpr int CB = CP / 8;
-    constexpr int G = 9 * CB;   // real 8-wide K groups; the rest have zero weights
-    static_assert((OUT_LINES * NT) % kWaves == 0, "tiles must split evenly over the waves");
-    const int kq = lane >> 4;
-#pragma unroll
-    for (int t = 0; t < OUT_LINES * NT / kWaves; ++t) {
-        const int tile = wv + kWaves * t;
-        const int nt = tile % NT;
-        const int i = tile / NT;
-        const int n = nt * 16 + (lane & 15);
-        f32x4 acc[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            acc[mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int ks = 0; ks < KP / 32; ++ks) {
-            int g = 4 * ks + kq;
-            g = g < G ? g : 0;
-            const int tap = g / CB, cb = g - CB * (g / CB);
-            const int da = tap / 3, dl = tap - 3 * (tap / 3);
-            const int line = i + da;
-            const __bf16 *src = (line >= x_lo && line < x_hi) ? X + (line - x_lo) * kPos * CP : zero;
-            const bf16x8 b = *reinterpret_cast<const bf16x8 *>(src + (n + dl) * CP + 8 * cb);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(F.a[mt][ks], b, acc[mt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            epi(i, mt * 16 + 4 * kq, n, acc[mt]);
-    }
-}
-
 // The forward weights of one orientation in registers: the three layers' A
 // fragments and this lane's biases (rows m0 .. m0 + 3 of its accumulators).
 struct FwdW {
@@ -130,32 +66,23 @@ struct FwdW {
     float b1[4], b2[4], b3[2][4];
 };
 
-// fb: the model's float block (in LDS).  With `paired`, layer 1's weights
-// are those of output-line pairs (rows 8..15 the second line's channels).
+// fb: the model's float block (in LDS).  Layer 1's weights are those of
+// output-line pairs (rows 8..15 the second line's channels).
 __device__ __forceinline__ void load_fwd_weights(FwdW &W, const uint8_t *model, bool hz,
-                                                 const float *fb, bool paired = false)
+                                                 const float *fb)
 {
     const __bf16 *A = reinterpret_cast<const __bf16 *>(model) + (hz ? 0 : kC2Orient);
-    W.w1 = load_frag<96, 1>(A + (paired ? kC2P1 : kC2A[0]));
+    W.w1 = load_frag<96, 1>(A + kC2P1);
     W.w2 = load_frag<96, 1>(A + kC2A[1]);
     W.w3 = load_frag<160, 2>(A + kC2A[2]);
     const int m0 = 4 * ((threadIdx.x & 63) >> 4);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        W.b1[j] = paired ? fb[kC2FB[0] + (m0 & 7) + j] : (m0 < 8 ? fb[kC2FB[0] + m0 + j] : 0.0f);
+        W.b1[j] = fb[kC2FB[0] + (m0 & 7) + j];
         W.b2[j] = fb[kC2FB[1] + m0 + j];
         W.b3[0][j] = fb[kC2FB[2] + m0 + j];
         W.b3[1][j] = fb[kC2FB[2] + 16 + m0 + j];
     }
-}
-
-// The model's float block into L.fb (a workgroup-wide copy; the caller
-// synchronises before reading it).
-__device__ void stage_floats(FwdLds &L, const uint8_t *model)
-{
-    const float *src = reinterpret_cast<const float *>(model + kC2FloatsOff);
-    for (int i = threadIdx.x; i < kC2Floats; i += kBlock)
-        L.fb[i] = src[i];
 }
 
 // Input encoding of one band position: colours normalised, coordinates in
@@ -177,83 +104,6 @@ __device__ __forceinline__ void encode(__bf16 *dst, uint32_t r, uint32_t g, uint
 __device__ __forceinline__ float coord_scale(int extent) { return 1.0f / (float)(2 * (extent - 1)); }
 
 __device__ __forceinline__ bool line_in(uint32_t line_ok, int j) { return (line_ok >> j) & 1u; }
-
-// Forward pass of the window whose input is in L.x0: logits of all 128
-// positions into L.z (exact where the whole receptive field is inside the
-// window).  line_ok bit j: band line j lies in the frame; positions outside
-// [lo, hi) are beyond the strip.
-__device__ void forward(FwdLds &L, const FwdW &W, uint32_t line_ok, int lo, int hi)
-{
-    gemm3x3<8, 96, 1, 5>(W.w1, L.x0, 0, kC2Band, nullptr,
-                         [&](int i, int m0, int n, const f32x4 &acc) {
-                             if (m0 >= 8)
-                                 return;
-                             const bool keep = line_in(line_ok, i + 1) && n >= lo && n < hi;
-                             bf16x4 o;
-#pragma unroll
-                             for (int j = 0; j < 4; ++j) {
-                                 const float v = fmaxf(acc[j] + W.b1[j], 0.0f);
-                                 o[j] = to_bf16(keep ? v : 0.0f);
-                             }
-                             *reinterpret_cast<bf16x4 *>(L.h1 + (i * kPos + n + 1) * 8 + m0) = o;
-                         });
-    __syncthreads();
-    gemm3x3<8, 96, 1, 3>(W.w2, L.h1, 0, 5, nullptr,
-                         [&](int i, int m0, int n, const f32x4 &acc) {
-                             const bool keep = line_in(line_ok, i + 2) && n >= lo && n < hi;
-                             bf16x4 o;
-#pragma unroll
-                             for (int j = 0; j < 4; ++j) {
-                                 const float v = fmaxf(acc[j] + W.b2[j], 0.0f);
-                                 o[j] = to_bf16(keep ? v : 0.0f);
-                             }
-                             *reinterpret_cast<bf16x4 *>(L.h2 + (i * kPos + n + 1) * 16 + m0) = o;
-                         });
-    __syncthreads();
-    gemm3x3<16, 160, 2, 1>(W.w3, L.h2, 0, 3, nullptr,
-                           [&](int, int m0, int n, const f32x4 &acc) {
-                               const bool keep = line_in(line_ok, 3) && n >= lo && n < hi;
-                               bf16x4 o;
-#pragma unroll
-                               for (int j = 0; j < 4; ++j) {
-                                   const float v = fmaxf(acc[j] + W.b3[m0 >> 4][j], 0.0f);
-                                   o[j] = to_bf16(keep ? v : 0.0f);
-                               }
-                               *reinterpret_cast<bf16x4 *>(L.h3 + (n + 1) * 32 + m0) = o;
-                           });
-    __syncthreads();
-    const int n = threadIdx.x;
-    if (n < kC2Win) {
-        const __bf16 *h = L.h3 + (n + 1) * 32;
-        float z = L.fb[kC2FB4];
-#pragma unroll
-        for (int o = 0; o < 32; ++o)
-            z = fmaf(L.fb[kC2FW4 + o], (float)h[o], z);
-        L.z[n] = z;
-    }
-    __syncthreads();
-}
-
-// The input of a rendered window [8][128][3] (lines line-3 .. line+4,
-// clamped to the frame): band lines 0..6, zero outside the frame or strip.
-__device__ void load_window(FwdLds &L, const uint8_t *src, const int32_t *g, const float *fb,
-                            uint32_t line_ok, int lo, int hi)
-{
-    const bool hz = g[0] != 0;
-    const int line = g[1], start = g[2], W = g[3], H = g[4];
-    for (int i = threadIdx.x; i < kC2Band * kC2Win; i += kBlock) {
-        const int j = i / kC2Win, n = i - kC2Win * (i / kC2Win);
-        __bf16 *dst = L.x0 + (j * kPos + n + 1) * 8;
-        if (!line_in(line_ok, j) || n < lo || n >= hi) {
-            *reinterpret_cast<bf16x8 *>(dst) = bf16x8{};
-            continue;
-        }
-        const uint8_t *px = src + (j * kC2Win + n) * 3;
-        const int across = line - 3 + j, along = start + n;
-        encode(dst, px[0], px[1], px[2], hz ? along : across, hz ? across : along, W, H,
-               coord_scale(W), coord_scale(H), fb);
-    }
-}
 
 __device__ __forceinline__ uint32_t band_lines(int line, int extent)
 {
@@ -451,7 +301,7 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_strips(Cnn2dStripArgs a)
     }
     __syncthreads();
     FwdW W;
-    load_fwd_weights(W, a.model, hz, s_fb, true);
+    load_fwd_weights(W, a.model, hz, s_fb);
     OutW O;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
@@ -562,34 +412,254 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_strips(Cnn2dStripArgs a)
     }
 }
 
-// Logits of positions 8 .. 119 of rendered windows (one workgroup per window,
-// grid-stride).
-__global__ __launch_bounds__(kBlock) void k_cnn2d_windows(const uint8_t *model,
-                                                          const uint8_t *win,
-                                                          const int32_t *geom,
-                                                          const int32_t *range, float *z_out,
-                                                          int n_windows)
+// Element offset of channels c .. c + 3 (c a multiple of 4) of position row
+// `pos` in a 16- or 32-channel buffer line.  The 16-byte chunks of a row are
+// permuted by position (XOR), which spreads 16 rows over all banks; shifting
+// by whole 16-row tiles keeps the permutation.
+__device__ __forceinline__ int off16(int pos, int c)
 {
-    __shared__ FwdLds L;
-    clear(L.x0, kC2Band * kPos * 8);
-    clear(L.h1, 5 * kPos * 8);
-    clear(L.h2, 3 * kPos * 16);
-    stage_floats(L, model);
-    __syncthreads();
-    FwdW W;
-    for (int wi = blockIdx.x; wi < n_windows; wi += gridDim.x) {
-        const int32_t *g = geom + 8 * wi;
-        const bool hz = g[0] != 0;
+    return pos * 16 + ((((c >> 3) ^ (pos >> 3)) & 1) << 3) + (c & 7);
+}
+__device__ __forceinline__ int off32(int pos, int c)
+{
+    return pos * 32 + ((((c >> 3) ^ (pos >> 2)) & 3) << 3) + (c & 7);
+}
+
+constexpr int kL8 = kPos * 8, kL16 = kPos * 16;   // elements of a buffer line
+
+// f(k) of this lane's K group k = 4 ks + g (small numbers): a byte of a
+// constant, one bit-field extract.
+template <class F>
+__device__ __forceinline__ int by_group(int ks, int g, F f)
+{
+    uint32_t packed = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        packed |= (uint32_t)f(4 * ks + i) << (8 * i);
+    return (int)((packed >> (8 * g)) & 0xFFu);
+}
+
+// The input of a rendered window for a workgroup: pixels p, p + 32, p + 64, p +
+// 96 (p = tid % 32) of band line tid / 32, fetched a window ahead (the fourth
+// byte of a word is the next pixel's or, the window having eight lines, the
+// next line's), encoded, and stored to [line][position][8 channels].
+struct WindowInput {
+    uint32_t raw[4];
+    bf16x8 enc[4];
+    int last_w = 0, last_h = 0;
+    float rw = 0.0f, rh = 0.0f;
+
+    static __device__ __forceinline__ bool loads(int tid) { return tid < kC2Band * 32; }
+
+    __device__ __forceinline__ void fetch(const uint8_t *win, int wi, int tid)
+    {
+        if (!loads(tid))
+            return;
+        const uint8_t *src =
+            win + (int64_t)wi * (8 * kC2Win * 3) + (tid >> 5) * (kC2Win * 3) + (tid & 31) * 3;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            __builtin_memcpy(&raw[k], src + 96 * k, 4);
+    }
+
+    // geo: the window's geometry, range: its strip range; fb: the model's
+    // float block.  Positions outside the frame or the strip are zero.
+    __device__ __forceinline__ void encode(const int32_t *geo, const int32_t *range,
+                                           const float *fb, int tid)
+    {
+        const bool hz = uniform_int(geo[0]) != 0;
+        const int line = uniform_int(geo[1]), start = uniform_int(geo[2]);
+        const int W = uniform_int(geo[3]), H = uniform_int(geo[4]);
+        const int lo = uniform_int(range[0]), hi = uniform_int(range[1]);
+        if (W != last_w || H != last_h) {
+            rw = coord_scale(W);
+            rh = coord_scale(H);
+            last_w = W;
+            last_h = H;
+        }
+        const int t = fresh(tid);
+        const int across = line - 3 + (t >> 5), n0 = t & 31;
+        const bool in_line = across >= 0 && across < (hz ? H : W);
+        const int x2 = 2 * (hz ? start + n0 : across) - (W - 1);
+        const int y2 = 2 * (hz ? across : start + n0) - (H - 1);
+        const int dx = hz ? 64 : 0, dy = 64 - dx;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int n = n0 + 32 * k;
+            bf16x8 v;
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                v[c] = to_bf16(((float)((raw[k] >> (8 * c)) & 0xFFu) - fb[kC2FMean + c])
+                               * fb[kC2FInv + c]);
+            v[3] = to_bf16((float)(x2 + k * dx) * rw);
+            v[4] = to_bf16((float)(y2 + k * dy) * rh);
+            v[5] = v[6] = v[7] = to_bf16(0.0f);
+            enc[k] = in_line && n >= lo && n < hi ? v : bf16x8{};
+        }
+    }
+
+    __device__ __forceinline__ void store(__bf16 *x0, int tid) const
+    {
+        if (!loads(tid))
+            return;
+        const int t = fresh(tid);
+        __bf16 *dst = x0 + (t >> 5) * kL8 + ((t & 31) + 1) * 8;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            *reinterpret_cast<bf16x8 *>(dst + 32 * 8 * k) = enc[k];
+    }
+};
+
+struct alignas(16) WindowLds {
+    __bf16 x0[kC2Band * kL8];
+    __bf16 h1[5 * kL8];
+    __bf16 h2[3 * kL16];
+    float fb[kC2Floats];
+};
+
+// Logits of positions 8 .. 119 of rendered windows: a workgroup takes a
+// contiguous share of the windows (those of one strip have one orientation,
+// whose weights stay in registers), a wave 32 positions of every layer.  The
+// sums run in the order of the single-line layers: K from zero, then the bias.
+//
+// Bound by the latency of the layers' chains between three barriers; four
+// workgroups of 38 KB share a compute unit.  Measured, 3,584 windows: 58 us
+// with the weights loaded and every byte encoded alone per window, 32 us so (kernel
+// trace).
+__global__ __launch_bounds__(kBlock, 4) void k_cnn2d_windows(const uint8_t *model,
+                                                             const uint8_t *win,
+                                                             const int32_t *geom,
+                                                             const int32_t *range, float *z_out,
+                                                             int n_windows)
+{
+    __shared__ WindowLds G;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wv = uniform_int(tid >> 6);
+    {
+        uint4 *z = reinterpret_cast<uint4 *>(&G);
+        for (int i = tid; i < (int)(sizeof(WindowLds) / 16); i += kBlock)
+            z[i] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        const float *src = reinterpret_cast<const float *>(model + kC2FloatsOff);
+        if (tid < kC2Floats)
+            G.fb[tid] = src[tid];
+        __syncthreads();
+    }
+    const int w_begin = (int)((int64_t)blockIdx.x * n_windows / gridDim.x);
+    const int w_end = (int)((int64_t)(blockIdx.x + 1) * n_windows / gridDim.x);
+    int cur = -1;
+    Frag<96, 1> w1, w2;
+    Frag<160, 2> w3;
+    WindowInput in;
+    if (w_begin < w_end) {
+        in.fetch(win, w_begin, tid);
+        in.encode(geom + 8 * w_begin, range + 2 * w_begin, G.fb, tid);
+    }
+    for (int wi = w_begin; wi < w_end; ++wi) {
+        const int32_t *geo = geom + 8 * wi;
+        const bool hz = uniform_int(geo[0]) != 0;
         const int lo = uniform_int(range[2 * wi]), hi = uniform_int(range[2 * wi + 1]);
-        const uint32_t line_ok = band_lines(g[1], hz ? g[4] : g[3]);
+        const uint32_t line_ok = band_lines(uniform_int(geo[1]), uniform_int(hz ? geo[4] : geo[3]));
+        if (cur != (int)hz) {
+            cur = (int)hz;
+            const __bf16 *A = reinterpret_cast<const __bf16 *>(model) + (hz ? 0 : kC2Orient);
+            w1 = load_frag<96, 1>(A + kC2A[0]);
+            w2 = load_frag<96, 1>(A + kC2A[1]);
+            w3 = load_frag<160, 2>(A + kC2A[2]);
+        }
+        in.store(G.x0, tid);
         __syncthreads();
-        load_window(L, win + (int64_t)wi * (8 * kC2Win * 3), g, L.fb, line_ok, lo, hi);
-        load_fwd_weights(W, model, hz, L.fb);
+        if (wi + 1 < w_end)
+            in.fetch(win, wi + 1, tid);
+        const Place L(fresh(lane));
+        const int p0 = 32 * wv + L.col;
+        float tops[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int n = p0 + 16 * t;
+            tops[t] = n >= lo && n < hi ? __builtin_inff() : 0.0f;
+        }
+        int o[3];   // K group k (of 9): da = k / 3, dl = k % 3
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks)
+            o[ks] = by_group(ks, L.g, [](int k) { return k < 9 ? k / 3 : 0; }) * kL8
+                    + (p0 + by_group(ks, L.g, [](int k) { return k < 9 ? k % 3 : 0; })) * 8;
+        auto biased = [&](const f32x4 &acc, const float *b) {
+            return acc + *reinterpret_cast<const f32x4 *>(b);
+        };
+        // one layer of single output lines from 8-channel lines
+        auto layer8 = [&](const Frag<96, 1> &w, const __bf16 *x, auto epi, int lines) {
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                if (i >= lines)
+                    break;
+                f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+                for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t] = mma(w.a[0][ks], frag_at(x + i * kL8 + o[ks] + t * 128), acc[t]);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    epi(i, t, acc[t]);
+            }
+        };
+        layer8(w1, G.x0, [&](int i, int t, const f32x4 &acc) {
+            if (L.g < 2)
+                *reinterpret_cast<bf16x4 *>(G.h1 + i * kL8 + (p0 + 16 * t + 1) * 8 + 4 * L.g) =
+                    relu_bf16(biased(acc, G.fb + kC2FB[0] + 4 * (L.g & 1)),
+                              line_in(line_ok, i + 1) ? tops[t] : 0.0f);
+        }, 5);
         __syncthreads();
-        forward(L, W, line_ok, lo, hi);
-        const int n = threadIdx.x;
-        if (n >= kTrainHalo && n < kC2Win - kTrainHalo)
-            z_out[(int64_t)wi * kTrainOut + n - kTrainHalo] = L.z[n];
+        layer8(w2, G.h1, [&](int i, int t, const f32x4 &acc) {
+            *reinterpret_cast<bf16x4 *>(G.h2 + i * kL16 + off16(p0 + 16 * t + 1, 4 * L.g)) =
+                relu_bf16(biased(acc, G.fb + kC2FB[1] + 4 * L.g),
+                          line_in(line_ok, i + 2) ? tops[t] : 0.0f);
+        }, 3);
+        __syncthreads();
+        {
+            f32x4 acc[2][2];
+            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                // K group k (of 18; two more have zero weights): tap k / 2,
+                // half k % 2
+                const __bf16 *x =
+                    G.h2 + by_group(ks, L.g, [](int k) { return k < 18 ? k / 6 : 0; }) * kL16
+                    + off16(p0 + by_group(ks, L.g, [](int k) { return k < 18 ? k / 2 % 3 : 0; }),
+                            8 * (L.g & 1));
+                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 256);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    acc[mt][0] = mma(w3.a[mt][ks], x0, acc[mt][0]);
+                    acc[mt][1] = mma(w3.a[mt][ks], x1, acc[mt][1]);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float top = line_in(line_ok, 3) ? tops[t] : 0.0f;
+                float z = 0.0f;
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const bf16x4 h =
+                        relu_bf16(biased(acc[mt][t], G.fb + kC2FB[2] + 16 * mt + 4 * L.g), top);
+                    const f32x4 w4 =
+                        *reinterpret_cast<const f32x4 *>(G.fb + kC2FW4 + 16 * mt + 4 * L.g);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        z = fmaf(w4[j], (float)h[j], z);
+                }
+                z += __shfl_xor(z, 16, 64);
+                z += __shfl_xor(z, 32, 64);
+                const int n = p0 + 16 * t;
+                if (L.g == t && n >= kTrainHalo && n < kC2Win - kTrainHalo)
+                    z_out[(int64_t)wi * kTrainOut + n - kTrainHalo] = G.fb[kC2FB4] + z;
+            }
+        }
+        if (wi + 1 < w_end)
+            in.encode(geom + 8 * (wi + 1), range + 2 * (wi + 1), G.fb, tid);
+        // (x0 was last read before the second barrier, h1 before the third;
+        // h2 is written after the next window's second)
     }
 }
 
@@ -646,34 +716,10 @@ static_assert(kPos * 32 <= 5 * kPos * 8, "dP3 fits where dP1 is kept");
 static_assert(sizeof(GradLds) <= 81920, "two workgroups per compute unit");
 static_assert((2 * kDB3 + 4 * 66) * sizeof(float) <= sizeof(GradLds), "sums fit the LDS");
 
-// Element offset of channels c .. c + 3 (c a multiple of 4) of position row
-// `pos` in a 16- or 32-channel buffer line (the chunk permutation above).
-__device__ __forceinline__ int off16(int pos, int c)
-{
-    return pos * 16 + ((((c >> 3) ^ (pos >> 3)) & 1) << 3) + (c & 7);
-}
-__device__ __forceinline__ int off32(int pos, int c)
-{
-    return pos * 32 + ((((c >> 3) ^ (pos >> 2)) & 3) << 3) + (c & 7);
-}
-
-// f(k) of this lane's K group k = 4 ks + g (small numbers): a byte of a
-// constant, one bit-field extract.
-template <class F>
-__device__ __forceinline__ int by_group(int ks, int g, F f)
-{
-    uint32_t packed = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        packed |= (uint32_t)f(4 * ks + i) << (8 * i);
-    return (int)((packed >> (8 * g)) & 0xFFu);
-}
-
 __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 {
     extern __shared__ __align__(16) uint8_t c2_smem[];
     GradLds &G = *reinterpret_cast<GradLds *>(c2_smem);
-    constexpr int kL8 = kPos * 8, kL16 = kPos * 16;   // elements of a buffer line
     const int tid = threadIdx.x;
     const int lane = tid & 63, wv = tid >> 6;
     {
@@ -707,60 +753,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
     const int w_begin = (int)((int64_t)blockIdx.x * a.n / gridDim.x);
     const int w_end = (int)((int64_t)(blockIdx.x + 1) * a.n / gridDim.x);
     int cur = -1;
-    // The next window's input: pixels p, p + 32, p + 64, p + 96 (p = tid % 32)
-    // of band line tid / 32, fetched a window ahead (the fourth byte of a word
-    // is the next pixel's or, the window having eight lines, the next line's)
-    // and encoded while dW1 runs.
-    uint32_t raw[4];
-    bf16x8 enc[4];
-    const bool loads = tid < kC2Band * 32;
-    auto fetch = [&](int wi) {
-        if (loads) {
-            const uint8_t *src = a.win + (int64_t)wi * (8 * kC2Win * 3) + (tid >> 5) * (kC2Win * 3)
-                                 + (tid & 31) * 3;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                __builtin_memcpy(&raw[k], src + 96 * k, 4);
-        }
-    };
-    int last_w = 0, last_h = 0;
-    float rw = 0.0f, rh = 0.0f;
-    auto encode_window = [&](int wi) {
-        const int32_t *geo = a.geom + 8 * wi;
-        const bool hz = uniform_int(geo[0]) != 0;
-        const int line = uniform_int(geo[1]), start = uniform_int(geo[2]);
-        const int W = uniform_int(geo[3]), H = uniform_int(geo[4]);
-        const int lo = uniform_int(a.range[2 * wi]), hi = uniform_int(a.range[2 * wi + 1]);
-        if (W != last_w || H != last_h) {
-            rw = coord_scale(W);
-            rh = coord_scale(H);
-            last_w = W;
-            last_h = H;
-        }
-        const int t = fresh(tid);
-        const int across = line - 3 + (t >> 5), n0 = t & 31;
-        const bool in_line = across >= 0 && across < (hz ? H : W);
-        int x2 = 2 * (hz ? start + n0 : across) - (W - 1);
-        int y2 = 2 * (hz ? across : start + n0) - (H - 1);
-        const int dx = hz ? 64 : 0, dy = 64 - dx;
-        const float *fb = G.fb;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int n = n0 + 32 * k;
-            bf16x8 v;
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                v[c] = to_bf16(((float)((raw[k] >> (8 * c)) & 0xFFu) - fb[kC2FMean + c])
-                               * fb[kC2FInv + c]);
-            v[3] = to_bf16((float)(x2 + k * dx) * rw);
-            v[4] = to_bf16((float)(y2 + k * dy) * rh);
-            v[5] = v[6] = v[7] = to_bf16(0.0f);
-            enc[k] = in_line && n >= lo && n < hi ? v : bf16x8{};
-        }
-    };
+    // the next window's input, fetched a window ahead and encoded while dW1 runs
+    WindowInput in;
     if (w_begin < w_end) {
-        fetch(w_begin);
-        encode_window(w_begin);
+        in.fetch(a.win, w_begin, tid);
+        in.encode(a.geom + 8 * w_begin, a.range + 2 * w_begin, G.fb, tid);
     }
     for (int wi = w_begin; wi < w_end; ++wi) {
         const int32_t *geo = a.geom + 8 * wi;
@@ -778,25 +775,19 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                 *reinterpret_cast<bf16x8 *>(G.w3 + f * 512 + lane * 8) = frag_at(src + 8 * g);
             }
         }
-        if (loads) {
-            const int t = fresh(tid);
-            __bf16 *dst = G.x0 + (t >> 5) * kL8 + ((t & 31) + 1) * 8;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                *reinterpret_cast<bf16x8 *>(dst + 32 * 8 * k) = enc[k];
-        }
+        in.store(G.x0, tid);
         __syncthreads();
         if (wi + 1 < w_end)
-            fetch(wi + 1);
+            in.fetch(a.win, wi + 1, tid);
         // targets and loss weights of this lane's two positions (zero where
         // a position carries no loss)
         float tgt[2], lw[2], tops[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int n = 32 * wv + (lane & 15) + 16 * t;
-            const bool in = n >= lo && n < hi;
-            const bool has = in && n >= kTrainHalo && n < kC2Win - kTrainHalo;
-            tops[t] = in ? __builtin_inff() : 0.0f;
+            const bool here = n >= lo && n < hi;
+            const bool has = here && n >= kTrainHalo && n < kC2Win - kTrainHalo;
+            tops[t] = here ? __builtin_inff() : 0.0f;
             const int64_t k = (int64_t)wi * kTrainOut + (has ? n - kTrainHalo : 0);
             tgt[t] = a.target[k];
             lw[t] = has ? a.scale * a.weight[k] : 0.0f;
@@ -1087,7 +1078,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             }
         }
         if (wi + 1 < w_end)
-            encode_window(wi + 1);
+            in.encode(a.geom + 8 * (wi + 1), a.range + 2 * (wi + 1), G.fb, tid);
         __syncthreads();
     }
 
@@ -1295,7 +1286,8 @@ hipError_t launch_cnn2d_windows(const uint8_t *model, const uint8_t *win, const 
 {
     if (n <= 0)
         return hipSuccess;
-    const int grid = n < 2048 ? n : 2048;
+    // four resident workgroups on each of 256 compute units
+    const int grid = n < 1024 ? n : 1024;
     hipLaunchKernelGGL(k_cnn2d_windows, dim3(grid), dim3(kBlock), 0, s, model, win, geom, range,
                        z, n);
     return hipGetLastError();
