@@ -689,8 +689,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
             // layer 1: 24 -> 16
             const Place L(fresh(lane));
             const int p0 = 32 * wv + L.col;
+            const f32x4 bias = *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[0] + 4 * L.g);
             f32x4 acc[2];
-            acc[0] = acc[1] = *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[0] + 4 * L.g);
+            acc[0] = acc[1] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 const bf16x8 w = weights(W + kCnnWOff[0], L, 128, 0, ks);
@@ -702,7 +703,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
                 *reinterpret_cast<bf16x4 *>(G.h1 + act_off<16>(p0 + 16 * t + kCnnGuard, 4 * L.g)) =
-                    relu_bf16(acc[t], tops[t]);
+                    relu_bf16(acc[t] + bias, tops[t]);
         }
         __syncthreads();
         {
@@ -710,10 +711,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
             const Place L(fresh(lane));
             const int p0 = 32 * wv + L.col;
             f32x4 acc[2][2];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                acc[mt][0] = acc[mt][1] =
-                    *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[1] + 16 * mt + 4 * L.g);
+            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks) {
                 const __bf16 *x =
@@ -732,7 +730,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
                 for (int t = 0; t < 2; ++t)
                     *reinterpret_cast<bf16x4 *>(
                         G.h2 + act_off<32>(p0 + 16 * t + kCnnGuard, 16 * mt + 4 * L.g)) =
-                        relu_bf16(acc[mt][t], tops[t]);
+                        relu_bf16(acc[mt][t]
+                                      + *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[1]
+                                                                         + 16 * mt + 4 * L.g),
+                                  tops[t]);
         }
         __syncthreads();
         {
@@ -741,10 +742,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
             const int p0 = 32 * wv + L.col;
             const int frag = (16 * L.g + L.col) * 8;
             f32x4 acc[2][2];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                acc[mt][0] = acc[mt][1] =
-                    *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[2] + 16 * mt + 4 * L.g);
+            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 5; ++ks) {
                 const __bf16 *x = G.h2 + act_off<32>(p0 + kCnnGuard - 2 + ks, 8 * L.g);
@@ -762,7 +760,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
                 for (int t = 0; t < 2; ++t)
                     *reinterpret_cast<bf16x4 *>(
                         G.h3 + act_off<32>(p0 + 16 * t + kCnnGuard, 16 * mt + 4 * L.g)) =
-                        relu_bf16(acc[mt][t], tops[t]);
+                        relu_bf16(acc[mt][t]
+                                      + *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[2]
+                                                                         + 16 * mt + 4 * L.g),
+                                  tops[t]);
         }
         __syncthreads();
         {
@@ -770,8 +771,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
             // 16 channels sit in the four lane groups of its column
             const Place L(fresh(lane));
             const int p0 = 32 * wv + L.col;
+            const f32x4 bias = *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[3] + 4 * L.g);
             f32x4 acc[2];
-            acc[0] = acc[1] = *reinterpret_cast<const f32x4 *>(G.fb + kCnnBOff[3] + 4 * L.g);
+            acc[0] = acc[1] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 5; ++ks) {
                 const bf16x8 w = weights(W + kCnnWOff[3], L, 160, 0, ks);
@@ -779,37 +781,29 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
                 acc[0] = mma(w, frag_at(x), acc[0]);
                 acc[1] = mma(w, frag_at(x + 512), acc[1]);
             }
+            bf16x4 h[2][1];
+            h[0][0] = relu_bf16(acc[0] + bias, tops[0]);
+            h[1][0] = relu_bf16(acc[1] + bias, tops[1]);
+            const int own = L.g & 1;   // this lane's tile from here
+            const float z = ordered_dot(G.fb + kCnnW5Off, h, G.fb[kCnnW5Off + 16]);
+            const float lw_own = own ? lw[1] : lw[0], tgt_own = own ? tgt[1] : tgt[0];
+            float dz[2];
+            to_all_groups(lw_own * (sigmoid(z) - tgt_own), dz);
             const f32x4 w5 = *reinterpret_cast<const f32x4 *>(G.fb + kCnnW5Off + 4 * L.g);
-            const float b5 = G.fb[kCnnW5Off + 16];
-            float zs[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const bf16x4 h = relu_bf16(acc[t], tops[t]);
-                float z = 0.0f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    z = fmaf(w5[j], (float)h[j], z);
-                z += __shfl_xor(z, 16, 64);
-                z += __shfl_xor(z, 32, 64);
-                z += b5;
-                zs[t] = z;
-                const float dz = lw[t] * (sigmoid(z) - tgt[t]);
-                pb5 += dz;    // every lane group alike; the first one's is taken
+                pb5 += dz[t];    // every lane group alike; the first one's is taken
                 f32x4 dp;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    pw5[j] = fmaf((float)h[j], dz, pw5[j]);
-                    dp[j] = w5[j] * dz;
+                    pw5[j] = fmaf((float)h[t][0][j], dz[t], pw5[j]);
+                    dp[j] = w5[j] * dz[t];
                 }
                 *reinterpret_cast<bf16x4 *>(G.d16 + act_off<16>(p0 + 16 * t + kCnnGuard, 4 * L.g)) =
-                    relu_mask(dp, h);
+                    relu_mask(dp, h[t][0]);
             }
-            if (L.g < 2) {   // lane group t takes tile t's loss
-                // soft binary cross entropy in its logit form
-                const float z = L.g ? zs[1] : zs[0], tg = L.g ? tgt[1] : tgt[0];
-                ploss += (L.g ? lw[1] : lw[0])
-                         * (fmaxf(z, 0.0f) - z * tg + log1pf(expf(-fabsf(z))));
-            }
+            if (L.g < 2)   // soft binary cross entropy in its logit form
+                ploss += lw_own * (fmaxf(z, 0.0f) - z * tgt_own + log1pf(expf(-fabsf(z))));
         }
         __syncthreads();
         const __bf16 one = to_bf16(1.0f);

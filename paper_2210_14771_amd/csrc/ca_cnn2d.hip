@@ -811,7 +811,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 f32x4 acc[2];
-                acc[0] = acc[1] = b1;
+                acc[0] = acc[1] = zero4;
 #pragma unroll
                 for (int ks = 0; ks < 3; ++ks) {
                     const __bf16 *x = G.x0 + 2 * i * kL8 + (i == 2 && ks == 2 ? o_last : o[ks]);
@@ -825,7 +825,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                     for (int t = 0; t < 2; ++t)
                         *reinterpret_cast<bf16x4 *>(G.h1 + ln * kL8 + (p0 + 16 * t + 1) * 8
                                                     + 4 * (L.g & 1)) =
-                            relu_bf16(acc[t], line_in(line_ok, ln + 1) ? tops[t] : 0.0f);
+                            relu_bf16(acc[t] + b1, line_in(line_ok, ln + 1) ? tops[t] : 0.0f);
             }
         }
         const Frag<96, 1> w2 = load_frag<96, 1>(A + kC2A[1]);
@@ -833,6 +833,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         {
             const Place L(fresh(lane));
             const int p0 = 32 * wv + L.col;
+            const f32x4 b2 = *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[1] + 4 * L.g);
             int o[3];   // K group k (of 9): da = k / 3, dl = k % 3
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks) {
@@ -843,7 +844,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 f32x4 acc[2];
-                acc[0] = acc[1] = *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[1] + 4 * L.g);
+                acc[0] = acc[1] = zero4;
 #pragma unroll
                 for (int ks = 0; ks < 3; ++ks)
 #pragma unroll
@@ -854,7 +855,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                 for (int t = 0; t < 2; ++t)
                     *reinterpret_cast<bf16x4 *>(G.h2 + i * kL16
                                                 + off16(p0 + 16 * t + 1, 4 * L.g)) =
-                        relu_bf16(acc[t], line_in(line_ok, i + 2) ? tops[t] : 0.0f);
+                        relu_bf16(acc[t] + b2, line_in(line_ok, i + 2) ? tops[t] : 0.0f);
             }
         }
         __syncthreads();
@@ -865,10 +866,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             const int p0 = 32 * wv + L.col;
             const int frag = (L.g * 16 + L.col) * 8;
             f32x4 acc[2][2];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                acc[mt][0] = acc[mt][1] =
-                    *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[2] + 16 * mt + 4 * L.g);
+            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 5; ++ks) {
                 // K group k (of 18; two more have zero weights): tap k / 2,
@@ -888,43 +886,37 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             f32x4 w4[2];
             w4[0] = *reinterpret_cast<const f32x4 *>(G.fb + kC2FW4 + 4 * L.g);
             w4[1] = *reinterpret_cast<const f32x4 *>(G.fb + kC2FW4 + 16 + 4 * L.g);
-            float zs[2];
+            bf16x4 h[2][2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+                    h[t][mt] = relu_bf16(
+                        acc[mt][t]
+                            + *reinterpret_cast<const f32x4 *>(G.fb + kC2FB[2] + 16 * mt + 4 * L.g),
+                        line_in(line_ok, 3) ? tops[t] : 0.0f);
+            const int own = L.g & 1;   // this lane's tile from here
+            const float z = ordered_dot(G.fb + kC2FW4, h, G.fb[kC2FB4]);
+            const float lw_own = own ? lw[1] : lw[0], tgt_own = own ? tgt[1] : tgt[0];
+            float dz[2];
+            to_all_groups(lw_own * (sigmoid(z) - tgt_own), dz);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const float top = line_in(line_ok, 3) ? tops[t] : 0.0f;
-                bf16x4 h[2];
-                float z = 0.0f;
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt) {
-                    h[mt] = relu_bf16(acc[mt][t], top);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        z = fmaf(w4[mt][j], (float)h[mt][j], z);
-                }
-                z += __shfl_xor(z, 16, 64);
-                z += __shfl_xor(z, 32, 64);
-                z += G.fb[kC2FB4];
-                zs[t] = z;
-                const float dz = lw[t] * (sigmoid(z) - tgt[t]);
-                pb4 += dz;    // every lane group alike; the first one's is taken
+                pb4 += dz[t];    // every lane group alike; the first one's is taken
 #pragma unroll
                 for (int mt = 0; mt < 2; ++mt) {
                     f32x4 dp;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        pw4[mt][j] = fmaf((float)h[mt][j], dz, pw4[mt][j]);
-                        dp[j] = w4[mt][j] * dz;
+                        pw4[mt][j] = fmaf((float)h[t][mt][j], dz[t], pw4[mt][j]);
+                        dp[j] = w4[mt][j] * dz[t];
                     }
                     *reinterpret_cast<bf16x4 *>(G.d + off32(p0 + 16 * t + 1, 16 * mt + 4 * L.g)) =
-                        relu_mask(dp, h[mt]);
+                        relu_mask(dp, h[t][mt]);
                 }
             }
-            if (L.g < 2) {   // lane group t takes tile t's loss
-                // -(t log s + (1 - t) log(1 - s)) = max(z, 0) - z t + log(1 + e^-|z|)
-                const float z = L.g ? zs[1] : zs[0], tg = L.g ? tgt[1] : tgt[0];
-                loss += (L.g ? lw[1] : lw[0])
-                        * (fmaxf(z, 0.0f) - z * tg + log1pf(__expf(-fabsf(z))));
-            }
+            if (L.g < 2)   // -(t log s + (1 - t) log(1 - s)) = max(z, 0) - z t + log(1 + e^-|z|)
+                loss += lw_own * (fmaxf(z, 0.0f) - z * tgt_own + log1pf(__expf(-fabsf(z))));
             if (tid < 8)   // guard positions of dP3
                 *reinterpret_cast<bf16x8 *>(G.d + (tid >> 2) * (kPos - 1) * 32 + (tid & 3) * 8) =
                     bf16x8{};
