@@ -474,7 +474,16 @@ __global__ __launch_bounds__(kCnnWaveBlock) __attribute__((amdgpu_waves_per_eu(2
     load_wave_frag(fr, a.model, lane);
     wave_clear(x0, lane);
     const int S = a.n_h + a.n_v;
-    for (int item = first + (int)(blockIdx.x >> 3); item < last; item += per_xcd_groups) {
+    // A workgroup's items rotate by half a frame's strips from turn to turn:
+    // horizontal and vertical strips differ in length, and a plain stride by
+    // the workgroup count, often a multiple of a frame's strips, gave half of
+    // the workgroups nothing but the long ones (64 1080p frames, 4 items each:
+    // 36 windows a wave against 20; about 290 us so, 265 us rotated).
+    for (int turn = 0;; ++turn) {
+        const int item = first + turn * per_xcd_groups
+                         + ((int)(blockIdx.x >> 3) + turn * (S / 2)) % per_xcd_groups;
+        if (item >= last)
+            break;
         const int f = uniform_int(a.frame0 + item / S);
         const int st = uniform_int(item % S);
         const FrameDev d = a.fd[f];
