@@ -413,16 +413,19 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_strips(Cnn2dStripArgs a)
 }
 
 // Element offset of channels c .. c + 3 (c a multiple of 4) of position row
-// `pos` in a 16- or 32-channel buffer line.  The 16-byte chunks of a row are
-// permuted by position (XOR), which spreads 16 rows over all banks; shifting
-// by whole 16-row tiles keeps the permutation.
-__device__ __forceinline__ int off16(int pos, int c)
-{
-    return pos * 16 + ((((c >> 3) ^ (pos >> 3)) & 1) << 3) + (c & 7);
-}
+// `pos` in a 16- or 32-channel buffer line.  With 32 channels the chunk pairs
+// of a row are exchanged in every other group of four rows, so that the 16
+// rows of each group of lanes that an LDS read serves together start in
+// distinct bank groups (lanes 0-3, 12-15 and 20-27; 4-11, 16-19 and 28-31; the
+// same of the upper half, measured; chunks permuted four ways met two-way
+// conflicts: 273.3 us a training step of 14,336 windows, 271.2 us so); 8- and
+// 16-channel rows need nothing at this line pitch (2 rows beyond a multiple of 16: the last tap of
+// a line and the first of the next share their banks' order).
+static_assert(kPos % 16 == 2 && (kC2Win / 2 + 2) % 16 == 2, "line pitch");
+__device__ __forceinline__ int off16(int pos, int c) { return pos * 16 + c; }
 __device__ __forceinline__ int off32(int pos, int c)
 {
-    return pos * 32 + ((((c >> 3) ^ (pos >> 2)) & 3) << 3) + (c & 7);
+    return pos * 32 + (((c >> 3) ^ ((pos >> 1) & 2)) << 3) + (c & 7);
 }
 
 constexpr int kL8 = kPos * 8, kL16 = kPos * 16;   // elements of a buffer line
@@ -685,8 +688,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_cnn2d_windows(const uint8_t *mode
 // Bound by LDS bandwidth: about 131 fragment reads of 1 KB a wave and window
 // (4,100 cycles a compute unit at 128 bytes a cycle) beside 2,400 cycles of
 // MFMA a SIMD; 80 KB of LDS and 256 registers let two workgroups share a
-// compute unit.  16-byte chunks of the 16- and 32-channel rows are permuted
-// by position (XOR), which spreads 16 rows over all banks.  Measured, 14,336
+// compute unit.  Measured, 14,336
 // windows: 3137 us with the weight gradients as 4 x 4 outer products on the
 // vector units (723 work units a workgroup), 295 us so (kernel trace); of a
 // SIMD's cycles
