@@ -502,7 +502,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
             if (ctx->cnn_groups_per_xcd == 0)
                 ctx->cnn_groups_per_xcd =
                     std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8 * ca::cnn_strips_blocks_per_cu());
-            ok = ca::launch_cnn_strips(c, std::min(c.per_xcd, ctx->cnn_groups_per_xcd), st, s0, s1)
+            ok = ca::launch_cnn_strips(c, ctx->cnn_groups_per_xcd, st, s0, s1)
                  == hipSuccess;
         } else if (f0 == 0 && f1 == n && !pl->dynamic
                    && (pl->classes.size() > 1

@@ -45,6 +45,7 @@ struct CnnStripArgs {
     int32_t n_items;
     int32_t per_xcd;
     int32_t frame0;
+    int32_t parts;            // waves that share a half strip (set by the launch)
 };
 
 struct CnnTrainArgs {
@@ -72,9 +73,9 @@ hipError_t launch_cnn_pack(const float *master, uint8_t *model, hipStream_t s);
 hipError_t launch_mfma_probe(float *out, hipStream_t s);
 hipError_t launch_cnn_windows(const uint8_t *model, const uint8_t *win, const int32_t *range,
                               float *z, int n, hipStream_t s);
-// Learned candidates; a.per_xcd = items per XCD slice, groups_per_xcd =
-// workgroups per XCD (each takes the slice's items in turn).
-hipError_t launch_cnn_strips(const CnnStripArgs &a, int groups_per_xcd, hipStream_t s,
+// Learned candidates; a.per_xcd = items per XCD slice, resident_per_xcd = the
+// workgroups that an XCD holds at once (each takes the slice's items in turn).
+hipError_t launch_cnn_strips(CnnStripArgs a, int resident_per_xcd, hipStream_t s,
                              hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // Resident workgroups of k_cnn_strips per compute unit.
 int cnn_strips_blocks_per_cu();

@@ -257,13 +257,7 @@ __device__ void wave_clear(__bf16 *x0, int lane)
         p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// Gather one window of a strip into a wave's x0: lane l fills positions 2l and
-// 2l + 1 (24 channels each: 8 lines x RGB, (v - 128) / 64); positions outside
-// the strip are zero.  Where the pair lies inside the strip and every dword
-// touched lies inside the frame (decided once per lane), bytes come from
-// aligned dword loads split with v_alignbyte (a horizontal strip: 6 bytes of
-// each of 8 rows; a vertical one: 24 bytes of each of 2 rows); elsewhere
-// (strip ends, clamped lines, frame edges) from byte loads.
+// One position's 24 input channels from its bytes: (v - 128) / 64.
 __device__ __forceinline__ void store_row24(__bf16 *row, const uint32_t (&u)[6])
 {
     typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
@@ -294,77 +288,6 @@ __device__ __forceinline__ void put_line(uint32_t (&u)[2][6], int j, uint32_t b0
     u[1][k >> 2] |= p1 << (8 * (k & 3));
     if ((k & 3) > 1)
         u[1][(k >> 2) + 1] |= p1 >> (32 - 8 * (k & 3));
-}
-
-__device__ __forceinline__ void wave_gather(__bf16 *x0, const uint8_t *frame, int W, int H, int rs,
-                                            bool horizontal, int pos, int L, int start, int lane)
-{
-    const int p = start + 2 * lane;
-    const int extent = horizontal ? H : W;
-    // every dword window below stays inside the frame: horizontal, 3p - 3 >= 0
-    // and 3p + 12 <= 3W; vertical, 3(pos - 3) - 3 >= 0 and 3(pos - 3) + 28 <= 3W
-    const bool fast = p >= 0 && p + 1 < L
-                      && (horizontal ? (p >= 1 && p <= W - 4) : (pos >= 4 && pos <= W - 7));
-    uint32_t u[2][6];
-    if (fast) {
-        if (horizontal) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int i = 0; i < 6; ++i)
-                    u[k][i] = 0;
-#pragma unroll
-            for (int j = 0; j < kCnnLines; ++j) {
-                int row = pos + j - 3;
-                row = row < 0 ? 0 : (row > extent - 1 ? extent - 1 : row);
-                const uint8_t *q = frame + (int64_t)row * rs + 3 * p;
-                const uint32_t sh = (uint32_t)(reinterpret_cast<uintptr_t>(q) & 3);
-                const uint32_t *w = reinterpret_cast<const uint32_t *>(q - sh);
-                const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
-                put_line(u, j, __builtin_amdgcn_alignbyte(w1, w0, sh),
-                         __builtin_amdgcn_alignbyte(w2, w1, sh));
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const uint8_t *q = frame + (int64_t)(p + k) * rs + 3 * (pos - 3);
-                const uint32_t sh = (uint32_t)(reinterpret_cast<uintptr_t>(q) & 3);
-                const uint32_t *w = reinterpret_cast<const uint32_t *>(q - sh);
-                uint32_t wd[7];
-#pragma unroll
-                for (int i = 0; i < 7; ++i)
-                    wd[i] = w[i];
-#pragma unroll
-                for (int i = 0; i < 6; ++i)
-                    u[k][i] = __builtin_amdgcn_alignbyte(wd[i + 1], wd[i], sh);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int pk = p + k;
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-                u[k][i] = 0x80808080u;   // (128 - 128) / 64 = 0
-            if (pk >= 0 && pk < L) {
-#pragma unroll
-                for (int j = 0; j < kCnnLines; ++j) {
-                    int across = pos + j - 3;
-                    across = across < 0 ? 0 : (across > extent - 1 ? extent - 1 : across);
-                    const uint8_t *px = horizontal ? frame + (int64_t)across * rs + 3 * pk
-                                                   : frame + (int64_t)pk * rs + 3 * across;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const int b = 3 * j + c;
-                        u[k][b >> 2] = (u[k][b >> 2] & ~(0xFFu << (8 * (b & 3))))
-                                       | ((uint32_t)px[c] << (8 * (b & 3)));
-                    }
-                }
-            }
-        }
-    }
-    store_row24(x0 + (2 * lane + kCnnGuard) * 24, u[0]);
-    store_row24(x0 + (2 * lane + 1 + kCnnGuard) * 24, u[1]);
 }
 
 // --------------------------------------------------------------- kernels --
@@ -451,93 +374,411 @@ __global__ __launch_bounds__(kCnnWaveBlock) void k_cnn_windows(const uint8_t *mo
     }
 }
 
-// Learned candidates: both half strips of each (frame, strip) item, scored
-// by the network, best pixel of each half (ties: outermost).  A workgroup of
-// kCnnWaveBlock / 64 waves takes items in turn (XCD-aware slices); its waves
-// share an item's windows.
-__global__ __launch_bounds__(kCnnWaveBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_cnn_strips(CnnStripArgs a)
+// ---------------------------------------------------------------- strips --
+//
+// Learned candidates: the best-scoring pixel of each half strip (ties:
+// outermost).  A wave walks along a half strip, or along a part of one, in
+// steps of 64 positions: layer l works two positions per layer behind the
+// input, so a step's outputs need only the step's rows of the layer before and
+// its last four rows of the step before, which stay in the layer's buffer.
+//
+// Column c of tile j is position 4 c + j of the step, so the inputs of tile j
+// at tap t are those of tile j + t at tap 0: the four tiles of a layer read
+// eight B fragments where tiles of 16 neighbours would read twenty.  Rows are
+// stored in four planes, row 4 i + j as row i of plane j.
+//
+// All weights stay in registers (230 with the rest), so two waves share a SIMD
+// and eight a workgroup's LDS.  With few half strips the waves of a workgroup
+// share them (the launch chooses 1, 2, 4 or 8 a half strip, as many as keep
+// every wave resident): a lone frame's are scored by 8 times 128 waves.
+//
+// Bound by the chain of layers within a step (LDS round trips that two waves
+// cover in part) beside about 340 vector instructions and 104 MFMAs a step.
+// Measured, 64 1080p frames, 32 + 32 strips (kernel trace): 277 us with windows
+// of 128 positions of which 112 are used and 68 KB of fragment reads per 64
+// positions; 244 us in steps of 32 positions with four waves a SIMD and the
+// larger layers' weights in LDS (98 KB: bound by LDS); 194 us so (32 KB).
+
+constexpr int kStep = 64;
+constexpr int kStripWaves = 8;
+
+// A layer's input rows: 4 of the step before, then the step's 64, in four
+// planes; C channels (24 padded with zeros to 32) at PITCH, ROWS a plane.
+template <int PITCH, int ROWS>
+struct alignas(16) StripPlanes {
+    static constexpr int kPlane = ROWS * PITCH;
+    __bf16 v[4 * kPlane];
+};
+
+struct StripRows {               // one wave's inputs of the four convolutions
+    StripPlanes<32, 17> x0;
+    StripPlanes<16, 18> h1;      // K is padded: a row that stays zero
+    StripPlanes<32, 17> h2, h3;
+};
+
+// Offset of channels c .. c + 3 (c a multiple of 4) of a plane's row.  With
+// 64-byte rows the chunk pairs are exchanged in every other group of four rows,
+// which spreads a fragment's rows over the banks.
+template <int PITCH>
+__device__ __forceinline__ int strip_off(int row, int c)
+{
+    if (PITCH == 16)
+        return row * 16 + c;
+    return row * 32 + (((c >> 3) ^ (((row >> 2) & 1) * 3)) << 3) + (c & 7);
+}
+
+// A half strip, or a part of one, as a wave walks along it.
+struct StripWalk {
+    const uint8_t *frame;
+    int64_t along, across;   // bytes from position to position, from line to line
+    int first;               // first line (may lie outside the frame)
+    int L, lines;            // positions; lines of the frame
+    bool packed;             // a position's 24 bytes adjoin and lie in the frame
+    bool last_row;           // the frame's last pixel may be among the inputs
+};
+
+// A lane's inputs of a step, position x + lane: 24 bytes, or a dword of three
+// bytes for each line.  A dword's fourth byte may belong to the next pixel or
+// row; only the frame's last pixel has none.
+__device__ __forceinline__ void strip_fetch(uint32_t (&px)[8], const StripWalk &k, int x, int lane)
+{
+    int p = x + lane;
+    p = p < 0 ? 0 : (p > k.L - 1 ? k.L - 1 : p);
+    const uint8_t *q = k.frame + p * k.along;
+    if (k.packed) {
+        __builtin_memcpy(px, q + k.first * k.across, 24);
+        return;
+    }
+    const bool bytes = k.last_row && x + kStep >= k.L;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        int line = k.first + j;
+        line = line < 0 ? 0 : (line > k.lines - 1 ? k.lines - 1 : line);
+        const uint8_t *v = q + line * k.across;
+        if (bytes)
+            px[j] = v[0] | (uint32_t)v[1] << 8 | (uint32_t)v[2] << 16;
+        else
+            __builtin_memcpy(&px[j], v, 4);
+    }
+}
+
+// The step's input rows, (v - 128) / 64, zero outside the strip.
+__device__ __forceinline__ void strip_encode(__bf16 *X, uint32_t (&px)[8], const StripWalk &k, int x,
+                                             const int (&xi)[3], int lane)
+{
+    if (!k.packed) {
+        // dwords j = 4 i .. 4 i + 3 of three bytes to three of four
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t a = px[4 * i], b = px[4 * i + 1], c = px[4 * i + 2], e = px[4 * i + 3];
+            px[3 * i] = __builtin_amdgcn_perm(b, a, 0x04020100u);
+            px[3 * i + 1] = __builtin_amdgcn_perm(c, b, 0x05040201u);
+            px[3 * i + 2] = __builtin_amdgcn_perm(e, c, 0x06050402u);
+        }
+    }
+    if (x < 0 || x + kStep > k.L) {
+        const bool in = (uint32_t)(x + lane) < (uint32_t)k.L;
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            px[i] = in ? px[i] : 0x80808080u;   // (128 - 128) / 64 = 0
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = (float)((px[2 * i + (e >> 2)] >> (8 * (e & 3))) & 0xFFu);
+            o[e] = to_bf16(fmaf(v, 1.0f / 64.0f, -2.0f));   // exact
+        }
+        *reinterpret_cast<bf16x8 *>(X + xi[i]) = o;
+    }
+}
+
+// The last four rows of a step become the first four of the next: row 16 of
+// each plane row 0 (of 16-channel planes the zero row too, as row 1, which the
+// next step writes before it is read).
+template <int PITCH, int ROWS>
+__device__ __forceinline__ uint32_t strip_keep(const StripPlanes<PITCH, ROWS> &X, int lane)
+{
+    return *reinterpret_cast<const uint32_t *>(X.v + (lane >> 4) * X.kPlane + 16 * PITCH
+                                               + 2 * (lane & 15));
+}
+template <int PITCH, int ROWS>
+__device__ __forceinline__ void strip_kept(StripPlanes<PITCH, ROWS> &X, uint32_t v, int lane)
+{
+    *reinterpret_cast<uint32_t *>(X.v + (lane >> 4) * X.kPlane + 2 * (lane & 15)) = v;
+}
+
+// Whether the step's outputs of a layer exist: +inf inside the strip, 0
+// outside, for this lane's column of each tile; n = position of the step's
+// first output.
+__device__ __forceinline__ void strip_tops(float (&top)[4], int n, int L, int lane)
+{
+    const bool inside = n >= 0 && n + kStep <= L;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        top[j] = __builtin_inff();
+    if (!inside) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            top[j] = (uint32_t)(n + 4 * (lane & 15) + j) < (uint32_t)L ? __builtin_inff() : 0.0f;
+    }
+}
+
+// Fragments s = 0 .. 7 of a 32-channel layer's input: positions 4 c + s, lane
+// group g its channels 8 g ..; xo: the offsets of rows c and c + 1.
+__device__ __forceinline__ void strip_frags(bf16x8 (&f)[8], const StripPlanes<32, 17> &X,
+                                            const int (&xo)[2])
+{
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+        f[s] = frag_at(X.v + (s & 3) * X.kPlane + xo[s >> 2]);
+}
+
+template <int MT, typename Y>
+__device__ __forceinline__ void strip_store(Y &out, const f32x4 (&acc)[4][MT], const int (&yo)[MT],
+                                            int n, int L, int lane)
+{
+    float top[4];
+    strip_tops(top, n, L, lane);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            *reinterpret_cast<bf16x4 *>(out.v + j * out.kPlane + yo[mt]) =
+                relu_bf16(acc[j][mt], top[j]);
+}
+
+__global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs a)
 {
     extern __shared__ __align__(16) uint8_t cnn_smem[];
-    __shared__ uint64_t s_best[kCnnWaveBlock / 64][2];
-    constexpr int kWaves = kCnnWaveBlock / 64;
+    __shared__ uint64_t s_best[kStripWaves];
+    StripRows *rows = reinterpret_cast<StripRows *>(cnn_smem);
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    __bf16 *x0 = reinterpret_cast<__bf16 *>(cnn_smem + wv * kWaveBytes);
-    __bf16 *hb = x0 + kWaveBuf;
+    const int wv = uniform_int(threadIdx.x >> 6);
+    const int group = blockIdx.x >> 3, groups = gridDim.x >> 3;
     const int xcd = blockIdx.x & 7;
-    const int per_xcd_groups = gridDim.x >> 3;
     const int first = xcd * a.per_xcd;
-    const int last = min(first + a.per_xcd, a.n_items);
-    if (first + (int)(blockIdx.x >> 3) >= last)
+    const int n_units = 2 * (min(first + a.per_xcd, a.n_items) - first);
+    const int sets = kStripWaves / a.parts;          // half strips a workgroup takes at a time
+    if (group * sets >= n_units)
         return;
-    WaveFrag fr;
-    load_wave_frag(fr, a.model, lane);
-    wave_clear(x0, lane);
-    const int S = a.n_h + a.n_v;
-    // A workgroup's items rotate by half a frame's strips from turn to turn:
-    // horizontal and vertical strips differ in length, and a plain stride by
-    // the workgroup count, often a multiple of a frame's strips, gave half of
-    // the workgroups nothing but the long ones (64 1080p frames, 4 items each:
-    // 36 windows a wave against 20; about 290 us so, 265 us rotated).
-    for (int turn = 0;; ++turn) {
-        const int item = first + turn * per_xcd_groups
-                         + ((int)(blockIdx.x >> 3) + turn * (S / 2)) % per_xcd_groups;
-        if (item >= last)
-            break;
-        const int f = uniform_int(a.frame0 + item / S);
-        const int st = uniform_int(item % S);
-        const FrameDev d = a.fd[f];
-        const uint8_t *frame = a.frames + d.offset;
-        const bool horizontal = st < a.n_h;
-        const int pos = uniform_int(a.strips[d.table + st]);
-        const int L = uniform_int(horizontal ? d.W : d.H);
-        const int n_win = (L + kCnnOut - 1) / kCnnOut;
-        uint64_t best[2] = {0, 0};
-        for (int w = wv; w < n_win; w += kWaves) {
-            const int p0 = w * kCnnOut;
-            const int start = p0 - kCnnHalo;
-            const int lo = start >= 0 ? 0 : -start;
-            const int hi = L - start < kCnnWin ? L - start : kCnnWin;
-            wave_sync();
-            wave_gather(x0, frame, d.W, d.H, d.rs, horizontal, pos, L, start, lane);
-            wave_forward(fr, x0, hb, lo, hi, lane, [&](int n, float z) {
-                const int p = start + n;
-                if (n >= kCnnHalo && n < kCnnWin - kCnnHalo && p < L) {
-                    const float sc = sigmoid(z);
-                    const int half = p < (L >> 1) ? 0 : 1;
-                    const int k = half == 0 ? p : L - 1 - p;
-                    const uint64_t key = ((uint64_t)__float_as_uint(sc) << 32)
-                                         | (uint64_t)(0xFFFFFFFFu - (uint32_t)k);
-                    best[half] = best[half] > key ? best[half] : key;
-                }
-            });
-        }
+    const __bf16 *W = reinterpret_cast<const __bf16 *>(a.model);
+    const float *fb = reinterpret_cast<const float *>(a.model + kCnnFloatsOff);
+    const int col = lane & 15, g = lane >> 4;
+    StripRows &R = rows[wv];
+    for (int i = lane; i < (int)(sizeof(StripRows) / 16); i += 64)
+        reinterpret_cast<uint4 *>(&R)[i] = make_uint4(0u, 0u, 0u, 0u);
+    bf16x8 w1[5], w2[2][3], w3[2][5], w4[5];
+    f32x4 b1, b2[2], b3[2], b4, w5;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            uint64_t v = best[half];
+    for (int t = 0; t < 5; ++t) {
+        // 24 channels a tap in the model's rows, 32 here
+        w1[t] = bf16x8{};
+        if (g < 3)
+            w1[t] = frag_at(W + kCnnWOff[0] + col * 128 + 24 * t + 8 * g);
+        w3[0][t] = frag_at(W + kCnnWOff[2] + col * 160 + 32 * t + 8 * g);
+        w3[1][t] = frag_at(W + kCnnWOff[2] + (16 + col) * 160 + 32 * t + 8 * g);
+        w4[t] = frag_at(W + kCnnWOff[3] + col * 160 + 32 * t + 8 * g);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) {
+        w2[0][ks] = frag_at(W + kCnnWOff[1] + col * 96 + 32 * ks + 8 * g);
+        w2[1][ks] = frag_at(W + kCnnWOff[1] + (16 + col) * 96 + 32 * ks + 8 * g);
+    }
+    auto four = [&](int at) { return *reinterpret_cast<const f32x4 *>(fb + at + 4 * g); };
+    b1 = four(kCnnBOff[0]);
+    b2[0] = four(kCnnBOff[1]);
+    b2[1] = four(kCnnBOff[1] + 16);
+    b3[0] = four(kCnnBOff[2]);
+    b3[1] = four(kCnnBOff[2] + 16);
+    b4 = four(kCnnBOff[3]);
+    w5 = four(kCnnW5Off);
+    const float b5 = fb[kCnnW5Off + 16];
+
+    // input rows of this lane's position; rows c and c + 1 of a 32-channel
+    // plane; of 16 channels, K groups g / 2 of a fragment lie one position
+    // apart, from plane 3 to plane 0 of the next row at every fourth; outputs
+    int xi[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        xi[i] = (lane & 3) * R.x0.kPlane + strip_off<32>((lane >> 2) + 1, 8 * i);
+    const int xo[2] = {strip_off<32>(col, 8 * g), strip_off<32>(col + 1, 8 * g)};
+    const int at2 = strip_off<16>(col, 8 * (g & 1));
+    const int xo2[2] = {at2 + (g >> 1) * R.h1.kPlane, at2 + (g >> 1) * (16 - 3 * R.h1.kPlane)};
+    const int yo1[1] = {strip_off<16>(col + 1, 4 * g)};
+    const int yo[2] = {strip_off<32>(col + 1, 4 * g), strip_off<32>(col + 1, 16 + 4 * g)};
+
+    const int S = a.n_h + a.n_v;
+    const int set = wv / a.parts, part = wv % a.parts;
+    const int slots = groups * sets;
+    for (int turn = 0; turn * slots < n_units; ++turn) {
+        // Half strips rotate by half a frame's from turn to turn: horizontal
+        // and vertical ones differ in length, and the slots are often a multiple
+        // of a frame's half strips, so a plain stride would give half of the
+        // waves nothing but the long ones.
+        const int unit = uniform_int(turn * slots + (group * sets + set + turn * S) % slots);
+        uint64_t best = 0;
+        int f = 0, st = 0, half = 0, pos = 0, L = 0;
+        bool horizontal = false;
+        if (unit < n_units) {
+            const int item = first + (unit >> 1);
+            half = unit & 1;
+            f = uniform_int(a.frame0 + item / S);
+            st = uniform_int(item % S);
+            const FrameDev d = a.fd[f];
+            horizontal = st < a.n_h;
+            pos = uniform_int(a.strips[d.table + st]);
+            StripWalk k;
+            k.frame = a.frames + d.offset;
+            k.along = horizontal ? 3 : d.rs;
+            k.across = horizontal ? d.rs : 3;
+            k.first = pos - 3;
+            k.L = L = uniform_int(horizontal ? d.W : d.H);
+            k.lines = uniform_int(horizontal ? d.H : d.W);
+            k.packed = !horizontal && pos >= 3 && pos + 4 < k.lines;
+            k.last_row = pos + 4 >= k.lines - 1;
+            const int h0 = half ? L >> 1 : 0, h1 = half ? L : L >> 1;
+            const int each = (h1 - h0 + a.parts - 1) / a.parts;
+            const int p0 = h0 + part * each, p1 = min(p0 + each, h1);
+            uint32_t px[8];
+            int x = p0 - kCnnHalo;   // first new input position of the step
+            if (p0 < p1)
+                strip_fetch(px, k, x, lane);
+            for (; p0 < p1 && x - kCnnHalo < p1; x += kStep) {
+                bf16x8 b[8];
+                strip_encode(R.x0.v, px, k, x, xi, lane);
+                if (x + kStep - kCnnHalo < p1)
+                    strip_fetch(px, k, x + kStep, lane);
+                wave_sync();
+                uint32_t kept = strip_keep(R.x0, lane);
+                strip_frags(b, R.x0, xo);
+                {
+                    f32x4 acc[4][1];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[j][0] = b1;
+#pragma unroll
+                    for (int t = 0; t < 5; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            acc[j][0] = mma(w1[t], b[j + t], acc[j][0]);
+                    strip_store<1>(R.h1, acc, yo1, x - 2, L, lane);
+                }
+                wave_sync();
+                strip_kept(R.x0, kept, lane);
+                kept = strip_keep(R.h1, lane);
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+                    b[s] = frag_at(R.h1.v + (s & 3) * R.h1.kPlane + (s >> 2) * 16
+                                   + xo2[(s & 3) == 3]);
+                {
+                    f32x4 acc[4][2];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        acc[j][0] = b2[0];
+                        acc[j][1] = b2[1];
+                    }
+#pragma unroll
+                    for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            acc[j][0] = mma(w2[0][ks], b[j + 2 * ks], acc[j][0]);
+                            acc[j][1] = mma(w2[1][ks], b[j + 2 * ks], acc[j][1]);
+                        }
+                    strip_store<2>(R.h2, acc, yo, x - 4, L, lane);
+                }
+                wave_sync();
+                strip_kept(R.h1, kept, lane);
+                kept = strip_keep(R.h2, lane);
+                strip_frags(b, R.h2, xo);
+                {
+                    f32x4 acc[4][2];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        acc[j][0] = b3[0];
+                        acc[j][1] = b3[1];
+                    }
+#pragma unroll
+                    for (int t = 0; t < 5; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            acc[j][0] = mma(w3[0][t], b[j + t], acc[j][0]);
+                            acc[j][1] = mma(w3[1][t], b[j + t], acc[j][1]);
+                        }
+                    strip_store<2>(R.h3, acc, yo, x - 6, L, lane);
+                }
+                wave_sync();
+                strip_kept(R.h2, kept, lane);
+                kept = strip_keep(R.h3, lane);
+                strip_frags(b, R.h3, xo);
+                float part_z[4];   // lane group's share of each tile's 1x1 layer
+                {
+                    f32x4 acc[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[j] = b4;
+#pragma unroll
+                    for (int t = 0; t < 5; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            acc[j] = mma(w4[t], b[j + t], acc[j]);
+                    float top[4];
+                    strip_tops(top, x - 8, L, lane);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const bf16x4 h = relu_bf16(acc[j], top[j]);
+                        float z = 0.0f;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            z = fmaf(w5[e], (float)h[e], z);
+                        part_z[j] = z;
+                    }
+                }
+                wave_sync();
+                strip_kept(R.h3, kept, lane);
+                // summed over the lane groups, (0 + 1) + (2 + 3): lane group q
+                // ends with tile q's
+                uint32_t z0 = __builtin_bit_cast(uint32_t, part_z[0]);
+                uint32_t z1 = __builtin_bit_cast(uint32_t, part_z[1]);
+                uint32_t z2 = __builtin_bit_cast(uint32_t, part_z[2]);
+                uint32_t z3 = __builtin_bit_cast(uint32_t, part_z[3]);
+                swap_rows(z0, z1);
+                swap_rows(z2, z3);
+                uint32_t low = __float_as_uint(__uint_as_float(z0) + __uint_as_float(z1));
+                uint32_t high = __float_as_uint(__uint_as_float(z2) + __uint_as_float(z3));
+                swap_halves(low, high);
+                const float z = b5 + (__uint_as_float(low) + __uint_as_float(high));
+                const int p = x - kCnnHalo + 4 * col + g;
+                if (p >= p0 && p < p1) {
+                    const uint64_t key = ((uint64_t)__float_as_uint(sigmoid(z)) << 32)
+                                         | (uint64_t)(0xFFFFFFFFu - (uint32_t)(half ? L - 1 - p : p));
+                    best = best > key ? best : key;
+                }
+            }
 #pragma unroll
             for (int dd = 32; dd >= 1; dd >>= 1) {
-                const uint64_t t = __shfl_xor(v, dd, 64);
-                v = v > t ? v : t;
+                const uint64_t t = __shfl_xor(best, dd, 64);
+                best = best > t ? best : t;
             }
-            if (lane == 0)
-                s_best[wv][half] = v;
         }
-        __syncthreads();
-        if (threadIdx.x < 2) {
-            const int half = threadIdx.x;
-            uint64_t bb = s_best[0][half];
-            for (int w2 = 1; w2 < kWaves; ++w2)
-                bb = bb > s_best[w2][half] ? bb : s_best[w2][half];
-            const int k = (int)(0xFFFFFFFFu - (uint32_t)bb);
+        if (a.parts > 1) {
+            if (lane == 0)
+                s_best[wv] = best;
+            __syncthreads();
+            for (int w = 1; w < a.parts; ++w)
+                best = best > s_best[set * a.parts + w] ? best : s_best[set * a.parts + w];
+            __syncthreads();
+        }
+        if (unit < n_units && part == 0 && lane == 0) {
+            const int k = (int)(0xFFFFFFFFu - (uint32_t)best);
             const int i = half == 0 ? k : L - 1 - k;
             ca_point pt;
             pt.x = (int16_t)(horizontal ? i : pos);
             pt.y = (int16_t)(horizontal ? pos : i);
-            pt.score = __uint_as_float((uint32_t)(bb >> 32));
+            pt.score = __uint_as_float((uint32_t)(best >> 32));
             a.cand[(int64_t)f * (2 * S) + 2 * st + half] = pt;
         }
-        __syncthreads();
     }
 }
 
@@ -1195,7 +1436,8 @@ hipError_t launch_cnn_windows(const uint8_t *model, const uint8_t *win, const in
 int cnn_strips_blocks_per_cu()
 {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnn_strips, kCnnWaveBlock, kCnnWaveLds)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnn_strips, 64 * kStripWaves,
+                                                     kStripWaves * sizeof(StripRows))
             != hipSuccess
         || b < 1) {
         (void)hipGetLastError();
@@ -1204,13 +1446,19 @@ int cnn_strips_blocks_per_cu()
     return b;
 }
 
-hipError_t launch_cnn_strips(const CnnStripArgs &a, int groups_per_xcd, hipStream_t s,
-                             hipEvent_t start, hipEvent_t stop)
+hipError_t launch_cnn_strips(CnnStripArgs a, int resident_per_xcd, hipStream_t s, hipEvent_t start,
+                             hipEvent_t stop)
 {
     if (a.n_items <= 0)
         return hipSuccess;
-    launch_maybe_timed(k_cnn_strips, dim3(8 * groups_per_xcd), dim3(kCnnWaveBlock), kCnnWaveLds, s,
-                       start, stop, a);
+    a.parts = 1;
+    const int units = 2 * a.per_xcd;
+    while (2 * a.parts <= kStripWaves && units * 2 * a.parts <= resident_per_xcd * kStripWaves)
+        a.parts *= 2;
+    const int sets = kStripWaves / a.parts;
+    const int groups = (units + sets - 1) / sets;
+    launch_maybe_timed(k_cnn_strips, dim3(8 * (groups < resident_per_xcd ? groups : resident_per_xcd)),
+                       dim3(64 * kStripWaves), kStripWaves * sizeof(StripRows), s, start, stop, a);
     return hipGetLastError();
 }
 
