@@ -75,7 +75,7 @@ hipError_t launch_cnn_windows(const uint8_t *model, const uint8_t *win, const in
                               float *z, int n, hipStream_t s);
 // Learned candidates; a.per_xcd = items per XCD slice, resident_per_xcd = the
 // workgroups that an XCD holds at once (each takes the slice's items in turn).
-hipError_t launch_cnn_strips(CnnStripArgs a, int resident_per_xcd, hipStream_t s,
+hipError_t launch_cnn_strips(const CnnStripArgs &a, int resident_per_xcd, hipStream_t s,
                              hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // Resident workgroups of k_cnn_strips per compute unit.
 int cnn_strips_blocks_per_cu();

@@ -1446,11 +1446,14 @@ int cnn_strips_blocks_per_cu()
     return b;
 }
 
-hipError_t launch_cnn_strips(CnnStripArgs a, int resident_per_xcd, hipStream_t s, hipEvent_t start,
-                             hipEvent_t stop)
+hipError_t launch_cnn_strips(const CnnStripArgs &args, int resident_per_xcd, hipStream_t s,
+                             hipEvent_t start, hipEvent_t stop)
 {
-    if (a.n_items <= 0)
+    if (args.n_items <= 0)
         return hipSuccess;
+    CnnStripArgs a = args;
+    // As many waves to a half strip as stay resident at once: a wave alone on
+    // a half strip of full HD takes 16 steps of some 4 us.
     a.parts = 1;
     const int units = 2 * a.per_xcd;
     while (2 * a.parts <= kStripWaves && units * 2 * a.parts <= resident_per_xcd * kStripWaves)
