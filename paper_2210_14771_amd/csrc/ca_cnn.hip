@@ -406,7 +406,7 @@ constexpr int kStripWaves = 8;
 // planes; C channels (24 padded with zeros to 32) at PITCH, ROWS a plane.
 template <int PITCH, int ROWS>
 struct alignas(16) StripPlanes {
-    static constexpr int kPlane = ROWS * PITCH;
+    static constexpr int kPlane = ROWS * PITCH + 8;
     __bf16 v[4 * kPlane];
 };
 
@@ -424,7 +424,7 @@ __device__ __forceinline__ int strip_off(int row, int c)
 {
     if (PITCH == 16)
         return row * 16 + c;
-    return row * 32 + (((c >> 3) ^ (((row >> 2) & 1) * 3)) << 3) + (c & 7);
+    return row * 32 + ((((c >> 3) ^ (row >> 2)) & 3) << 3) + (c & 7);
 }
 
 // A half strip, or a part of one, as a wave walks along it.
