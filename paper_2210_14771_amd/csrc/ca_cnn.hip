@@ -449,16 +449,21 @@ __device__ __forceinline__ void strip_fetch(uint32_t (&px)[8], const StripWalk &
         __builtin_memcpy(px, q + k.first * k.across, 24);
         return;
     }
-    const bool bytes = k.last_row && x + kStep >= k.L;
+    const uint8_t *v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         int line = k.first + j;
         line = line < 0 ? 0 : (line > k.lines - 1 ? k.lines - 1 : line);
-        const uint8_t *v = q + line * k.across;
-        if (bytes)
-            px[j] = v[0] | (uint32_t)v[1] << 8 | (uint32_t)v[2] << 16;
-        else
-            __builtin_memcpy(&px[j], v, 4);
+        v[j] = q + line * k.across;
+    }
+    if (k.last_row && x + kStep >= k.L) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            px[j] = v[j][0] | (uint32_t)v[j][1] << 8 | (uint32_t)v[j][2] << 16;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            __builtin_memcpy(&px[j], v[j], 4);
     }
 }
 
@@ -727,11 +732,14 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
                     strip_tops(top, x - 8, L, lane);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const bf16x4 h = relu_bf16(acc[j], top[j]);
-                        float z = 0.0f;
+                        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                        const u32x2 h = __builtin_bit_cast(u32x2, relu_bf16(acc[j], top[j]));
+                        float z = 0.0f;   // a bfloat16 is a float's upper half
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            z = fmaf(w5[e], (float)h[e], z);
+                        for (int e = 0; e < 2; ++e) {
+                            z = fmaf(w5[2 * e], __uint_as_float(h[e] << 16), z);
+                            z = fmaf(w5[2 * e + 1], __uint_as_float(h[e] & 0xFFFF0000u), z);
+                        }
                         part_z[j] = z;
                     }
                 }
