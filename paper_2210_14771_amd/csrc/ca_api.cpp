@@ -486,6 +486,8 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
             c.n_items = a2.n_items;
             c.per_xcd = a2.per_xcd;
             c.frame0 = f0;
+            // its LDS fills a compute unit
+            c.resident_per_xcd = std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8);
             ok = ca::launch_cnn2d_strips(c, st, s0, s1) == hipSuccess;
         } else if (learned) {
             ca::CnnStripArgs c;

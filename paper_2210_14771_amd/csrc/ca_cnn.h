@@ -126,6 +126,8 @@ struct Cnn2dStripArgs {
     int32_t n_items;
     int32_t per_xcd;
     int32_t frame0;
+    int32_t resident_per_xcd;   // workgroups that an XCD holds at once
+    int32_t parts;              // waves that share a half strip (set by the launch)
 };
 
 struct Cnn2dTrainArgs {

@@ -22,6 +22,7 @@
 #include "ca_launch.h"
 #include "ca_mfma.h"
 #include "ca_reduce.h"
+#include "ca_strip.h"
 
 namespace ca {
 namespace {
@@ -83,15 +84,6 @@ __device__ void load_wave_frag(WaveFrag &fr, const uint8_t *model, int lane)
     for (int j = 0; j < 4; ++j)
         fr.w5[j] = fb[kCnnW5Off + 4 * (lane >> 4) + j];
     fr.b5 = fb[kCnnW5Off + 16];
-}
-
-// LDS written by some lanes of the wave and read by others next: keep the
-// compiler from moving memory operations across (the hardware keeps a wave's
-// LDS operations in order).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // One convolution layer over the window: groups of kNB position tiles with
@@ -399,9 +391,6 @@ __global__ __launch_bounds__(kCnnWaveBlock) void k_cnn_windows(const uint8_t *mo
 // positions; 244 us in steps of 32 positions with four waves a SIMD and the
 // larger layers' weights in LDS (98 KB: bound by LDS); 194 us so (32 KB).
 
-constexpr int kStep = 64;
-constexpr int kStripWaves = 8;
-
 // A layer's input rows: 4 of the step before, then the step's 64, in four
 // planes; C channels (24 padded with zeros to 32) at PITCH, ROWS a plane.
 template <int PITCH, int ROWS>
@@ -425,46 +414,6 @@ __device__ __forceinline__ int strip_off(int row, int c)
     if (PITCH == 16)
         return row * 16 + c;
     return row * 32 + ((((c >> 3) ^ (row >> 2)) & 3) << 3) + (c & 7);
-}
-
-// A half strip, or a part of one, as a wave walks along it.
-struct StripWalk {
-    const uint8_t *frame;
-    int64_t along, across;   // bytes from position to position, from line to line
-    int first;               // first line (may lie outside the frame)
-    int L, lines;            // positions; lines of the frame
-    bool packed;             // a position's 24 bytes adjoin and lie in the frame
-    bool last_row;           // the frame's last pixel may be among the inputs
-};
-
-// A lane's inputs of a step, position x + lane: 24 bytes, or a dword of three
-// bytes for each line.  A dword's fourth byte may belong to the next pixel or
-// row; only the frame's last pixel has none.
-__device__ __forceinline__ void strip_fetch(uint32_t (&px)[8], const StripWalk &k, int x, int lane)
-{
-    int p = x + lane;
-    p = p < 0 ? 0 : (p > k.L - 1 ? k.L - 1 : p);
-    const uint8_t *q = k.frame + p * k.along;
-    if (k.packed) {
-        __builtin_memcpy(px, q + k.first * k.across, 24);
-        return;
-    }
-    const uint8_t *v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int line = k.first + j;
-        line = line < 0 ? 0 : (line > k.lines - 1 ? k.lines - 1 : line);
-        v[j] = q + line * k.across;
-    }
-    if (k.last_row && x + kStep >= k.L) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            px[j] = v[j][0] | (uint32_t)v[j][1] << 8 | (uint32_t)v[j][2] << 16;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            __builtin_memcpy(&px[j], v[j], 4);
-    }
 }
 
 // The step's input rows, (v - 128) / 64, zero outside the strip.
@@ -635,26 +584,20 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
             horizontal = st < a.n_h;
             pos = uniform_int(a.strips[d.table + st]);
             StripWalk k;
-            k.frame = a.frames + d.offset;
-            k.along = horizontal ? 3 : d.rs;
-            k.across = horizontal ? d.rs : 3;
-            k.first = pos - 3;
-            k.L = L = uniform_int(horizontal ? d.W : d.H);
-            k.lines = uniform_int(horizontal ? d.H : d.W);
-            k.packed = !horizontal && pos >= 3 && pos + 4 < k.lines;
-            k.last_row = pos + 4 >= k.lines - 1;
+            strip_walk<kCnnLines>(k, a.frames, d, horizontal, pos);
+            L = k.L;
             const int h0 = half ? L >> 1 : 0, h1 = half ? L : L >> 1;
             const int each = (h1 - h0 + a.parts - 1) / a.parts;
             const int p0 = h0 + part * each, p1 = min(p0 + each, h1);
             uint32_t px[8];
             int x = p0 - kCnnHalo;   // first new input position of the step
             if (p0 < p1)
-                strip_fetch(px, k, x, lane);
+                strip_fetch<kCnnLines>(px, k, x, lane);
             for (; p0 < p1 && x - kCnnHalo < p1; x += kStep) {
                 bf16x8 b[8];
                 strip_encode(R.x0.v, px, k, x, xi, lane);
                 if (x + kStep - kCnnHalo < p1)
-                    strip_fetch(px, k, x + kStep, lane);
+                    strip_fetch<kCnnLines>(px, k, x + kStep, lane);
                 wave_sync();
                 uint32_t kept = strip_keep(R.x0, lane);
                 strip_frags(b, R.x0, xo);
@@ -745,30 +688,14 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
                 }
                 wave_sync();
                 strip_kept(R.h3, kept, lane);
-                // summed over the lane groups, (0 + 1) + (2 + 3): lane group q
-                // ends with tile q's
-                uint32_t z0 = __builtin_bit_cast(uint32_t, part_z[0]);
-                uint32_t z1 = __builtin_bit_cast(uint32_t, part_z[1]);
-                uint32_t z2 = __builtin_bit_cast(uint32_t, part_z[2]);
-                uint32_t z3 = __builtin_bit_cast(uint32_t, part_z[3]);
-                swap_rows(z0, z1);
-                swap_rows(z2, z3);
-                uint32_t low = __float_as_uint(__uint_as_float(z0) + __uint_as_float(z1));
-                uint32_t high = __float_as_uint(__uint_as_float(z2) + __uint_as_float(z3));
-                swap_halves(low, high);
-                const float z = b5 + (__uint_as_float(low) + __uint_as_float(high));
+                const float z = b5 + tile_sums(part_z);
                 const int p = x - kCnnHalo + 4 * col + g;
                 if (p >= p0 && p < p1) {
-                    const uint64_t key = ((uint64_t)__float_as_uint(sigmoid(z)) << 32)
-                                         | (uint64_t)(0xFFFFFFFFu - (uint32_t)(half ? L - 1 - p : p));
+                    const uint64_t key = strip_key(z, p, half, L);
                     best = best > key ? best : key;
                 }
             }
-#pragma unroll
-            for (int dd = 32; dd >= 1; dd >>= 1) {
-                const uint64_t t = __shfl_xor(best, dd, 64);
-                best = best > t ? best : t;
-            }
+            best = wave_max(best);
         }
         if (a.parts > 1) {
             if (lane == 0)
@@ -779,13 +706,7 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
             __syncthreads();
         }
         if (unit < n_units && part == 0 && lane == 0) {
-            const int k = (int)(0xFFFFFFFFu - (uint32_t)best);
-            const int i = half == 0 ? k : L - 1 - k;
-            ca_point pt;
-            pt.x = (int16_t)(horizontal ? i : pos);
-            pt.y = (int16_t)(horizontal ? pos : i);
-            pt.score = __uint_as_float((uint32_t)(best >> 32));
-            a.cand[(int64_t)f * (2 * S) + 2 * st + half] = pt;
+            a.cand[(int64_t)f * (2 * S) + 2 * st + half] = strip_point(best, horizontal, pos, half, L);
         }
     }
 }
@@ -1460,16 +1381,8 @@ hipError_t launch_cnn_strips(const CnnStripArgs &args, int resident_per_xcd, hip
     if (args.n_items <= 0)
         return hipSuccess;
     CnnStripArgs a = args;
-    // As many waves to a half strip as stay resident at once: a wave alone on
-    // a half strip of full HD takes 16 steps of some 4 us.
-    a.parts = 1;
-    const int units = 2 * a.per_xcd;
-    while (2 * a.parts <= kStripWaves && units * 2 * a.parts <= resident_per_xcd * kStripWaves)
-        a.parts *= 2;
-    const int sets = kStripWaves / a.parts;
-    const int groups = (units + sets - 1) / sets;
-    launch_maybe_timed(k_cnn_strips, dim3(8 * (groups < resident_per_xcd ? groups : resident_per_xcd)),
-                       dim3(64 * kStripWaves), kStripWaves * sizeof(StripRows), s, start, stop, a);
+    const int groups = strip_split(a.parts, 2 * a.per_xcd, resident_per_xcd);
+    launch_maybe_timed(k_cnn_strips, dim3(8 * groups), dim3(64 * kStripWaves), kStripWaves * sizeof(StripRows), s, start, stop, a);
     return hipGetLastError();
 }
 

@@ -23,6 +23,7 @@
 #include "ca_launch.h"
 #include "ca_mfma.h"
 #include "ca_reduce.h"
+#include "ca_strip.h"
 
 namespace ca {
 namespace {
@@ -57,34 +58,6 @@ __device__ __forceinline__ Frag<KP, MT> load_frag(const __bf16 *A)
     return f;
 }
 
-// The forward weights of one orientation in registers: the three layers' A
-// fragments and this lane's biases (rows m0 .. m0 + 3 of its accumulators).
-struct FwdW {
-    Frag<96, 1> w1;
-    Frag<96, 1> w2;
-    Frag<160, 2> w3;
-    float b1[4], b2[4], b3[2][4];
-};
-
-// fb: the model's float block (in LDS).  Layer 1's weights are those of
-// output-line pairs (rows 8..15 the second line's channels).
-__device__ __forceinline__ void load_fwd_weights(FwdW &W, const uint8_t *model, bool hz,
-                                                 const float *fb)
-{
-    const __bf16 *A = reinterpret_cast<const __bf16 *>(model) + (hz ? 0 : kC2Orient);
-    W.w1 = load_frag<96, 1>(A + kC2P1);
-    W.w2 = load_frag<96, 1>(A + kC2A[1]);
-    W.w3 = load_frag<160, 2>(A + kC2A[2]);
-    const int m0 = 4 * ((threadIdx.x & 63) >> 4);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        W.b1[j] = fb[kC2FB[0] + (m0 & 7) + j];
-        W.b2[j] = fb[kC2FB[1] + m0 + j];
-        W.b3[0][j] = fb[kC2FB[2] + m0 + j];
-        W.b3[1][j] = fb[kC2FB[2] + 16 + m0 + j];
-    }
-}
-
 // Input encoding of one band position: colours normalised, coordinates in
 // [-0.5, 0.5] as (2 x - (W - 1)) / (2 (W - 1)), taken as a product with the
 // reciprocal rw = 1 / (2 (W - 1)) (and rh for y); channels 5..7 are zero.
@@ -117,298 +90,315 @@ __device__ __forceinline__ uint32_t band_lines(int line, int extent)
 
 // ----------------------------------------------------------- inference --
 
-// Learned candidates, wave level.  A workgroup takes one (frame, strip) item
-// (XCD-aware: workgroup b takes item (b % 8) per_xcd + b / 8); each of its
-// four waves scores windows of 64 positions of the strip on its own --
-// window w by wave w mod 4 -- with private LDS buffers and the layers'
-// weights in its registers, so no workgroup barrier separates the layers and
-// the waves of a compute unit overlap one another's memory and LDS latency.
-// The pixels of a wave's next window are loaded into registers while its
-// current window's layers run.  The workgroup joins its waves' best pixels
-// per half strip (ties: outermost).
+// Learned candidates: the best-scoring pixel of each half strip (ties:
+// outermost).  A wave walks along a half strip, or along a part of one, in
+// steps of 64 positions with private LDS buffers and the layers' weights of the
+// strip's orientation in its registers: layer l works one position per layer
+// behind the input, so a step's outputs need only the step's positions of the
+// layer before and its last two of the step before, which stay at the head of
+// the layer's lines.  The next step's pixels are loaded while a step's layers
+// run.
+//
+// Bound by issue: about 520 vector instructions of 4 cycles and 112 MFMAs of 16
+// a step, which add up to four fifths of a SIMD's cycles.  Measured, 64 1080p
+// frames, 32 + 32 strips (kernel trace): 313 us with windows of 64 positions of
+// which 58 are used (770 vector instructions, mostly addresses, selects and
+// conversions at the input), 252 us so.
 
-constexpr int kWWin = 64;                        // positions of a wave window
-constexpr int kWPos = kWWin + 2;                 // with a guard position at each end
-constexpr int kWStride = kWWin - 2 * kC2Halo;    // exact logits per wave window
-// A wave's two buffers: P holds the input (7 lines x 8 channels) and later
-// layer 2 (3 x 16), Q layer 1 (5 x 8) and later layer 3 (1 x 32).  Guard
-// positions and rows of one layout read under another hold stale finite
-// values (the buffers are zeroed once); they only feed the 3 halo positions
-// at each window end, whose outputs are discarded.
-constexpr int kWP = kC2Band * kWPos * 8 > 3 * kWPos * 16 ? kC2Band * kWPos * 8 : 3 * kWPos * 16;
-constexpr int kWQ = 5 * kWPos * 8 > kWPos * 32 ? 5 * kWPos * 8 : kWPos * 32;
-struct alignas(16) WaveBufs {
-    __bf16 p[kWP];
-    __bf16 q[kWQ];
+constexpr int kC2Rows = kStep + 2;   // positions of a buffer line
+struct alignas(16) Strip2dRows {     // one wave's inputs of the three layers
+    __bf16 x0[kC2Band * kC2Rows * 8];
+    __bf16 h1[5 * kC2Rows * 8];
+    __bf16 h2[3 * kC2Rows * 16];
 };
 
-// LDS written by some lanes of a wave and read by others next: keep the
-// compiler from moving memory operations across (the hardware keeps a
-// wave's LDS operations in order).
-__device__ __forceinline__ void wave_sync()
+// The last two positions of each line of a step become the first two of the
+// next; lanes beyond the lines' dwords repeat the last one's.
+template <int LINES, int C>
+__device__ __forceinline__ int strip2d_at(int lane)
 {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    constexpr int kWords = 2 * C / 2;   // dwords of two positions
+    const int i = lane < LINES * kWords ? lane : LINES * kWords - 1;
+    return i / kWords * (kC2Rows * C) + 2 * (i % kWords);
+}
+template <int C>
+__device__ __forceinline__ uint32_t strip2d_keep(const __bf16 *X, int at)
+{
+    return *reinterpret_cast<const uint32_t *>(X + at + kStep * C);
+}
+__device__ __forceinline__ void strip2d_kept(__bf16 *X, uint32_t v, int at)
+{
+    *reinterpret_cast<uint32_t *>(X + at) = v;
 }
 
-// One 3x3 layer over a wave window, all tiles by this wave: for output line
-// i, acc[m][n] = bias[m] + sum_k A[m][k] X[line i + da][n + dl - 1][c] with
-// k = (3 da + dl) CP + c.  The lane's B offsets (its K group of each k-step)
-// are computed once; tiles then differ by constant offsets.  epi(i, nt, mt,
-// acc) receives rows 16 mt + 4 (lane / 16) .. + 3 of column 16 nt + lane % 16.
-// NLO input lines per output index (3; 4 for layer 1 by output-line pairs,
-// whose output index i covers lines 2 i and 2 i + 1: LSTEP = 2).
-template <int CP, int KP, int MT, int OUT_LINES, int NLO = 3, int LSTEP = 1, class Epi>
-__device__ __forceinline__ void wave_gemm3x3(const Frag<KP, MT> &F, const float (&bias)[MT][4],
-                                             const __bf16 *X, Epi epi)
+// Bits of +inf where the step's outputs of a layer exist along the strip, of 0
+// elsewhere, for this lane's column of each tile; n = the first output's
+// position.
+__device__ __forceinline__ void strip2d_tops(uint32_t (&top)[4], int n, int L, int lane)
 {
-    const int lane = threadIdx.x & 63;
-    constexpr int NT = kWWin / 16;
-    constexpr int CB = CP / 8;
-    constexpr int G = 3 * NLO * CB;   // real 8-wide K groups; the rest have zero weights
-    constexpr int KS = KP / 32;
-    int boff[KS];
+    constexpr uint32_t kInf = 0x7F800000u;
+    const bool inside = n >= 0 && n + kStep <= L;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        top[t] = kInf;
+    if (!inside) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            top[t] = (uint32_t)(n + 16 * t + (lane & 15)) < (uint32_t)L ? kInf : 0u;
+    }
+}
+
+// One output line (or pair of lines) of a 3x3 layer: four position tiles, all
+// output-channel tiles, accumulators seeded with the bias.
+template <int C, int MT, int KS>
+__device__ __forceinline__ void strip2d_conv(f32x4 (&acc)[4][MT], const bf16x8 (&w)[MT][KS],
+                                             const f32x4 (&bias)[MT], const __bf16 *X,
+                                             const int (&xo)[KS])
+{
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            acc[t][mt] = bias[mt];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        int g = 4 * ks + (lane >> 4);
-        g = g < G ? g : 0;
-        const int tap = g / CB, cb = g - CB * (g / CB);
-        const int da = tap / 3, dl = tap - 3 * (tap / 3);
-        boff[ks] = ((da * kWPos + dl + (lane & 15)) * CP + 8 * cb);
-    }
-    // one output line at a time, its NT position tiles together: their
-    // accumulator chains are independent, so their MFMAs interleave
+        bf16x8 b[4];
 #pragma unroll
-    for (int i = 0; i < OUT_LINES; ++i) {
-        const __bf16 *b0 = X + LSTEP * i * kWPos * CP;
-        f32x4 acc[NT][MT];
+        for (int t = 0; t < 4; ++t)
+            b[t] = frag_at(X + 16 * t * C + xo[ks]);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[nt][mt] = f32x4{bias[mt][0], bias[mt][1], bias[mt][2], bias[mt][3]};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 b[NT];
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                b[nt] = *reinterpret_cast<const bf16x8 *>(b0 + nt * 16 * CP + boff[ks]);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(F.a[mt][ks], b[nt],
-                                                                          acc[nt][mt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                epi(i, nt, mt, acc[nt][mt]);
+            for (int t = 0; t < 4; ++t)
+                acc[t][mt] = mma(w[mt][ks], b[t], acc[t][mt]);
     }
 }
 
-// The 1x1 layer's weights this lane needs (its 8 of layer 3's 32 channels).
-struct OutW {
-    float w4[2][4];
-    float b4;
-};
-
-// Logit of position `lane` of the wave window whose input is in B.p.  The
-// 1x1 layer is folded into layer 3's epilogue: each lane dots its 8
-// channels, the four lane groups holding a position's 32 channels add up by
-// shuffles, and lane group q keeps position tile q.
-__device__ __forceinline__ float wave_forward2d(WaveBufs &B, const FwdW &W, const OutW &O,
-                                                uint32_t line_ok, int lo, int hi)
+__global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStripArgs a)
 {
+    extern __shared__ __align__(16) uint8_t strip_smem[];
+    __shared__ uint64_t s_best[kStripWaves];
     const int lane = threadIdx.x & 63;
-    const int col = lane & 15, m0 = 4 * (lane >> 4);
-    // tops[nt]: the mask of this lane's column in position tile nt
-    float tops[kWWin / 16];
-#pragma unroll
-    for (int nt = 0; nt < kWWin / 16; ++nt) {
-        const int n = nt * 16 + col;
-        tops[nt] = (n >= lo && n < hi) ? __builtin_inff() : 0.0f;
-    }
-    const float b1[1][4] = {{W.b1[0], W.b1[1], W.b1[2], W.b1[3]}};
-    const float b2[1][4] = {{W.b2[0], W.b2[1], W.b2[2], W.b2[3]}};
-    // layer 1 by output-line pairs (1, 2), (3, 4), (5, -): lane groups 0-1
-    // hold the pair's first line, 2-3 its second
-    wave_gemm3x3<8, 96, 1, 3, 4, 2>(W.w1, b1, B.p, [&](int i, int nt, int, const f32x4 &acc) {
-        const int line = 2 * i + (m0 >> 3);
-        if (line >= 5)
-            return;
-        const float top = line_in(line_ok, line + 1) ? tops[nt] : 0.0f;
-        *reinterpret_cast<bf16x4 *>(B.q + (line * kWPos + nt * 16 + col + 1) * 8 + (m0 & 7)) =
-            relu_bf16(acc, top);
-    });
-    wave_sync();
-    wave_gemm3x3<8, 96, 1, 3>(W.w2, b2, B.q, [&](int i, int nt, int, const f32x4 &acc) {
-        const float top = line_in(line_ok, i + 2) ? tops[nt] : 0.0f;
-        *reinterpret_cast<bf16x4 *>(B.p + (i * kWPos + nt * 16 + col + 1) * 16 + m0) =
-            relu_bf16(acc, top);
-    });
-    wave_sync();
-    float part[kWWin / 16];
-#pragma unroll
-    for (int nt = 0; nt < kWWin / 16; ++nt)
-        part[nt] = 0.0f;
-    const bool mid = line_in(line_ok, 3);
-    wave_gemm3x3<16, 160, 2, 1>(W.w3, W.b3, B.p, [&](int, int nt, int mt, const f32x4 &acc) {
-        const bf16x4 h = relu_bf16(acc, mid ? tops[nt] : 0.0f);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            part[nt] = fmaf(O.w4[mt][j], (float)h[j], part[nt]);
-    });
-    float mine = 0.0f;
-#pragma unroll
-    for (int nt = 0; nt < kWWin / 16; ++nt) {
-        float v = part[nt];
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        mine = (lane >> 4) == nt ? v : mine;
-    }
-    return O.b4 + mine;
-}
-
-__global__ __launch_bounds__(kBlock) void k_cnn2d_strips(Cnn2dStripArgs a)
-{
-    __shared__ WaveBufs wb[kWaves];
-    __shared__ float s_fb[kC2Floats];
-    __shared__ uint64_t s_best[kWaves][2];
-    const int item = (int)(blockIdx.x & 7) * a.per_xcd + (int)(blockIdx.x >> 3);
-    if (item >= a.n_items || (int)(blockIdx.x >> 3) >= a.per_xcd)
+    const int wv = uniform_int(threadIdx.x >> 6);
+    const int group = blockIdx.x >> 3, groups = gridDim.x >> 3;
+    const int xcd = blockIdx.x & 7;
+    const int first = xcd * a.per_xcd;
+    const int n_units = 2 * (min(first + a.per_xcd, a.n_items) - first);
+    const int sets = kStripWaves / a.parts;          // half strips a workgroup takes at a time
+    if (group * sets >= n_units)
         return;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int S = a.n_h + a.n_v;
-    const int f = uniform_int(a.frame0 + item / S);
-    const int st = uniform_int(item % S);
-    const FrameDev d = a.fd[f];
-    const uint8_t *frame = a.frames + d.offset;
-    const bool hz = st < a.n_h;
-    const int pos = uniform_int(a.strips[d.table + st]);
-    const int L_ = hz ? d.W : d.H;
-    const int extent = hz ? d.H : d.W;
-    const uint32_t line_ok = band_lines(pos, extent);
-    WaveBufs &B = wb[wv];
-    {
-        const float *src = reinterpret_cast<const float *>(a.model + kC2FloatsOff);
-        for (int i = threadIdx.x; i < kC2Floats; i += kBlock)
-            s_fb[i] = src[i];
-        uint4 *z = reinterpret_cast<uint4 *>(&B);
-        for (int i = lane; i < (int)(sizeof(WaveBufs) / 16); i += 64)
-            z[i] = make_uint4(0u, 0u, 0u, 0u);
-    }
-    __syncthreads();
-    FwdW W;
-    load_fwd_weights(W, a.model, hz, s_fb);
-    OutW O;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    const float *fb = reinterpret_cast<const float *>(a.model + kC2FloatsOff);
+    const int col = lane & 15, g = lane >> 4;
+    Strip2dRows &R = reinterpret_cast<Strip2dRows *>(strip_smem)[wv];
+    for (int i = lane; i < (int)(sizeof(Strip2dRows) / 16); i += 64)
+        reinterpret_cast<uint4 *>(&R)[i] = make_uint4(0u, 0u, 0u, 0u);
+    // layer 1's weights are those of output-line pairs: rows 8 .. 15, so lane
+    // groups 2 and 3, are the second line's channels
+    bf16x8 w1[1][3], w2[1][3], w3[2][5];
+    f32x4 b1[1], b2[1], b3[2], w4[2];
+    auto four = [&](int at) {
+        f32x4 v;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            O.w4[mt][j] = s_fb[kC2FW4 + 16 * mt + 4 * (lane >> 4) + j];
-    O.b4 = s_fb[kC2FB4];
-    uint64_t best[2] = {0, 0};
-    const int n_win = (L_ + kWStride - 1) / kWStride;
-    const float rw = coord_scale(d.W), rh = coord_scale(d.H);
+            v[j] = fb[at + j];
+        return v;
+    };
+    b1[0] = four(kC2FB[0] + 4 * (g & 1));
+    b2[0] = four(kC2FB[1] + 4 * g);
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        b3[mt] = four(kC2FB[2] + 16 * mt + 4 * g);
+        w4[mt] = four(kC2FW4 + 16 * mt + 4 * g);
+    }
+    const float b4 = fb[kC2FB4];
+    // B fragment offsets of the first tile's column: K group k = tap C / 8 +
+    // channel half, tap = 3 (line) + position; the groups beyond the taps have
+    // zero weights
+    int xo1[3], xo2[3], xo3[5];
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) {
+        const int k = 4 * ks + g, k2 = k < 9 ? k : 0;
+        xo1[ks] = (k / 3 * kC2Rows + k % 3 + col) * 8;
+        xo2[ks] = (k2 / 3 * kC2Rows + k2 % 3 + col) * 8;
+    }
+#pragma unroll
+    for (int ks = 0; ks < 5; ++ks) {
+        const int k = 4 * ks + g < 18 ? 4 * ks + g : 0;
+        xo3[ks] = (k / 6 * kC2Rows + k / 2 % 3 + col) * 16 + 8 * (k & 1);
+    }
+    const int at0 = strip2d_at<kC2Band, 8>(lane), at1 = strip2d_at<5, 8>(lane);
+    const int at2 = strip2d_at<3, 16>(lane);
 
-    // This wave's next window's pixels, fetched one window ahead: band
-    // position i = lane + 64 k in slot k (horizontal strips: positions
-    // fastest; vertical strips: lines fastest -- adjacent pixels of a row).
-    constexpr int kSlots = kC2Band * kWWin / 64;
-    // raw bytes: R | G << 8 and B of each slot, split only when encoded, so
-    // nothing waits for the loads before the next window's turn; slots
-    // outside the frame or the strip load pixel (0, 0) and are dropped
-    uint32_t prg[kSlots], pb[kSlots];
-    uint32_t have = 0;
-    auto window = [&](int w, int &start, int &lo, int &hi) {
-        start = w * kWStride - kC2Halo;
-        lo = start >= 0 ? 0 : -start;
-        hi = L_ - start < kWWin ? L_ - start : kWWin;
-    };
-    auto slot_pos = [&](int k, int &j, int &n) {
-        const int i = lane + 64 * k;
-        j = hz ? i / kWWin : i % kC2Band;
-        n = hz ? i % kWWin : i / kC2Band;
-    };
-    auto fetch = [&](int w) {
-        int start, lo, hi;
-        window(w, start, lo, hi);
-        have = 0;
+    const int S = a.n_h + a.n_v;
+    const int set = wv / a.parts, part = wv % a.parts;
+    const int slots = groups * sets;
+    int loaded = -1;   // the orientation whose weights are held
+    for (int turn = 0; turn * slots < n_units; ++turn) {
+        // half strips rotate from turn to turn, so that every wave takes long and
+        // short ones (ca_cnn.hip)
+        const int unit = uniform_int(turn * slots + (group * sets + set + turn * S) % slots);
+        uint64_t best = 0;
+        int f = 0, st = 0, half = 0, pos = 0, L = 0;
+        bool horizontal = false;
+        if (unit < n_units) {
+            const int item = first + (unit >> 1);
+            half = unit & 1;
+            f = uniform_int(a.frame0 + item / S);
+            st = uniform_int(item % S);
+            const FrameDev d = a.fd[f];
+            horizontal = st < a.n_h;
+            pos = uniform_int(a.strips[d.table + st]);
+            if (loaded != (int)horizontal) {
+                const __bf16 *A =
+                    reinterpret_cast<const __bf16 *>(a.model) + (horizontal ? 0 : kC2Orient);
 #pragma unroll
-        for (int k = 0; k < kSlots; ++k) {
-            int j, n;
-            slot_pos(k, j, n);
-            const bool ok = line_in(line_ok, j) && n >= lo && n < hi;
-            const int across = pos - 3 + j, along = start + n;
-            const int x = ok ? (hz ? along : across) : 0, y = ok ? (hz ? across : along) : 0;
-            const uint8_t *px = frame + (int64_t)y * d.rs + 3 * x;
-            uint16_t rg;
-            __builtin_memcpy(&rg, px, 2);
-            prg[k] = rg;
-            pb[k] = px[2];
-            have |= ok ? 1u << k : 0u;
-        }
-    };
-    if (wv < n_win)
-        fetch(wv);
-    for (int w = wv; w < n_win; w += kWaves) {
-        int start, lo, hi;
-        window(w, start, lo, hi);
+                for (int ks = 0; ks < 3; ++ks) {
+                    w1[0][ks] = frag_at(A + kC2P1 + col * 96 + 32 * ks + 8 * g);
+                    w2[0][ks] = frag_at(A + kC2A[1] + col * 96 + 32 * ks + 8 * g);
+                }
 #pragma unroll
-        for (int k = 0; k < kSlots; ++k) {
-            int j, n;
-            slot_pos(k, j, n);
-            __bf16 *dst = B.p + (j * kWPos + n + 1) * 8;
-            if (!((have >> k) & 1u)) {
-                *reinterpret_cast<bf16x8 *>(dst) = bf16x8{};
-                continue;
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int ks = 0; ks < 5; ++ks)
+                        w3[mt][ks] = frag_at(A + kC2A[2] + (16 * mt + col) * 160 + 32 * ks + 8 * g);
+                loaded = (int)horizontal;
             }
-            const int across = pos - 3 + j, along = start + n;
-            encode(dst, prg[k] & 0xFFu, prg[k] >> 8, pb[k], hz ? along : across,
-                   hz ? across : along, d.W, d.H, rw, rh, s_fb);
-        }
-        wave_sync();
-        if (w + kWaves < n_win)
-            fetch(w + kWaves);
-        const float z = wave_forward2d(B, W, O, line_ok, lo, hi);
-        const int p = start + lane;
-        if (lane >= kC2Halo && lane < kWWin - kC2Halo && p < L_) {
-            const float sc = sigmoid(z);
-            const int half = p < (L_ >> 1) ? 0 : 1;
-            const int k = half == 0 ? p : L_ - 1 - p;
-            const uint64_t key = ((uint64_t)__float_as_uint(sc) << 32)
-                                 | (uint64_t)(0xFFFFFFFFu - (uint32_t)k);
-            best[half] = best[half] > key ? best[half] : key;
-        }
-        // the next window's input overwrites P, which layer 3 has read
-        wave_sync();
-    }
+            StripWalk k;
+            strip_walk<kC2Band>(k, a.frames, d, horizontal, pos);
+            L = k.L;
+            const int h0 = half ? L >> 1 : 0, h1 = half ? L : L >> 1;
+            const int each = (h1 - h0 + a.parts - 1) / a.parts;
+            const int p0 = h0 + part * each, p1 = min(p0 + each, h1);
+            const uint32_t line_ok = band_lines(pos, k.lines);
+            // the masks of the output lines, of layer 1 by pairs (1, 2), (3, 4),
+            // (5, -)
+            uint32_t line1[3], line2[3];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        uint64_t v = best[half];
+            for (int i = 0; i < 3; ++i) {
+                line1[i] = line_in(line_ok, 2 * i + (g >> 1) + 1) ? 0x7F800000u : 0u;
+                line2[i] = line_in(line_ok, i + 2) ? 0x7F800000u : 0u;
+            }
+            const uint32_t line3 = line_in(line_ok, 3) ? 0x7F800000u : 0u;
+            // the coordinates: along the strip in the lane, across it by line
+            const float scale_x = coord_scale(d.W), scale_y = coord_scale(d.H);
+            const float scale_along = horizontal ? scale_x : scale_y;
+            float across[kC2Band];
 #pragma unroll
-        for (int dd = 32; dd >= 1; dd >>= 1) {
-            const uint64_t t = __shfl_xor(v, dd, 64);
-            v = v > t ? v : t;
+            for (int j = 0; j < kC2Band; ++j)
+                across[j] = (float)(2 * (k.first + j) - (k.lines - 1))
+                            * (horizontal ? scale_y : scale_x);
+            uint32_t px[8];
+            int x = p0 - kC2Halo;   // first new input position of the step
+            if (p0 < p1)
+                strip_fetch<kC2Band>(px, k, x, lane);
+            for (; p0 < p1 && x - kC2Halo < p1; x += kStep) {
+                {
+                    if (k.packed) {   // 21 bytes to a dword of three for each line
+#pragma unroll
+                        for (int j = kC2Band - 1; j >= 0; --j)
+                            px[j] = __builtin_amdgcn_alignbyte(px[(3 * j >> 2) + 1], px[3 * j >> 2],
+                                                               3 * j & 3);
+                    }
+                    const float along = (float)(2 * (x + lane) - (L - 1)) * scale_along;
+                    const bool whole = line_ok == 0x7Fu && x >= 0 && x + kStep <= L;
+                    const bool in = (uint32_t)(x + lane) < (uint32_t)L;
+#pragma unroll
+                    for (int j = 0; j < kC2Band; ++j) {
+                        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                        bf16x8 v;
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+                            v[c] = to_bf16(((float)((px[j] >> (8 * c)) & 0xFFu) - fb[kC2FMean + c])
+                                           * fb[kC2FInv + c]);
+                        v[3] = to_bf16(horizontal ? along : across[j]);
+                        v[4] = to_bf16(horizontal ? across[j] : along);
+                        v[5] = v[6] = v[7] = to_bf16(0.0f);
+                        u32x4 u = __builtin_bit_cast(u32x4, v);
+                        if (!whole) {
+                            const uint32_t m = in && line_in(line_ok, j) ? ~0u : 0u;
+                            u = u32x4{u[0] & m, u[1] & m, u[2] & m, 0u};
+                        }
+                        *reinterpret_cast<u32x4 *>(R.x0 + (j * kC2Rows + lane + 2) * 8) = u;
+                    }
+                }
+                if (x + kStep - kC2Halo < p1)
+                    strip_fetch<kC2Band>(px, k, x + kStep, lane);
+                wave_sync();
+                uint32_t top[4];
+                uint32_t kept = strip2d_keep<8>(R.x0, at0);
+                strip2d_tops(top, x - 1, L, lane);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    f32x4 acc[4][1];
+                    strip2d_conv<8>(acc, w1, b1, R.x0 + 2 * i * kC2Rows * 8, xo1);
+                    if (i < 2 || g < 2)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            *reinterpret_cast<bf16x4 *>(
+                                R.h1 + ((2 * i + (g >> 1)) * kC2Rows + 16 * t + col + 2) * 8
+                                + 4 * (g & 1)) =
+                                relu_bf16(acc[t][0], __uint_as_float(top[t] & line1[i]));
+                }
+                wave_sync();
+                strip2d_kept(R.x0, kept, at0);
+                kept = strip2d_keep<8>(R.h1, at1);
+                strip2d_tops(top, x - 2, L, lane);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    f32x4 acc[4][1];
+                    strip2d_conv<8>(acc, w2, b2, R.h1 + i * kC2Rows * 8, xo2);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        *reinterpret_cast<bf16x4 *>(R.h2 + (i * kC2Rows + 16 * t + col + 2) * 16
+                                                    + 4 * g) =
+                            relu_bf16(acc[t][0], __uint_as_float(top[t] & line2[i]));
+                }
+                wave_sync();
+                strip2d_kept(R.h1, kept, at1);
+                kept = strip2d_keep<16>(R.h2, at2);
+                strip2d_tops(top, x - 3, L, lane);
+                float part_z[4];   // lane group's share of each tile's 1x1 layer
+                {
+                    f32x4 acc[4][2];
+                    strip2d_conv<16>(acc, w3, b3, R.h2, xo3);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        float z = 0.0f;
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) {
+                            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                            const u32x2 h = __builtin_bit_cast(
+                                u32x2, relu_bf16(acc[t][mt], __uint_as_float(top[t] & line3)));
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) {   // a bfloat16 is a float's upper half
+                                z = fmaf(w4[mt][2 * e], __uint_as_float(h[e] << 16), z);
+                                z = fmaf(w4[mt][2 * e + 1], __uint_as_float(h[e] & 0xFFFF0000u), z);
+                            }
+                        }
+                        part_z[t] = z;
+                    }
+                }
+                wave_sync();
+                strip2d_kept(R.h2, kept, at2);
+                const float z = b4 + tile_sums(part_z);
+                const int p = x - kC2Halo + lane;   // column lane % 16 of tile lane / 16
+                if (p >= p0 && p < p1) {
+                    const uint64_t key = strip_key(z, p, half, L);
+                    best = best > key ? best : key;
+                }
+            }
+            best = wave_max(best);
         }
-        if (lane == 0)
-            s_best[wv][half] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        const int half = threadIdx.x;
-        uint64_t bb = s_best[0][half];
-        for (int w2 = 1; w2 < kWaves; ++w2)
-            bb = bb > s_best[w2][half] ? bb : s_best[w2][half];
-        const int k = (int)(0xFFFFFFFFu - (uint32_t)bb);
-        const int i = half == 0 ? k : L_ - 1 - k;
-        ca_point pt;
-        pt.x = (int16_t)(hz ? i : pos);
-        pt.y = (int16_t)(hz ? pos : i);
-        pt.score = __uint_as_float((uint32_t)(bb >> 32));
-        a.cand[(int64_t)f * (2 * S) + 2 * st + half] = pt;
+        if (a.parts > 1) {
+            if (lane == 0)
+                s_best[wv] = best;
+            __syncthreads();
+            for (int w = 1; w < a.parts; ++w)
+                best = best > s_best[set * a.parts + w] ? best : s_best[set * a.parts + w];
+            __syncthreads();
+        }
+        if (unit < n_units && part == 0 && lane == 0)
+            a.cand[(int64_t)f * (2 * S) + 2 * st + half] = strip_point(best, horizontal, pos, half, L);
     }
 }
 
@@ -1271,7 +1261,10 @@ hipError_t launch_cnn2d_strips(const Cnn2dStripArgs &a, hipStream_t s, hipEvent_
 {
     if (a.n_items <= 0)
         return hipSuccess;
-    launch_maybe_timed(k_cnn2d_strips, dim3(8 * a.per_xcd), dim3(kBlock), 0, s, start, stop, a);
+    Cnn2dStripArgs b = a;
+    const int groups = strip_split(b.parts, 2 * a.per_xcd, a.resident_per_xcd);
+    launch_maybe_timed(k_cnn2d_strips, dim3(8 * groups), dim3(64 * kStripWaves),
+                       kStripWaves * sizeof(Strip2dRows), s, start, stop, b);
     return hipGetLastError();
 }
 
