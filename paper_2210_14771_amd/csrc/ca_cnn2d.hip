@@ -99,11 +99,11 @@ __device__ __forceinline__ uint32_t band_lines(int line, int extent)
 // the layer's lines.  The next step's pixels are loaded while a step's layers
 // run.
 //
-// Bound by issue: about 520 vector instructions of 4 cycles and 112 MFMAs of 16
+// Bound by issue: about 490 vector instructions of 4 cycles and 112 MFMAs of 16
 // a step, which add up to four fifths of a SIMD's cycles.  Measured, 64 1080p
 // frames, 32 + 32 strips (kernel trace): 313 us with windows of 64 positions of
 // which 58 are used (770 vector instructions, mostly addresses, selects and
-// conversions at the input), 252 us so.
+// conversions at the input), 245 us so.
 
 constexpr int kC2Rows = kStep + 2;   // positions of a buffer line
 struct alignas(16) Strip2dRows {     // one wave's inputs of the three layers
@@ -129,6 +129,39 @@ __device__ __forceinline__ uint32_t strip2d_keep(const __bf16 *X, int at)
 __device__ __forceinline__ void strip2d_kept(__bf16 *X, uint32_t v, int at)
 {
     *reinterpret_cast<uint32_t *>(X + at) = v;
+}
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 v = {to_bf16(a), to_bf16(b)};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// A position's input rows, seven lines' three bytes in px: colours normalised,
+// the coordinates along and across the strip (x and y, or y and x), zeros.
+// CLIP: lines may lie outside the frame, or the position outside the strip (in).
+template <bool HZ, bool CLIP>
+__device__ __forceinline__ void strip2d_encode(__bf16 *row, const uint32_t (&px)[8],
+                                               const float (&norm)[6], float along,
+                                               const float (&across)[kC2Band], uint32_t line_ok,
+                                               uint32_t in)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int j = 0; j < kC2Band; ++j) {
+        float c[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            c[i] = ((float)((px[j] >> (8 * i)) & 0xFFu) - norm[i]) * norm[3 + i];
+        u32x4 u = {bf16_pair(c[0], c[1]), bf16_pair(c[2], HZ ? along : across[j]),
+                   bf16_pair(HZ ? across[j] : along, 0.0f), 0u};
+        if (CLIP) {
+            const uint32_t m = line_in(line_ok, j) ? in : 0u;
+            u = u32x4{u[0] & m, u[1] & m, u[2] & m, 0u};
+        }
+        *reinterpret_cast<u32x4 *>(row + j * (kC2Rows * 8)) = u;
+    }
 }
 
 // Bits of +inf where the step's outputs of a layer exist along the strip, of 0
@@ -211,6 +244,10 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStrip
         w4[mt] = four(kC2FW4 + 16 * mt + 4 * g);
     }
     const float b4 = fb[kC2FB4];
+    float norm[6];   // the colours' means, then their inverse deviations
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+        norm[i] = __uint_as_float(uniform_int(__float_as_uint(fb[kC2FMean + i])));
     // B fragment offsets of the first tile's column: K group k = tap C / 8 +
     // channel half, tap = 3 (line) + position; the groups beyond the taps have
     // zero weights
@@ -300,26 +337,17 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStrip
                                                                3 * j & 3);
                     }
                     const float along = (float)(2 * (x + lane) - (L - 1)) * scale_along;
+                    const uint32_t in = (uint32_t)(x + lane) < (uint32_t)L ? ~0u : 0u;
                     const bool whole = line_ok == 0x7Fu && x >= 0 && x + kStep <= L;
-                    const bool in = (uint32_t)(x + lane) < (uint32_t)L;
-#pragma unroll
-                    for (int j = 0; j < kC2Band; ++j) {
-                        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                        bf16x8 v;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c)
-                            v[c] = to_bf16(((float)((px[j] >> (8 * c)) & 0xFFu) - fb[kC2FMean + c])
-                                           * fb[kC2FInv + c]);
-                        v[3] = to_bf16(horizontal ? along : across[j]);
-                        v[4] = to_bf16(horizontal ? across[j] : along);
-                        v[5] = v[6] = v[7] = to_bf16(0.0f);
-                        u32x4 u = __builtin_bit_cast(u32x4, v);
-                        if (!whole) {
-                            const uint32_t m = in && line_in(line_ok, j) ? ~0u : 0u;
-                            u = u32x4{u[0] & m, u[1] & m, u[2] & m, 0u};
-                        }
-                        *reinterpret_cast<u32x4 *>(R.x0 + (j * kC2Rows + lane + 2) * 8) = u;
-                    }
+                    __bf16 *row = R.x0 + (lane + 2) * 8;
+                    if (horizontal && whole)
+                        strip2d_encode<true, false>(row, px, norm, along, across, line_ok, in);
+                    else if (horizontal)
+                        strip2d_encode<true, true>(row, px, norm, along, across, line_ok, in);
+                    else if (whole)
+                        strip2d_encode<false, false>(row, px, norm, along, across, line_ok, in);
+                    else
+                        strip2d_encode<false, true>(row, px, norm, along, across, line_ok, in);
                 }
                 if (x + kStep - kC2Halo < p1)
                     strip_fetch<kC2Band>(px, k, x + kStep, lane);
