@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import dataclasses
+import struct
 from typing import Sequence
 
 import torch
@@ -84,31 +85,34 @@ class Result:
 
 
 _layout_cache: dict = {}
+_MASK32, _MASK64 = 0xFFFFFFFF, 0xFFFFFFFFFFFFFFFF
+_pack_desc = struct.Struct("=IIIIqQ").pack_into   # the fields of a FrameDesc
 
 
 def _batch_layout(frames: torch.Tensor, frame_uids):
     """Descriptors of a [B, H, W, 3] tensor computed from its strides (cached)."""
-    if frames.dtype != torch.uint8:
+    if frames.dtype is not torch.uint8:
         raise ValueError("frames must be uint8 [B, H, W, 3]")
-    if frames.device.type != "cuda":
+    if not frames.is_cuda:
         raise ValueError("frames must be on a GPU")
-    if frames.stride(2) != 3 or frames.stride(3) != 1:
+    shape, stride = frames.shape, frames.stride()
+    if stride[2] != 3 or stride[3] != 1:
         raise ValueError("pixels must be packed RGB (stride 3 along W, 1 along channels)")
-    B, H, W, _ = frames.shape
-    uids = tuple(range(B)) if frame_uids is None else tuple(int(u) for u in frame_uids)
-    if len(uids) != B:
+    B = shape[0]
+    uids = None if frame_uids is None else tuple(int(u) for u in frame_uids)
+    if uids is not None and len(uids) != B:
         raise ValueError("frame_uids must have one entry per frame")
-    key = (tuple(frames.shape), tuple(frames.stride()), uids)
+    key = (shape, stride, uids)
     descs = _layout_cache.get(key)
     if descs is None:
         descs = (N.FrameDesc * B)()
         for i in range(B):
             d = descs[i]
-            d.width, d.height = W, H
-            d.row_stride = frames.stride(1)
+            d.width, d.height = shape[2], shape[1]
+            d.row_stride = stride[1]
             d.pixel_stride = 3
-            d.byte_offset = i * frames.stride(0)
-            d.frame_uid = uids[i] & 0xFFFFFFFFFFFFFFFF
+            d.byte_offset = i * stride[0]
+            d.frame_uid = (i if uids is None else uids[i]) & _MASK64
         if len(_layout_cache) > 64:
             _layout_cache.clear()
         _layout_cache[key] = descs
@@ -132,29 +136,29 @@ def _frames_layout(frames, frame_uids):
         if not items:
             raise ValueError("empty frame list")
         dev = items[0].device
+    on_gpu, rows = dev.type == "cuda", []
     for t in items:
-        if t.dtype != torch.uint8 or t.dim() != 3 or t.shape[-1] != 3:
+        shape = t.shape
+        if t.dtype is not torch.uint8 or len(shape) != 3 or shape[2] != 3:
             raise ValueError("each frame must be uint8 [H, W, 3]")
-        if t.device != dev or dev.type != "cuda":
+        if not on_gpu or t.device != dev:
             raise ValueError("frames must all be on one GPU")
-        if t.stride(2) != 1 or t.stride(1) != 3:
+        stride = t.stride()
+        if stride[2] != 1 or stride[1] != 3:
             raise ValueError("pixels must be packed RGB (stride 3 along W, 1 along channels)")
+        rows.append((t.data_ptr(), shape[1], shape[0], stride[0]))
     n = len(items)
     if frame_uids is None:
-        uids = list(range(n))
+        uids = range(n)
     else:
         uids = [int(u) for u in frame_uids]
         if len(uids) != n:
             raise ValueError("frame_uids must have one entry per frame")
-    base = min(t.data_ptr() for t in items)
+    base = min(rows)[0]
     descs = (N.FrameDesc * n)()
-    for i, t in enumerate(items):
-        d = descs[i]
-        d.width, d.height = t.shape[1], t.shape[0]
-        d.row_stride = t.stride(0)
-        d.pixel_stride = 3
-        d.byte_offset = t.data_ptr() - base
-        d.frame_uid = uids[i] & 0xFFFFFFFFFFFFFFFF
+    for i, (ptr, width, height, row_stride) in enumerate(rows):
+        _pack_desc(descs, i * 32, width & _MASK32, height & _MASK32, row_stride & _MASK32, 3,
+                   ptr - base, uids[i] & _MASK64)
     return base, descs, n, dev
 
 
@@ -380,7 +384,9 @@ class Estimator:
         if dev.index != self.device.index:
             raise ValueError(f"frames on {dev}, estimator on {self.device}")
         p = _as_params(params)
-        s = stream if stream is not None else torch.cuda.current_stream(self.device)
+        # the handle alone: a Stream object costs more than the launches' set-up
+        s = (torch._C._cuda_getCurrentRawStream(self.device.index) if stream is None
+             else stream.cuda_stream)
         return base, descs, n, p, s
 
     def estimate_area(self, frames, params=None, frame_uids: Sequence[int] | None = None,
@@ -389,8 +395,8 @@ class Estimator:
         base, descs, n, p, s = self._prep(frames, params, frame_uids, stream)
         if out is None:
             out = torch.empty((n, 8), dtype=torch.int32, device=self.device)
-        rc = N.lib().ca_estimate_area(self._ctx, C.c_void_p(base), descs, n, C.byref(p),
-                                      C.c_void_p(out.data_ptr()), C.c_void_p(s.cuda_stream))
+        rc = N.lib().ca_estimate_area(self._ctx, base, descs, n, C.byref(p),
+                                      out.data_ptr(), s)
         N.check(rc, "ca_estimate_area")
         return Result(out)
 
@@ -402,9 +408,9 @@ class Estimator:
         base, descs, n, p, s = self._prep(frames, params, frame_uids, stream)
         if out is None:
             out = torch.empty((n, 8), dtype=torch.int32, device=self.device)
-        rc = N.lib().ca_estimate_area_noalloc(self._ctx, C.c_void_p(base), descs, n, C.byref(p),
-                                              C.c_void_p(out.data_ptr()),
-                                              C.c_void_p(s.cuda_stream))
+        rc = N.lib().ca_estimate_area_noalloc(self._ctx, base, descs, n, C.byref(p),
+                                              out.data_ptr(),
+                                              s)
         N.check(rc, "ca_estimate_area_noalloc")
         return Result(out)
 
@@ -415,8 +421,8 @@ class Estimator:
         returns {(width, height): T}."""
         base, descs, n, p, s = self._prep(frames, params, frame_uids, None)
         sched = C.c_int32(-1)
-        N.check(N.lib().ca_autotune(self._ctx, C.c_void_p(base), descs, n, C.byref(p), reps,
-                                    C.c_void_p(s.cuda_stream), C.byref(sched)), "ca_autotune")
+        N.check(N.lib().ca_autotune(self._ctx, base, descs, n, C.byref(p), reps,
+                                    s, C.byref(sched)), "ca_autotune")
         out = {}
         for i in range(n):
             key = (descs[i].width, descs[i].height)
@@ -442,8 +448,8 @@ class Estimator:
         if out is None:
             out = torch.empty((n, 8), dtype=torch.int32, device=self.device)
         g = C.c_void_p()
-        rc = N.lib().ca_graph_create(self._ctx, C.c_void_p(base), descs, n, C.byref(p),
-                                     C.c_void_p(out.data_ptr()), calls, C.byref(g))
+        rc = N.lib().ca_graph_create(self._ctx, base, descs, n, C.byref(p),
+                                     out.data_ptr(), calls, C.byref(g))
         N.check(rc, "ca_graph_create")
         return Graph(self, g, Result(out), frames)
 
@@ -453,9 +459,9 @@ class Estimator:
         P = 2 * (p.n_hstrips + p.n_vstrips)
         out = torch.empty((n, 8), dtype=torch.int32, device=self.device)
         pts = torch.empty((n, P, 2), dtype=torch.int32, device=self.device)
-        rc = N.lib().ca_debug_candidates(self._ctx, C.c_void_p(base), descs, n, C.byref(p),
-                                         C.c_void_p(pts.data_ptr()), C.c_void_p(out.data_ptr()),
-                                         C.c_void_p(s.cuda_stream))
+        rc = N.lib().ca_debug_candidates(self._ctx, base, descs, n, C.byref(p),
+                                         C.c_void_p(pts.data_ptr()), out.data_ptr(),
+                                         s)
         N.check(rc, "ca_debug_candidates")
         return Result(out), pts
 
@@ -465,9 +471,9 @@ class Estimator:
         A = p.ransac_attempts
         out = torch.empty((n, 8), dtype=torch.int32, device=self.device)
         att = torch.empty((n, A, 56), dtype=torch.uint8, device=self.device)
-        rc = N.lib().ca_debug_attempts(self._ctx, C.c_void_p(base), descs, n, C.byref(p),
-                                       C.c_void_p(att.data_ptr()), C.c_void_p(out.data_ptr()),
-                                       C.c_void_p(s.cuda_stream))
+        rc = N.lib().ca_debug_attempts(self._ctx, base, descs, n, C.byref(p),
+                                       C.c_void_p(att.data_ptr()), out.data_ptr(),
+                                       s)
         N.check(rc, "ca_debug_attempts")
         return Result(out), att
 
@@ -480,7 +486,7 @@ class Graph:
 
     def launch(self, stream=None) -> Result:
         s = stream if stream is not None else torch.cuda.current_stream(self._est.device)
-        N.check(N.lib().ca_graph_launch(self._g, C.c_void_p(s.cuda_stream)), "ca_graph_launch")
+        N.check(N.lib().ca_graph_launch(self._g, s), "ca_graph_launch")
         return self.result
 
     def close(self):
