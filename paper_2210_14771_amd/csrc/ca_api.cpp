@@ -174,6 +174,12 @@ int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const c
         if ((d.byte_offset % 16) != 0 || (d.row_stride % 16) != 0)
             pl->rows_aligned = false;
     }
+    // the largest first: a launch over all shapes starts its longest items
+    // first, so the short ones fill its tail
+    auto area = [](const Shape &sh) { return (int64_t)sh.W * sh.H; };
+    for (int32_t k = 1; k < n_shapes; ++k)
+        for (int32_t j = k; j > 0 && area(shapes[j]) > area(shapes[j - 1]); --j)
+            std::swap(shapes[j], shapes[j - 1]);
     pl->line_pitch = (int32_t)align_up((size_t)longest, 16);
     pl->lds = ca::strip_lds_bytes(sg_len, pl->line_pitch);
     pl->fused_lds = ca::fused_lds_bytes(sg_len, pl->line_pitch);
@@ -239,6 +245,30 @@ int fused_grid(const ca_ctx *ctx, size_t fused_lds)
     return per_cu * ctx->n_cu;
 }
 
+// How one launch deals the frames of several shapes, the largest first: whole
+// frames to the XCDs, whose L2 then holds the lines that a frame's strips share,
+// unless that would leave one XCD with over a tenth more than its share of the
+// pixels; then strip by strip.  128 frames of four resolutions: 167 us a call
+// with a launch for each shape, 152 us dealt strip by strip, 124 us by frames.
+int32_t mixed_spread(const std::vector<Plan::ShapeClass> &classes)
+{
+    double xcd[8] = {}, all = 0.0;
+    int32_t n = 0;
+    for (const Plan::ShapeClass &c : classes)
+        n += c.count;
+    for (int x = 0; x < 8; ++x)
+        for (int32_t j = 0; 8 * j < n; ++j) {
+            const int32_t k = ca::spread_frame(x, j);
+            for (const Plan::ShapeClass &c : classes)
+                if (k >= c.first && k < c.first + c.count)
+                    xcd[x] += (double)c.W * c.H;
+        }
+    for (const double v : xcd)
+        all += v;
+    return 8.0 * *std::max_element(xcd, xcd + 8) <= 1.1 * all ? ca::kSpreadFrames
+                                                              : ca::kSpreadItems;
+}
+
 int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_params &p, Plan **out)
 {
     Plan *pl = new (std::nothrow) Plan();
@@ -269,6 +299,7 @@ int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_param
         pl->classes.push_back({sh.W, sh.H, first, count});
         first += count;
     }
+    pl->spread = mixed_spread(pl->classes);
     pl->shapes = shapes;
     pl->fused_grid = fused_grid(ctx, pl->fused_lds);
 
@@ -509,7 +540,19 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
         } else if (f0 == 0 && f1 == n && !pl->dynamic
                    && (pl->classes.size() > 1
                        || strips_per_group(ctx, pl->classes[0].W, pl->classes[0].H, p) != 1)) {
-            // the whole batch: one launch per frame shape, each with its tile
+            // the whole batch: one launch if every shape takes its strips one at
+            // a time, else one per shape, each with its tile
+            bool ones = true;
+            for (const Plan::ShapeClass &c : pl->classes)
+                ones = ones && strips_per_group(ctx, c.W, c.H, p) == 1;
+            if (ones) {
+                a2.frame_list = pl->flist;
+                a2.spread = pl->spread;
+                if (a2.spread == ca::kSpreadFrames)
+                    a2.per_xcd = (n + 7) / 8 * S;
+                ok = ca::launch_strips(a2, pl->lds, st, s0, s1) == hipSuccess;
+                return ok && ca::launch_ransac(r2, se, f1 - f0, st, r0, r1) == hipSuccess;
+            }
             ok = !s0 || hipEventRecord(s0, st) == hipSuccess;
             for (const Plan::ShapeClass &c : pl->classes)
                 ok = ok

@@ -40,6 +40,7 @@ struct Plan {
         int32_t W, H, first, count;
     };
     std::vector<ShapeClass> classes;
+    int32_t spread = 0;         // of a launch over all shapes (StripSpread)
     std::vector<Shape> shapes;  // distinct frame shapes; shape k's strips at table k * S
     bool dynamic = false;       // a serving plan: descriptors rewritten per batch, not cached
     int32_t tuned_schedule = -1; // faster schedule of this batch (ca_autotune), -1 untuned

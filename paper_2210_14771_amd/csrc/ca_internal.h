@@ -42,6 +42,16 @@ struct Record {
     int32_t pad[2];
 };
 
+// Workgroup b runs on XCD b % 8.
+enum StripSpread {
+    kSpreadSlices = 0,   // an XCD takes a contiguous slice of the items
+    kSpreadItems = 1,    // workgroup b takes item b
+    kSpreadFrames = 2    // an XCD takes whole frames: x, 15 - x, 16 + x, ...
+};
+
+// The frame of an XCD's j-th turn under kSpreadFrames.
+constexpr int spread_frame(int xcd, int j) { return 8 * j + ((j & 1) ? 7 - xcd : xcd); }
+
 struct StripArgs {
     const uint8_t *frames;
     const FrameDev *fd;
@@ -57,6 +67,7 @@ struct StripArgs {
     int32_t frame0;         // first frame of this launch (items cover frames frame0 ..)
     const int32_t *frame_list;  // or the frames of this launch (null: frame0, frame0 + 1, ..)
     int32_t items_per_group;    // strip items one workgroup takes in turn (tables loaded once)
+    int32_t spread = 0;         // how items are dealt to the workgroups (StripSpread)
     // With keep set (the handcrafted pass of the learned scorer's fallback),
     // frames whose learned result keep[f] stands under the fallback rule at
     // keep_frac are skipped: their handcrafted result is never used.

@@ -1177,6 +1177,17 @@ __device__ __forceinline__ bool learned_kept(const ca_result &r, float frac)
     return !(r.n_points < 3 || (float)r.inliers < frac * (float)r.n_points);
 }
 
+// The item of workgroup b, of per_frame items a frame (n_items or more: none).
+__device__ __forceinline__ int strip_item(const StripArgs &a, int b, int per_frame)
+{
+    const int i = b >> 3;
+    if (a.spread == kSpreadItems)
+        return b;
+    if (a.spread == kSpreadFrames)
+        return spread_frame(b & 7, i / per_frame) * per_frame + i % per_frame;
+    return (b & 7) * a.per_xcd + i;
+}
+
 __global__ __launch_bounds__(kBlock) void k_strips(StripArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -1188,10 +1199,10 @@ __global__ __launch_bounds__(kBlock) void k_strips(StripArgs a)
     // A workgroup takes items_per_group consecutive items (a strip tile):
     // the score tables are staged in LDS once for all of them.
     const int b = blockIdx.x;
-    const int first = ((b & 7) * a.per_xcd + (b >> 3)) * a.items_per_group;
+    const int S0 = a.n_h + a.n_v;
+    const int first = strip_item(a, b, S0) * a.items_per_group;
     if (first >= a.n_items)
         return;
-    const int S0 = a.n_h + a.n_v;
     if (a.keep && a.items_per_group == 1) {
         const int k = first / S0;
         if (learned_kept(a.keep[a.frame_list ? a.frame_list[k] : a.frame0 + k], a.keep_frac))
@@ -1224,10 +1235,10 @@ __global__ __launch_bounds__(2 * kBlock) void k_strips_pair(StripArgs a)
     __shared__ uint32_t s_scan[2][4];
     __shared__ uint64_t s_best[2][4];
     const int b = blockIdx.x;
-    const int item = (b & 7) * a.per_xcd + (b >> 3);
+    const int pairs = (a.n_h + a.n_v) >> 1;
+    const int item = strip_item(a, b, pairs);
     if (item >= a.n_items)
         return;
-    const int pairs = (a.n_h + a.n_v) >> 1;
     const int k = item / pairs;
     const int pr = item - k * pairs;
     const int f = uniform(a.frame_list ? a.frame_list[k] : a.frame0 + k);
@@ -1472,7 +1483,7 @@ hipError_t launch_strips(const StripArgs &a, size_t lds_bytes, hipStream_t s, hi
     if (a.items_per_group == 1 && a.n_h % 2 == 0 && a.n_v % 2 == 0 && pair_lds <= kPairLdsMax) {
         StripArgs p = a;
         p.n_items = a.n_items / 2;
-        p.per_xcd = (p.n_items + 7) / 8;
+        p.per_xcd = a.spread == kSpreadFrames ? a.per_xcd / 2 : (p.n_items + 7) / 8;
         launch_maybe_timed(k_strips_pair, dim3(8 * p.per_xcd), dim3(2 * kBlock), pair_lds, s, start,
                            stop, p);
         return hipGetLastError();
