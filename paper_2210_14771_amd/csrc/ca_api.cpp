@@ -245,28 +245,27 @@ int fused_grid(const ca_ctx *ctx, size_t fused_lds)
     return per_cu * ctx->n_cu;
 }
 
-// How one launch deals the frames of several shapes, the largest first: whole
-// frames to the XCDs, whose L2 then holds the lines that a frame's strips share,
-// unless that would leave one XCD with over a tenth more than its share of the
-// pixels; then strip by strip.  128 frames of four resolutions: 167 us a call
-// with a launch for each shape, 152 us dealt strip by strip, 124 us by frames.
-int32_t mixed_spread(const std::vector<Plan::ShapeClass> &classes)
+// How one launch deals the frames of several shapes, given by their pixels in
+// the launch's order, the largest first: whole frames to the XCDs, whose L2 then
+// holds the lines that a frame's strips share, unless that would leave one XCD
+// with over a tenth more than its share; then strip by strip.  128 frames of
+// four resolutions: 167 us a call with a launch for each shape, 152 us dealt
+// strip by strip, 124 us by frames.
+int32_t mixed_spread(const std::vector<int64_t> &area)
 {
-    double xcd[8] = {}, all = 0.0;
-    int32_t n = 0;
-    for (const Plan::ShapeClass &c : classes)
-        n += c.count;
-    for (int x = 0; x < 8; ++x)
-        for (int32_t j = 0; 8 * j < n; ++j) {
+    if (area.empty() || area.front() == area.back())
+        return ca::kSpreadSlices;
+    int64_t most = 0, all = 0;
+    for (int x = 0; x < 8; ++x) {
+        int64_t mine = 0;
+        for (int32_t j = 0; 8 * j < (int32_t)area.size(); ++j) {
             const int32_t k = ca::spread_frame(x, j);
-            for (const Plan::ShapeClass &c : classes)
-                if (k >= c.first && k < c.first + c.count)
-                    xcd[x] += (double)c.W * c.H;
+            mine += k < (int32_t)area.size() ? area[(size_t)k] : 0;
         }
-    for (const double v : xcd)
-        all += v;
-    return 8.0 * *std::max_element(xcd, xcd + 8) <= 1.1 * all ? ca::kSpreadFrames
-                                                              : ca::kSpreadItems;
+        most = std::max(most, mine);
+        all += mine;
+    }
+    return 80 * most <= 11 * all ? ca::kSpreadFrames : ca::kSpreadItems;
 }
 
 int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_params &p, Plan **out)
@@ -292,14 +291,16 @@ int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_param
     }
     shapes.resize((size_t)L.n_shapes);
     int32_t first = 0;
+    std::vector<int64_t> area;
     for (const Shape &sh : shapes) {
         int32_t count = 0;
         for (int32_t i = 0; i < n; ++i)
             count += dims[i].width == sh.W && dims[i].height == sh.H;
         pl->classes.push_back({sh.W, sh.H, first, count});
         first += count;
+        area.insert(area.end(), (size_t)count, (int64_t)sh.W * sh.H);
     }
-    pl->spread = mixed_spread(pl->classes);
+    pl->spread = mixed_spread(area);
     pl->shapes = shapes;
     pl->fused_grid = fused_grid(ctx, pl->fused_lds);
 
@@ -488,6 +489,13 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
             return CA_E_DEVICE;
         return CA_OK;
     }
+    // whether every shape of the batch takes one strip a workgroup
+    auto one_each = [&] {
+        for (const Plan::ShapeClass &c : pl->classes)
+            if (strips_per_group(ctx, c.W, c.H, p) != 1)
+                return false;
+        return true;
+    };
     // strips then RANSAC for frames [f0, f1) on stream st
     const int S = p.n_hstrips + p.n_vstrips;
     const bool learned = p.scorer == CA_SCORER_LEARNED;
@@ -537,22 +545,17 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
                     std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8 * ca::cnn_strips_blocks_per_cu());
             ok = ca::launch_cnn_strips(c, ctx->cnn_groups_per_xcd, st, s0, s1)
                  == hipSuccess;
+        } else if (f0 == 0 && f1 == n && pl->spread != ca::kSpreadSlices && one_each()) {
+            // several shapes, each taking its strips one at a time
+            a2.frame_list = pl->flist;
+            a2.spread = pl->spread;
+            if (a2.spread == ca::kSpreadFrames)
+                a2.per_xcd = (n + 7) / 8 * S;
+            ok = ca::launch_strips(a2, pl->lds, st, s0, s1) == hipSuccess;
         } else if (f0 == 0 && f1 == n && !pl->dynamic
                    && (pl->classes.size() > 1
                        || strips_per_group(ctx, pl->classes[0].W, pl->classes[0].H, p) != 1)) {
-            // the whole batch: one launch if every shape takes its strips one at
-            // a time, else one per shape, each with its tile
-            bool ones = true;
-            for (const Plan::ShapeClass &c : pl->classes)
-                ones = ones && strips_per_group(ctx, c.W, c.H, p) == 1;
-            if (ones) {
-                a2.frame_list = pl->flist;
-                a2.spread = pl->spread;
-                if (a2.spread == ca::kSpreadFrames)
-                    a2.per_xcd = (n + 7) / 8 * S;
-                ok = ca::launch_strips(a2, pl->lds, st, s0, s1) == hipSuccess;
-                return ok && ca::launch_ransac(r2, se, f1 - f0, st, r0, r1) == hipSuccess;
-            }
+            // the whole batch: one launch per frame shape, each with its tile
             ok = !s0 || hipEventRecord(s0, st) == hipSuccess;
             for (const Plan::ShapeClass &c : pl->classes)
                 ok = ok

@@ -146,6 +146,7 @@ const float *cached_tables(ca_ctx *ctx, const ca_params &p, int32_t *sg_len);
 // shapes[0 .. max_shapes).  With `image`, also writes the host image
 // (image_cap >= L->image_bytes).  CA_E_NOMEM for more than max_shapes
 // shapes or a short image, CA_E_UNSUPPORTED when a strip tile exceeds LDS.
+int32_t mixed_spread(const std::vector<int64_t> &area);
 int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_params &p,
                 const float *lut, int32_t sg_len, Shape *shapes, int32_t max_shapes, Plan *pl,
                 PlanLayout *L, uint8_t *image, size_t image_cap);

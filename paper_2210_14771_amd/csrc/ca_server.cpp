@@ -26,6 +26,7 @@
 #include <deque>
 #include <map>
 #include <new>
+#include <numeric>
 #include <unordered_map>
 #include <vector>
 
@@ -180,8 +181,9 @@ void free_batch(Batch &b)
 // The launch facts of a batch: its frames' descriptors and the strip tables
 // of its distinct shapes into the slot's pinned staging (laid out as the
 // head of the device block), the LDS line pitch of its longest extent.
+// The frames' launch order, the largest first, goes behind the n_runs runs.
 // Returns the bytes to upload.
-size_t stage_batch(ca_server *s, Batch &b, size_t n)
+size_t stage_batch(ca_server *s, Batch &b, size_t n, int32_t n_runs)
 {
     const int32_t S = s->cfg.params.n_hstrips + s->cfg.params.n_vstrips;
     ca::FrameDev *fd = reinterpret_cast<ca::FrameDev *>(b.stage + s->layout.o_fd);
@@ -216,7 +218,17 @@ size_t stage_batch(ca_server *s, Batch &b, size_t n)
         longest = std::max(longest, std::max(e.st->W, e.st->H));
         aligned = aligned && (d.rs % 16) == 0;     // ring slots start 256-byte aligned
     }
+    int32_t *order = reinterpret_cast<int32_t *>(b.runs_host + n_runs);
+    std::iota(order, order + n, 0);
+    std::stable_sort(order, order + n, [&](int32_t x, int32_t y) {
+        return (int64_t)fd[x].W * fd[x].H > (int64_t)fd[y].W * fd[y].H;
+    });
+    std::vector<int64_t> area(n);
+    for (size_t i = 0; i < n; ++i)
+        area[i] = (int64_t)fd[order[i]].W * fd[order[i]].H;
     cahost::Plan &pl = b.plan;
+    pl.flist = reinterpret_cast<int32_t *>(b.runs_dev + n_runs);
+    pl.spread = cahost::mixed_spread(area);
     pl.n_frames = (int32_t)n;
     pl.line_pitch = (int32_t)cahost::align_up((size_t)longest, 16);
     pl.lds = ca::strip_lds_bytes(pl.sg_len, pl.line_pitch);
@@ -407,11 +419,12 @@ int launch(ca_server *s)
             else
                 b.runs_host[n_runs - 1].z = (int)i + 1;
         }
-        const size_t upload = stage_batch(s, b, n);
+        const size_t upload = stage_batch(s, b, n, n_runs);
         // the batch's frames were copied earlier on the same stream
         const hipStream_t cs = s->compute;
         if (hipMemcpyAsync(b.plan.mem, b.stage, upload, hipMemcpyHostToDevice, cs) != hipSuccess
-            || hipMemcpyAsync(b.runs_dev, b.runs_host, (size_t)n_runs * sizeof(int4),
+            || hipMemcpyAsync(b.runs_dev, b.runs_host,
+                              (size_t)n_runs * sizeof(int4) + n * sizeof(int32_t),
                               hipMemcpyHostToDevice, cs) != hipSuccess)
             return CA_E_DEVICE;
         int rc = cahost::enqueue(s->ctx, &b.plan, s->arena_mem, (int32_t)n, s->cfg.params, nullptr,
@@ -515,9 +528,9 @@ int ca_server_create(ca_ctx *ctx, const ca_server_config *cfg, ca_server **out)
                     == hipSuccess
              && hipMalloc(&b.res_dev, B * sizeof(ca_result)) == hipSuccess
              && hipMalloc(&b.filt_dev, B * sizeof(float4)) == hipSuccess
-             && hipMalloc(&b.runs_dev, B * sizeof(int4)) == hipSuccess
+             && hipMalloc(&b.runs_dev, B * (sizeof(int4) + sizeof(int32_t))) == hipSuccess
              && hipHostMalloc(&b.stage, stage_bytes) == hipSuccess
-             && hipHostMalloc(&b.runs_host, B * sizeof(int4)) == hipSuccess
+             && hipHostMalloc(&b.runs_host, B * (sizeof(int4) + sizeof(int32_t))) == hipSuccess
              && hipHostMalloc(&b.res_host, B * sizeof(ca_result)) == hipSuccess
              && hipHostMalloc(&b.filt_host, B * sizeof(float4)) == hipSuccess
              && hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess;
