@@ -6,18 +6,16 @@
 // logit, a sigmoid.  Weights and hidden activations are bfloat16, sums are
 // float32 (MFMA accumulators).
 //
-// A strip is processed in windows of 128 positions advancing by 112: the
-// 8 positions at each end of a window are the receptive-field halo, so the
-// 112 central logits of every window are exact and the windows tile the
-// strip.  Positions beyond the strip ends are zero in every layer's input.
+// A strip is walked in steps of 64 positions (inference), or taken in windows of
+// 128 positions of which the 112 central ones have exact logits: the 8 at each
+// end are the receptive-field halo (training, and logits of given windows).
+// Positions beyond the strip ends are zero in every layer's input.
 //
-// Each convolution is one GEMM per window: with activations stored
-// position-major (channels contiguous), the 5 taps x C_in inputs of output
-// position n are the contiguous run X[(n - 2) C_in .. (n + 3) C_in), so the
-// im2col matrix is the activation buffer itself.  Tiles are
-// v_mfma_f32_16x16x32_bf16: A = weights [C_out][5 C_in] (padded to a
-// multiple of 32 with zeros), B = activations, 16 output channels x 16
-// positions per tile.
+// Each convolution is one GEMM: K = tap * C_in + c over position-major
+// activations (channels contiguous), so an output position's B fragments are
+// rows of the activation buffer.  Tiles are v_mfma_f32_16x16x32_bf16: A =
+// weights [C_out][5 C_in] (padded to a multiple of 32 with zeros), B =
+// activations, 16 output channels x 16 positions per tile.
 #include "ca_cnn.h"
 #include "ca_launch.h"
 #include "ca_mfma.h"
@@ -26,261 +24,6 @@
 
 namespace ca {
 namespace {
-
-// --------------------------------------------------- wave-level forward --
-//
-// Inference: one wavefront computes one whole window, with every weight
-// fragment of the four convolutions resident in its registers (the A
-// operands: 25 x 16 bytes per lane) and its own activation buffers in LDS, so
-// the layers need no workgroup barrier.  Each B fragment (activations) is read
-// once per k-step and used for every output-channel tile of the layer; the 1x1
-// layer is folded into the last convolution's epilogue (a sum over the four
-// lane groups holding a position's 16 channels).
-
-// Two activation buffers per wave, 32 channels wide, used in turn: A holds
-// the input (24 channels) and later the second layer's output, B the first
-// and the third layer's.  Rows of one layout read under another (guard rows,
-// the tail of a narrower layout) hold stale finite values; they only ever
-// feed halo positions, whose outputs are discarded.
-constexpr int kWaveBuf = kCnnRows * 32;                   // bf16 elements per buffer
-constexpr int kWaveBytes = 2 * kWaveBuf * 2;              // A and B of one wave
-
-struct WaveFrag {
-    bf16x8 w1[1][4];
-    bf16x8 w2[2][3];
-    bf16x8 w3[2][5];
-    bf16x8 w4[1][5];
-    float b1[1][4], b2[2][4], b3[2][4], b4[1][4];
-    float w5[4];
-    float b5;
-};
-
-template <int MT, int KS>
-__device__ __forceinline__ void load_frag(bf16x8 (&f)[MT][KS], float (&b)[MT][4], const __bf16 *W,
-                                          const float *bias, int lane)
-{
-    constexpr int KP = KS * 32;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            f[mt][ks] = *reinterpret_cast<const bf16x8 *>(W + (mt * 16 + (lane & 15)) * KP
-                                                          + 32 * ks + 8 * (lane >> 4));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            b[mt][j] = bias[mt * 16 + 4 * (lane >> 4) + j];
-    }
-}
-
-__device__ void load_wave_frag(WaveFrag &fr, const uint8_t *model, int lane)
-{
-    const __bf16 *W = reinterpret_cast<const __bf16 *>(model);
-    const float *fb = reinterpret_cast<const float *>(model + kCnnFloatsOff);
-    load_frag<1, 4>(fr.w1, fr.b1, W + kCnnWOff[0], fb + kCnnBOff[0], lane);
-    load_frag<2, 3>(fr.w2, fr.b2, W + kCnnWOff[1], fb + kCnnBOff[1], lane);
-    load_frag<2, 5>(fr.w3, fr.b3, W + kCnnWOff[2], fb + kCnnBOff[2], lane);
-    load_frag<1, 5>(fr.w4, fr.b4, W + kCnnWOff[3], fb + kCnnBOff[3], lane);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        fr.w5[j] = fb[kCnnW5Off + 4 * (lane >> 4) + j];
-    fr.b5 = fb[kCnnW5Off + 16];
-}
-
-// One convolution layer over the window: groups of kNB position tiles with
-// independent accumulators (their MFMA chains interleave), every output-
-// channel tile per B fragment.
-constexpr int kNB = 4;
-
-// Element offset of channels c .. c + 7 (c a multiple of 4) of row `row` in
-// a wave's position-major buffer of C channels.  With 32 or 16 channels the
-// 16-byte chunks of a row are permuted by row (XOR with bits of the row
-// index) so that the 16 lanes of one LDS pass, which read or write 16
-// consecutive rows at the same channel, hit 16 distinct groups of 4 banks
-// instead of 4 (32 channels) or 8 (16 channels); 24-channel rows already do.
-// The permutation depends only on row / 4 mod 4 (row / 8 mod 2), so shifting
-// by whole 16-row tiles keeps it.
-template <int C>
-__device__ __forceinline__ int act_off(int row, int c)
-{
-    static_assert(C == 16 || C == 24 || C == 32, "buffer width");
-    if (C == 32)
-        return row * 32 + ((((c >> 3) ^ (row >> 2)) & 3) << 3) + (c & 7);
-    if (C == 16)
-        return row * 16 + ((((c >> 3) ^ (row >> 3)) & 1) << 3) + (c & 7);
-    return row * 24 + c;
-}
-
-template <int CIN, int COUT, int MT, int KS>
-__device__ __forceinline__ void wave_conv(const bf16x8 (&A)[MT][KS], const float (&bias)[MT][4],
-                                          const __bf16 *X, __bf16 *Y, int lo, int hi, int lane)
-{
-    const int kq = 8 * (lane >> 4);
-    // this lane's B-fragment offsets (K index 32 ks + kq = tap * CIN + c) and
-    // output offsets, for position lane % 16; tiles 16 rows on add t 16 CIN
-    int boff[KS], yoff[MT];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const int k = 32 * ks + kq;
-        boff[ks] = act_off<CIN>((lane & 15) + kCnnGuard - 2 + k / CIN, k % CIN);
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-        yoff[mt] = act_off<COUT>((lane & 15) + kCnnGuard, mt * 16 + 4 * (lane >> 4));
-#pragma unroll 1
-    for (int g = 0; g < kCnnWin / 16 / kNB; ++g) {
-        const int n0 = g * kNB * 16 + (lane & 15);
-        const __bf16 *b0 = X + g * kNB * 16 * CIN;
-        // accumulators start at the bias
-        f32x4 acc[kNB][MT];
-#pragma unroll
-        for (int t = 0; t < kNB; ++t)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[t][mt] = f32x4{bias[mt][0], bias[mt][1], bias[mt][2], bias[mt][3]};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 bv[kNB];
-#pragma unroll
-            for (int t = 0; t < kNB; ++t)
-                bv[t] = *reinterpret_cast<const bf16x8 *>(b0 + t * 16 * CIN + boff[ks]);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int t = 0; t < kNB; ++t)
-                    acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[mt][ks], bv[t],
-                                                                          acc[t][mt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < kNB; ++t) {
-            const int n = n0 + 16 * t;
-            // ReLU and the strip mask in one median: clamp to [0, +inf)
-            // inside the strip, to [0, 0] outside
-            const float top = (n >= lo && n < hi) ? __builtin_inff() : 0.0f;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                bf16x4 o;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    o[j] = to_bf16(__builtin_amdgcn_fmed3f(acc[t][mt][j], 0.0f, top));
-                *reinterpret_cast<bf16x4 *>(Y + (n - (lane & 15)) * COUT + yoff[mt]) = o;
-            }
-        }
-    }
-}
-
-// Last convolution (32 -> 16) with the 1x1 layer folded in: z[n] for the
-// wave's 128 positions, handed out in two calls of `emit(n, z)` in which
-// every lane holds one position (lane group q takes position tile q of the
-// group), so the sigmoid and the argmax that follow run on full waves.
-template <typename Emit>
-__device__ __forceinline__ void wave_conv_out(const WaveFrag &fr, const __bf16 *X, int lo, int hi,
-                                              int lane, Emit emit)
-{
-    const int kq = 8 * (lane >> 4);
-    int boff[5];
-#pragma unroll
-    for (int ks = 0; ks < 5; ++ks)
-        boff[ks] = act_off<32>((lane & 15) + kCnnGuard - 2 + ks, kq);
-#pragma unroll 1
-    for (int g = 0; g < kCnnWin / 16 / kNB; ++g) {
-        const int n0 = g * kNB * 16 + (lane & 15);
-        const __bf16 *b0 = X + g * kNB * 16 * 32;
-        f32x4 acc[kNB];
-#pragma unroll
-        for (int t = 0; t < kNB; ++t)
-            acc[t] = f32x4{fr.b4[0][0], fr.b4[0][1], fr.b4[0][2], fr.b4[0][3]};
-#pragma unroll
-        for (int ks = 0; ks < 5; ++ks) {
-            bf16x8 bv[kNB];
-#pragma unroll
-            for (int t = 0; t < kNB; ++t)
-                bv[t] = *reinterpret_cast<const bf16x8 *>(b0 + t * 16 * 32 + boff[ks]);
-#pragma unroll
-            for (int t = 0; t < kNB; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.w4[0][ks], bv[t], acc[t], 0, 0,
-                                                                 0);
-        }
-        static_assert(kNB == 4, "one position tile per lane group");
-        float mine = 0.0f;
-#pragma unroll
-        for (int t = 0; t < kNB; ++t) {
-            const int n = n0 + 16 * t;
-            const float top = (n >= lo && n < hi) ? __builtin_inff() : 0.0f;
-            float part = 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float h = (float)to_bf16(__builtin_amdgcn_fmed3f(acc[t][j], 0.0f, top));
-                part = fmaf(fr.w5[j], h, part);
-            }
-            part += __shfl_xor(part, 16, 64);
-            part += __shfl_xor(part, 32, 64);
-            mine = (lane >> 4) == t ? part : mine;
-        }
-        emit(n0 + 16 * (lane >> 4), fr.b5 + mine);
-    }
-}
-
-// Logits of one window whose input rows are in w.x0: all 128 positions, in
-// 2 calls of emit, one position per lane (positions outside the strip carry
-// unspecified values).
-template <typename Emit>
-__device__ __forceinline__ void wave_forward(const WaveFrag &fr, __bf16 *A, __bf16 *B, int lo,
-                                             int hi, int lane, Emit emit)
-{
-    wave_sync();
-    wave_conv<24, 16, 1, 4>(fr.w1, fr.b1, A, B, lo, hi, lane);
-    wave_sync();
-    wave_conv<16, 32, 2, 3>(fr.w2, fr.b2, B, A, lo, hi, lane);
-    wave_sync();
-    wave_conv<32, 32, 2, 5>(fr.w3, fr.b3, A, B, lo, hi, lane);
-    wave_sync();
-    wave_conv_out(fr, B, lo, hi, lane, emit);
-    wave_sync();
-}
-
-// Zero one wave's buffers once: afterwards every row holds a finite value.
-// Guard rows and halo positions only ever feed halo outputs (the receptive
-// field of a central position stays inside the window), so later windows
-// may leave stale finite values there.
-__device__ void wave_clear(__bf16 *x0, int lane)
-{
-    uint4 *p = reinterpret_cast<uint4 *>(x0);
-    for (int i = lane; i < kWaveBytes / 16; i += 64)
-        p[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
-// One position's 24 input channels from its bytes: (v - 128) / 64.
-__device__ __forceinline__ void store_row24(__bf16 *row, const uint32_t (&u)[6])
-{
-    typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
-    bf16x8v *dst = reinterpret_cast<bf16x8v *>(row);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        bf16x8v o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = 8 * c + e;
-            const float b = (float)((u[k >> 2] >> (8 * (k & 3))) & 0xFFu);
-            o[e] = to_bf16(fmaf(b, 1.0f / 64.0f, -2.0f));   // exact: (b - 128) / 64
-        }
-        dst[c] = o;
-    }
-}
-
-// Line j's six bytes of two adjacent positions (b03: the first four, b45: the
-// other two in its low half) into bytes 3j .. 3j + 2 of each position's 24.
-__device__ __forceinline__ void put_line(uint32_t (&u)[2][6], int j, uint32_t b03, uint32_t b45)
-{
-    const uint32_t p0 = b03 & 0xFFFFFFu;
-    const uint32_t p1 = (b03 >> 24) | ((b45 & 0xFFFFu) << 8);
-    const int k = 3 * j;
-    u[0][k >> 2] |= p0 << (8 * (k & 3));
-    if ((k & 3) > 1)
-        u[0][(k >> 2) + 1] |= p0 >> (32 - 8 * (k & 3));
-    u[1][k >> 2] |= p1 << (8 * (k & 3));
-    if ((k & 3) > 1)
-        u[1][(k >> 2) + 1] |= p1 >> (32 - 8 * (k & 3));
-}
 
 // --------------------------------------------------------------- kernels --
 
@@ -303,67 +46,6 @@ __global__ __launch_bounds__(kBlock) void k_mfma_probe(float *out)
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
     for (int j = 0; j < 4; ++j)
         out[(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
-}
-
-// Logits of the central positions of uint8 windows [n][8][128][3]: one
-// wavefront per window.  A byte at a time (48 rounds of loads, divisions and
-// two-byte LDS writes a lane) the input took longer than the layers: 37.5 us
-// for 3,584 windows, 22.6 with two loads a line, fetched a window ahead.
-__global__ __launch_bounds__(kCnnWaveBlock) void k_cnn_windows(const uint8_t *model,
-                                                               const uint8_t *win,
-                                                               const int32_t *range, float *z_out,
-                                                               int n_windows)
-{
-    extern __shared__ __align__(16) uint8_t cnn_smem[];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    __bf16 *x0 = reinterpret_cast<__bf16 *>(cnn_smem + wv * kWaveBytes);
-    __bf16 *hb = x0 + kWaveBuf;
-    WaveFrag fr;
-    load_wave_frag(fr, model, lane);
-    wave_clear(x0, lane);
-    const int waves = gridDim.x * (kCnnWaveBlock / 64);
-    // the next window's bytes: six of each line, positions 2 lane and 2 lane +
-    // 1, loaded while a window's layers run
-    uint32_t four[kCnnLines];
-    uint16_t two[kCnnLines];
-    auto fetch = [&](int wi) {
-        const uint8_t *src = win + (int64_t)wi * (kCnnLines * kCnnWin * 3) + 6 * lane;
-#pragma unroll
-        for (int j = 0; j < kCnnLines; ++j) {
-            __builtin_memcpy(&four[j], src + j * (kCnnWin * 3), 4);
-            __builtin_memcpy(&two[j], src + j * (kCnnWin * 3) + 4, 2);
-        }
-    };
-    const int first = blockIdx.x * (kCnnWaveBlock / 64) + wv;
-    if (first < n_windows)
-        fetch(first);
-    for (int wi = first; wi < n_windows; wi += waves) {
-        const int lo = uniform_int(range[2 * wi]);
-        const int hi = uniform_int(range[2 * wi + 1]);
-        wave_sync();
-        {
-            uint32_t u[2][6] = {};
-#pragma unroll
-            for (int j = 0; j < kCnnLines; ++j)
-                put_line(u, j, four[j], two[j]);
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int n = 2 * lane + k;
-                if (!(n >= lo && n < hi))
-#pragma unroll
-                    for (int i = 0; i < 6; ++i)
-                        u[k][i] = 0x80808080u;   // (128 - 128) / 64 = 0
-                store_row24(x0 + (n + kCnnGuard) * 24, u[k]);
-            }
-        }
-        if (wi + waves < n_windows)
-            fetch(wi + waves);
-        wave_forward(fr, x0, hb, lo, hi, lane, [&](int n, float z) {
-            if (n >= kCnnHalo && n < kCnnWin - kCnnHalo)
-                z_out[(int64_t)wi * kCnnOut + n - kCnnHalo] = z;
-        });
-    }
 }
 
 // ---------------------------------------------------------------- strips --
@@ -417,10 +99,10 @@ __device__ __forceinline__ int strip_off(int row, int c)
 }
 
 // The step's input rows, (v - 128) / 64, zero outside the strip.
-__device__ __forceinline__ void strip_encode(__bf16 *X, uint32_t (&px)[8], const StripWalk &k, int x,
+__device__ __forceinline__ void strip_encode(__bf16 *X, uint32_t (&px)[8], bool packed, int x, int L,
                                              const int (&xi)[3], int lane)
 {
-    if (!k.packed) {
+    if (!packed) {
         // dwords j = 4 i .. 4 i + 3 of three bytes to three of four
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -430,8 +112,8 @@ __device__ __forceinline__ void strip_encode(__bf16 *X, uint32_t (&px)[8], const
             px[3 * i + 2] = __builtin_amdgcn_perm(e, c, 0x06050402u);
         }
     }
-    if (x < 0 || x + kStep > k.L) {
-        const bool in = (uint32_t)(x + lane) < (uint32_t)k.L;
+    if (x < 0 || x + kStep > L) {
+        const bool in = (uint32_t)(x + lane) < (uint32_t)L;
 #pragma unroll
         for (int i = 0; i < 6; ++i)
             px[i] = in ? px[i] : 0x80808080u;   // (128 - 128) / 64 = 0
@@ -503,6 +185,222 @@ __device__ __forceinline__ void strip_store(Y &out, const f32x4 (&acc)[4][MT], c
                 relu_bf16(acc[j][mt], top[j]);
 }
 
+
+// The network in a wave's registers: A fragments, biases, and the lane's offsets
+// in StripRows.
+struct StripNet {
+    bf16x8 w1[5], w2[2][3], w3[2][5], w4[5];
+    f32x4 b1, b2[2], b3[2], b4, w5;
+    float b5;
+    // input rows of this lane's position; rows c and c + 1 of a 32-channel
+    // plane; of 16 channels, K groups g / 2 of a fragment lie one position
+    // apart, from plane 3 to plane 0 of the next row at every fourth; outputs
+    int xi[3], xo[2], xo2[2], yo1[1], yo[2];
+
+    __device__ __forceinline__ StripNet(const uint8_t *model, int lane)
+    {
+        const __bf16 *W = reinterpret_cast<const __bf16 *>(model);
+        const float *fb = reinterpret_cast<const float *>(model + kCnnFloatsOff);
+        const int col = lane & 15, g = lane >> 4;
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            // 24 channels a tap in the model's rows, 32 here
+            w1[t] = bf16x8{};
+            if (g < 3)
+                w1[t] = frag_at(W + kCnnWOff[0] + col * 128 + 24 * t + 8 * g);
+            w3[0][t] = frag_at(W + kCnnWOff[2] + col * 160 + 32 * t + 8 * g);
+            w3[1][t] = frag_at(W + kCnnWOff[2] + (16 + col) * 160 + 32 * t + 8 * g);
+            w4[t] = frag_at(W + kCnnWOff[3] + col * 160 + 32 * t + 8 * g);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks) {
+            w2[0][ks] = frag_at(W + kCnnWOff[1] + col * 96 + 32 * ks + 8 * g);
+            w2[1][ks] = frag_at(W + kCnnWOff[1] + (16 + col) * 96 + 32 * ks + 8 * g);
+        }
+        auto four = [&](int at) { return *reinterpret_cast<const f32x4 *>(fb + at + 4 * g); };
+        b1 = four(kCnnBOff[0]);
+        b2[0] = four(kCnnBOff[1]);
+        b2[1] = four(kCnnBOff[1] + 16);
+        b3[0] = four(kCnnBOff[2]);
+        b3[1] = four(kCnnBOff[2] + 16);
+        b4 = four(kCnnBOff[3]);
+        w5 = four(kCnnW5Off);
+        b5 = fb[kCnnW5Off + 16];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            xi[i] = (lane & 3) * StripPlanes<32, 17>::kPlane + strip_off<32>((lane >> 2) + 1, 8 * i);
+        constexpr int kPlane2 = StripPlanes<16, 18>::kPlane;
+        const int at2 = strip_off<16>(col, 8 * (g & 1));
+        xo2[0] = at2 + (g >> 1) * kPlane2;
+        xo2[1] = at2 + (g >> 1) * (16 - 3 * kPlane2);
+        yo1[0] = strip_off<16>(col + 1, 4 * g);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            xo[i] = strip_off<32>(col + i, 8 * g);
+            yo[i] = strip_off<32>(col + 1, 16 * i + 4 * g);
+        }
+    }
+
+    // One step, its input rows in R.x0, x the first one's position of a strip of
+    // L: the logit of position x - 8 + 4 (lane % 16) + lane / 16.
+    __device__ __forceinline__ float step(StripRows &R, int x, int L, int lane) const
+    {
+        bf16x8 b[8];
+        wave_sync();
+        uint32_t kept = strip_keep(R.x0, lane);
+        strip_frags(b, R.x0, xo);
+        {
+            f32x4 acc[4][1];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[j][0] = b1;
+#pragma unroll
+            for (int t = 0; t < 5; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j][0] = mma(w1[t], b[j + t], acc[j][0]);
+            strip_store<1>(R.h1, acc, yo1, x - 2, L, lane);
+        }
+        wave_sync();
+        strip_kept(R.x0, kept, lane);
+        kept = strip_keep(R.h1, lane);
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            b[s] = frag_at(R.h1.v + (s & 3) * R.h1.kPlane + (s >> 2) * 16
+                           + xo2[(s & 3) == 3]);
+        {
+            f32x4 acc[4][2];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[j][0] = b2[0];
+                acc[j][1] = b2[1];
+            }
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    acc[j][0] = mma(w2[0][ks], b[j + 2 * ks], acc[j][0]);
+                    acc[j][1] = mma(w2[1][ks], b[j + 2 * ks], acc[j][1]);
+                }
+            strip_store<2>(R.h2, acc, yo, x - 4, L, lane);
+        }
+        wave_sync();
+        strip_kept(R.h1, kept, lane);
+        kept = strip_keep(R.h2, lane);
+        strip_frags(b, R.h2, xo);
+        {
+            f32x4 acc[4][2];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[j][0] = b3[0];
+                acc[j][1] = b3[1];
+            }
+#pragma unroll
+            for (int t = 0; t < 5; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    acc[j][0] = mma(w3[0][t], b[j + t], acc[j][0]);
+                    acc[j][1] = mma(w3[1][t], b[j + t], acc[j][1]);
+                }
+            strip_store<2>(R.h3, acc, yo, x - 6, L, lane);
+        }
+        wave_sync();
+        strip_kept(R.h2, kept, lane);
+        kept = strip_keep(R.h3, lane);
+        strip_frags(b, R.h3, xo);
+        float part_z[4];   // lane group's share of each tile's 1x1 layer
+        {
+            f32x4 acc[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[j] = b4;
+#pragma unroll
+            for (int t = 0; t < 5; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j] = mma(w4[t], b[j + t], acc[j]);
+            float top[4];
+            strip_tops(top, x - 8, L, lane);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                const u32x2 h = __builtin_bit_cast(u32x2, relu_bf16(acc[j], top[j]));
+                float z = 0.0f;   // a bfloat16 is a float's upper half
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    z = fmaf(w5[2 * e], __uint_as_float(h[e] << 16), z);
+                    z = fmaf(w5[2 * e + 1], __uint_as_float(h[e] & 0xFFFF0000u), z);
+                }
+                part_z[j] = z;
+            }
+        }
+        wave_sync();
+        strip_kept(R.h3, kept, lane);
+        return b5 + tile_sums(part_z);
+    }
+};
+
+__device__ __forceinline__ void strip_clear(StripRows &R, int lane)
+{
+    for (int i = lane; i < (int)(sizeof(StripRows) / 16); i += 64)
+        reinterpret_cast<uint4 *>(&R)[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Logits of the central positions of uint8 windows [n][8][128][3]: a window is a
+// strip of two steps, and the rows that the first one finds in place of its
+// predecessor's feed only the window's halo.  One wave a window, two a workgroup
+// (a small batch spreads over more compute units); the next step's bytes are
+// loaded while a step's layers run.  Bound by the chain of layers within a step:
+// a wave has few windows.  Measured, 3,584 windows (a call): 43.6 us with a byte
+// at a time loaded at each window's turn, 19.3 us with the window's words
+// fetched ahead and tiles of 16 neighbours, 17.0 us so.
+__global__ __launch_bounds__(kCnnWaveBlock, 2) void k_cnn_windows(const uint8_t *model,
+                                                                  const uint8_t *win,
+                                                                  const int32_t *range, float *z_out,
+                                                                  int n_windows)
+{
+    extern __shared__ __align__(16) uint8_t cnn_smem[];
+    const int lane = threadIdx.x & 63;
+    const int wv = uniform_int(threadIdx.x >> 6);
+    StripRows &R = reinterpret_cast<StripRows *>(cnn_smem)[wv];
+    strip_clear(R, lane);
+    const int waves = gridDim.x * (kCnnWaveBlock / 64);
+    uint32_t px[8];
+    auto fetch = [&](int wi, int x) {
+        StripWalk k;
+        k.frame = win + (int64_t)wi * (kCnnLines * kCnnWin * 3);
+        k.along = 3;
+        k.across = 3 * kCnnWin;
+        k.first = 0;
+        k.L = kCnnWin;
+        k.lines = kCnnLines;
+        k.packed = false;
+        k.last_row = wi == n_windows - 1;
+        strip_fetch<kCnnLines>(px, k, x, lane);
+    };
+    const int first = blockIdx.x * (kCnnWaveBlock / 64) + wv;
+    if (first < n_windows)
+        fetch(first, 0);
+    const StripNet net(model, lane);
+    for (int wi = first; wi < n_windows; wi += waves) {
+        const int lo = uniform_int(min(max(range[2 * wi], 0), kCnnWin));
+        const int L = max(uniform_int(min(range[2 * wi + 1], kCnnWin)) - lo, 0);
+#pragma unroll 1
+        for (int x = 0; x < kCnnWin; x += kStep) {
+            wave_sync();
+            strip_encode(R.x0.v, px, false, x - lo, L, net.xi, lane);
+            if (x == 0)
+                fetch(wi, kStep);
+            else if (wi + waves < n_windows)
+                fetch(wi + waves, 0);
+            const float z = net.step(R, x - lo, L, lane);
+            const int n = x - kCnnHalo + 4 * (lane & 15) + (lane >> 4);
+            if (n >= kCnnHalo && n < kCnnWin - kCnnHalo)
+                z_out[(int64_t)wi * kCnnOut + n - kCnnHalo] = z;
+        }
+    }
+}
+
 __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs a)
 {
     extern __shared__ __align__(16) uint8_t cnn_smem[];
@@ -517,51 +415,9 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
     const int sets = kStripWaves / a.parts;          // half strips a workgroup takes at a time
     if (group * sets >= n_units)
         return;
-    const __bf16 *W = reinterpret_cast<const __bf16 *>(a.model);
-    const float *fb = reinterpret_cast<const float *>(a.model + kCnnFloatsOff);
-    const int col = lane & 15, g = lane >> 4;
     StripRows &R = rows[wv];
-    for (int i = lane; i < (int)(sizeof(StripRows) / 16); i += 64)
-        reinterpret_cast<uint4 *>(&R)[i] = make_uint4(0u, 0u, 0u, 0u);
-    bf16x8 w1[5], w2[2][3], w3[2][5], w4[5];
-    f32x4 b1, b2[2], b3[2], b4, w5;
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-        // 24 channels a tap in the model's rows, 32 here
-        w1[t] = bf16x8{};
-        if (g < 3)
-            w1[t] = frag_at(W + kCnnWOff[0] + col * 128 + 24 * t + 8 * g);
-        w3[0][t] = frag_at(W + kCnnWOff[2] + col * 160 + 32 * t + 8 * g);
-        w3[1][t] = frag_at(W + kCnnWOff[2] + (16 + col) * 160 + 32 * t + 8 * g);
-        w4[t] = frag_at(W + kCnnWOff[3] + col * 160 + 32 * t + 8 * g);
-    }
-#pragma unroll
-    for (int ks = 0; ks < 3; ++ks) {
-        w2[0][ks] = frag_at(W + kCnnWOff[1] + col * 96 + 32 * ks + 8 * g);
-        w2[1][ks] = frag_at(W + kCnnWOff[1] + (16 + col) * 96 + 32 * ks + 8 * g);
-    }
-    auto four = [&](int at) { return *reinterpret_cast<const f32x4 *>(fb + at + 4 * g); };
-    b1 = four(kCnnBOff[0]);
-    b2[0] = four(kCnnBOff[1]);
-    b2[1] = four(kCnnBOff[1] + 16);
-    b3[0] = four(kCnnBOff[2]);
-    b3[1] = four(kCnnBOff[2] + 16);
-    b4 = four(kCnnBOff[3]);
-    w5 = four(kCnnW5Off);
-    const float b5 = fb[kCnnW5Off + 16];
-
-    // input rows of this lane's position; rows c and c + 1 of a 32-channel
-    // plane; of 16 channels, K groups g / 2 of a fragment lie one position
-    // apart, from plane 3 to plane 0 of the next row at every fourth; outputs
-    int xi[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        xi[i] = (lane & 3) * R.x0.kPlane + strip_off<32>((lane >> 2) + 1, 8 * i);
-    const int xo[2] = {strip_off<32>(col, 8 * g), strip_off<32>(col + 1, 8 * g)};
-    const int at2 = strip_off<16>(col, 8 * (g & 1));
-    const int xo2[2] = {at2 + (g >> 1) * R.h1.kPlane, at2 + (g >> 1) * (16 - 3 * R.h1.kPlane)};
-    const int yo1[1] = {strip_off<16>(col + 1, 4 * g)};
-    const int yo[2] = {strip_off<32>(col + 1, 4 * g), strip_off<32>(col + 1, 16 + 4 * g)};
+    strip_clear(R, lane);
+    const StripNet net(a.model, lane);
 
     const int S = a.n_h + a.n_v;
     const int set = wv / a.parts, part = wv % a.parts;
@@ -594,102 +450,11 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
             if (p0 < p1)
                 strip_fetch<kCnnLines>(px, k, x, lane);
             for (; p0 < p1 && x - kCnnHalo < p1; x += kStep) {
-                bf16x8 b[8];
-                strip_encode(R.x0.v, px, k, x, xi, lane);
+                strip_encode(R.x0.v, px, k.packed, x, L, net.xi, lane);
                 if (x + kStep - kCnnHalo < p1)
                     strip_fetch<kCnnLines>(px, k, x + kStep, lane);
-                wave_sync();
-                uint32_t kept = strip_keep(R.x0, lane);
-                strip_frags(b, R.x0, xo);
-                {
-                    f32x4 acc[4][1];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[j][0] = b1;
-#pragma unroll
-                    for (int t = 0; t < 5; ++t)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[j][0] = mma(w1[t], b[j + t], acc[j][0]);
-                    strip_store<1>(R.h1, acc, yo1, x - 2, L, lane);
-                }
-                wave_sync();
-                strip_kept(R.x0, kept, lane);
-                kept = strip_keep(R.h1, lane);
-#pragma unroll
-                for (int s = 0; s < 8; ++s)
-                    b[s] = frag_at(R.h1.v + (s & 3) * R.h1.kPlane + (s >> 2) * 16
-                                   + xo2[(s & 3) == 3]);
-                {
-                    f32x4 acc[4][2];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acc[j][0] = b2[0];
-                        acc[j][1] = b2[1];
-                    }
-#pragma unroll
-                    for (int ks = 0; ks < 3; ++ks)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            acc[j][0] = mma(w2[0][ks], b[j + 2 * ks], acc[j][0]);
-                            acc[j][1] = mma(w2[1][ks], b[j + 2 * ks], acc[j][1]);
-                        }
-                    strip_store<2>(R.h2, acc, yo, x - 4, L, lane);
-                }
-                wave_sync();
-                strip_kept(R.h1, kept, lane);
-                kept = strip_keep(R.h2, lane);
-                strip_frags(b, R.h2, xo);
-                {
-                    f32x4 acc[4][2];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acc[j][0] = b3[0];
-                        acc[j][1] = b3[1];
-                    }
-#pragma unroll
-                    for (int t = 0; t < 5; ++t)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            acc[j][0] = mma(w3[0][t], b[j + t], acc[j][0]);
-                            acc[j][1] = mma(w3[1][t], b[j + t], acc[j][1]);
-                        }
-                    strip_store<2>(R.h3, acc, yo, x - 6, L, lane);
-                }
-                wave_sync();
-                strip_kept(R.h2, kept, lane);
-                kept = strip_keep(R.h3, lane);
-                strip_frags(b, R.h3, xo);
-                float part_z[4];   // lane group's share of each tile's 1x1 layer
-                {
-                    f32x4 acc[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[j] = b4;
-#pragma unroll
-                    for (int t = 0; t < 5; ++t)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[j] = mma(w4[t], b[j + t], acc[j]);
-                    float top[4];
-                    strip_tops(top, x - 8, L, lane);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                        const u32x2 h = __builtin_bit_cast(u32x2, relu_bf16(acc[j], top[j]));
-                        float z = 0.0f;   // a bfloat16 is a float's upper half
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            z = fmaf(w5[2 * e], __uint_as_float(h[e] << 16), z);
-                            z = fmaf(w5[2 * e + 1], __uint_as_float(h[e] & 0xFFFF0000u), z);
-                        }
-                        part_z[j] = z;
-                    }
-                }
-                wave_sync();
-                strip_kept(R.h3, kept, lane);
-                const float z = b5 + tile_sums(part_z);
-                const int p = x - kCnnHalo + 4 * col + g;
+                const float z = net.step(R, x, L, lane);
+                const int p = x - kCnnHalo + 4 * (lane & 15) + (lane >> 4);
                 if (p >= p0 && p < p1) {
                     const uint64_t key = strip_key(z, p, half, L);
                     best = best > key ? best : key;
@@ -743,6 +508,25 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
 // workgroups share a compute unit.  Measured, 14,336 windows: 791 us with
 // channel-major copies of the signals and element-wise gathered operands, 258
 // us so (kernel trace).
+
+// Element offset of channels c .. c + 7 (c a multiple of 4) of row `row` in
+// a position-major buffer of C channels.  With 32 or 16 channels the
+// 16-byte chunks of a row are permuted by row (XOR with bits of the row
+// index) so that the 16 lanes of one LDS pass, which read or write 16
+// consecutive rows at the same channel, hit 16 distinct groups of 4 banks
+// instead of 4 (32 channels) or 8 (16 channels); 24-channel rows already do.
+// The permutation depends only on row / 4 mod 4 (row / 8 mod 2), so shifting
+// by whole 16-row tiles keeps it.
+template <int C>
+__device__ __forceinline__ int act_off(int row, int c)
+{
+    static_assert(C == 16 || C == 24 || C == 32, "buffer width");
+    if (C == 32)
+        return row * 32 + ((((c >> 3) ^ (row >> 2)) & 3) << 3) + (c & 7);
+    if (C == 16)
+        return row * 16 + ((((c >> 3) ^ (row >> 3)) & 1) << 3) + (c & 7);
+    return row * 24 + c;
+}
 
 struct alignas(16) CnnGradLds {
     __bf16 w3[10 * 512];          // layer 3's A fragments, [5 mt + ks][lane][8]
@@ -1347,7 +1131,7 @@ hipError_t launch_mfma_probe(float *out, hipStream_t s)
     return hipGetLastError();
 }
 
-constexpr size_t kCnnWaveLds = (size_t)(kCnnWaveBlock / 64) * kWaveBytes;
+constexpr size_t kCnnWaveLds = (size_t)(kCnnWaveBlock / 64) * sizeof(StripRows);
 
 hipError_t launch_cnn_windows(const uint8_t *model, const uint8_t *win, const int32_t *range,
                               float *z, int n, hipStream_t s)
