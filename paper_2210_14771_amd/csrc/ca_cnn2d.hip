@@ -30,11 +30,11 @@ namespace {
 
 constexpr int kPos = kC2Win + 2;   // positions of a buffer line, guards included
 constexpr int kC2Halo = 3;         // the network's receptive-field radius
-constexpr int kC2Stride = kC2Win - 2 * kC2Halo;   // exact logits per strip window
 constexpr int kTrainHalo = 8;      // training windows carry logits 8 .. 119
 constexpr int kTrainOut = kC2Win - 2 * kTrainHalo;
 constexpr int kC2Floats = 96;      // floats of the model's float block
 constexpr int kWaves = kBlock / 64;
+constexpr int kC2WindowBlock = 128;   // window logits: two waves, a window each
 
 // The A operand of a layer's GEMMs (weights [M][KP], M = 16 MT output
 // channels) as this lane's MFMA fragments: loaded once, kept in registers
@@ -112,6 +112,21 @@ struct alignas(16) Strip2dRows {     // one wave's inputs of the three layers
     __bf16 h2[3 * kC2Rows * 16];
 };
 
+__device__ __forceinline__ void strip2d_clear(Strip2dRows &R, int lane)
+{
+    for (int i = lane; i < (int)(sizeof(Strip2dRows) / 16); i += 64)
+        reinterpret_cast<uint4 *>(&R)[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Offset of channels c .. c + 3 (c a multiple of 4) of a position of a line of
+// h2.  The two 16-byte halves are exchanged in every other group of eight
+// positions, so a store's 16 positions meet all banks; a fragment read takes 8
+// cycles either way.
+__device__ __forceinline__ int strip2d_off16(int pos, int c)
+{
+    return pos * 16 + ((((c >> 3) ^ (pos >> 3)) & 1) << 3) + (c & 7);
+}
+
 // The last two positions of each line of a step become the first two of the
 // next; lanes beyond the lines' dwords repeat the last one's.
 template <int LINES, int C>
@@ -181,9 +196,61 @@ __device__ __forceinline__ void strip2d_tops(uint32_t (&top)[4], int n, int L, i
     }
 }
 
+// A band's geometry: which lines lie in the frame, and the coordinates, across
+// the strip by line, along it as (2 p - last) scale.
+struct Band {
+    uint32_t line_ok;
+    uint32_t line1[3], line2[3], line3;   // masks of the output lines (strip2d_tops)
+    float across[kC2Band];
+    float scale;
+    int last;
+    bool horizontal;
+
+    __device__ __forceinline__ Band(bool hz, int line, int W, int H, int lane)
+        : horizontal(hz)
+    {
+        const int lines = hz ? H : W;
+        line_ok = band_lines(line, lines);
+        // layer 1's by pairs (1, 2), (3, 4), (5, -)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            line1[i] = line_in(line_ok, 2 * i + (lane >> 5) + 1) ? 0x7F800000u : 0u;
+            line2[i] = line_in(line_ok, i + 2) ? 0x7F800000u : 0u;
+        }
+        line3 = line_in(line_ok, 3) ? 0x7F800000u : 0u;
+        const float scale_x = coord_scale(W), scale_y = coord_scale(H);
+        scale = hz ? scale_x : scale_y;
+        last = (hz ? W : H) - 1;
+#pragma unroll
+        for (int j = 0; j < kC2Band; ++j)
+            across[j] = (float)(2 * (line - 3 + j) - (lines - 1)) * (hz ? scale_y : scale_x);
+    }
+
+    // A step's input rows from its pixels: p, this lane's position in the frame;
+    // x, the step's first position of a strip of L.
+    __device__ __forceinline__ void encode(__bf16 *x0, const uint32_t (&px)[8],
+                                           const float (&norm)[6], int p, int x, int L,
+                                           int lane) const
+    {
+        const float along = (float)(2 * p - last) * scale;
+        const uint32_t in = (uint32_t)(x + lane) < (uint32_t)L ? ~0u : 0u;
+        const bool whole = line_ok == 0x7Fu && x >= 0 && x + kStep <= L;
+        __bf16 *row = x0 + (lane + 2) * 8;
+        if (horizontal && whole)
+            strip2d_encode<true, false>(row, px, norm, along, across, line_ok, in);
+        else if (horizontal)
+            strip2d_encode<true, true>(row, px, norm, along, across, line_ok, in);
+        else if (whole)
+            strip2d_encode<false, false>(row, px, norm, along, across, line_ok, in);
+        else
+            strip2d_encode<false, true>(row, px, norm, along, across, line_ok, in);
+    }
+};
+
 // One output line (or pair of lines) of a 3x3 layer: four position tiles, all
-// output-channel tiles, accumulators seeded with the bias.
-template <int C, int MT, int KS>
+// output-channel tiles.  SEED: the sums start at the bias (learned strips);
+// else it is added to them (window logits).
+template <bool SEED, int C, int MT, int KS>
 __device__ __forceinline__ void strip2d_conv(f32x4 (&acc)[4][MT], const bf16x8 (&w)[MT][KS],
                                              const f32x4 (&bias)[MT], const __bf16 *X,
                                              const int (&xo)[KS])
@@ -192,7 +259,7 @@ __device__ __forceinline__ void strip2d_conv(f32x4 (&acc)[4][MT], const bf16x8 (
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            acc[t][mt] = bias[mt];
+            acc[t][mt] = SEED ? bias[mt] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         bf16x8 b[4];
@@ -205,7 +272,153 @@ __device__ __forceinline__ void strip2d_conv(f32x4 (&acc)[4][MT], const bf16x8 (
             for (int t = 0; t < 4; ++t)
                 acc[t][mt] = mma(w[mt][ks], b[t], acc[t][mt]);
     }
+    if (!SEED)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[t][mt] += bias[mt];
 }
+
+// The network in a wave's registers, for one orientation at a time: A
+// fragments, biases, and the lane's offsets in Strip2dRows.
+template <bool SEED>
+struct Strip2dNet {
+    // layer 1's weights are those of output-line pairs: rows 8 .. 15, so lane
+    // groups 2 and 3, are the second line's channels
+    bf16x8 w1[1][3], w2[1][3], w3[2][5];
+    f32x4 b1[1], b2[1], b3[2], w4[2];
+    float b4;
+    float norm[6];   // the colours' means, then their inverse deviations
+    int xo1[3], xo2[3], xo3[5], at0, at1, at2;
+    int loaded = -1;   // the orientation whose weights are held
+
+    __device__ __forceinline__ Strip2dNet(const uint8_t *model, int lane)
+    {
+        const float *fb = reinterpret_cast<const float *>(model + kC2FloatsOff);
+        const int col = lane & 15, g = lane >> 4;
+        auto four = [&](int at) {
+            f32x4 v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v[j] = fb[at + j];
+            return v;
+        };
+        b1[0] = four(kC2FB[0] + 4 * (g & 1));
+        b2[0] = four(kC2FB[1] + 4 * g);
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            b3[mt] = four(kC2FB[2] + 16 * mt + 4 * g);
+            w4[mt] = four(kC2FW4 + 16 * mt + 4 * g);
+        }
+        b4 = fb[kC2FB4];
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            norm[i] = __uint_as_float(uniform_int(__float_as_uint(fb[kC2FMean + i])));
+        // B fragment offsets of the first tile's column: K group k = tap C / 8 +
+        // channel half, tap = 3 (line) + position; the groups beyond the taps
+        // have zero weights
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks) {
+            const int k = 4 * ks + g, k2 = k < 9 ? k : 0;
+            xo1[ks] = (k / 3 * kC2Rows + k % 3 + col) * 8;
+            xo2[ks] = (k2 / 3 * kC2Rows + k2 % 3 + col) * 8;
+        }
+#pragma unroll
+        for (int ks = 0; ks < 5; ++ks) {
+            const int k = 4 * ks + g < 18 ? 4 * ks + g : 0;
+            xo3[ks] = k / 6 * kC2Rows * 16 + strip2d_off16(k / 2 % 3 + col, 8 * (k & 1));
+        }
+        at0 = strip2d_at<kC2Band, 8>(lane);
+        at1 = strip2d_at<5, 8>(lane);
+        at2 = strip2d_at<3, 16>(lane);
+    }
+
+    __device__ __forceinline__ void turn_to(bool horizontal, const uint8_t *model, int lane)
+    {
+        if (loaded == (int)horizontal)
+            return;
+        const int col = lane & 15, g = lane >> 4;
+        const __bf16 *A = reinterpret_cast<const __bf16 *>(model) + (horizontal ? 0 : kC2Orient);
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks) {
+            w1[0][ks] = frag_at(A + kC2P1 + col * 96 + 32 * ks + 8 * g);
+            w2[0][ks] = frag_at(A + kC2A[1] + col * 96 + 32 * ks + 8 * g);
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks)
+                w3[mt][ks] = frag_at(A + kC2A[2] + (16 * mt + col) * 160 + 32 * ks + 8 * g);
+        loaded = (int)horizontal;
+    }
+
+    // One step, its input rows in R.x0, x the first one's position of a strip of
+    // L: the logit of position x - 3 + lane.
+    __device__ __forceinline__ float step(Strip2dRows &R, const Band &band, int x, int L,
+                                          int lane) const
+    {
+        const int col = lane & 15, g = lane >> 4;
+        wave_sync();
+        uint32_t top[4];
+        uint32_t kept = strip2d_keep<8>(R.x0, at0);
+        strip2d_tops(top, x - 1, L, lane);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            f32x4 acc[4][1];
+            strip2d_conv<SEED, 8>(acc, w1, b1, R.x0 + 2 * i * kC2Rows * 8, xo1);
+            if (i < 2 || g < 2)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    *reinterpret_cast<bf16x4 *>(
+                        R.h1 + ((2 * i + (g >> 1)) * kC2Rows + 16 * t + col + 2) * 8
+                        + 4 * (g & 1)) =
+                        relu_bf16(acc[t][0], __uint_as_float(top[t] & band.line1[i]));
+        }
+        wave_sync();
+        strip2d_kept(R.x0, kept, at0);
+        kept = strip2d_keep<8>(R.h1, at1);
+        strip2d_tops(top, x - 2, L, lane);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            f32x4 acc[4][1];
+            strip2d_conv<SEED, 8>(acc, w2, b2, R.h1 + i * kC2Rows * 8, xo2);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                *reinterpret_cast<bf16x4 *>(R.h2 + (i * kC2Rows + 16 * t) * 16
+                                            + strip2d_off16(col + 2, 4 * g)) =
+                    relu_bf16(acc[t][0], __uint_as_float(top[t] & band.line2[i]));
+        }
+        wave_sync();
+        strip2d_kept(R.h1, kept, at1);
+        kept = strip2d_keep<16>(R.h2, at2);
+        strip2d_tops(top, x - 3, L, lane);
+        float part_z[4];   // lane group's share of each tile's 1x1 layer
+        {
+            f32x4 acc[4][2];
+            strip2d_conv<SEED, 16>(acc, w3, b3, R.h2, xo3);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float z = 0.0f;
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    const u32x2 h = __builtin_bit_cast(
+                        u32x2, relu_bf16(acc[t][mt], __uint_as_float(top[t] & band.line3)));
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {   // a bfloat16 is a float's upper half
+                        z = fmaf(w4[mt][2 * e], __uint_as_float(h[e] << 16), z);
+                        z = fmaf(w4[mt][2 * e + 1], __uint_as_float(h[e] & 0xFFFF0000u), z);
+                    }
+                }
+                part_z[t] = z;
+            }
+        }
+        wave_sync();
+        strip2d_kept(R.h2, kept, at2);
+        return b4 + tile_sums(part_z);
+    }
+};
 
 __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStripArgs a)
 {
@@ -220,56 +433,13 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStrip
     const int sets = kStripWaves / a.parts;          // half strips a workgroup takes at a time
     if (group * sets >= n_units)
         return;
-    const float *fb = reinterpret_cast<const float *>(a.model + kC2FloatsOff);
-    const int col = lane & 15, g = lane >> 4;
     Strip2dRows &R = reinterpret_cast<Strip2dRows *>(strip_smem)[wv];
-    for (int i = lane; i < (int)(sizeof(Strip2dRows) / 16); i += 64)
-        reinterpret_cast<uint4 *>(&R)[i] = make_uint4(0u, 0u, 0u, 0u);
-    // layer 1's weights are those of output-line pairs: rows 8 .. 15, so lane
-    // groups 2 and 3, are the second line's channels
-    bf16x8 w1[1][3], w2[1][3], w3[2][5];
-    f32x4 b1[1], b2[1], b3[2], w4[2];
-    auto four = [&](int at) {
-        f32x4 v;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            v[j] = fb[at + j];
-        return v;
-    };
-    b1[0] = four(kC2FB[0] + 4 * (g & 1));
-    b2[0] = four(kC2FB[1] + 4 * g);
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-        b3[mt] = four(kC2FB[2] + 16 * mt + 4 * g);
-        w4[mt] = four(kC2FW4 + 16 * mt + 4 * g);
-    }
-    const float b4 = fb[kC2FB4];
-    float norm[6];   // the colours' means, then their inverse deviations
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-        norm[i] = __uint_as_float(uniform_int(__float_as_uint(fb[kC2FMean + i])));
-    // B fragment offsets of the first tile's column: K group k = tap C / 8 +
-    // channel half, tap = 3 (line) + position; the groups beyond the taps have
-    // zero weights
-    int xo1[3], xo2[3], xo3[5];
-#pragma unroll
-    for (int ks = 0; ks < 3; ++ks) {
-        const int k = 4 * ks + g, k2 = k < 9 ? k : 0;
-        xo1[ks] = (k / 3 * kC2Rows + k % 3 + col) * 8;
-        xo2[ks] = (k2 / 3 * kC2Rows + k2 % 3 + col) * 8;
-    }
-#pragma unroll
-    for (int ks = 0; ks < 5; ++ks) {
-        const int k = 4 * ks + g < 18 ? 4 * ks + g : 0;
-        xo3[ks] = (k / 6 * kC2Rows + k / 2 % 3 + col) * 16 + 8 * (k & 1);
-    }
-    const int at0 = strip2d_at<kC2Band, 8>(lane), at1 = strip2d_at<5, 8>(lane);
-    const int at2 = strip2d_at<3, 16>(lane);
+    strip2d_clear(R, lane);
+    Strip2dNet<true> net(a.model, lane);
 
     const int S = a.n_h + a.n_v;
     const int set = wv / a.parts, part = wv % a.parts;
     const int slots = groups * sets;
-    int loaded = -1;   // the orientation whose weights are held
     for (int turn = 0; turn * slots < n_units; ++turn) {
         // half strips rotate from turn to turn, so that every wave takes long and
         // short ones (ca_cnn.hip)
@@ -285,130 +455,29 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStrip
             const FrameDev d = a.fd[f];
             horizontal = st < a.n_h;
             pos = uniform_int(a.strips[d.table + st]);
-            if (loaded != (int)horizontal) {
-                const __bf16 *A =
-                    reinterpret_cast<const __bf16 *>(a.model) + (horizontal ? 0 : kC2Orient);
-#pragma unroll
-                for (int ks = 0; ks < 3; ++ks) {
-                    w1[0][ks] = frag_at(A + kC2P1 + col * 96 + 32 * ks + 8 * g);
-                    w2[0][ks] = frag_at(A + kC2A[1] + col * 96 + 32 * ks + 8 * g);
-                }
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                    for (int ks = 0; ks < 5; ++ks)
-                        w3[mt][ks] = frag_at(A + kC2A[2] + (16 * mt + col) * 160 + 32 * ks + 8 * g);
-                loaded = (int)horizontal;
-            }
+            net.turn_to(horizontal, a.model, lane);
             StripWalk k;
             strip_walk<kC2Band>(k, a.frames, d, horizontal, pos);
             L = k.L;
             const int h0 = half ? L >> 1 : 0, h1 = half ? L : L >> 1;
             const int each = (h1 - h0 + a.parts - 1) / a.parts;
             const int p0 = h0 + part * each, p1 = min(p0 + each, h1);
-            const uint32_t line_ok = band_lines(pos, k.lines);
-            // the masks of the output lines, of layer 1 by pairs (1, 2), (3, 4),
-            // (5, -)
-            uint32_t line1[3], line2[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                line1[i] = line_in(line_ok, 2 * i + (g >> 1) + 1) ? 0x7F800000u : 0u;
-                line2[i] = line_in(line_ok, i + 2) ? 0x7F800000u : 0u;
-            }
-            const uint32_t line3 = line_in(line_ok, 3) ? 0x7F800000u : 0u;
-            // the coordinates: along the strip in the lane, across it by line
-            const float scale_x = coord_scale(d.W), scale_y = coord_scale(d.H);
-            const float scale_along = horizontal ? scale_x : scale_y;
-            float across[kC2Band];
-#pragma unroll
-            for (int j = 0; j < kC2Band; ++j)
-                across[j] = (float)(2 * (k.first + j) - (k.lines - 1))
-                            * (horizontal ? scale_y : scale_x);
+            const Band band(horizontal, pos, uniform_int(d.W), uniform_int(d.H), lane);
             uint32_t px[8];
             int x = p0 - kC2Halo;   // first new input position of the step
             if (p0 < p1)
                 strip_fetch<kC2Band>(px, k, x, lane);
             for (; p0 < p1 && x - kC2Halo < p1; x += kStep) {
-                {
-                    if (k.packed) {   // 21 bytes to a dword of three for each line
+                if (k.packed) {   // 21 bytes to a dword of three for each line
 #pragma unroll
-                        for (int j = kC2Band - 1; j >= 0; --j)
-                            px[j] = __builtin_amdgcn_alignbyte(px[(3 * j >> 2) + 1], px[3 * j >> 2],
-                                                               3 * j & 3);
-                    }
-                    const float along = (float)(2 * (x + lane) - (L - 1)) * scale_along;
-                    const uint32_t in = (uint32_t)(x + lane) < (uint32_t)L ? ~0u : 0u;
-                    const bool whole = line_ok == 0x7Fu && x >= 0 && x + kStep <= L;
-                    __bf16 *row = R.x0 + (lane + 2) * 8;
-                    if (horizontal && whole)
-                        strip2d_encode<true, false>(row, px, norm, along, across, line_ok, in);
-                    else if (horizontal)
-                        strip2d_encode<true, true>(row, px, norm, along, across, line_ok, in);
-                    else if (whole)
-                        strip2d_encode<false, false>(row, px, norm, along, across, line_ok, in);
-                    else
-                        strip2d_encode<false, true>(row, px, norm, along, across, line_ok, in);
+                    for (int j = kC2Band - 1; j >= 0; --j)
+                        px[j] = __builtin_amdgcn_alignbyte(px[(3 * j >> 2) + 1], px[3 * j >> 2],
+                                                           3 * j & 3);
                 }
+                band.encode(R.x0, px, net.norm, x + lane, x, L, lane);
                 if (x + kStep - kC2Halo < p1)
                     strip_fetch<kC2Band>(px, k, x + kStep, lane);
-                wave_sync();
-                uint32_t top[4];
-                uint32_t kept = strip2d_keep<8>(R.x0, at0);
-                strip2d_tops(top, x - 1, L, lane);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    f32x4 acc[4][1];
-                    strip2d_conv<8>(acc, w1, b1, R.x0 + 2 * i * kC2Rows * 8, xo1);
-                    if (i < 2 || g < 2)
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            *reinterpret_cast<bf16x4 *>(
-                                R.h1 + ((2 * i + (g >> 1)) * kC2Rows + 16 * t + col + 2) * 8
-                                + 4 * (g & 1)) =
-                                relu_bf16(acc[t][0], __uint_as_float(top[t] & line1[i]));
-                }
-                wave_sync();
-                strip2d_kept(R.x0, kept, at0);
-                kept = strip2d_keep<8>(R.h1, at1);
-                strip2d_tops(top, x - 2, L, lane);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    f32x4 acc[4][1];
-                    strip2d_conv<8>(acc, w2, b2, R.h1 + i * kC2Rows * 8, xo2);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        *reinterpret_cast<bf16x4 *>(R.h2 + (i * kC2Rows + 16 * t + col + 2) * 16
-                                                    + 4 * g) =
-                            relu_bf16(acc[t][0], __uint_as_float(top[t] & line2[i]));
-                }
-                wave_sync();
-                strip2d_kept(R.h1, kept, at1);
-                kept = strip2d_keep<16>(R.h2, at2);
-                strip2d_tops(top, x - 3, L, lane);
-                float part_z[4];   // lane group's share of each tile's 1x1 layer
-                {
-                    f32x4 acc[4][2];
-                    strip2d_conv<16>(acc, w3, b3, R.h2, xo3);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        float z = 0.0f;
-#pragma unroll
-                        for (int mt = 0; mt < 2; ++mt) {
-                            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                            const u32x2 h = __builtin_bit_cast(
-                                u32x2, relu_bf16(acc[t][mt], __uint_as_float(top[t] & line3)));
-#pragma unroll
-                            for (int e = 0; e < 2; ++e) {   // a bfloat16 is a float's upper half
-                                z = fmaf(w4[mt][2 * e], __uint_as_float(h[e] << 16), z);
-                                z = fmaf(w4[mt][2 * e + 1], __uint_as_float(h[e] & 0xFFFF0000u), z);
-                            }
-                        }
-                        part_z[t] = z;
-                    }
-                }
-                wave_sync();
-                strip2d_kept(R.h2, kept, at2);
-                const float z = b4 + tile_sums(part_z);
+                const float z = net.step(R, band, x, L, lane);
                 const int p = x - kC2Halo + lane;   // column lane % 16 of tile lane / 16
                 if (p >= p0 && p < p1) {
                     const uint64_t key = strip_key(z, p, half, L);
@@ -427,6 +496,72 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStrip
         }
         if (unit < n_units && part == 0 && lane == 0)
             a.cand[(int64_t)f * (2 * S) + 2 * st + half] = strip_point(best, horizontal, pos, half, L);
+    }
+}
+
+// Logits of positions 8 .. 119 of rendered windows [n][8][128][3]: a window is a
+// strip of two steps from position 5 on (the halo of 3 before the first logit);
+// the rows that the first step finds in place of its predecessor's feed only
+// positions before.  A wave takes a contiguous share of the windows (those of
+// one strip have one orientation), two waves a workgroup; the next step's pixels
+// are loaded while a step's layers run.  The sums run as the training kernel's:
+// K from zero, then the bias.
+//
+// Bound by the chain of layers within a step: a wave has few windows.  Measured,
+// 3,584 windows (a call): 57 us with the weights loaded and every byte encoded
+// alone per window, 28.8 us by workgroups of 32 positions a wave, 22.5 us so.
+__global__ __launch_bounds__(kC2WindowBlock, 2) void k_cnn2d_windows(const uint8_t *model,
+                                                                     const uint8_t *win,
+                                                                     const int32_t *geom,
+                                                                     const int32_t *range,
+                                                                     float *z_out, int n_windows)
+{
+    extern __shared__ __align__(16) uint8_t strip_smem[];
+    const int lane = threadIdx.x & 63;
+    const int wv = uniform_int(threadIdx.x >> 6);
+    constexpr int kPerBlock = kC2WindowBlock / 64;
+    constexpr int kFirst = kTrainHalo - kC2Halo;   // first input position
+    const int64_t wave = (int64_t)blockIdx.x * kPerBlock + wv, waves = gridDim.x * kPerBlock;
+    const int w_begin = (int)(wave * n_windows / waves);
+    const int w_end = (int)((wave + 1) * n_windows / waves);
+    Strip2dRows &R = reinterpret_cast<Strip2dRows *>(strip_smem)[wv];
+    strip2d_clear(R, lane);
+    uint32_t px[8];
+    auto fetch = [&](int wi, int x) {
+        StripWalk k;
+        k.frame = win + (int64_t)wi * (8 * kC2Win * 3);
+        k.along = 3;
+        k.across = 3 * kC2Win;
+        k.first = 0;
+        k.L = kC2Win;
+        k.lines = 8;
+        k.packed = k.last_row = false;   // an eighth line follows the band's seven
+        strip_fetch<kC2Band>(px, k, x, lane);
+    };
+    if (w_begin < w_end)
+        fetch(w_begin, kFirst);
+    Strip2dNet<false> net(model, lane);
+    for (int wi = w_begin; wi < w_end; ++wi) {
+        const int32_t *geo = geom + 8 * wi;
+        const bool hz = uniform_int(geo[0]) != 0;
+        const int line = uniform_int(geo[1]), start = uniform_int(geo[2]);
+        const Band band(hz, line, uniform_int(geo[3]), uniform_int(geo[4]), lane);
+        const int lo = uniform_int(min(max(range[2 * wi], 0), kC2Win));
+        const int L = max(uniform_int(min(range[2 * wi + 1], kC2Win)) - lo, 0);
+        net.turn_to(hz, model, lane);
+#pragma unroll 1
+        for (int x = kFirst; x < kC2Win; x += kStep) {
+            wave_sync();
+            band.encode(R.x0, px, net.norm, start + x + lane, x - lo, L, lane);
+            if (x == kFirst)
+                fetch(wi, x + kStep);
+            else if (wi + 1 < w_end)
+                fetch(wi + 1, kFirst);
+            const float z = net.step(R, band, x - lo, L, lane);
+            const int n = x - kC2Halo + lane;
+            if (n >= kTrainHalo && n < kC2Win - kTrainHalo)
+                z_out[(int64_t)wi * kTrainOut + n - kTrainHalo] = z;
+        }
     }
 }
 
@@ -530,159 +665,6 @@ struct WindowInput {
             *reinterpret_cast<bf16x8 *>(dst + 32 * 8 * k) = enc[k];
     }
 };
-
-struct alignas(16) WindowLds {
-    __bf16 x0[kC2Band * kL8];
-    __bf16 h1[5 * kL8];
-    __bf16 h2[3 * kL16];
-    float fb[kC2Floats];
-};
-
-// Logits of positions 8 .. 119 of rendered windows: a workgroup takes a
-// contiguous share of the windows (those of one strip have one orientation,
-// whose weights stay in registers), a wave 32 positions of every layer.  The
-// sums run in the order of the single-line layers: K from zero, then the bias.
-//
-// Bound by the latency of the layers' chains between three barriers; four
-// workgroups of 38 KB share a compute unit.  Measured, 3,584 windows: 58 us
-// with the weights loaded and every byte encoded alone per window, 32 us so (kernel
-// trace).
-__global__ __launch_bounds__(kBlock, 4) void k_cnn2d_windows(const uint8_t *model,
-                                                             const uint8_t *win,
-                                                             const int32_t *geom,
-                                                             const int32_t *range, float *z_out,
-                                                             int n_windows)
-{
-    __shared__ WindowLds G;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = uniform_int(tid >> 6);
-    {
-        uint4 *z = reinterpret_cast<uint4 *>(&G);
-        for (int i = tid; i < (int)(sizeof(WindowLds) / 16); i += kBlock)
-            z[i] = make_uint4(0u, 0u, 0u, 0u);
-        __syncthreads();
-        const float *src = reinterpret_cast<const float *>(model + kC2FloatsOff);
-        if (tid < kC2Floats)
-            G.fb[tid] = src[tid];
-        __syncthreads();
-    }
-    const int w_begin = (int)((int64_t)blockIdx.x * n_windows / gridDim.x);
-    const int w_end = (int)((int64_t)(blockIdx.x + 1) * n_windows / gridDim.x);
-    int cur = -1;
-    Frag<96, 1> w1, w2;
-    Frag<160, 2> w3;
-    WindowInput in;
-    if (w_begin < w_end) {
-        in.fetch(win, w_begin, tid);
-        in.encode(geom + 8 * w_begin, range + 2 * w_begin, G.fb, tid);
-    }
-    for (int wi = w_begin; wi < w_end; ++wi) {
-        const int32_t *geo = geom + 8 * wi;
-        const bool hz = uniform_int(geo[0]) != 0;
-        const int lo = uniform_int(range[2 * wi]), hi = uniform_int(range[2 * wi + 1]);
-        const uint32_t line_ok = band_lines(uniform_int(geo[1]), uniform_int(hz ? geo[4] : geo[3]));
-        if (cur != (int)hz) {
-            cur = (int)hz;
-            const __bf16 *A = reinterpret_cast<const __bf16 *>(model) + (hz ? 0 : kC2Orient);
-            w1 = load_frag<96, 1>(A + kC2A[0]);
-            w2 = load_frag<96, 1>(A + kC2A[1]);
-            w3 = load_frag<160, 2>(A + kC2A[2]);
-        }
-        in.store(G.x0, tid);
-        __syncthreads();
-        if (wi + 1 < w_end)
-            in.fetch(win, wi + 1, tid);
-        const Place L(fresh(lane));
-        const int p0 = 32 * wv + L.col;
-        float tops[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int n = p0 + 16 * t;
-            tops[t] = n >= lo && n < hi ? __builtin_inff() : 0.0f;
-        }
-        int o[3];   // K group k (of 9): da = k / 3, dl = k % 3
-#pragma unroll
-        for (int ks = 0; ks < 3; ++ks)
-            o[ks] = by_group(ks, L.g, [](int k) { return k < 9 ? k / 3 : 0; }) * kL8
-                    + (p0 + by_group(ks, L.g, [](int k) { return k < 9 ? k % 3 : 0; })) * 8;
-        auto biased = [&](const f32x4 &acc, const float *b) {
-            return acc + *reinterpret_cast<const f32x4 *>(b);
-        };
-        // one layer of single output lines from 8-channel lines
-        auto layer8 = [&](const Frag<96, 1> &w, const __bf16 *x, auto epi, int lines) {
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if (i >= lines)
-                    break;
-                f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
-#pragma unroll
-                for (int ks = 0; ks < 3; ++ks)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        acc[t] = mma(w.a[0][ks], frag_at(x + i * kL8 + o[ks] + t * 128), acc[t]);
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-                    epi(i, t, acc[t]);
-            }
-        };
-        layer8(w1, G.x0, [&](int i, int t, const f32x4 &acc) {
-            if (L.g < 2)
-                *reinterpret_cast<bf16x4 *>(G.h1 + i * kL8 + (p0 + 16 * t + 1) * 8 + 4 * L.g) =
-                    relu_bf16(biased(acc, G.fb + kC2FB[0] + 4 * (L.g & 1)),
-                              line_in(line_ok, i + 1) ? tops[t] : 0.0f);
-        }, 5);
-        __syncthreads();
-        layer8(w2, G.h1, [&](int i, int t, const f32x4 &acc) {
-            *reinterpret_cast<bf16x4 *>(G.h2 + i * kL16 + off16(p0 + 16 * t + 1, 4 * L.g)) =
-                relu_bf16(biased(acc, G.fb + kC2FB[1] + 4 * L.g),
-                          line_in(line_ok, i + 2) ? tops[t] : 0.0f);
-        }, 3);
-        __syncthreads();
-        {
-            f32x4 acc[2][2];
-            acc[0][0] = acc[0][1] = acc[1][0] = acc[1][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int ks = 0; ks < 5; ++ks) {
-                // K group k (of 18; two more have zero weights): tap k / 2,
-                // half k % 2
-                const __bf16 *x =
-                    G.h2 + by_group(ks, L.g, [](int k) { return k < 18 ? k / 6 : 0; }) * kL16
-                    + off16(p0 + by_group(ks, L.g, [](int k) { return k < 18 ? k / 2 % 3 : 0; }),
-                            8 * (L.g & 1));
-                const bf16x8 x0 = frag_at(x), x1 = frag_at(x + 256);
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt) {
-                    acc[mt][0] = mma(w3.a[mt][ks], x0, acc[mt][0]);
-                    acc[mt][1] = mma(w3.a[mt][ks], x1, acc[mt][1]);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const float top = line_in(line_ok, 3) ? tops[t] : 0.0f;
-                float z = 0.0f;
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt) {
-                    const bf16x4 h =
-                        relu_bf16(biased(acc[mt][t], G.fb + kC2FB[2] + 16 * mt + 4 * L.g), top);
-                    const f32x4 w4 =
-                        *reinterpret_cast<const f32x4 *>(G.fb + kC2FW4 + 16 * mt + 4 * L.g);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        z = fmaf(w4[j], (float)h[j], z);
-                }
-                z += __shfl_xor(z, 16, 64);
-                z += __shfl_xor(z, 32, 64);
-                const int n = p0 + 16 * t;
-                if (L.g == t && n >= kTrainHalo && n < kC2Win - kTrainHalo)
-                    z_out[(int64_t)wi * kTrainOut + n - kTrainHalo] = G.fb[kC2FB4] + z;
-            }
-        }
-        if (wi + 1 < w_end)
-            in.encode(geom + 8 * (wi + 1), range + 2 * (wi + 1), G.fb, tid);
-        // (x0 was last read before the second barrier, h1 before the third;
-        // h2 is written after the next window's second)
-    }
-}
 
 // ------------------------------------------------------------- training --
 //
@@ -1302,9 +1284,10 @@ hipError_t launch_cnn2d_windows(const uint8_t *model, const uint8_t *win, const 
     if (n <= 0)
         return hipSuccess;
     // four resident workgroups on each of 256 compute units
-    const int grid = n < 1024 ? n : 1024;
-    hipLaunchKernelGGL(k_cnn2d_windows, dim3(grid), dim3(kBlock), 0, s, model, win, geom, range,
-                       z, n);
+    constexpr int kPerBlock = kC2WindowBlock / 64;
+    const int want = (n + kPerBlock - 1) / kPerBlock, grid = want < 1024 ? want : 1024;
+    hipLaunchKernelGGL(k_cnn2d_windows, dim3(grid), dim3(kC2WindowBlock),
+                       kPerBlock * sizeof(Strip2dRows), s, model, win, geom, range, z, n);
     return hipGetLastError();
 }
 
