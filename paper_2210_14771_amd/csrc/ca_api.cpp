@@ -467,6 +467,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
     se.P = pl->P;
     se.groups = groups;
     se.n_frames = n;
+    se.add_reason = keep ? CA_REASON_FALLBACK : 0;
 
     hipEvent_t *ev = nullptr;
     if (timed && ctx->prof_used < ctx->prof_capacity)
@@ -600,10 +601,9 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
 }
 
 // One call: the learned scorer's pipeline, then, with a fallback fraction,
-// the handcrafted pipeline into the plan's second result array and a
-// per-frame choice between the two.  The handcrafted kernels skip the frames
-// whose learned result stands (the same rule as the choice), so that pass
-// costs in proportion to the frames that fall back.
+// the handcrafted pipeline over the frames whose learned result does not stand
+// (its kernels skip the others, so that pass costs in proportion to the frames
+// that fall back); its results take the learned ones' place.
 int enqueue(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const ca_params &p,
             ca_point *points_out, ca_attempt *attempts_out, ca_result *out, hipStream_t s,
             bool timed)
@@ -614,13 +614,8 @@ int enqueue(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const ca_pa
     ca_params h = p;
     h.scorer = CA_SCORER_HANDCRAFTED;
     h.fallback_inlier_frac = 0.0f;
-    rc = enqueue_one(ctx, pl, frames, n, h, nullptr, nullptr, pl->res2, s, false, out,
-                     p.fallback_inlier_frac);
-    if (rc != CA_OK)
-        return rc;
-    return ca::launch_fallback(out, pl->res2, n, p.fallback_inlier_frac, s) == hipSuccess
-               ? CA_OK
-               : CA_E_DEVICE;
+    return enqueue_one(ctx, pl, frames, n, h, nullptr, nullptr, out, s, false, out,
+                       p.fallback_inlier_frac);
 }
 
 int run(ca_ctx *ctx, const uint8_t *frames, const ca_frame_desc *dims, int32_t n,

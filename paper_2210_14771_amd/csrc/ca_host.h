@@ -34,7 +34,7 @@ struct Plan {
     ca_point *cand = nullptr;
     Record *rec = nullptr;
     uint32_t *ctl = nullptr;    // fused-kernel control words (zero between calls)
-    ca_result *res2 = nullptr;  // handcrafted results of a learned call with fallback
+    ca_result *res2 = nullptr;  // results of the calls that autotune times
     int32_t *flist = nullptr;   // frame indices grouped by frame shape
     struct ShapeClass {
         int32_t W, H, first, count;
@@ -132,7 +132,7 @@ int strip_positions(int32_t extent, int32_t n, double alpha, int32_t *pos);
 // Byte layout of a plan's device block.  Its first image_bytes bytes
 // (frame descriptors, strip tables, score tables, frame list grouped by
 // shape, zeroed control words) are built on the host and uploaded with one
-// copy; candidates, attempt-group records and fallback results follow and
+// copy; candidates, attempt-group records and a result array follow and
 // are written by the kernels only.
 struct PlanLayout {
     size_t o_fd = 0, o_strips = 0, o_lut = 0, o_flist = 0, o_ctl = 0, image_bytes = 0;

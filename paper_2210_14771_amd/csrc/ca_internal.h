@@ -70,7 +70,7 @@ struct StripArgs {
     int32_t spread = 0;         // how items are dealt to the workgroups (StripSpread)
     // With keep set (the handcrafted pass of the learned scorer's fallback),
     // frames whose learned result keep[f] stands under the fallback rule at
-    // keep_frac are skipped: their handcrafted result is never used.
+    // keep_frac are skipped; the others' results take its place.
     const ca_result *keep = nullptr;
     float keep_frac = 0.0f;
 };
@@ -103,6 +103,7 @@ struct SelectArgs {
     int32_t P;
     int32_t groups;
     int32_t n_frames;
+    int32_t add_reason = 0; // CA_REASON_FALLBACK in the fallback's handcrafted pass
 };
 
 // Control words of the fused kernel (zero between calls; the kernel restores
@@ -139,10 +140,6 @@ hipError_t launch_fused(const FusedArgs &a, int grid, size_t lds_bytes, hipStrea
 // filtered circle (cx, cy, r, weight); filt[i] = the state after frame i.
 hipError_t launch_stream_update(const ca_result *res, const int4 *runs, int n_runs, float4 *state,
                                 float4 *filt, float decay, hipStream_t s);
-// out[f] = fallback[f] (reason + CA_REASON_FALLBACK) where out[f] has fewer
-// than 3 points or inliers < frac * n_points.
-hipError_t launch_fallback(ca_result *out, const ca_result *fallback, int n, float frac,
-                           hipStream_t s);
 hipError_t fused_occupancy(size_t lds_bytes, int *blocks_per_cu);
 
 // Serving: the frame copies of one step into ring slots, in one launch.

@@ -1139,6 +1139,7 @@ __device__ void select_frame(const SelectArgs &a, int f)
         o.valid = (double)qsum >= a.threshold ? 1 : 0;
         o.reason = o.valid ? 0 : 3;
     }
+    o.reason += a.add_reason;
     a.out[f] = o;
 }
 
@@ -1170,8 +1171,10 @@ __device__ void load_tables(const StripArgs &a, uint8_t *smem, int nthreads = kB
 
 // The fallback rule of the learned scorer: a frame keeps its learned result
 // unless its best circle explains fewer than `frac` of its kept points, or
-// fewer than three points were kept.  k_fallback applies it; the handcrafted
-// pass before it skips the frames it keeps, by the same expression.
+// fewer than three points were kept.  The handcrafted pass skips the frames that
+// it keeps and writes the others' results in their place: a frame's last attempt
+// group, which does so, ends after all of them have read the learned result.
+// (A choice by a kernel of its own cost a launch, 2 us of a call.)
 __device__ __forceinline__ bool learned_kept(const ca_result &r, float frac)
 {
     return !(r.n_points < 3 || (float)r.inliers < frac * (float)r.n_points);
@@ -1412,21 +1415,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_fused(FusedArgs a)
     }
 }
 
-// Learned-scorer fallback: a frame whose best circle explains less than
-// `frac` of its kept points takes the handcrafted pipeline's result.
-__global__ __launch_bounds__(kBlock) void k_fallback(ca_result *out, const ca_result *fb, int n,
-                                                     float frac)
-{
-    const int f = blockIdx.x * kBlock + threadIdx.x;
-    if (f >= n)
-        return;
-    if (!learned_kept(out[f], frac)) {
-        ca_result b = fb[f];
-        b.reason += CA_REASON_FALLBACK;
-        out[f] = b;
-    }
-}
-
 // Temporal filter of the serving loop: w' = decay w + q, c' = (decay w c +
 // q c_frame) / w' for a valid result of score q; w' = decay w otherwise.
 __global__ __launch_bounds__(kBlock) void k_stream_update(const ca_result *res, const int4 *runs,
@@ -1520,16 +1508,6 @@ hipError_t launch_fused(const FusedArgs &a, int grid, size_t lds_bytes, hipStrea
     if (a.se.n_frames <= 0)
         return hipSuccess;
     launch_maybe_timed(k_fused, dim3(grid), dim3(kBlock), lds_bytes, s, start, stop, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_fallback(ca_result *out, const ca_result *fallback, int n, float frac,
-                           hipStream_t s)
-{
-    if (n <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_fallback, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, out,
-                       fallback, n, frac);
     return hipGetLastError();
 }
 
