@@ -122,13 +122,17 @@ struct Entry {                          // one frame from copy to retirement
 
 struct Batch {                          // one in-flight slot
     cahost::Plan plan;                  // buffers for max_batch frames, one device block
-    ca_result *res_dev = nullptr;       // [max_batch]
-    float4 *filt_dev = nullptr;         // [max_batch]
-    int4 *runs_dev = nullptr;           // [max_batch]
-    uint8_t *stage = nullptr;           // pinned: descriptors, then strip tables
+    // one upload: the runs and the launch order, ending at the plan's block, then
+    // the descriptors and the strip tables, with which that block begins
+    uint8_t *up_dev = nullptr;
+    uint8_t *up_host = nullptr;         // pinned, laid out alike
+    uint8_t *stage = nullptr;           // the plan's block in up_host
+    int4 *runs_dev = nullptr;           // of the current batch
     int4 *runs_host = nullptr;
+    // one download: the batch's results, then its filtered circles
+    ca_result *res_dev = nullptr;       // [max_batch], with room for as many float4
     ca_result *res_host = nullptr;
-    float4 *filt_host = nullptr;
+    float4 *filt_host = nullptr;        // of the current batch
     hipEvent_t done = nullptr;
     std::vector<Entry> entries;
     int64_t t_launch = 0;
@@ -153,6 +157,7 @@ struct ca_server {
     std::deque<size_t> inflight;        // batch slots in launch order
     std::deque<ca_served> done;         // served, not yet returned
     cahost::PlanLayout layout;          // of every slot's block (max_batch frames)
+    size_t runs_bytes = 0;              // before it: room for max_batch runs and the order
     std::map<int32_t, int32_t> fused_grid;  // per LDS line pitch (fused schedule only)
     int64_t n_submitted = 0, n_served = 0, n_batches = 0;
 };
@@ -168,14 +173,10 @@ void free_batch(Batch &b)
 {
     if (b.done)
         (void)hipEventDestroy(b.done);
-    (void)hipFree(b.plan.mem);
+    (void)hipFree(b.up_dev);
     (void)hipFree(b.res_dev);
-    (void)hipFree(b.filt_dev);
-    (void)hipFree(b.runs_dev);
-    (void)hipHostFree(b.stage);
-    (void)hipHostFree(b.runs_host);
+    (void)hipHostFree(b.up_host);
     (void)hipHostFree(b.res_host);
-    (void)hipHostFree(b.filt_host);
 }
 
 // The launch facts of a batch: its frames' descriptors and the strip tables
@@ -412,31 +413,35 @@ int launch(ca_server *s)
             return x.st->state != y.st->state ? x.st->state < y.st->state : x.seq < y.seq;
         });
         int32_t n_runs = 0;
-        for (size_t i = 0; i < n; ++i) {
+        for (size_t i = 0; i < n; ++i)
+            n_runs += i == 0 || b.entries[i - 1].st != b.entries[i].st;
+        const size_t head = cahost::align_up(
+            (size_t)n_runs * sizeof(int4) + n * sizeof(int32_t), sizeof(int4));
+        b.runs_host = reinterpret_cast<int4 *>(b.stage - head);
+        b.runs_dev = reinterpret_cast<int4 *>(static_cast<uint8_t *>(b.plan.mem) - head);
+        for (size_t i = 0, r = 0; i < n; ++i) {
             const Entry &e = b.entries[i];
             if (i == 0 || b.entries[i - 1].st != e.st)
-                b.runs_host[n_runs++] = make_int4(e.st->state, (int)i, (int)i + 1, 0);
+                b.runs_host[r++] = make_int4(e.st->state, (int)i, (int)i + 1, 0);
             else
-                b.runs_host[n_runs - 1].z = (int)i + 1;
+                b.runs_host[r - 1].z = (int)i + 1;
         }
         const size_t upload = stage_batch(s, b, n, n_runs);
         // the batch's frames were copied earlier on the same stream
         const hipStream_t cs = s->compute;
-        if (hipMemcpyAsync(b.plan.mem, b.stage, upload, hipMemcpyHostToDevice, cs) != hipSuccess
-            || hipMemcpyAsync(b.runs_dev, b.runs_host,
-                              (size_t)n_runs * sizeof(int4) + n * sizeof(int32_t),
-                              hipMemcpyHostToDevice, cs) != hipSuccess)
+        if (hipMemcpyAsync(b.runs_dev, b.runs_host, head + upload, hipMemcpyHostToDevice, cs)
+            != hipSuccess)
             return CA_E_DEVICE;
         int rc = cahost::enqueue(s->ctx, &b.plan, s->arena_mem, (int32_t)n, s->cfg.params, nullptr,
                                  nullptr, b.res_dev, cs, false);
         if (rc != CA_OK)
             return rc;
-        if (ca::launch_stream_update(b.res_dev, b.runs_dev, n_runs, s->state_dev, b.filt_dev,
+        float4 *filt = reinterpret_cast<float4 *>(b.res_dev + n);
+        b.filt_host = reinterpret_cast<float4 *>(b.res_host + n);
+        if (ca::launch_stream_update(b.res_dev, b.runs_dev, n_runs, s->state_dev, filt,
                                      s->cfg.smooth, cs) != hipSuccess
-            || hipMemcpyAsync(b.res_host, b.res_dev, n * sizeof(ca_result), hipMemcpyDeviceToHost,
-                              cs) != hipSuccess
-            || hipMemcpyAsync(b.filt_host, b.filt_dev, n * sizeof(float4), hipMemcpyDeviceToHost,
-                              cs) != hipSuccess
+            || hipMemcpyAsync(b.res_host, b.res_dev, n * (sizeof(ca_result) + sizeof(float4)),
+                              hipMemcpyDeviceToHost, cs) != hipSuccess
             || hipEventRecord(b.done, cs) != hipSuccess)
             return CA_E_DEVICE;
         b.t_launch = now_ns();
@@ -518,22 +523,25 @@ int ca_server_create(ca_ctx *ctx, const ca_server_config *cfg, ca_server **out)
     }
     s->batches.resize(ok ? (size_t)cfg->max_inflight : 0);
     const size_t stage_bytes = s->layout.image_bytes;
+    s->runs_bytes = cahost::align_up(B * (sizeof(int4) + sizeof(int32_t)), 256);
     for (Batch &b : s->batches) {
         b.plan.P = proto.P;
         b.plan.groups = proto.groups;
         b.plan.sg_len = proto.sg_len;
         b.plan.dynamic = true;
-        ok = ok && hipMalloc(&b.plan.mem, s->layout.total) == hipSuccess
-             && hipMemcpy(b.plan.mem, image.data(), image.size(), hipMemcpyHostToDevice)
-                    == hipSuccess
-             && hipMalloc(&b.res_dev, B * sizeof(ca_result)) == hipSuccess
-             && hipMalloc(&b.filt_dev, B * sizeof(float4)) == hipSuccess
-             && hipMalloc(&b.runs_dev, B * (sizeof(int4) + sizeof(int32_t))) == hipSuccess
-             && hipHostMalloc(&b.stage, stage_bytes) == hipSuccess
-             && hipHostMalloc(&b.runs_host, B * (sizeof(int4) + sizeof(int32_t))) == hipSuccess
-             && hipHostMalloc(&b.res_host, B * sizeof(ca_result)) == hipSuccess
-             && hipHostMalloc(&b.filt_host, B * sizeof(float4)) == hipSuccess
+        constexpr size_t kOut = sizeof(ca_result) + sizeof(float4);
+        ok = ok && hipMalloc(&b.up_dev, s->runs_bytes + s->layout.total) == hipSuccess
+             && hipMalloc(&b.res_dev, B * kOut) == hipSuccess
+             && hipHostMalloc(&b.up_host, s->runs_bytes + stage_bytes) == hipSuccess
+             && hipHostMalloc(&b.res_host, B * kOut) == hipSuccess
              && hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess;
+        if (ok) {
+            b.plan.mem = b.up_dev + s->runs_bytes;
+            b.stage = b.up_host + s->runs_bytes;
+        }
+        ok = ok
+             && hipMemcpy(b.plan.mem, image.data(), image.size(), hipMemcpyHostToDevice)
+                    == hipSuccess;
         if (ok)
             cahost::plan_pointers(&b.plan, b.plan.mem, s->layout);
     }
