@@ -63,8 +63,8 @@ hipError_t launch_cnn_grad(const CnnTrainArgs &a, int grid, hipStream_t s);
 // Sum `grid` partials, then (file order) grad_out[i] and loss_out[0].
 hipError_t launch_cnn_reduce(const float *partial, int grid, float *grad_out, float *loss_out,
                              hipStream_t s);
-// SGD with momentum on the float32 master weights (file order), then repack
-// the device model block.
+// SGD with momentum on the float32 master weights (file order) and on their
+// copies in the (packed) device model block.
 hipError_t launch_cnn_update(float *master, float *momentum, const float *grad, float lr,
                              float mom, uint8_t *model, hipStream_t s);
 // Repack the device model block from master weights.

@@ -1060,15 +1060,40 @@ __global__ __launch_bounds__(kReduceThreads) void k_cnn_reduce(const float *part
 }
 
 // SGD with momentum: m = mu m + g, p -= lr m.
-__global__ __launch_bounds__(kBlock) void k_cnn_sgd(float *master, float *mom, const float *grad,
-                                                    float lr, float mu)
+// SGD with momentum on the master weights (file order), each weight's copies in
+// the device model block with it (k_cnn_pack's layout; the padding stays): a
+// repack of its own cost a launch, 1.8 us of a step.
+__global__ __launch_bounds__(kBlock) void k_cnn_update(float *master, float *mom,
+                                                       const float *grad, float lr, float mu,
+                                                       uint8_t *model)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= kCnnParams)
         return;
     const float m = mu * mom[i] + grad[i];
     mom[i] = m;
-    master[i] -= lr * m;
+    const float v = master[i] - lr * m;
+    master[i] = v;
+    __bf16 *w = reinterpret_cast<__bf16 *>(model);
+    float *fb = reinterpret_cast<float *>(model + kCnnFloatsOff);
+    __bf16 *wf = reinterpret_cast<__bf16 *>(model + kCnnFlipOff);
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        const FileLayer L = file_layer(l);
+        const int r = i - L.fw;
+        if (r >= 0 && r < L.cout * L.cin * 5) {
+            const int t = r % 5, c = r / 5 % L.cin, o = r / 5 / L.cin;
+            w[L.woff + o * L.kp + t * L.cin + c] = to_bf16(v);
+            if (l > 0)
+                wf[kCnnFOff[l - 1] + c * (l == 3 ? 96 : 160) + (4 - t) * L.cout + o] = to_bf16(v);
+        }
+        if (i >= L.fb && i < L.fb + L.cout)
+            fb[kCnnBOff[l] + i - L.fb] = v;
+    }
+    if (i >= kFileW5 && i < kFileW5 + 16)
+        fb[kCnnW5Off + i - kFileW5] = (float)to_bf16(v);
+    if (i == kFileB5)
+        fb[kCnnW5Off + 16] = v;
 }
 
 // Device model block from float32 master weights: every slot (padding
@@ -1193,12 +1218,9 @@ hipError_t launch_cnn_reduce(const float *partial, int grid, float *grad_out, fl
 hipError_t launch_cnn_update(float *master, float *momentum, const float *grad, float lr,
                              float mom, uint8_t *model, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cnn_sgd, dim3((kCnnParams + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                       master, momentum, grad, lr, mom);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    return launch_cnn_pack(master, model, s);
+    hipLaunchKernelGGL(k_cnn_update, dim3((kCnnParams + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+                       master, momentum, grad, lr, mom, model);
+    return hipGetLastError();
 }
 
 hipError_t launch_cnn_pack(const float *master, uint8_t *model, hipStream_t s)

@@ -1168,15 +1168,53 @@ __global__ __launch_bounds__(kReduceThreads) void k_cnn2d_reduce(const float *pa
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_cnn2d_sgd(float *master, float *mom, const float *grad,
-                                                      float lr, float mu)
+// SGD with momentum on the master weights (file order), each weight's copies in
+// the device model block with it (k_cnn2d_pack's layout; the padding stays): a
+// repack of its own cost a launch, 1.6 us of a step.
+__global__ __launch_bounds__(kBlock) void k_cnn2d_update(float *master, float *mom,
+                                                         const float *grad, float lr, float mu,
+                                                         uint8_t *model)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= kC2Params)
         return;
     const float m = mu * mom[i] + grad[i];
     mom[i] = m;
-    master[i] -= lr * m;
+    const float v = master[i] - lr * m;
+    master[i] = v;
+    const __bf16 h = to_bf16(v);
+    float *fb = reinterpret_cast<float *>(model + kC2FloatsOff);
+    constexpr int cin[3] = {5, 8, 16}, cout[3] = {8, 16, 32}, cp[3] = {8, 8, 16};
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const int r = i - kC2FileW[l];
+        if (r >= 0 && r < cout[l] * cin[l] * 9) {
+            const int dx = r % 3, dy = r / 3 % 3, c = r / 9 % cin[l], o = r / 9 / cin[l];
+#pragma unroll
+            for (int orient = 0; orient < 2; ++orient) {
+                __bf16 *w = reinterpret_cast<__bf16 *>(model) + orient * kC2Orient;
+                const int da = orient == 0 ? dy : dx, dl = orient == 0 ? dx : dy;
+                w[kC2A[l] + o * kC2KP[l] + (3 * da + dl) * cp[l] + c] = h;
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) {   // the lines of a pair
+                    if (l == 0)
+                        w[kC2P1 + (8 * sl + o) * 96 + (3 * (da + sl) + dl) * 8 + c] = h;
+                    if (l == 1)
+                        w[kC2F2 + (8 * sl + c) * 192 + (3 * (2 - da + sl) + 2 - dl) * 16 + o] = h;
+                }
+                if (l == 2)
+                    w[kC2F3 + c * 288 + (3 * (2 - da) + 2 - dl) * 32 + o] = h;
+            }
+        }
+        if (i >= kC2FileB[l] && i < kC2FileB[l] + cout[l])
+            fb[kC2FB[l] + i - kC2FileB[l]] = v;
+    }
+    if (i >= kC2FileW4 && i < kC2FileW4 + 32)
+        fb[kC2FW4 + i - kC2FileW4] = (float)h;
+    if (i == kC2FileB4)
+        fb[kC2FB4] = v;
+    if (i < 6)   // the colours' means and inverse deviations
+        fb[kC2FMean + i] = v;
 }
 
 // Device model block from the float32 master weights (file order); every
@@ -1322,12 +1360,9 @@ hipError_t launch_cnn2d_reduce(const float *partial, int grid, float *grad_out, 
 hipError_t launch_cnn2d_update(float *master, float *momentum, const float *grad, float lr,
                                float mom, uint8_t *model, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cnn2d_sgd, dim3((kC2Params + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                       master, momentum, grad, lr, mom);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    return launch_cnn2d_pack(master, model, s);
+    hipLaunchKernelGGL(k_cnn2d_update, dim3((kC2Params + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+                       master, momentum, grad, lr, mom, model);
+    return hipGetLastError();
 }
 
 hipError_t launch_cnn2d_pack(const float *master, uint8_t *model, hipStream_t s)
