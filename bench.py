@@ -4,7 +4,7 @@ One step = one call of the whole hot path (strip scoring, candidate
 selection, RANSAC with refits, best-circle selection) on a batch of 64
 synthetic 1920x1080 RGB frames already resident in HBM.  The timed steps
 replay captured HIP graphs with six batches in flight (six contexts on
-six HIP streams taking turns, so one batch's FP64 RANSAC overlaps other
+six HIP streams taking turns, so one batch's RANSAC (ALU) overlaps other
 batches' strip loads, and the strip loads of several batches together keep
 more DRAM pages busy); the same steps with one batch in flight, and eager
 calls, are reported beside.  Prints one JSON
@@ -118,10 +118,12 @@ def ransac_flops(n_points, attempts: int, refine: int) -> float:
 
 
 def ransac_issued_flops(n_points, attempts: int, refine: int) -> float:
-    """FP64 operations the kernel issues for the same passes: per point and
+    """FP64 operations of the same passes on the vector units: per point and
     refit pass the squared distance (5) and 9 moment FMAs accumulating the
     integer sums exactly in float64 (18), masked rather than branched; per
-    point in the final pass the distance and 2 FMAs (9)."""
+    point in the final pass the distance and 2 FMAs (9).  The kernel does this
+    work on the matrix units (float32 products that decide all but the close
+    points, exact sums of 8-bit digits)."""
     return float(sum(attempts * n * (refine * 23 + 9) for n in n_points if n >= 3))
 
 
@@ -623,7 +625,7 @@ def main():
     # timed region: the same K calls replayed from captured HIP graphs (G
     # calls per graph, one graph per resident batch per context).  With
     # several batches in flight, each context (its own plan buffers, output
-    # and HIP stream) takes the graphs in turn, so one batch's RANSAC (FP64
+    # and HIP stream) takes the graphs in turn, so one batch's RANSAC (
     # ALU) overlaps the next one's strip loads (HBM); every batch still runs
     # the whole path.
     n_inflight = contexts_in_flight(K, args.inflight, args.graph_calls)
@@ -726,9 +728,10 @@ def main():
                  "flops_note": "the method's FP64 work: one squared distance (5 flops) per "
                                "attempt, point and pass (3 refits + final count); band compares "
                                "and integer moment sums not counted",
-                 "issued_tflops": issued / (ransac_ms * 1e-3) / 1e12,
-                 "issued_note": "FP64 operations the kernel issues (23 per point and refit "
-                                "pass, 9 per point in the final pass)"}
+                 "vector_equivalent_tflops": issued / (ransac_ms * 1e-3) / 1e12,
+                 "vector_equivalent_note": "FP64 operations of the passes on the vector units "
+                                           "(23 per point and refit pass, 9 in the final one); "
+                                           "the kernel takes the matrix units instead"}
     rl_ransac["frac"] = rl_ransac["achieved"] / rl_ransac["peak"]
     roofline = dict(rl_ransac if dominant == "ransac" else rl_strips)
     roofline["kernel"] = {"fused": "k_fused", "strips": skern, "ransac": "k_ransac"}[dominant]
