@@ -625,9 +625,9 @@ def main():
     # timed region: the same K calls replayed from captured HIP graphs (G
     # calls per graph, one graph per resident batch per context).  With
     # several batches in flight, each context (its own plan buffers, output
-    # and HIP stream) takes the graphs in turn, so one batch's RANSAC (
-    # ALU) overlaps the next one's strip loads (HBM); every batch still runs
-    # the whole path.
+    # and HIP stream) takes the graphs in turn, so one batch's RANSAC (ALU)
+    # overlaps the next one's strip loads (HBM); every batch still runs the
+    # whole path.
     n_inflight = contexts_in_flight(K, args.inflight, args.graph_calls)
     G = graph_calls(K, args.graph_calls, n_inflight)
     extra = [make_estimator()[0] for _ in range(n_inflight - 1)]
