@@ -504,6 +504,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
     // tev (timed calls): the strip kernel between tev[0] and tev[1], RANSAC
     // between tev[2] and tev[3], each pair taken by the dispatch itself (the
     // per-shape strip launches of a mixed batch between two marker events)
+    const bool mixed = pl->dynamic ? pl->spread != ca::kSpreadSlices : pl->classes.size() > 1;
     auto launch_range = [&](int32_t f0, int32_t f1, hipStream_t st, hipEvent_t *tev) {
         hipEvent_t s0 = tev ? tev[0] : nullptr, s1 = tev ? tev[1] : nullptr;
         hipEvent_t r0 = tev ? tev[2] : nullptr, r1 = tev ? tev[3] : nullptr;
@@ -526,6 +527,8 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
             c.n_items = a2.n_items;
             c.per_xcd = a2.per_xcd;
             c.frame0 = f0;
+            c.longest = pl->line_pitch;
+            c.mixed = mixed ? 1 : 0;
             // its LDS fills a compute unit
             c.resident_per_xcd = std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8);
             ok = ca::launch_cnn2d_strips(c, st, s0, s1) == hipSuccess;
@@ -541,6 +544,8 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
             c.n_items = a2.n_items;
             c.per_xcd = a2.per_xcd;
             c.frame0 = f0;
+            c.longest = pl->line_pitch;
+            c.mixed = mixed ? 1 : 0;
             if (ctx->cnn_groups_per_xcd == 0)
                 ctx->cnn_groups_per_xcd =
                     std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8 * ca::cnn_strips_blocks_per_cu());

@@ -45,6 +45,8 @@ struct CnnStripArgs {
     int32_t n_items;
     int32_t per_xcd;
     int32_t frame0;
+    int32_t longest;          // longest side of the frames
+    int32_t mixed;            // the frames differ in shape
     int32_t parts;            // waves that share a half strip (set by the launch)
 };
 
@@ -127,6 +129,8 @@ struct Cnn2dStripArgs {
     int32_t per_xcd;
     int32_t frame0;
     int32_t resident_per_xcd;   // workgroups that an XCD holds at once
+    int32_t longest;            // longest side of the frames
+    int32_t mixed;              // the frames differ in shape
     int32_t parts;              // waves that share a half strip (set by the launch)
 };
 

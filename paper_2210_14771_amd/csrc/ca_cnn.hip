@@ -63,8 +63,7 @@ __global__ __launch_bounds__(kBlock) void k_mfma_probe(float *out)
 //
 // All weights stay in registers (230 with the rest), so two waves share a SIMD
 // and eight a workgroup's LDS.  With few half strips the waves of a workgroup
-// share them (the launch chooses 1, 2, 4 or 8 a half strip, as many as keep
-// every wave resident): a lone frame's are scored by 8 times 128 waves.
+// share them (the launch chooses 1, 2, 4 or 8 a half strip: strip_split): a lone frame's are scored by 8 times 128 waves.
 //
 // Bound by the chain of layers within a step (LDS round trips that two waves
 // cover in part) beside about 340 vector instructions and 104 MFMAs a step.
@@ -1196,7 +1195,8 @@ hipError_t launch_cnn_strips(const CnnStripArgs &args, int resident_per_xcd, hip
     if (args.n_items <= 0)
         return hipSuccess;
     CnnStripArgs a = args;
-    const int groups = strip_split(a.parts, 2 * a.per_xcd, resident_per_xcd);
+    const int groups = strip_split(a.parts, 2 * a.per_xcd, resident_per_xcd, a.longest,
+                                   a.mixed != 0, kCnnHalo);
     launch_maybe_timed(k_cnn_strips, dim3(8 * groups), dim3(64 * kStripWaves), kStripWaves * sizeof(StripRows), s, start, stop, a);
     return hipGetLastError();
 }

@@ -1310,7 +1310,8 @@ hipError_t launch_cnn2d_strips(const Cnn2dStripArgs &a, hipStream_t s, hipEvent_
     if (a.n_items <= 0)
         return hipSuccess;
     Cnn2dStripArgs b = a;
-    const int groups = strip_split(b.parts, 2 * a.per_xcd, a.resident_per_xcd);
+    const int groups = strip_split(b.parts, 2 * a.per_xcd, a.resident_per_xcd, a.longest,
+                                   a.mixed != 0, kC2Halo);
     launch_maybe_timed(k_cnn2d_strips, dim3(8 * groups), dim3(64 * kStripWaves),
                        kStripWaves * sizeof(Strip2dRows), s, start, stop, b);
     return hipGetLastError();

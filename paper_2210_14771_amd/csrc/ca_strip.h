@@ -116,18 +116,29 @@ __device__ __forceinline__ ca_point strip_point(uint64_t key, bool horizontal, i
     return pt;
 }
 
-// Waves that share a half strip and workgroups per XCD, for `units` half
-// strips and at most `resident` workgroups an XCD: as many waves to a half
-// strip as stay resident at once, since a wave alone on a half strip of full
-// HD takes 16 steps of some 3 us.
-inline int strip_split(int32_t &parts, int units, int resident)
+// Waves that share a half strip and workgroups per XCD, for `units` half strips
+// an XCD of frames of at most `longest` pixels a side, at most `resident`
+// workgroups an XCD and a halo of `halo` positions: the split with the fewest
+// steps until the last wave ends.  Frames of one shape are taken by resident
+// workgroups in turns; of several shapes (mixed) each workgroup takes one turn
+// and the dispatch evens out their lengths, for about a step's time of loading
+// weights.  A wave alone on a half strip of full HD takes 16 steps of some 3 us.
+inline int strip_split(int32_t &parts, int units, int resident, int longest, bool mixed, int halo)
 {
-    parts = 1;
-    while (2 * parts <= kStripWaves && units * 2 * parts <= resident * kStripWaves)
-        parts *= 2;
+    int64_t best = 0;
+    for (int32_t p = 1; p <= kStripWaves; p *= 2) {
+        const int64_t slots = (int64_t)resident * kStripWaves;
+        const int64_t turns = ((int64_t)units * p + slots - 1) / slots;
+        const int64_t steps = (((longest + 1) / 2 + p - 1) / p + 2 * halo + kStep - 1) / kStep;
+        const int64_t cost = turns * (steps + (mixed ? 1 : 0));
+        if (p == 1 || cost < best) {
+            best = cost;
+            parts = p;
+        }
+    }
     const int sets = kStripWaves / parts;
     const int groups = (units + sets - 1) / sets;
-    return groups < resident ? groups : resident;
+    return mixed || groups < resident ? groups : resident;
 }
 
 }  // namespace ca

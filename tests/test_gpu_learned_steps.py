@@ -1,7 +1,8 @@
 """Learned candidates at the edges of a wave's steps: half strips shorter than a
 step, of one step (64 positions less the halo's 16, or 6 of the 2-D network), of
-one position more and of several, alone (a half strip shared by several waves) and in batches
-that leave a half strip to four waves, to two and to one."""
+one position more and of several, alone (a half strip shared by several waves),
+in batches that leave fewer waves to a half strip, and among frames of other
+shapes."""
 import numpy as np
 import pytest
 
@@ -63,3 +64,14 @@ def test_candidates_at_step_edges(torch_dev, w, h, scorer):
                     assert abs(float(alone[c]["score"]) - sc[at[0]]) <= tol
             for f in range(n):
                 assert np.array_equal(g[f], alone), (name, n, f)
+    # every third of a batch of several shapes
+    other = [torch.from_numpy(rng.integers(0, 256, (hh, ww, 3), dtype=np.uint8)).cuda()
+             for ww, hh in ((64, 48), (640, 480))]
+    for n in (3, 39, 240):
+        say(f"learned steps, scorer {scorer}, {w}x{h} mixed x {n}")
+        batch = [views["crop"] if f % 3 == 1 else other[f % 3 // 2] for f in range(n)]
+        _, pts = est.debug_candidates(batch, p, list(range(n)))
+        torch.cuda.synchronize()
+        g = api.points_numpy(pts)
+        for f in range(1, n, 3):
+            assert np.array_equal(g[f], alone), ("mixed", n, f)
