@@ -636,17 +636,21 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
         __syncthreads();
         if (wi + 1 < w_end)
             fetch(wi + 1);
-        // targets and loss weights of this lane's two positions (weight zero
-        // where a position carries no loss)
+        // targets and loss weights of this lane's two positions; where a position
+        // carries no loss neither counts, nor does its logit (zero times a value
+        // that is not finite is not zero)
         float tgt[2], lw[2], tops[2];
+        bool carries[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int n = 32 * wv + (lane & 15) + 16 * t;
             const bool in = n >= lo && n < hi;
             const bool has = in && n >= kCnnHalo && n < kCnnWin - kCnnHalo;
+            carries[t] = has;
             tops[t] = in ? __builtin_inff() : 0.0f;
             const int64_t j = (int64_t)wi * kCnnOut + (has ? n - kCnnHalo : 0);
-            tgt[t] = a.target[j];
+            const float target = a.target[j];
+            tgt[t] = has ? target : 0.0f;
             lw[t] = has ? a.weight[j] * a.scale : 0.0f;
         }
         // A fragment (mt, ks) of a layer's weights in global memory
@@ -755,8 +759,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
             const int own = L.g & 1;   // this lane's tile from here
             const float z = ordered_dot(G.fb + kCnnW5Off, h, G.fb[kCnnW5Off + 16]);
             const float lw_own = own ? lw[1] : lw[0], tgt_own = own ? tgt[1] : tgt[0];
+            const bool carries_own = own ? carries[1] : carries[0];
             float dz[2];
-            to_all_groups(lw_own * (sigmoid(z) - tgt_own), dz);
+            to_all_groups(carries_own ? lw_own * (sigmoid(z) - tgt_own) : 0.0f, dz);
             const f32x4 w5 = *reinterpret_cast<const f32x4 *>(G.fb + kCnnW5Off + 4 * L.g);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -770,7 +775,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn_grad(CnnTrainArgs a)
                 *reinterpret_cast<bf16x4 *>(G.d16 + act_off<16>(p0 + 16 * t + kCnnGuard, 4 * L.g)) =
                     relu_mask(dp, h[t][0]);
             }
-            if (L.g < 2)   // soft binary cross entropy in its logit form
+            if (L.g < 2 && carries_own)   // soft binary cross entropy in its logit form
                 ploss += lw_own * (fmaxf(z, 0.0f) - z * tgt_own + log1pf(expf(-fabsf(z))));
         }
         __syncthreads();

@@ -781,17 +781,21 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
         __syncthreads();
         if (wi + 1 < w_end)
             in.fetch(a.win, wi + 1, tid);
-        // targets and loss weights of this lane's two positions (zero where
-        // a position carries no loss)
+        // targets and loss weights of this lane's two positions; where a position
+        // carries no loss neither counts, nor does its logit (zero times a value
+        // that is not finite is not zero)
         float tgt[2], lw[2], tops[2];
+        bool carries[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int n = 32 * wv + (lane & 15) + 16 * t;
             const bool here = n >= lo && n < hi;
             const bool has = here && n >= kTrainHalo && n < kC2Win - kTrainHalo;
+            carries[t] = has;
             tops[t] = here ? __builtin_inff() : 0.0f;
             const int64_t k = (int64_t)wi * kTrainOut + (has ? n - kTrainHalo : 0);
-            tgt[t] = a.target[k];
+            const float target = a.target[k];
+            tgt[t] = has ? target : 0.0f;
             lw[t] = has ? a.scale * a.weight[k] : 0.0f;
         }
         {
@@ -900,8 +904,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             const int own = L.g & 1;   // this lane's tile from here
             const float z = ordered_dot(G.fb + kC2FW4, h, G.fb[kC2FB4]);
             const float lw_own = own ? lw[1] : lw[0], tgt_own = own ? tgt[1] : tgt[0];
+            const bool carries_own = own ? carries[1] : carries[0];
             float dz[2];
-            to_all_groups(lw_own * (sigmoid(z) - tgt_own), dz);
+            to_all_groups(carries_own ? lw_own * (sigmoid(z) - tgt_own) : 0.0f, dz);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 pb4 += dz[t];    // every lane group alike; the first one's is taken
@@ -917,7 +922,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                         relu_mask(dp, h[t][mt]);
                 }
             }
-            if (L.g < 2)   // -(t log s + (1 - t) log(1 - s)) = max(z, 0) - z t + log(1 + e^-|z|)
+            if (L.g < 2 && carries_own)   // -(t log s + (1 - t) log(1 - s)) = max(z, 0) - z t + log(1 + e^-|z|)
                 loss += lw_own * (fmaxf(z, 0.0f) - z * tgt_own + log1pf(__expf(-fabsf(z))));
             if (tid < 8)   // guard positions of dP3
                 *reinterpret_cast<bf16x8 *>(G.d + (tid >> 2) * (kPos - 1) * 32 + (tid & 3) * 8) =
