@@ -168,8 +168,9 @@ int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const c
         if (k == n_shapes) {
             if (n_shapes == max_shapes)
                 return CA_E_NOMEM;
-            shapes[n_shapes++] = {d.width, d.height};
+            shapes[n_shapes++] = {d.width, d.height, 0, 0};
         }
+        ++shapes[k].count;
         longest = std::max(longest, std::max(d.width, d.height));
         if ((d.byte_offset % 16) != 0 || (d.row_stride % 16) != 0)
             pl->rows_aligned = false;
@@ -180,6 +181,16 @@ int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const c
     for (int32_t k = 1; k < n_shapes; ++k)
         for (int32_t j = k; j > 0 && area(shapes[j]) > area(shapes[j - 1]); --j)
             std::swap(shapes[j], shapes[j - 1]);
+    for (int32_t k = 1; k < n_shapes; ++k)
+        shapes[k].first = shapes[k - 1].first + shapes[k - 1].count;
+    pl->shapes = shapes;
+    pl->n_shapes = n_shapes;
+    int32_t at_shape = 0;
+    pl->spread = n_shapes == 1 ? ca::kSpreadSlices : mixed_spread(n, [&](int32_t k) {
+        while (k >= shapes[at_shape].first + shapes[at_shape].count)
+            ++at_shape;
+        return area(shapes[at_shape]);
+    });
     pl->line_pitch = (int32_t)align_up((size_t)longest, 16);
     pl->lds = ca::strip_lds_bytes(sg_len, pl->line_pitch);
     pl->fused_lds = ca::fused_lds_bytes(sg_len, pl->line_pitch);
@@ -245,29 +256,6 @@ int fused_grid(const ca_ctx *ctx, size_t fused_lds)
     return per_cu * ctx->n_cu;
 }
 
-// How one launch deals the frames of several shapes, given by their pixels in
-// the launch's order, the largest first: whole frames to the XCDs, whose L2 then
-// holds the lines that a frame's strips share, unless that would leave one XCD
-// with over a tenth more than its share; then strip by strip.  128 frames of
-// four resolutions: 167 us a call with a launch for each shape, 152 us dealt
-// strip by strip, 124 us by frames.
-int32_t mixed_spread(const std::vector<int64_t> &area)
-{
-    if (area.empty() || area.front() == area.back())
-        return ca::kSpreadSlices;
-    int64_t most = 0, all = 0;
-    for (int x = 0; x < 8; ++x) {
-        int64_t mine = 0;
-        for (int32_t j = 0; 8 * j < (int32_t)area.size(); ++j) {
-            const int32_t k = ca::spread_frame(x, j);
-            mine += k < (int32_t)area.size() ? area[(size_t)k] : 0;
-        }
-        most = std::max(most, mine);
-        all += mine;
-    }
-    return 80 * most <= 11 * all ? ca::kSpreadFrames : ca::kSpreadItems;
-}
-
 int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_params &p, Plan **out)
 {
     Plan *pl = new (std::nothrow) Plan();
@@ -276,7 +264,8 @@ int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_param
     pl->dims.assign(dims, dims + n);
     int32_t sg_len = 0;
     const float *lut = cached_tables(ctx, p, &sg_len);
-    std::vector<Shape> shapes((size_t)n);
+    std::vector<Shape> &shapes = pl->own_shapes;
+    shapes.resize((size_t)n);
     PlanLayout L;
     int rc = plan_layout(ctx, dims, n, p, lut, sg_len, shapes.data(), n, pl, &L, nullptr, 0);
     std::vector<uint8_t> image;
@@ -290,18 +279,6 @@ int build_plan(ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_param
         return rc;
     }
     shapes.resize((size_t)L.n_shapes);
-    int32_t first = 0;
-    std::vector<int64_t> area;
-    for (const Shape &sh : shapes) {
-        int32_t count = 0;
-        for (int32_t i = 0; i < n; ++i)
-            count += dims[i].width == sh.W && dims[i].height == sh.H;
-        pl->classes.push_back({sh.W, sh.H, first, count});
-        first += count;
-        area.insert(area.end(), (size_t)count, (int64_t)sh.W * sh.H);
-    }
-    pl->spread = mixed_spread(area);
-    pl->shapes = shapes;
     pl->fused_grid = fused_grid(ctx, pl->fused_lds);
 
     // evict least recently used unpinned plans until this one fits the budget
@@ -374,7 +351,7 @@ int32_t strips_per_group(const ca_ctx *ctx, int32_t W, int32_t H, const ca_param
 
 // Strip launches of one shape class with T items per workgroup.
 hipError_t launch_class_strips(const ca::StripArgs &base, const Plan *pl,
-                               const Plan::ShapeClass &c, int32_t T, int32_t S, hipStream_t st)
+                               const Shape &c, int32_t T, int32_t S, hipStream_t st)
 {
     ca::StripArgs a = base;
     a.frame0 = 0;
@@ -492,8 +469,8 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
     }
     // whether every shape of the batch takes one strip a workgroup
     auto one_each = [&] {
-        for (const Plan::ShapeClass &c : pl->classes)
-            if (strips_per_group(ctx, c.W, c.H, p) != 1)
+        for (int32_t k = 0; k < pl->n_shapes; ++k)
+            if (strips_per_group(ctx, pl->shapes[k].W, pl->shapes[k].H, p) != 1)
                 return false;
         return true;
     };
@@ -504,7 +481,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
     // tev (timed calls): the strip kernel between tev[0] and tev[1], RANSAC
     // between tev[2] and tev[3], each pair taken by the dispatch itself (the
     // per-shape strip launches of a mixed batch between two marker events)
-    const bool mixed = pl->dynamic ? pl->spread != ca::kSpreadSlices : pl->classes.size() > 1;
+    const bool mixed = pl->n_shapes > 1;
     auto launch_range = [&](int32_t f0, int32_t f1, hipStream_t st, hipEvent_t *tev) {
         hipEvent_t s0 = tev ? tev[0] : nullptr, s1 = tev ? tev[1] : nullptr;
         hipEvent_t r0 = tev ? tev[2] : nullptr, r1 = tev ? tev[3] : nullptr;
@@ -551,7 +528,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
                     std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8 * ca::cnn_strips_blocks_per_cu());
             ok = ca::launch_cnn_strips(c, ctx->cnn_groups_per_xcd, st, s0, s1)
                  == hipSuccess;
-        } else if (f0 == 0 && f1 == n && pl->spread != ca::kSpreadSlices && one_each()) {
+        } else if (f0 == 0 && f1 == n && mixed && (pl->dynamic || one_each())) {
             // several shapes, each taking its strips one at a time
             a2.frame_list = pl->flist;
             a2.spread = pl->spread;
@@ -559,14 +536,16 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
                 a2.per_xcd = (n + 7) / 8 * S;
             ok = ca::launch_strips(a2, pl->lds, st, s0, s1) == hipSuccess;
         } else if (f0 == 0 && f1 == n && !pl->dynamic
-                   && (pl->classes.size() > 1
-                       || strips_per_group(ctx, pl->classes[0].W, pl->classes[0].H, p) != 1)) {
+                   && (mixed
+                       || strips_per_group(ctx, pl->shapes[0].W, pl->shapes[0].H, p) != 1)) {
             // the whole batch: one launch per frame shape, each with its tile
             ok = !s0 || hipEventRecord(s0, st) == hipSuccess;
-            for (const Plan::ShapeClass &c : pl->classes)
+            for (int32_t k = 0; k < pl->n_shapes; ++k) {
+                const Shape &c = pl->shapes[k];
                 ok = ok
                      && launch_class_strips(sa, pl, c, strips_per_group(ctx, c.W, c.H, p), S, st)
                             == hipSuccess;
+            }
             ok = ok && (!s1 || hipEventRecord(s1, st) == hipSuccess);
         } else {
             ok = ca::launch_strips(a2, pl->lds, st, s0, s1) == hipSuccess;
@@ -1298,7 +1277,8 @@ int ca_autotune(ca_ctx *ctx, const uint8_t *frames, const ca_frame_desc *dims, i
         return CA_E_DEVICE;
     }
     rc = CA_OK;
-    for (const Plan::ShapeClass &c : pl->classes) {
+    for (int32_t k = 0; k < pl->n_shapes; ++k) {
+        const Shape &c = pl->shapes[k];
         int32_t best_t = 1;
         float best_ms = 0.0f;
         for (int32_t T : {1, 2, 4, 8}) {

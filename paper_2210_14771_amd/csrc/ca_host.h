@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <array>
 #include <map>
 #include <vector>
@@ -16,8 +17,10 @@ namespace cahost {
 using ca::FrameDev;
 using ca::Record;
 
+// One frame shape of a batch: its strips at table k * S for shape k, its frames
+// at flist[first .. first + count).
 struct Shape {
-    int32_t W, H;
+    int32_t W, H, first, count;
 };
 
 struct Plan {
@@ -35,14 +38,13 @@ struct Plan {
     Record *rec = nullptr;
     uint32_t *ctl = nullptr;    // fused-kernel control words (zero between calls)
     ca_result *res2 = nullptr;  // results of the calls that autotune times
-    int32_t *flist = nullptr;   // frame indices grouped by frame shape
-    struct ShapeClass {
-        int32_t W, H, first, count;
-    };
-    std::vector<ShapeClass> classes;
+    int32_t *flist = nullptr;   // frame indices by frame shape, the largest first
+    const Shape *shapes = nullptr;  // the batch's n_shapes distinct frame shapes, likewise
+    int32_t n_shapes = 0;
+    std::vector<Shape> own_shapes;  // where they are kept by a cached plan
     int32_t spread = 0;         // of a launch over all shapes (StripSpread)
-    std::vector<Shape> shapes;  // distinct frame shapes; shape k's strips at table k * S
-    bool dynamic = false;       // a serving plan: descriptors rewritten per batch, not cached
+    bool dynamic = false;       // not cached: a serving slot's plan, rewritten per batch, or a
+                                // call's without allocation
     int32_t tuned_schedule = -1; // faster schedule of this batch (ca_autotune), -1 untuned
     int32_t tuned_pipeline = 1;  // sub-batches of its split calls (ca_autotune)
     // launch facts
@@ -142,14 +144,31 @@ struct PlanLayout {
 // The context's score tables for p (computed once per (t_g, t_theta, t_iota)).
 const float *cached_tables(ca_ctx *ctx, const ca_params &p, int32_t *sg_len);
 // Launch facts of pl (P, groups, sg_len, line pitch, LDS sizes, row
-// alignment; not the fused grid) and the layout L; the distinct shapes go to
-// shapes[0 .. max_shapes).  With `image`, also writes the host image
-// (image_cap >= L->image_bytes).  CA_E_NOMEM for more than max_shapes
-// shapes or a short image, CA_E_UNSUPPORTED when a strip tile exceeds LDS.
-int32_t mixed_spread(const std::vector<int64_t> &area);
+// alignment, shapes and their spread; not the fused grid) and the layout L; the
+// distinct shapes go to shapes[0 .. max_shapes), where pl refers to them.  With
+// `image`, also writes the host image (image_cap >= L->image_bytes).
+// CA_E_NOMEM for more than max_shapes shapes or a short image,
+// CA_E_UNSUPPORTED when a strip tile exceeds LDS.
 int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const ca_params &p,
                 const float *lut, int32_t sg_len, Shape *shapes, int32_t max_shapes, Plan *pl,
                 PlanLayout *L, uint8_t *image, size_t image_cap);
+// How one launch deals the n frames of several shapes; area(k): the pixels of the
+// k-th frame in the launch's order, the largest first.  Whole frames to the XCDs,
+// whose L2 then holds the lines that a frame's strips share, unless that would
+// leave one XCD with over a tenth more than its share; then strip by strip.  128
+// frames of four resolutions: 167 us a call with a launch for each shape, 152 us
+// dealt strip by strip, 124 us by frames.
+template <class Area>
+int32_t mixed_spread(int32_t n, Area area)
+{
+    int64_t mine[8] = {}, all = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        mine[ca::spread_xcd(k)] += area(k);
+        all += area(k);
+    }
+    return 80 * *std::max_element(mine, mine + 8) <= 11 * all ? ca::kSpreadFrames
+                                                              : ca::kSpreadItems;
+}
 // Points pl's buffers into the device block at base.
 void plan_pointers(Plan *pl, void *base, const PlanLayout &L);
 // Resident workgroups of the fused kernel for this LDS size.

@@ -51,6 +51,8 @@ enum StripSpread {
 
 // The frame of an XCD's j-th turn under kSpreadFrames.
 constexpr int spread_frame(int xcd, int j) { return 8 * j + ((j & 1) ? 7 - xcd : xcd); }
+// The XCD that takes the k-th frame.
+constexpr int spread_xcd(int k) { return (k >> 3 & 1) ? 7 - (k & 7) : k & 7; }
 
 struct StripArgs {
     const uint8_t *frames;

@@ -115,7 +115,7 @@ extern "C" int ca_estimate_area_noalloc(ca_ctx *ctx, const uint8_t *frames,
         if (d.recorded && hipEventSynchronize(d.uploaded) != hipSuccess)
             return CA_E_DEVICE;
         Plan pl;
-        pl.dynamic = true;          // one strip launch over all shapes, nothing cached
+        pl.dynamic = true;          // nothing cached
         int32_t sg_len = 0;
         const float *lut = cached_tables(ctx, p, &sg_len);
         PlanLayout L;

@@ -135,6 +135,7 @@ struct Batch {                          // one in-flight slot
     float4 *filt_host = nullptr;        // of the current batch
     hipEvent_t done = nullptr;
     std::vector<Entry> entries;
+    std::vector<cahost::Shape> shapes;  // of the batch's frames (room for max_batch)
     int64_t t_launch = 0;
     bool busy = false;
 };
@@ -189,18 +190,20 @@ size_t stage_batch(ca_server *s, Batch &b, size_t n, int32_t n_runs)
     const int32_t S = s->cfg.params.n_hstrips + s->cfg.params.n_vstrips;
     ca::FrameDev *fd = reinterpret_cast<ca::FrameDev *>(b.stage + s->layout.o_fd);
     int32_t *tables = reinterpret_cast<int32_t *>(b.stage + s->layout.o_strips);
-    std::vector<const Stream *> shapes;  // one strip table per distinct shape
+    std::vector<cahost::Shape> &shapes = b.shapes;   // one strip table per distinct shape
+    shapes.clear();
     int32_t longest = 0;
     bool aligned = true;
     for (size_t i = 0; i < n; ++i) {
         const Entry &e = b.entries[i];
         size_t k = 0;
-        while (k < shapes.size() && !(shapes[k]->W == e.st->W && shapes[k]->H == e.st->H))
+        while (k < shapes.size() && !(shapes[k].W == e.st->W && shapes[k].H == e.st->H))
             ++k;
         if (k == shapes.size()) {
-            shapes.push_back(e.st);
+            shapes.push_back({e.st->W, e.st->H, 0, 0});
             std::memcpy(tables + k * (size_t)S, e.st->table.data(), sizeof(int32_t) * (size_t)S);
         }
+        ++shapes[k].count;
         ca::FrameDev &d = fd[i];
         if (e.slot >= 0) {
             d.offset = (int64_t)(e.st->ring_off + (size_t)e.slot * e.st->slot_bytes);
@@ -221,15 +224,15 @@ size_t stage_batch(ca_server *s, Batch &b, size_t n, int32_t n_runs)
     }
     int32_t *order = reinterpret_cast<int32_t *>(b.runs_host + n_runs);
     std::iota(order, order + n, 0);
-    std::stable_sort(order, order + n, [&](int32_t x, int32_t y) {
-        return (int64_t)fd[x].W * fd[x].H > (int64_t)fd[y].W * fd[y].H;
-    });
-    std::vector<int64_t> area(n);
-    for (size_t i = 0; i < n; ++i)
-        area[i] = (int64_t)fd[order[i]].W * fd[order[i]].H;
+    auto area = [&](int32_t f) { return (int64_t)fd[f].W * fd[f].H; };
+    std::stable_sort(order, order + n, [&](int32_t x, int32_t y) { return area(x) > area(y); });
     cahost::Plan &pl = b.plan;
     pl.flist = reinterpret_cast<int32_t *>(b.runs_dev + n_runs);
-    pl.spread = cahost::mixed_spread(area);
+    pl.shapes = shapes.data();
+    pl.n_shapes = (int32_t)shapes.size();
+    pl.spread = shapes.size() == 1
+                    ? ca::kSpreadSlices
+                    : cahost::mixed_spread((int32_t)n, [&](int32_t k) { return area(order[k]); });
     pl.n_frames = (int32_t)n;
     pl.line_pitch = (int32_t)cahost::align_up((size_t)longest, 16);
     pl.lds = ca::strip_lds_bytes(pl.sg_len, pl.line_pitch);
@@ -529,6 +532,7 @@ int ca_server_create(ca_ctx *ctx, const ca_server_config *cfg, ca_server **out)
         b.plan.groups = proto.groups;
         b.plan.sg_len = proto.sg_len;
         b.plan.dynamic = true;
+        b.shapes.reserve(B);
         constexpr size_t kOut = sizeof(ca_result) + sizeof(float4);
         ok = ok && hipMalloc(&b.up_dev, s->runs_bytes + s->layout.total) == hipSuccess
              && hipMalloc(&b.res_dev, B * kOut) == hipSuccess
