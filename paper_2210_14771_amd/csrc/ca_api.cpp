@@ -203,7 +203,8 @@ int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const c
     L->o_lut = align_up(L->o_strips + sizeof(int32_t) * (size_t)n_shapes * (size_t)S, 256);
     L->o_flist = align_up(L->o_lut + sizeof(float) * lut_len, 256);
     L->o_ctl = align_up(L->o_flist + sizeof(int32_t) * (size_t)n, 256);
-    L->image_bytes = L->o_ctl + sizeof(uint32_t) * ca::ctl_words(n);
+    L->o_edges = align_up(L->o_ctl + sizeof(uint32_t) * ca::ctl_words(n), 256);
+    L->image_bytes = L->o_edges + kEdgeBytes;
     L->o_cand = align_up(L->image_bytes, 256);
     L->o_rec = align_up(L->o_cand + sizeof(ca_point) * (size_t)n * (size_t)pl->P, 256);
     L->o_res2 = align_up(L->o_rec + sizeof(Record) * (size_t)n * (size_t)pl->rec_groups, 256);
@@ -241,6 +242,7 @@ void plan_pointers(Plan *pl, void *base_mem, const PlanLayout &L)
     pl->lut = reinterpret_cast<float *>(base + L.o_lut);
     pl->flist = reinterpret_cast<int32_t *>(base + L.o_flist);
     pl->ctl = reinterpret_cast<uint32_t *>(base + L.o_ctl);
+    pl->edges = reinterpret_cast<uint64_t *>(base + L.o_edges);
     pl->cand = reinterpret_cast<ca_point *>(base + L.o_cand);
     pl->rec = reinterpret_cast<Record *>(base + L.o_rec);
     pl->res2 = reinterpret_cast<ca_result *>(base + L.o_res2);
@@ -482,7 +484,27 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
     // between tev[2] and tev[3], each pair taken by the dispatch itself (the
     // per-shape strip launches of a mixed batch between two marker events)
     const bool mixed = pl->n_shapes > 1;
-    auto launch_range = [&](int32_t f0, int32_t f1, hipStream_t st, hipEvent_t *tev) {
+    // at most `resident` workgroups per XCD; side: whose edge words they take
+    auto learned_launch = [&](auto &c, const uint8_t *model, int32_t f0, int32_t f1, int side,
+                              int resident, int halo) {
+        c.frames = frames;
+        c.fd = pl->fd;
+        c.strips = pl->strips;
+        c.model = model;
+        c.cand = sa.cand;
+        c.n_h = p.n_hstrips;
+        c.n_v = p.n_vstrips;
+        c.n_items = (f1 - f0) * S;
+        c.frame0 = f0;
+        c.mixed = mixed ? 1 : 0;
+        c.deal = ca::strip_deal(pl->shapes, pl->n_shapes, f1 - f0, n, p.n_hstrips, p.n_vstrips,
+                                resident, halo);
+        c.edges = pl->edges + side * ca::kStripGroups;
+    };
+    const int cu_per_xcd = std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / ca::kXcds);
+    if (learned && ctx->cnn_groups_per_xcd == 0)
+        ctx->cnn_groups_per_xcd = cu_per_xcd * ca::cnn_strips_blocks_per_cu();
+    auto launch_range = [&](int32_t f0, int32_t f1, hipStream_t st, int side, hipEvent_t *tev) {
         hipEvent_t s0 = tev ? tev[0] : nullptr, s1 = tev ? tev[1] : nullptr;
         hipEvent_t r0 = tev ? tev[2] : nullptr, r1 = tev ? tev[3] : nullptr;
         ca::StripArgs a2 = sa;
@@ -492,42 +514,26 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
         ca::RansacArgs r2 = ra;
         r2.frame0 = f0;
         bool ok;
-        if (learned2d) {
-            ca::Cnn2dStripArgs c;
-            c.frames = frames;
-            c.fd = pl->fd;
-            c.strips = pl->strips;
-            c.model = ctx->model2d;
-            c.cand = sa.cand;
-            c.n_h = p.n_hstrips;
-            c.n_v = p.n_vstrips;
-            c.n_items = a2.n_items;
-            c.per_xcd = a2.per_xcd;
-            c.frame0 = f0;
-            c.longest = pl->line_pitch;
-            c.mixed = mixed ? 1 : 0;
-            // its LDS fills a compute unit
-            c.resident_per_xcd = std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8);
-            ok = ca::launch_cnn2d_strips(c, st, s0, s1) == hipSuccess;
-        } else if (learned) {
-            ca::CnnStripArgs c;
-            c.frames = frames;
-            c.fd = pl->fd;
-            c.strips = pl->strips;
-            c.model = ctx->model;
-            c.cand = sa.cand;
-            c.n_h = p.n_hstrips;
-            c.n_v = p.n_vstrips;
-            c.n_items = a2.n_items;
-            c.per_xcd = a2.per_xcd;
-            c.frame0 = f0;
-            c.longest = pl->line_pitch;
-            c.mixed = mixed ? 1 : 0;
-            if (ctx->cnn_groups_per_xcd == 0)
-                ctx->cnn_groups_per_xcd =
-                    std::max(1, (ctx->n_cu > 0 ? ctx->n_cu : 256) / 8 * ca::cnn_strips_blocks_per_cu());
-            ok = ca::launch_cnn_strips(c, ctx->cnn_groups_per_xcd, st, s0, s1)
-                 == hipSuccess;
+        if (learned || learned2d) {
+            // (one launch, but for very many frames)
+            const bool several = f1 - f0 > ca::kDealFrames;
+            ok = !several || !s0 || hipEventRecord(s0, st) == hipSuccess;
+            for (int32_t b0 = f0; b0 < f1 && ok; b0 += ca::kDealFrames) {
+                const int32_t b1 = std::min(f1, b0 + ca::kDealFrames);
+                hipEvent_t e0 = several ? nullptr : s0, e1 = several ? nullptr : s1;
+                if (learned2d) {
+                    ca::Cnn2dStripArgs c;
+                    // (its LDS fills a compute unit)
+                    learned_launch(c, ctx->model2d, b0, b1, side, cu_per_xcd, ca::kC2Halo);
+                    ok = ca::launch_cnn2d_strips(c, st, e0, e1) == hipSuccess;
+                } else {
+                    ca::CnnStripArgs c;
+                    learned_launch(c, ctx->model, b0, b1, side, ctx->cnn_groups_per_xcd,
+                                   ca::kCnnHalo);
+                    ok = ca::launch_cnn_strips(c, c.deal.groups, st, e0, e1) == hipSuccess;
+                }
+            }
+            ok = ok && (!several || !s1 || hipEventRecord(s1, st) == hipSuccess);
         } else if (f0 == 0 && f1 == n && mixed && (pl->dynamic || one_each())) {
             // several shapes, each taking its strips one at a time
             a2.frame_list = pl->flist;
@@ -556,7 +562,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
                          : (ctx->schedule == CA_SCHEDULE_AUTO ? pl->tuned_pipeline : 1);
     const int32_t nsub = want > 1 ? (int32_t)std::min<int64_t>(want, n) : 1;
     if (nsub == 1) {
-        return launch_range(0, n, s, ev) ? CA_OK : CA_E_DEVICE;
+        return launch_range(0, n, s, 0, ev) ? CA_OK : CA_E_DEVICE;
     }
     // sub-batches alternate over two side streams, forked from and joined
     // back into the caller's stream: one sub-batch's RANSAC (ALU bound)
@@ -571,7 +577,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
     for (int32_t j = 0; j < nsub; ++j) {
         const int32_t f0 = (int32_t)((int64_t)j * n / nsub);
         const int32_t f1 = (int32_t)((int64_t)(j + 1) * n / nsub);
-        if (f1 > f0 && !launch_range(f0, f1, ctx->side[j & 1], nullptr))
+        if (f1 > f0 && !launch_range(f0, f1, ctx->side[j & 1], j & 1, nullptr))
             return CA_E_DEVICE;
     }
     for (int k = 0; k < used; ++k)

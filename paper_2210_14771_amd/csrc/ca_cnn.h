@@ -1,6 +1,7 @@
 // Internal interface of the learned strip scorer (host core <-> kernels).
 #pragma once
 
+#include "ca_deal.h"
 #include "ca_internal.h"
 
 namespace ca {
@@ -43,11 +44,10 @@ struct CnnStripArgs {
     ca_point *cand;
     int32_t n_h, n_v;
     int32_t n_items;
-    int32_t per_xcd;
     int32_t frame0;
-    int32_t longest;          // longest side of the frames
     int32_t mixed;            // the frames differ in shape
-    int32_t parts;            // waves that share a half strip (set by the launch)
+    StripDeal deal;           // the waves' shares of the half strips
+    uint64_t *edges;          // [kStripGroups] zeros, zero again afterwards
 };
 
 struct CnnTrainArgs {
@@ -75,9 +75,8 @@ hipError_t launch_cnn_pack(const float *master, uint8_t *model, hipStream_t s);
 hipError_t launch_mfma_probe(float *out, hipStream_t s);
 hipError_t launch_cnn_windows(const uint8_t *model, const uint8_t *win, const int32_t *range,
                               float *z, int n, hipStream_t s);
-// Learned candidates; a.per_xcd = items per XCD slice, resident_per_xcd = the
-// workgroups that an XCD holds at once (each takes the slice's items in turn).
-hipError_t launch_cnn_strips(const CnnStripArgs &a, int resident_per_xcd, hipStream_t s,
+// Learned candidates, by groups_per_xcd workgroups on each XCD (a.deal's).
+hipError_t launch_cnn_strips(const CnnStripArgs &a, int groups_per_xcd, hipStream_t s,
                              hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // Resident workgroups of k_cnn_strips per compute unit.
 int cnn_strips_blocks_per_cu();
@@ -95,6 +94,7 @@ constexpr int kC2FileW4 = 6182;
 constexpr int kC2FileB4 = 6214;
 constexpr int kC2Win = 128;    // positions of a window
 constexpr int kC2Band = 7;     // lines of a band
+constexpr int kC2Halo = 3;     // the network's receptive-field radius
 // Device model block, per band orientation (0: horizontal strips, weights
 // [dy][dx]; 1: vertical strips, [dx][dy]): bfloat16 GEMM weights A[m][k]
 // with k = (3 da + dl) C_pad + c for the forward convolutions, and flipped
@@ -126,12 +126,10 @@ struct Cnn2dStripArgs {
     ca_point *cand;
     int32_t n_h, n_v;
     int32_t n_items;
-    int32_t per_xcd;
     int32_t frame0;
-    int32_t resident_per_xcd;   // workgroups that an XCD holds at once
-    int32_t longest;            // longest side of the frames
     int32_t mixed;              // the frames differ in shape
-    int32_t parts;              // waves that share a half strip (set by the launch)
+    StripDeal deal;             // the waves' shares of the half strips
+    uint64_t *edges;            // [kStripGroups] zeros, zero again afterwards
 };
 
 struct Cnn2dTrainArgs {

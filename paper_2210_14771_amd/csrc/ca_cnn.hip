@@ -62,8 +62,8 @@ __global__ __launch_bounds__(kBlock) void k_mfma_probe(float *out)
 // stored in four planes, row 4 i + j as row i of plane j.
 //
 // All weights stay in registers (230 with the rest), so two waves share a SIMD
-// and eight a workgroup's LDS.  With few half strips the waves of a workgroup
-// share them (the launch chooses 1, 2, 4 or 8 a half strip: strip_split): a lone frame's are scored by 8 times 128 waves.
+// and eight a workgroup's LDS; each takes an equal share of the half strips' steps
+// (ca_deal.h).
 //
 // Bound by the chain of layers within a step (LDS round trips that two waves
 // cover in part) beside about 340 vector instructions and 104 MFMAs a step.
@@ -406,79 +406,41 @@ __global__ __launch_bounds__(kCnnWaveBlock, 2) void k_cnn_windows(const uint8_t 
     }
 }
 
+template <bool MIXED>
 __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs a)
 {
     extern __shared__ __align__(16) uint8_t cnn_smem[];
-    __shared__ uint64_t s_best[kStripWaves];
-    StripRows *rows = reinterpret_cast<StripRows *>(cnn_smem);
+    __shared__ StripMeet meet;
     const int lane = threadIdx.x & 63;
     const int wv = uniform_int(threadIdx.x >> 6);
-    const int group = blockIdx.x >> 3, groups = gridDim.x >> 3;
-    const int xcd = blockIdx.x & 7;
-    const int first = xcd * a.per_xcd;
-    const int n_units = 2 * (min(first + a.per_xcd, a.n_items) - first);
-    const int sets = kStripWaves / a.parts;          // half strips a workgroup takes at a time
-    if (group * sets >= n_units)
-        return;
-    StripRows &R = rows[wv];
+    if (threadIdx.x <= kStripWaves)
+        meet.best[threadIdx.x] = 0;
+    __syncthreads();
+    StripRows &R = reinterpret_cast<StripRows *>(cnn_smem)[wv];
     strip_clear(R, lane);
     const StripNet net(a.model, lane);
-
-    const int S = a.n_h + a.n_v;
-    const int set = wv / a.parts, part = wv % a.parts;
-    const int slots = groups * sets;
-    for (int turn = 0; turn * slots < n_units; ++turn) {
-        // Half strips rotate by half a frame's from turn to turn: horizontal
-        // and vertical ones differ in length, and the slots are often a multiple
-        // of a frame's half strips, so a plain stride would give half of the
-        // waves nothing but the long ones.
-        const int unit = uniform_int(turn * slots + (group * sets + set + turn * S) % slots);
+    strip_shares<kCnnHalo, MIXED>(a, meet, lane, wv, [&](const FrameDev &d, bool horizontal,
+                                                         int pos, int half, int p0, int p1) {
+        StripWalk k;
+        strip_walk<kCnnLines>(k, a.frames, d, horizontal, pos);
         uint64_t best = 0;
-        int f = 0, st = 0, half = 0, pos = 0, L = 0;
-        bool horizontal = false;
-        if (unit < n_units) {
-            const int item = first + (unit >> 1);
-            half = unit & 1;
-            f = uniform_int(a.frame0 + item / S);
-            st = uniform_int(item % S);
-            const FrameDev d = a.fd[f];
-            horizontal = st < a.n_h;
-            pos = uniform_int(a.strips[d.table + st]);
-            StripWalk k;
-            strip_walk<kCnnLines>(k, a.frames, d, horizontal, pos);
-            L = k.L;
-            const int h0 = half ? L >> 1 : 0, h1 = half ? L : L >> 1;
-            const int each = (h1 - h0 + a.parts - 1) / a.parts;
-            const int p0 = h0 + part * each, p1 = min(p0 + each, h1);
-            uint32_t px[8];
-            int x = p0 - kCnnHalo;   // first new input position of the step
-            if (p0 < p1)
-                strip_fetch<kCnnLines>(px, k, x, lane);
-            for (; p0 < p1 && x - kCnnHalo < p1; x += kStep) {
-                strip_encode(R.x0.v, px, k.packed, x, L, net.xi, lane);
-                if (x + kStep - kCnnHalo < p1)
-                    strip_fetch<kCnnLines>(px, k, x + kStep, lane);
-                const float z = net.step(R, x, L, lane);
-                const int p = x - kCnnHalo + 4 * (lane & 15) + (lane >> 4);
-                if (p >= p0 && p < p1) {
-                    const uint64_t key = strip_key(z, p, half, L);
-                    best = best > key ? best : key;
-                }
+        uint32_t px[8];
+        int x = p0 - kCnnHalo;   // first new input position of the step
+        if (p0 < p1)
+            strip_fetch<kCnnLines>(px, k, x, lane);
+        for (; p0 < p1 && x - kCnnHalo < p1; x += kStep) {
+            strip_encode(R.x0.v, px, k.packed, x, k.L, net.xi, lane);
+            if (x + kStep - kCnnHalo < p1)
+                strip_fetch<kCnnLines>(px, k, x + kStep, lane);
+            const float z = net.step(R, x, k.L, lane);
+            const int p = x - kCnnHalo + 4 * (lane & 15) + (lane >> 4);
+            if (p >= p0 && p < p1) {
+                const uint64_t key = strip_key(z, p, half, k.L);
+                best = best > key ? best : key;
             }
-            best = wave_max(best);
         }
-        if (a.parts > 1) {
-            if (lane == 0)
-                s_best[wv] = best;
-            __syncthreads();
-            for (int w = 1; w < a.parts; ++w)
-                best = best > s_best[set * a.parts + w] ? best : s_best[set * a.parts + w];
-            __syncthreads();
-        }
-        if (unit < n_units && part == 0 && lane == 0) {
-            a.cand[(int64_t)f * (2 * S) + 2 * st + half] = strip_point(best, horizontal, pos, half, L);
-        }
-    }
+        return wave_max(best);
+    });
 }
 
 // ------------------------------------------------------------- training --
@@ -1184,7 +1146,7 @@ hipError_t launch_cnn_windows(const uint8_t *model, const uint8_t *win, const in
 int cnn_strips_blocks_per_cu()
 {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnn_strips, 64 * kStripWaves,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnn_strips<false>, 64 * kStripWaves,
                                                      kStripWaves * sizeof(StripRows))
             != hipSuccess
         || b < 1) {
@@ -1194,15 +1156,14 @@ int cnn_strips_blocks_per_cu()
     return b;
 }
 
-hipError_t launch_cnn_strips(const CnnStripArgs &args, int resident_per_xcd, hipStream_t s,
+hipError_t launch_cnn_strips(const CnnStripArgs &a, int groups_per_xcd, hipStream_t s,
                              hipEvent_t start, hipEvent_t stop)
 {
-    if (args.n_items <= 0)
+    if (a.n_items <= 0)
         return hipSuccess;
-    CnnStripArgs a = args;
-    const int groups = strip_split(a.parts, 2 * a.per_xcd, resident_per_xcd, a.longest,
-                                   a.mixed != 0, kCnnHalo);
-    launch_maybe_timed(k_cnn_strips, dim3(8 * groups), dim3(64 * kStripWaves), kStripWaves * sizeof(StripRows), s, start, stop, a);
+    launch_maybe_timed(a.mixed ? k_cnn_strips<true> : k_cnn_strips<false>,
+                       dim3(kXcds * groups_per_xcd), dim3(64 * kStripWaves),
+                       kStripWaves * sizeof(StripRows), s, start, stop, a);
     return hipGetLastError();
 }
 

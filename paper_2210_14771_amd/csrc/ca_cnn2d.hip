@@ -29,7 +29,6 @@ namespace ca {
 namespace {
 
 constexpr int kPos = kC2Win + 2;   // positions of a buffer line, guards included
-constexpr int kC2Halo = 3;         // the network's receptive-field radius
 constexpr int kTrainHalo = 8;      // training windows carry logits 8 .. 119
 constexpr int kTrainOut = kC2Win - 2 * kTrainHalo;
 constexpr int kC2Floats = 96;      // floats of the model's float block
@@ -58,22 +57,8 @@ __device__ __forceinline__ Frag<KP, MT> load_frag(const __bf16 *A)
     return f;
 }
 
-// Input encoding of one band position: colours normalised, coordinates in
-// [-0.5, 0.5] as (2 x - (W - 1)) / (2 (W - 1)), taken as a product with the
-// reciprocal rw = 1 / (2 (W - 1)) (and rh for y); channels 5..7 are zero.
-// (x, y) is the pixel, (W, H) the frame.
-__device__ __forceinline__ void encode(__bf16 *dst, uint32_t r, uint32_t g, uint32_t b, int x,
-                                       int y, int W, int H, float rw, float rh, const float *fb)
-{
-    bf16x8 v;
-    v[0] = to_bf16(((float)r - fb[kC2FMean + 0]) * fb[kC2FInv + 0]);
-    v[1] = to_bf16(((float)g - fb[kC2FMean + 1]) * fb[kC2FInv + 1]);
-    v[2] = to_bf16(((float)b - fb[kC2FMean + 2]) * fb[kC2FInv + 2]);
-    v[3] = to_bf16((float)(2 * x - (W - 1)) * rw);
-    v[4] = to_bf16((float)(2 * y - (H - 1)) * rh);
-    v[5] = v[6] = v[7] = to_bf16(0.0f);
-    *reinterpret_cast<bf16x8 *>(dst) = v;
-}
+// Coordinates are normalised to [-0.5, 0.5] as (2 x - (W - 1)) / (2 (W - 1)),
+// taken as a product with this reciprocal.
 __device__ __forceinline__ float coord_scale(int extent) { return 1.0f / (float)(2 * (extent - 1)); }
 
 __device__ __forceinline__ bool line_in(uint32_t line_ok, int j) { return (line_ok >> j) & 1u; }
@@ -420,83 +405,49 @@ struct Strip2dNet {
     }
 };
 
+template <bool MIXED>
 __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStripArgs a)
 {
     extern __shared__ __align__(16) uint8_t strip_smem[];
-    __shared__ uint64_t s_best[kStripWaves];
+    __shared__ StripMeet meet;
     const int lane = threadIdx.x & 63;
     const int wv = uniform_int(threadIdx.x >> 6);
-    const int group = blockIdx.x >> 3, groups = gridDim.x >> 3;
-    const int xcd = blockIdx.x & 7;
-    const int first = xcd * a.per_xcd;
-    const int n_units = 2 * (min(first + a.per_xcd, a.n_items) - first);
-    const int sets = kStripWaves / a.parts;          // half strips a workgroup takes at a time
-    if (group * sets >= n_units)
-        return;
+    if (threadIdx.x <= kStripWaves)
+        meet.best[threadIdx.x] = 0;
+    __syncthreads();
     Strip2dRows &R = reinterpret_cast<Strip2dRows *>(strip_smem)[wv];
     strip2d_clear(R, lane);
     Strip2dNet<true> net(a.model, lane);
-
-    const int S = a.n_h + a.n_v;
-    const int set = wv / a.parts, part = wv % a.parts;
-    const int slots = groups * sets;
-    for (int turn = 0; turn * slots < n_units; ++turn) {
-        // half strips rotate from turn to turn, so that every wave takes long and
-        // short ones (ca_cnn.hip)
-        const int unit = uniform_int(turn * slots + (group * sets + set + turn * S) % slots);
+    strip_shares<kC2Halo, MIXED>(a, meet, lane, wv, [&](const FrameDev &d, bool horizontal,
+                                                        int pos, int half, int p0, int p1) {
+        net.turn_to(horizontal, a.model, lane);
+        StripWalk k;
+        strip_walk<kC2Band>(k, a.frames, d, horizontal, pos);
+        const Band band(horizontal, pos, uniform_int(d.W), uniform_int(d.H), lane);
         uint64_t best = 0;
-        int f = 0, st = 0, half = 0, pos = 0, L = 0;
-        bool horizontal = false;
-        if (unit < n_units) {
-            const int item = first + (unit >> 1);
-            half = unit & 1;
-            f = uniform_int(a.frame0 + item / S);
-            st = uniform_int(item % S);
-            const FrameDev d = a.fd[f];
-            horizontal = st < a.n_h;
-            pos = uniform_int(a.strips[d.table + st]);
-            net.turn_to(horizontal, a.model, lane);
-            StripWalk k;
-            strip_walk<kC2Band>(k, a.frames, d, horizontal, pos);
-            L = k.L;
-            const int h0 = half ? L >> 1 : 0, h1 = half ? L : L >> 1;
-            const int each = (h1 - h0 + a.parts - 1) / a.parts;
-            const int p0 = h0 + part * each, p1 = min(p0 + each, h1);
-            const Band band(horizontal, pos, uniform_int(d.W), uniform_int(d.H), lane);
-            uint32_t px[8];
-            int x = p0 - kC2Halo;   // first new input position of the step
-            if (p0 < p1)
-                strip_fetch<kC2Band>(px, k, x, lane);
-            for (; p0 < p1 && x - kC2Halo < p1; x += kStep) {
-                if (k.packed) {   // 21 bytes to a dword of three for each line
+        uint32_t px[8];
+        int x = p0 - kC2Halo;   // first new input position of the step
+        if (p0 < p1)
+            strip_fetch<kC2Band>(px, k, x, lane);
+        for (; p0 < p1 && x - kC2Halo < p1; x += kStep) {
+            if (k.packed) {   // 21 bytes to a dword of three for each line
 #pragma unroll
-                    for (int j = kC2Band - 1; j >= 0; --j)
-                        px[j] = __builtin_amdgcn_alignbyte(px[(3 * j >> 2) + 1], px[3 * j >> 2],
-                                                           3 * j & 3);
-                }
-                band.encode(R.x0, px, net.norm, x + lane, x, L, lane);
-                if (x + kStep - kC2Halo < p1)
-                    strip_fetch<kC2Band>(px, k, x + kStep, lane);
-                const float z = net.step(R, band, x, L, lane);
-                const int p = x - kC2Halo + lane;   // column lane % 16 of tile lane / 16
-                if (p >= p0 && p < p1) {
-                    const uint64_t key = strip_key(z, p, half, L);
-                    best = best > key ? best : key;
-                }
+                for (int j = kC2Band - 1; j >= 0; --j)
+                    px[j] = __builtin_amdgcn_alignbyte(px[(3 * j >> 2) + 1], px[3 * j >> 2],
+                                                       3 * j & 3);
             }
-            best = wave_max(best);
+            band.encode(R.x0, px, net.norm, x + lane, x, k.L, lane);
+            if (x + kStep - kC2Halo < p1)
+                strip_fetch<kC2Band>(px, k, x + kStep, lane);
+            const float z = net.step(R, band, x, k.L, lane);
+            const int p = x - kC2Halo + lane;   // column lane % 16 of tile lane / 16
+            if (p >= p0 && p < p1) {
+                const uint64_t key = strip_key(z, p, half, k.L);
+                best = best > key ? best : key;
+            }
         }
-        if (a.parts > 1) {
-            if (lane == 0)
-                s_best[wv] = best;
-            __syncthreads();
-            for (int w = 1; w < a.parts; ++w)
-                best = best > s_best[set * a.parts + w] ? best : s_best[set * a.parts + w];
-            __syncthreads();
-        }
-        if (unit < n_units && part == 0 && lane == 0)
-            a.cand[(int64_t)f * (2 * S) + 2 * st + half] = strip_point(best, horizontal, pos, half, L);
-    }
+        return wave_max(best);
+    });
 }
 
 // Logits of positions 8 .. 119 of rendered windows [n][8][128][3]: a window is a
@@ -1314,11 +1265,9 @@ hipError_t launch_cnn2d_strips(const Cnn2dStripArgs &a, hipStream_t s, hipEvent_
 {
     if (a.n_items <= 0)
         return hipSuccess;
-    Cnn2dStripArgs b = a;
-    const int groups = strip_split(b.parts, 2 * a.per_xcd, a.resident_per_xcd, a.longest,
-                                   a.mixed != 0, kC2Halo);
-    launch_maybe_timed(k_cnn2d_strips, dim3(8 * groups), dim3(64 * kStripWaves),
-                       kStripWaves * sizeof(Strip2dRows), s, start, stop, b);
+    launch_maybe_timed(a.mixed ? k_cnn2d_strips<true> : k_cnn2d_strips<false>,
+                       dim3(kXcds * a.deal.groups), dim3(64 * kStripWaves),
+                       kStripWaves * sizeof(Strip2dRows), s, start, stop, a);
     return hipGetLastError();
 }
 

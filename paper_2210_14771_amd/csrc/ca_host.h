@@ -37,6 +37,8 @@ struct Plan {
     ca_point *cand = nullptr;
     Record *rec = nullptr;
     uint32_t *ctl = nullptr;    // fused-kernel control words (zero between calls)
+    uint64_t *edges = nullptr;  // learned launches' [kStripGroups], one set for each stream
+                                // of a call's sub-batches (zero between calls)
     ca_result *res2 = nullptr;  // results of the calls that autotune times
     int32_t *flist = nullptr;   // frame indices by frame shape, the largest first
     const Shape *shapes = nullptr;  // the batch's n_shapes distinct frame shapes, likewise
@@ -113,7 +115,7 @@ struct ca_ctx {
     int grad2d_grid = 0;
     int64_t strips_per_group = 0;   // 0: tuned per frame shape
     int64_t ransac_lanes = 0;       // 0: chosen per batch from its attempt workgroups
-    int cnn_groups_per_xcd = 0;     // resident learned-strip workgroups per XCD (0: not queried)
+    int cnn_groups_per_xcd = 0;     // resident workgroups of k_cnn_strips per XCD (0: not queried)
     std::map<std::array<int32_t, 4>, int32_t> tuned;   // (W, H, n_h, n_v) -> strip items per group
     // score tables of the last (t_g, t_theta, t_iota): SG[lut_sg_len] | ST | SI
     bool lut_valid = false;
@@ -131,13 +133,15 @@ int validate(const ca_frame_desc *dims, int32_t n, const ca_params &p);
 // Eq. 1 positions of n strips across an extent (floor, clamped to [1, extent - 2]).
 int strip_positions(int32_t extent, int32_t n, double alpha, int32_t *pos);
 
+constexpr size_t kEdgeBytes = 2 * ca::kStripGroups * sizeof(uint64_t);
 // Byte layout of a plan's device block.  Its first image_bytes bytes
 // (frame descriptors, strip tables, score tables, frame list grouped by
-// shape, zeroed control words) are built on the host and uploaded with one
+// shape, zeroed control and edge words) are built on the host and uploaded with one
 // copy; candidates, attempt-group records and a result array follow and
 // are written by the kernels only.
 struct PlanLayout {
-    size_t o_fd = 0, o_strips = 0, o_lut = 0, o_flist = 0, o_ctl = 0, image_bytes = 0;
+    size_t o_fd = 0, o_strips = 0, o_lut = 0, o_flist = 0, o_ctl = 0, o_edges = 0;
+    size_t image_bytes = 0;
     size_t o_cand = 0, o_rec = 0, o_res2 = 0, total = 0;
     int32_t n_shapes = 0;
 };

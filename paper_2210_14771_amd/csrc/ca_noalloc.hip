@@ -16,21 +16,25 @@ namespace {
 constexpr size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 // The uploaded part of a call (descriptors, strip tables of at most
-// CA_NOALLOC_MAX_SHAPES shapes, score tables, frame list, control words) at
-// its largest, in the layout cahost::plan_layout gives it.
+// CA_NOALLOC_MAX_SHAPES shapes, score tables, frame list, control and edge
+// words) at its largest, in the layout cahost::plan_layout gives it.
 constexpr size_t kImageBytes =
     up256(sizeof(ca::FrameDev) * CA_NOALLOC_MAX_FRAMES)
     + up256(sizeof(int32_t) * CA_NOALLOC_MAX_SHAPES * 2 * CA_MAX_STRIPS)
     + up256(sizeof(float) * (CA_SG_CAPACITY + ca::kQtBins + ca::kLumaLevels))
     + up256(sizeof(int32_t) * CA_NOALLOC_MAX_FRAMES)
-    + sizeof(uint32_t) * (ca::kCtlFrames + 2 * (size_t)CA_NOALLOC_MAX_FRAMES);
+    + up256(sizeof(uint32_t) * (ca::kCtlFrames + 2 * (size_t)CA_NOALLOC_MAX_FRAMES))
+    + cahost::kEdgeBytes;
 static_assert(kImageBytes < CA_NOALLOC_SCRATCH_BYTES, "scratch smaller than its upload");
 
 constexpr int kMaxDevices = 16;
 
 // One call's device workspace.  Every device the library runs on holds its
 // own copy until the process ends; all calls on one device share it.
-static __device__ __align__(256) uint8_t scratch[CA_NOALLOC_SCRATCH_BYTES];
+// The edge words come on top of the documented bytes: they refuse no call.
+constexpr size_t kScratchBytes = CA_NOALLOC_SCRATCH_BYTES + cahost::kEdgeBytes;
+static_assert(cahost::kEdgeBytes % 256 == 0, "the other parts keep their alignment");
+static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 struct DeviceSlot {
     std::mutex mu;               // one call at a time builds and uploads the image
@@ -125,7 +129,7 @@ extern "C" int ca_estimate_area_noalloc(ca_ctx *ctx, const uint8_t *frames,
             return CA_E_SCRATCH;    // more frame shapes than the scratch holds tables for
         if (rc != CA_OK)
             return rc;
-        if (L.total > CA_NOALLOC_SCRATCH_BYTES)
+        if (L.total > kScratchBytes)
             return CA_E_SCRATCH;
         pl.fused_grid = fused_grid(ctx, pl.fused_lds);
         plan_pointers(&pl, d.ptr, L);

@@ -2,13 +2,11 @@
 // candidates that both learned scorers' strip kernels share.
 #pragma once
 
+#include "ca_deal.h"
 #include "ca_internal.h"
 #include "ca_mfma.h"
 
 namespace ca {
-
-constexpr int kStep = 64;         // positions a wave advances by
-constexpr int kStripWaves = 8;    // waves of a workgroup
 
 // LDS written by some lanes of the wave and read by others next: keep the
 // compiler from moving memory operations across (the hardware keeps a wave's
@@ -116,29 +114,178 @@ __device__ __forceinline__ ca_point strip_point(uint64_t key, bool horizontal, i
     return pt;
 }
 
-// Waves that share a half strip and workgroups per XCD, for `units` half strips
-// an XCD of frames of at most `longest` pixels a side, at most `resident`
-// workgroups an XCD and a halo of `halo` positions: the split with the fewest
-// steps until the last wave ends.  Frames of one shape are taken by resident
-// workgroups in turns; of several shapes (mixed) each workgroup takes one turn
-// and the dispatch evens out their lengths, for about a step's time of loading
-// weights.  A wave alone on a half strip of full HD takes 16 steps of some 3 us.
-inline int strip_split(int32_t &parts, int units, int resident, int longest, bool mixed, int halo)
+// A key of a piece of a half strip that several workgroups share, kept in `word`
+// until the last of `parts` of them comes, whose key becomes the best of all
+// (true) and which leaves the word zero, as it was.  Nobody waits: the word holds
+// the best key so far (of the distance 14 bits suffice) and the number of keys.
+__device__ __forceinline__ bool edge_merge(uint64_t *word, uint64_t &key, int parts)
 {
-    int64_t best = 0;
-    for (int32_t p = 1; p <= kStripWaves; p *= 2) {
-        const int64_t slots = (int64_t)resident * kStripWaves;
-        const int64_t turns = ((int64_t)units * p + slots - 1) / slots;
-        const int64_t steps = (((longest + 1) / 2 + p - 1) / p + 2 * halo + kStep - 1) / kStep;
-        const int64_t cost = turns * (steps + (mixed ? 1 : 0));
-        if (p == 1 || cost < best) {
-            best = cost;
-            parts = p;
+    constexpr uint64_t kScore = 0xFFFFFFFF00000000ull, kCount = 0xFFFFu;
+    const uint64_t mine = (key & kScore) | (key & 0xFFFFu) << 16;
+    uint64_t old = 0;   // as the first one finds it
+    for (;;) {
+        const uint64_t best = mine > (old & ~kCount) ? mine : old & ~kCount;
+        const uint64_t count = (old & kCount) + 1;
+        if (count == (uint64_t)parts) {   // (never of the guess: parts > 1)
+            __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            key = (best & kScore) | 0xFFFF0000u | (best >> 16 & 0xFFFFu);
+            return true;
+        }
+        if (__hip_atomic_compare_exchange_strong(word, &old, best | count, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return false;
+    }
+}
+
+// A half strip, its entries in the launch's list from `start` on.
+struct StripHalf {
+    int frame, unit, pos, L, start, entries;
+};
+// What the waves of a workgroup share: best keys (0: of the half strip that an
+// earlier workgroup began, 1 + w: of the one that wave w begins and does not end),
+// and the former half strip.
+struct StripMeet {
+    uint64_t best[kStripWaves + 1];
+    StripHalf ended;
+};
+
+// The candidates of a launch: this wave's share of the half strips.
+// piece(frame, horizontal, pos, half, p0, p1): the best key of positions [p0, p1)
+// of a half strip.  The waves that share a half strip meet in `meet` (best keys
+// zero on entry), and workgroups in the launch's edge words, at the first one's.
+// All threads of the workgroup call this.  MIXED: the frames differ in shape.
+template <int HALO, bool MIXED, class Args, class Piece>
+__device__ __forceinline__ void strip_shares(const Args &a, StripMeet &meet, int lane, int wv,
+                                             Piece piece)
+{
+    const int S = a.n_h + a.n_v;
+    const int n = a.n_items / S;
+    const int group = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int w0 = group * kStripWaves, w = w0 + wv;
+    StripDeal deal = a.deal;
+    int &row = deal.row, &col = deal.col, &each = deal.each;
+    auto entries_of = [&](int f) {
+        const FrameDev &d = a.fd[a.frame0 + f];
+        row = extent_entries(d.W, HALO, deal);
+        col = extent_entries(d.H, HALO, deal);
+        each = 2 * (a.n_h * row + a.n_v * col);
+    };
+    // entries of frames base .. base + 63 up to and with this lane's
+    auto scan = [&](int base) {
+        int v = 0;
+        if (base + lane < n) {
+            entries_of(base + lane);
+            v = each;
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            const int t = __shfl_up(v, d, 64);
+            v += lane >= d ? t : 0;
+        }
+        return v;
+    };
+    int f = 0, r = 0;   // frame, entry within it
+    int t, end;
+    if (!MIXED) {
+        t = wave_start(deal, w);
+        end = wave_start(deal, w + 1);
+        f = t / each;
+        r = t - f * each;
+    } else {
+        int upto = scan(0), total = __shfl(upto, 63, 64);
+        for (int base = 64; base < n; base += 64)
+            total += __shfl(scan(base), 63, 64);
+        total = uniform_int(total);
+        deal.share = total / (int)gridDim.x;
+        deal.extra = total - deal.share * (int)gridDim.x;
+        t = wave_start(deal, w);
+        end = wave_start(deal, w + 1);
+        r = t;
+        for (int base = 0; t < end; base += 64) {
+            if (base)
+                upto = scan(base);
+            const uint64_t later = __ballot(upto > r);
+            if (later) {
+                const int at = __builtin_ctzll(later);
+                f = base + at;
+                r -= at ? uniform_int(__shfl(upto, at - 1, 64)) : 0;
+                break;
+            }
+            r -= uniform_int(__shfl(upto, 63, 64));
         }
     }
-    const int sets = kStripWaves / parts;
-    const int groups = (units + sets - 1) / sets;
-    return mixed || groups < resident ? groups : resident;
+
+    auto write = [&](const StripHalf &h, uint64_t key) {
+        if (lane == 0)
+            a.cand[(int64_t)h.frame * (2 * S) + h.unit] =
+                strip_point(key, h.unit < 2 * a.n_h, h.pos, h.unit & 1, h.L);
+    };
+    StripHalf h;
+    int table = -1;
+    bool begins = false, ends = false;   // whether this wave completes a shared half strip
+    if (MIXED && t < end)
+        entries_of(f);
+    StripPlace q = {};
+    if (t < end)
+        q = strip_place(deal, a.n_h, a.n_v, r);
+    while (t < end) {
+        h.frame = uniform_int(a.frame0 + f);
+        const FrameDev d = a.fd[h.frame];
+        const bool horizontal = uniform_int(q.horizontal) != 0;
+        const int half = uniform_int(q.half), at = uniform_int(q.at);
+        h.entries = uniform_int(q.entries);
+        h.unit = uniform_int(2 * (horizontal ? q.strip : a.n_h + q.strip)) + half;
+        if (MIXED || table < 0)   // (frames of one shape share the table)
+            table = uniform_int(d.table);
+        h.pos = uniform_int(a.strips[table + (h.unit >> 1)]);
+        h.start = t - at;
+        h.L = uniform_int(horizontal ? d.W : d.H);
+        const int h0 = half ? h.L >> 1 : 0, len = half ? h.L - (h.L >> 1) : h.L >> 1;
+        const int to = min(h.entries, at + end - t);
+        const int from = at ? uniform_int(wave_of(deal, h.start)) : w;   // its first wave
+        auto start_of = [&](int entry, int waves) {
+            return piece_start(len, HALO, entry, cuts_before(deal.share, entry, waves), deal.grain);
+        };
+        const int p0 = h0 + (at ? start_of(at, w - from) : 0);
+        const int p1 = h0 + (to == h.entries ? len : start_of(to, w - from + 1));
+        const uint64_t best = piece(d, horizontal, h.pos, half, p0, p1);
+        if (to - at == h.entries) {
+            write(h, best);
+        } else {
+            if (lane == 0)
+                atomicMax((unsigned long long *)&meet.best[from < w0 ? 0 : 1 + from - w0],
+                          (unsigned long long)best);
+            begins = from == w;   // (the last piece then)
+            if (from < w0 && wv == 0) {
+                ends = true;
+                meet.ended = h;
+            }
+        }
+        t += to - at;
+        if (!strip_next(deal, a.n_h, a.n_v, q)) {
+            ++f;
+            if (MIXED && t < end) {
+                entries_of(f);
+                q.entries = q.horizontal ? row : col;
+            }
+        }
+    }
+    __syncthreads();
+    auto complete = [&](const StripHalf &h, uint64_t key) {
+        const int first = group_of(deal, h.start);
+        const int last = group_of(deal, h.start + h.entries - 1);
+        bool all = true;
+        if (last > first && lane == 0)
+            all = edge_merge(a.edges + first, key, last - first + 1);
+        if (all)
+            write(h, key);
+    };
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+        if (k == 0 ? begins : ends)
+            complete(h, meet.best[k == 0 ? 1 + wv : 0]);
+        h = meet.ended;
+    }
 }
 
 }  // namespace ca
