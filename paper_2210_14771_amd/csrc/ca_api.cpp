@@ -469,13 +469,13 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
             return CA_E_DEVICE;
         return CA_OK;
     }
-    // whether every shape of the batch takes one strip a workgroup
-    auto one_each = [&] {
-        for (int32_t k = 0; k < pl->n_shapes; ++k)
-            if (strips_per_group(ctx, pl->shapes[k].W, pl->shapes[k].H, p) != 1)
-                return false;
-        return true;
-    };
+    // A batch of several shapes takes one launch over all of them, unless tiles of
+    // several strips were asked for, or found faster for this batch: a shape's own
+    // tile was timed alone, and a launch a shape, however tiled, costs more than
+    // it gains (mixed_spread).
+    const bool one_launch = pl->dynamic
+                            || (ctx->strips_per_group > 0 ? ctx->strips_per_group == 1
+                                                          : !pl->tuned_tiles);
     // strips then RANSAC for frames [f0, f1) on stream st
     const int S = p.n_hstrips + p.n_vstrips;
     const bool learned = p.scorer == CA_SCORER_LEARNED;
@@ -534,8 +534,7 @@ int enqueue_one(ca_ctx *ctx, Plan *pl, const uint8_t *frames, int32_t n, const c
                 }
             }
             ok = ok && (!several || !s1 || hipEventRecord(s1, st) == hipSuccess);
-        } else if (f0 == 0 && f1 == n && mixed && (pl->dynamic || one_each())) {
-            // several shapes, each taking its strips one at a time
+        } else if (f0 == 0 && f1 == n && mixed && one_launch) {
             a2.frame_list = pl->flist;
             a2.spread = pl->spread;
             if (a2.spread == ca::kSpreadFrames)
@@ -1308,8 +1307,9 @@ int ca_autotune(ca_ctx *ctx, const uint8_t *frames, const ca_frame_desc *dims, i
             break;
         ctx->tuned[{c.W, c.H, p.n_hstrips, p.n_vstrips}] = best_t;
     }
-    // whole calls of this batch: the split schedule (with the tiles just
-    // chosen) in one call or cut into 2 or 4 pipelined sub-batches, against
+    // whole calls of this batch: the split schedule (with the tile just
+    // chosen; several shapes: in one launch, and in a launch for each with its
+    // tile) in one call or cut into 2 or 4 pipelined sub-batches, against
     // the persistent one; the fastest serves CA_SCHEDULE_AUTO (with the
     // pipeline option at 0).  Each is timed eagerly and replayed from a
     // captured one-call graph, and counts by the slower of the two (the
@@ -1344,14 +1344,21 @@ int ca_autotune(ca_ctx *ctx, const uint8_t *frames, const ca_frame_desc *dims, i
         const int64_t saved_schedule = ctx->schedule, saved_pipeline = ctx->pipeline;
         struct Trial {
             int64_t schedule, pipeline;
+            bool tiles;
         };
-        const Trial trials[4] = {{CA_SCHEDULE_SPLIT, 1}, {CA_SCHEDULE_SPLIT, 2},
-                                 {CA_SCHEDULE_SPLIT, 4}, {CA_SCHEDULE_FUSED, 1}};
+        const Trial trials[5] = {{CA_SCHEDULE_SPLIT, 1, false}, {CA_SCHEDULE_SPLIT, 2, false},
+                                 {CA_SCHEDULE_SPLIT, 4, false}, {CA_SCHEDULE_FUSED, 1, false},
+                                 {CA_SCHEDULE_SPLIT, 1, true}};
+        bool tiled = false;   // some shape of several takes a tile
+        for (int32_t k = 0; k < pl->n_shapes; ++k)
+            tiled = tiled || (pl->n_shapes > 1
+                              && strips_per_group(ctx, pl->shapes[k].W, pl->shapes[k].H, p) != 1);
         int best = 0;
         float best_ms = 0.0f;
-        for (int k = 0; k < 4 && rc == CA_OK; ++k) {
-            if (trials[k].pipeline > n)
+        for (int k = 0; k < 5 && rc == CA_OK; ++k) {
+            if (trials[k].pipeline > n || (trials[k].tiles && !tiled))
                 continue;
+            pl->tuned_tiles = trials[k].tiles;
             ctx->schedule = trials[k].schedule;
             ctx->pipeline = trials[k].pipeline;
             bool ok = enqueue(ctx, pl, frames, n, p, nullptr, nullptr, pl->res2, st, false) == CA_OK
@@ -1371,6 +1378,7 @@ int ca_autotune(ca_ctx *ctx, const uint8_t *frames, const ca_frame_desc *dims, i
         }
         ctx->schedule = saved_schedule;
         ctx->pipeline = saved_pipeline;
+        pl->tuned_tiles = rc == CA_OK && trials[best].tiles;
         if (rc == CA_OK) {
             pl->tuned_schedule = (int32_t)trials[best].schedule;
             pl->tuned_pipeline = (int32_t)trials[best].pipeline;

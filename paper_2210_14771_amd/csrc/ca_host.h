@@ -49,6 +49,7 @@ struct Plan {
                                 // call's without allocation
     int32_t tuned_schedule = -1; // faster schedule of this batch (ca_autotune), -1 untuned
     int32_t tuned_pipeline = 1;  // sub-batches of its split calls (ca_autotune)
+    bool tuned_tiles = false;    // several shapes: a launch for each, with its tile (ca_autotune)
     // launch facts
     int32_t n_frames = 0, P = 0, groups = 0, sg_len = 0, line_pitch = 0;
     int32_t rec_groups = 0;     // attempt-group records per frame the block holds (16 lanes)
