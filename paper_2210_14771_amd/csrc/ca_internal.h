@@ -15,7 +15,7 @@ constexpr int kHalfThreads = 128; // threads per half strip
 // Lanes that compute on one RANSAC attempt (its triple and its solves; the
 // inlier passes are tiles of 16 attempts): 1, 2 or 4, that is 4, 2 or 1 tiles a
 // wavefront and 256, 128 or 64 attempts a workgroup.
-constexpr int kLanesPerAttempt = 4;   // fused schedule (two tiles a wavefront spill beside the strips)
+constexpr int kLanesPerAttempt = 2;   // fused schedule
 constexpr int kMaxLanesPerAttempt = 4;   // small batches spread attempts over more workgroups
 constexpr int kRecordLanes = 16;      // the plan's record array is laid out for 16 lanes
 // Attempt groups (workgroups) per frame with `lanes` lanes per attempt.

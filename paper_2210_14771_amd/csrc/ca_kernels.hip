@@ -1338,7 +1338,13 @@ constexpr int kFusedTiles = 4 / kLanesPerAttempt;
 typedef Lds<1> FusedLds;
 static_assert(sizeof(FusedLds) <= 18944, "LDS of a fused workgroup beside its score tables");
 
-__global__ __launch_bounds__(kBlock, 4) void k_fused(FusedArgs a)
+// Two tiles a wavefront, three workgroups a compute unit (168 registers, where
+// four leave 128 and spill).  A call, with the inlier passes in float64 on the
+// vector units; one tile and four workgroups; so: 512 frames of four resolutions,
+// 16 + 16 strips, 256 attempts 315, 365 and 277 us; 64 x 1080p, 32 + 32, 1024
+// attempts 130, 123 and 113; 8 x 640x480 36.2, 36.8 and 32.3; 128 frames of four
+// resolutions, 32 + 32, 132, 132 and 134.
+__global__ __launch_bounds__(kBlock, 3) void k_fused(FusedArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ uint32_t s_scan[4];
