@@ -179,7 +179,7 @@ int ca_estimate_area(ca_ctx *ctx, const uint8_t *frames_dev, const ca_frame_desc
  * copy on `stream`, and waits on the host for the previous call's upload
  * to have been read.  Limits: at most CA_NOALLOC_MAX_FRAMES frames of at
  * most CA_NOALLOC_MAX_SHAPES distinct shapes, and the layout must fit the
- * scratch (about 3.6 KB per frame at 64 + 64 strips and 4096 attempts);
+ * scratch (about 14 KB per frame at 64 + 64 strips and 4096 attempts);
  * beyond them CA_E_SCRATCH, with nothing enqueued. */
 #define CA_NOALLOC_SCRATCH_BYTES (4u << 20)
 #define CA_NOALLOC_MAX_FRAMES 1024

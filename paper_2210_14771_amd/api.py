@@ -486,7 +486,7 @@ class Graph:
 
     def launch(self, stream=None) -> Result:
         s = stream if stream is not None else torch.cuda.current_stream(self._est.device)
-        N.check(N.lib().ca_graph_launch(self._g, s), "ca_graph_launch")
+        N.check(N.lib().ca_graph_launch(self._g, s.cuda_stream), "ca_graph_launch")
         return self.result
 
     def close(self):

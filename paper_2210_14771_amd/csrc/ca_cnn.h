@@ -97,16 +97,15 @@ constexpr int kC2Band = 7;     // lines of a band
 constexpr int kC2Halo = 3;     // the network's receptive-field radius
 // Device model block, per band orientation (0: horizontal strips, weights
 // [dy][dx]; 1: vertical strips, [dx][dy]): bfloat16 GEMM weights A[m][k]
-// with k = (3 da + dl) C_pad + c for the forward convolutions, and flipped
-// weights F[c][(3 da' + dl') C_out + o] = W[o][c][2 - da'][2 - dl'] for the
-// input gradients of layer 3; layer 1 again for two output lines at once
+// with k = (3 da + dl) C + c for the forward convolutions of layers 2 and 3, and
+// flipped weights F[c][(3 da' + dl') C_out + o] = W[o][c][2 - da'][2 - dl'] for the
+// input gradients of layer 3; layer 1 for two output lines at once
 // (P[8 s + o][(3 lo + dl) 8 + c] = W1[o][c][lo - s][dl] over the pair's four
 // input lines lo, zero where lo - s is not a tap), and the flipped layer 2
 // likewise (F[8 s + c][(3 lo + dl') 16 + o], da' = lo - s); then float32
 // b1, b2, b3, w4 (values of bfloat16), b4, mean, inv_std.
-constexpr int kC2KP[3] = {96, 96, 160};          // padded K of the forward GEMMs
-constexpr int kC2A[3] = {0, 16 * 96, 2 * 16 * 96};  // offsets within an orientation
-constexpr int kC2F2 = 2 * 16 * 96 + 32 * 160;    // flipped layer 2 by line pairs: [16][192]
+constexpr int kC2A2 = 0, kC2A3 = 16 * 96;        // layer 2: [16][96], layer 3: [32][160]
+constexpr int kC2F2 = 16 * 96 + 32 * 160;        // flipped layer 2 by line pairs: [16][192]
 constexpr int kC2F3 = kC2F2 + 16 * 192;          // flipped layer 3: [16][288]
 constexpr int kC2P1 = kC2F3 + 16 * 288;          // layer 1 by output-line pairs: [16][96]
 constexpr int kC2Orient = kC2P1 + 16 * 96;       // bfloat16 elements per orientation

@@ -1031,9 +1031,8 @@ __global__ __launch_bounds__(kReduceThreads) void k_cnn_reduce(const float *part
     }
 }
 
-// SGD with momentum: m = mu m + g, p -= lr m.
-// SGD with momentum on the master weights (file order), each weight's copies in
-// the device model block with it (k_cnn_pack's layout; the padding stays): a
+// SGD with momentum (m = mu m + g, p -= lr m) on the master weights (file order),
+// each weight's copies in the device model block with it (k_cnn_pack's layout; the padding stays): a
 // repack of its own cost a launch, 1.8 us of a step.
 __global__ __launch_bounds__(kBlock) void k_cnn_update(float *master, float *mom,
                                                        const float *grad, float lr, float mu,

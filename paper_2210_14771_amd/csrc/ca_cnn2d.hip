@@ -328,13 +328,13 @@ struct Strip2dNet {
 #pragma unroll
         for (int ks = 0; ks < 3; ++ks) {
             w1[0][ks] = frag_at(A + kC2P1 + col * 96 + 32 * ks + 8 * g);
-            w2[0][ks] = frag_at(A + kC2A[1] + col * 96 + 32 * ks + 8 * g);
+            w2[0][ks] = frag_at(A + kC2A2 + col * 96 + 32 * ks + 8 * g);
         }
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
             for (int ks = 0; ks < 5; ++ks)
-                w3[mt][ks] = frag_at(A + kC2A[2] + (16 * mt + col) * 160 + 32 * ks + 8 * g);
+                w3[mt][ks] = frag_at(A + kC2A3 + (16 * mt + col) * 160 + 32 * ks + 8 * g);
         loaded = (int)horizontal;
     }
 
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
             cur = (int)hz;
             const int col = lane & 15, g = lane >> 4;
             for (int f = wv; f < 19; f += kWaves) {
-                const __bf16 *src = f < 10 ? A + kC2A[2] + ((f / 5) * 16 + col) * 160 + 32 * (f % 5)
+                const __bf16 *src = f < 10 ? A + kC2A3 + ((f / 5) * 16 + col) * 160 + 32 * (f % 5)
                                            : A + kC2F3 + col * 288 + 32 * (f - 10);
                 *reinterpret_cast<bf16x8 *>(G.w3 + f * 512 + lane * 8) = frag_at(src + 8 * g);
             }
@@ -785,7 +785,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cnn2d_grad(Cnn2dTrainArgs a)
                             relu_bf16(acc[t] + b1, line_in(line_ok, ln + 1) ? tops[t] : 0.0f);
             }
         }
-        const Frag<96, 1> w2 = load_frag<96, 1>(A + kC2A[1]);
+        const Frag<96, 1> w2 = load_frag<96, 1>(A + kC2A2);
         __syncthreads();
         {
             const Place L(fresh(lane));
@@ -1140,7 +1140,7 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_update(float *master, float *m
     master[i] = v;
     const __bf16 h = to_bf16(v);
     float *fb = reinterpret_cast<float *>(model + kC2FloatsOff);
-    constexpr int cin[3] = {5, 8, 16}, cout[3] = {8, 16, 32}, cp[3] = {8, 8, 16};
+    constexpr int cin[3] = {5, 8, 16}, cout[3] = {8, 16, 32};
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
         const int r = i - kC2FileW[l];
@@ -1150,7 +1150,9 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_update(float *master, float *m
             for (int orient = 0; orient < 2; ++orient) {
                 __bf16 *w = reinterpret_cast<__bf16 *>(model) + orient * kC2Orient;
                 const int da = orient == 0 ? dy : dx, dl = orient == 0 ? dx : dy;
-                w[kC2A[l] + o * kC2KP[l] + (3 * da + dl) * cp[l] + c] = h;
+                if (l > 0)
+                    w[(l == 1 ? kC2A2 : kC2A3) + o * (l == 1 ? 96 : 160) + (3 * da + dl) * cin[l]
+                      + c] = h;
 #pragma unroll
                 for (int sl = 0; sl < 2; ++sl) {   // the lines of a pair
                     if (l == 0)
@@ -1178,7 +1180,7 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_update(float *master, float *m
 __global__ __launch_bounds__(kBlock) void k_cnn2d_pack(const float *master, uint8_t *model)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    constexpr int cin[3] = {5, 8, 16}, cout[3] = {8, 16, 32}, cp[3] = {8, 8, 16};
+    constexpr int cin[3] = {5, 8, 16};
     if (i < 2 * kC2Orient) {
         const int orient = i / kC2Orient, e = i - kC2Orient * (i / kC2Orient);
         float v = 0.0f;
@@ -1198,15 +1200,14 @@ __global__ __launch_bounds__(kBlock) void k_cnn2d_pack(const float *master, uint
             dl = g % 3;
             real = c < cin[0] && da >= 0 && da < 3;
         } else if (e < kC2F2) {
-            l = e < kC2A[1] ? 0 : e < kC2A[2] ? 1 : 2;
-            const int r = e - kC2A[l];
-            const int m = r / kC2KP[l], k = r % kC2KP[l];
-            const int tap = k / cp[l];
-            c = k % cp[l];
-            o = m;
+            l = e < kC2A3 ? 1 : 2;
+            const int r = e - (l == 1 ? kC2A2 : kC2A3), kp = l == 1 ? 96 : 160;
+            const int k = r % kp, tap = k / cin[l];
+            o = r / kp;
+            c = k % cin[l];
             da = tap / 3;
             dl = tap % 3;
-            real = m < cout[l] && tap < 9 && c < cin[l];
+            real = tap < 9;
         } else if (e < kC2F3) {
             // flipped layer 2 for two output lines at once: row m = 8 s + c is
             // input channel c at the pair's line s; K = (3 lo + dl') 16 + o

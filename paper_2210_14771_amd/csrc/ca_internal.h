@@ -17,7 +17,9 @@ constexpr int kHalfThreads = 128; // threads per half strip
 // wavefront and 256, 128 or 64 attempts a workgroup.
 constexpr int kLanesPerAttempt = 2;   // fused schedule
 constexpr int kMaxLanesPerAttempt = 4;   // small batches spread attempts over more workgroups
-constexpr int kRecordLanes = 16;      // the plan's record array is laid out for 16 lanes
+// The plan's record array is laid out for 16 lanes: the frames that the scratch of
+// the calls without allocation holds are counted so.
+constexpr int kRecordLanes = 16;
 // Attempt groups (workgroups) per frame with `lanes` lanes per attempt.
 inline int attempt_groups(int attempts, int lanes) { return (attempts * lanes + kBlock - 1) / kBlock; }
 constexpr int kChunk = 8;        // most pixels one thread scores per pass (a 1920-pixel line in one pass)

@@ -35,6 +35,7 @@
 // inlier moments (summed here exactly, as 8-bit digits).
 #include "ca_internal.h"
 #include "ca_launch.h"
+#include "ca_mfma.h"
 
 namespace ca {
 namespace {
@@ -628,17 +629,7 @@ __device__ bool coope_solve(const Moments &s, double &cx, double &cy, double &r2
     return true;
 }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-// LDS written by some lanes of a wave and read by others next: keep the
-// compiler from moving memory operations across (the hardware keeps a wave's
-// LDS operations in order).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // The float32 form of an attempt's inlier test.  d^2 - mid = z - 2 cx u - 2 cy
 // v + (|c|^2 - mid), with mid and half the middle and half width of
@@ -647,9 +638,10 @@ __device__ __forceinline__ void wave_sync()
 // numbers, the float64 test does, so every decision is the float64 one.
 // E bounds what float32 loses, with u = 2^-24 and S the sum of the terms'
 // largest absolute values Z = U^2 + V^2, A, B, K: the coefficients are rounded
-// once (u (A + B + K), and z beyond 2^24 u Z), and the matrix unit forms the
-// sum as a chain of fused multiply-adds from z on (u (Z + A) + u (Z + A + B) +
-// u half): below 3 u S + u half together.  A fourth u S covers float64's own
+// once (u (A + B + K), and z beyond 2^24 u Z), and the matrix unit rounds each
+// addition of the four exact products: in any order the sums before the last
+// lose at most 2 u S, and the last, at the edge of the band, u half: below
+// 3 u S + u half together.  A fourth u S covers float64's own
 // roundings of |c|^2, mid and d^2, together below 2^-48 (|c|^2 + Z): with m the
 // smaller of U and V, |c| <= S / (2 m), so S < 2^26 m^2 keeps them below it.
 struct Quick {

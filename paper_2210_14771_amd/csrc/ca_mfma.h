@@ -1,4 +1,4 @@
-// Device helpers of the two learned scorers' MFMA kernels.
+// Device helpers of the MFMA kernels (the two learned scorers, RANSAC).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,6 +9,15 @@ namespace ca {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS written by some lanes of the wave and read by others next: keep the
+// compiler from moving memory operations across (the hardware keeps a wave's
+// LDS operations in order).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }

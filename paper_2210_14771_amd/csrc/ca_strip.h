@@ -8,15 +8,6 @@
 
 namespace ca {
 
-// LDS written by some lanes of the wave and read by others next: keep the
-// compiler from moving memory operations across (the hardware keeps a wave's
-// LDS operations in order).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // A half strip, or a part of one, as a wave walks along it.
 struct StripWalk {
     const uint8_t *frame;
