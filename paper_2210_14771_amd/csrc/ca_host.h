@@ -159,20 +159,28 @@ int plan_layout(const ca_ctx *ctx, const ca_frame_desc *dims, int32_t n, const c
                 PlanLayout *L, uint8_t *image, size_t image_cap);
 // How one launch deals the n frames of several shapes; area(k): the pixels of the
 // k-th frame in the launch's order, the largest first.  Whole frames to the XCDs,
-// whose L2 then holds the lines that a frame's strips share, unless that would
-// leave one XCD with over a tenth more than its share; then strip by strip.  128
-// frames of four resolutions: 167 us a call with a launch for each shape, 152 us
-// dealt strip by strip, 124 us by frames.
+// whose L2 then holds the lines that a frame's strips share (strips of 4K frames
+// lie too far apart to share any), unless few frames would leave one XCD with over
+// a quarter more than its share; then strip by strip.  By frames and by strips, us
+// a call, 32 + 32 strips, with the largest share in parts of the mean one: 128
+// frames of four resolutions 84 and 103 (1.0; a launch for each shape 94); 33 full
+// HD and 3 SD 49 and 60 (1.2); one 4K and 31 full HD 48 and 60 (1.6); 10 4K and 22
+// SD 48 and 48 (1.5; 16 + 16 strips 35.1 and 34.8); 5 full HD and 5 720p 25 and 27
+// (1.1); one 4K and 7 SD 30.9 and 30.7 (5.9); 2 full HD and 2 720p 24 and 23 (2.8;
+// 16 + 16 strips 23.2 and 20.5); one 4K and one SD 31 and 28 (7.6).
 template <class Area>
 int32_t mixed_spread(int32_t n, Area area)
 {
+    constexpr int32_t kEnough = 16;
+    if (n >= kEnough)
+        return ca::kSpreadFrames;
     int64_t mine[8] = {}, all = 0;
     for (int32_t k = 0; k < n; ++k) {
         mine[ca::spread_xcd(k)] += area(k);
         all += area(k);
     }
-    return 80 * *std::max_element(mine, mine + 8) <= 11 * all ? ca::kSpreadFrames
-                                                              : ca::kSpreadItems;
+    return 32 * *std::max_element(mine, mine + 8) <= 5 * all ? ca::kSpreadFrames
+                                                             : ca::kSpreadItems;
 }
 // Points pl's buffers into the device block at base.
 void plan_pointers(Plan *pl, void *base, const PlanLayout &L);
