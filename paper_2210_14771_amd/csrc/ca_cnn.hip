@@ -419,7 +419,7 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn_strips(CnnStripArgs
     StripRows &R = reinterpret_cast<StripRows *>(cnn_smem)[wv];
     strip_clear(R, lane);
     const StripNet net(a.model, lane);
-    strip_shares<kCnnHalo, MIXED>(a, meet, lane, wv, [&](const FrameDev &d, bool horizontal,
+    strip_shares<kCnnHalo, MIXED, true>(a, meet, lane, wv, [&](const FrameDev &d, bool horizontal,
                                                          int pos, int half, int p0, int p1) {
         StripWalk k;
         strip_walk<kCnnLines>(k, a.frames, d, horizontal, pos);

@@ -418,7 +418,7 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void k_cnn2d_strips(Cnn2dStrip
     Strip2dRows &R = reinterpret_cast<Strip2dRows *>(strip_smem)[wv];
     strip2d_clear(R, lane);
     Strip2dNet<true> net(a.model, lane);
-    strip_shares<kC2Halo, MIXED>(a, meet, lane, wv, [&](const FrameDev &d, bool horizontal,
+    strip_shares<kC2Halo, MIXED, false>(a, meet, lane, wv, [&](const FrameDev &d, bool horizontal,
                                                         int pos, int half, int p0, int p1) {
         net.turn_to(horizontal, a.model, lane);
         StripWalk k;

@@ -128,6 +128,17 @@ __device__ __forceinline__ bool edge_merge(uint64_t *word, uint64_t &key, int pa
     }
 }
 
+// Read-only data at a uniform address, through the scalar cache: a wave's vector
+// loads would wait for its weights, and for the candidate that it stored last.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T *p)
+{
+    static_assert(sizeof(T) % 4 == 0, "dwords");
+    typedef uint32_t words __attribute__((ext_vector_type(sizeof(T) / 4)));
+    typedef const words __attribute__((address_space(4))) *const_ptr;
+    return __builtin_bit_cast(T, *(const_ptr)(uintptr_t)p);
+}
+
 // A half strip, its entries in the launch's list from `start` on.
 struct StripHalf {
     int frame, unit, pos, L, start, entries;
@@ -145,7 +156,11 @@ struct StripMeet {
 // of a half strip.  The waves that share a half strip meet in `meet` (best keys
 // zero on entry), and workgroups in the launch's edge words, at the first one's.
 // All threads of the workgroup call this.  MIXED: the frames differ in shape.
-template <int HALO, bool MIXED, class Args, class Piece>
+// SCALAR: half strips are looked up through the scalar cache (1-D network, 64 x
+// 1080p with fallback: 219 us a call otherwise, 216 so; of the 2-D network the two
+// waves of a SIMD then run in step and meet in its layers: 218 us a launch
+// otherwise, 228 so).
+template <int HALO, bool MIXED, bool SCALAR, class Args, class Piece>
 __device__ __forceinline__ void strip_shares(const Args &a, StripMeet &meet, int lane, int wv,
                                              Piece piece)
 {
@@ -221,14 +236,15 @@ __device__ __forceinline__ void strip_shares(const Args &a, StripMeet &meet, int
         q = strip_place(deal, a.n_h, a.n_v, r);
     while (t < end) {
         h.frame = uniform_int(a.frame0 + f);
-        const FrameDev d = a.fd[h.frame];
+        const FrameDev d = SCALAR ? uniform_load(a.fd + h.frame) : a.fd[h.frame];
         const bool horizontal = uniform_int(q.horizontal) != 0;
         const int half = uniform_int(q.half), at = uniform_int(q.at);
         h.entries = uniform_int(q.entries);
         h.unit = uniform_int(2 * (horizontal ? q.strip : a.n_h + q.strip)) + half;
         if (MIXED || table < 0)   // (frames of one shape share the table)
             table = uniform_int(d.table);
-        h.pos = uniform_int(a.strips[table + (h.unit >> 1)]);
+        const int32_t *pos = a.strips + table + (h.unit >> 1);
+        h.pos = SCALAR ? uniform_load(pos) : uniform_int(*pos);
         h.start = t - at;
         h.L = uniform_int(horizontal ? d.W : d.H);
         const int h0 = half ? h.L >> 1 : 0, len = half ? h.L - (h.L >> 1) : h.L >> 1;
