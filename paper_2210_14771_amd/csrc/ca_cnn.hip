@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kBlock) void k_mfma_probe(float *out)
 // Measured, 64 1080p frames, 32 + 32 strips (kernel trace): 277 us with windows
 // of 128 positions of which 112 are used and 68 KB of fragment reads per 64
 // positions; 244 us in steps of 32 positions with four waves a SIMD and the
-// larger layers' weights in LDS (98 KB: bound by LDS); 194 us so (32 KB).
+// larger layers' weights in LDS (98 KB: bound by LDS); 173 us so (32 KB).
 
 // A layer's input rows: 4 of the step before, then the step's 64, in four
 // planes; C channels (24 padded with zeros to 32) at PITCH, ROWS a plane.

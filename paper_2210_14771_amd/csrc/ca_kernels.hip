@@ -1332,10 +1332,12 @@ static_assert(sizeof(FusedLds) <= 18944, "LDS of a fused workgroup beside its sc
 
 // Two tiles a wavefront, three workgroups a compute unit (168 registers, where
 // four leave 128 and spill).  A call, with the inlier passes in float64 on the
-// vector units; one tile and four workgroups; so: 512 frames of four resolutions,
-// 16 + 16 strips, 256 attempts 315, 365 and 277 us; 64 x 1080p, 32 + 32, 1024
-// attempts 130, 123 and 113; 8 x 640x480 36.2, 36.8 and 32.3; 128 frames of four
-// resolutions, 32 + 32, 132, 132 and 134.
+// vector units (four workgroups); one tile and four workgroups; so: 512 frames of
+// four resolutions, 16 + 16 strips, 256 attempts 328, 365 and 284 us; 64 x 1080p,
+// 32 + 32, 1024 attempts 130, 123 and 112; 8 x 640x480 36, 37 and 31.  Batches of
+// many frames with many strips and few attempts miss the fourth workgroup: the 512
+// frames with 32 + 32 strips 509, 539 and 523 at 1024 attempts, but 428, 442 and
+// 467 at 256.
 __global__ __launch_bounds__(kBlock, 3) void k_fused(FusedArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -1375,8 +1377,14 @@ __global__ __launch_bounds__(kBlock, 3) void k_fused(FusedArgs a)
         const Ticket tk = decode_ticket(uniform(s_ticket), q, a.nq, B, S, G, a.lag);
         if (tk.kind < 0)
             break;
+        // the arguments are read anew for every item: kept in registers over the
+        // loop they spilled
+        typedef const FusedArgs __attribute__((address_space(4))) *const_args;
+        const_args kernarg = (const_args)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(kernarg));
+        const FusedArgs &now = *(const FusedArgs *)kernarg;
         if (tk.kind == 0) {
-            strip_work(a.s, c, tk.f, tk.idx, threadIdx.x);
+            strip_work(now.s, c, tk.f, tk.idx, threadIdx.x);
             if (tid == 0)
                 add_dev(strips_done + tk.f, 1u);
         } else {
@@ -1393,12 +1401,12 @@ __global__ __launch_bounds__(kBlock, 3) void k_fused(FusedArgs a)
                 }
             }
             __syncthreads();
-            ransac_work<kFusedTiles, 1>(a.r, L, tk.f, tk.idx);
+            ransac_work<kFusedTiles, 1>(now.r, L, tk.f, tk.idx);
             if (tid == 0)
                 s_last = add_dev(groups_done + tk.f, 1u) == (uint32_t)(G - 1);
             __syncthreads();
             if (uniform(s_last) && tid == 0) {
-                select_frame(a.se, tk.f);
+                select_frame(now.se, tk.f);
                 // every group of this frame has finished: rearm its counters
                 store_dev(strips_done + tk.f, 0u);
                 store_dev(groups_done + tk.f, 0u);
