@@ -177,7 +177,9 @@ def run(server: Server, streams, realtime: bool = True, only=None, timeout_s: fl
         if progress is not None and now >= next_report:
             progress(f"t={now:.1f}s submitted {i} served {len(served)} {server.stats()}")
             next_report += 1.0
-        while i < len(events) and (not realtime or events[i][0] <= now):
+        # (by the clock, not by `now`: a frame that arrives while others are
+        # submitted joins their step)
+        while i < len(events) and (not realtime or events[i][0] <= time.perf_counter() - t0):
             _, sid, k = events[i]
             st = by_id[sid]
             server.submit(sid, k, st.frames[k % len(st.frames)], lend)
